@@ -1,8 +1,10 @@
-"""ctypes binding of libtir.so: same names as the C ABI, argument marshalling only.
+"""Binding of libtir.so: same names as the C ABI, argument marshalling only.
 
 Every operator call ends in one of the ``extern "C"`` entry points declared in ``include/tir.h``;
 there is no Python or PyTorch fallback.  If the library has not been built, loading fails loudly.
-PyTorch is used for device memory and streams only.
+PyTorch is used for device memory and streams only.  The operators themselves go through ``_native``, a CPython
+extension over the same library (csrc/native_binding.cpp), because marshalling through ctypes costs more than a
+launch; queries, tuning and test hooks use ctypes.
 """
 from __future__ import annotations
 
@@ -45,6 +47,16 @@ class TirError(RuntimeError):
 
 
 _lib = None
+_native = None
+
+
+def _load_native():
+    """The extension module with the operators' fast call path (lib() first: it binds libtir.so to torch's HIP runtime)."""
+    global _native
+    lib()
+    from . import _native as module
+    _native = module
+    return module
 
 
 def lib() -> ctypes.CDLL:
@@ -181,20 +193,25 @@ def tir_conv2d_status(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, p
 
 
 def tir_gemm(A, B, C, M, N, K, a_rs, a_cs, b_rs, b_cs, c_rs, c_cs, in_dtype, out_dtype, stream=None) -> None:
-    _check(tir_gemm_status(A, B, C, M, N, K, a_rs, a_cs, b_rs, b_cs, c_rs, c_cs, in_dtype, out_dtype,
-                           _stream(stream)))
+    st = (_native or _load_native()).tir_gemm_fused(A, B, C, M, N, K, a_rs, a_cs, b_rs, b_cs, c_rs, c_cs, in_dtype, out_dtype, None, stream)
+    if st:
+        _check(st)
 
 
 def tir_batch_matmul(A, B, C, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, c_bs, c_rs, c_cs,
                      in_dtype, out_dtype, stream=None) -> None:
-    _check(tir_batch_matmul_status(A, B, C, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, c_bs, c_rs, c_cs,
-                                   in_dtype, out_dtype, _stream(stream)))
+    st = (_native or _load_native()).tir_batch_matmul_fused(A, B, C, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, c_bs, c_rs,
+                                                               c_cs, in_dtype, out_dtype, None, stream)
+    if st:
+        _check(st)
 
 
 def tir_conv2d(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, groups,
                in_dtype, out_dtype, stream=None) -> None:
-    _check(tir_conv2d_status(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, groups,
-                             in_dtype, out_dtype, _stream(stream)))
+    st = (_native or _load_native()).tir_conv2d_fused(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, groups,
+                                                         in_dtype, out_dtype, None, stream)
+    if st:
+        _check(st)
 
 
 def tir_gemm_variant(batch, M, N, K, a_rs, a_cs, b_rs, b_cs, c_rs, c_cs, in_dtype, out_dtype) -> str:
@@ -288,40 +305,47 @@ def _ep_arg(ep):
 
 def tir_gemm_fused(A, B, C, M, N, K, a_rs, a_cs, b_rs, b_cs, c_rs, c_cs, in_dtype, out_dtype, ep=None, stream=None) -> None:
     """ep: an Epilogue from make_epilogue(), or None for the plain operator."""
-    _check(lib().tir_gemm_fused(_ptr(A), _ptr(B), _ptr(C), M, N, K, a_rs, a_cs, b_rs, b_cs, c_rs, c_cs, _code(in_dtype),
-                                _code(out_dtype), _ep_arg(ep), _stream(stream)))
+    st = (_native or _load_native()).tir_gemm_fused(A, B, C, M, N, K, a_rs, a_cs, b_rs, b_cs, c_rs, c_cs, in_dtype, out_dtype, ep, stream)
+    if st:
+        _check(st)
 
 
 def tir_batch_matmul_fused(A, B, C, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, c_bs, c_rs, c_cs,
                            in_dtype, out_dtype, ep=None, stream=None) -> None:
-    _check(lib().tir_batch_matmul_fused(_ptr(A), _ptr(B), _ptr(C), batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs,
-                                        c_bs, c_rs, c_cs, _code(in_dtype), _code(out_dtype), _ep_arg(ep),
-                                        _stream(stream)))
+    st = (_native or _load_native()).tir_batch_matmul_fused(A, B, C, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, c_bs, c_rs,
+                                                               c_cs, in_dtype, out_dtype, ep, stream)
+    if st:
+        _check(st)
 
 
 def tir_conv2d_fused(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, groups,
                      in_dtype, out_dtype, ep=None, stream=None) -> None:
-    _check(lib().tir_conv2d_fused(_ptr(x), _ptr(w), _ptr(y), N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w,
-                                  dil_h, dil_w, groups, _code(in_dtype), _code(out_dtype), _ep_arg(ep),
-                                  _stream(stream)))
+    st = (_native or _load_native()).tir_conv2d_fused(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, groups,
+                                                         in_dtype, out_dtype, ep, stream)
+    if st:
+        _check(st)
 
 
 def tir_conv1d(x, w, y, N, L, C, K, R, stride, pad, dil, groups, in_dtype, out_dtype, ep=None, stream=None) -> None:
-    _check(lib().tir_conv1d(_ptr(x), _ptr(w), _ptr(y), N, L, C, K, R, stride, pad, dil, groups, _code(in_dtype),
-                            _code(out_dtype), _ep_arg(ep), _stream(stream)))
+    st = (_native or _load_native()).tir_conv1d(x, w, y, N, L, C, K, R, stride, pad, dil, groups, in_dtype, out_dtype, ep, stream)
+    if st:
+        _check(st)
 
 
 def tir_conv3d(x, w, y, N, D, H, W, C, K, T, R, S, stride, pad, dil, groups, in_dtype, out_dtype, ep=None, stream=None) -> None:
     """stride, pad, dil: (depth, height, width) triples."""
-    _check(lib().tir_conv3d(_ptr(x), _ptr(w), _ptr(y), N, D, H, W, C, K, T, R, S, *stride, *pad, *dil, groups,
-                            _code(in_dtype), _code(out_dtype), _ep_arg(ep), _stream(stream)))
+    st = (_native or _load_native()).tir_conv3d(x, w, y, N, D, H, W, C, K, T, R, S, *stride, *pad, *dil, groups, in_dtype, out_dtype, ep, stream)
+    if st:
+        _check(st)
 
 
 def tir_conv2d_transpose(x, w, y, N, H, W, C, K, R, S, stride, pad, dil, outpad, groups, in_dtype, out_dtype, ep=None,
                          stream=None) -> None:
     """stride, pad, dil, outpad: (height, width) pairs."""
-    _check(lib().tir_conv2d_transpose(_ptr(x), _ptr(w), _ptr(y), N, H, W, C, K, R, S, *stride, *pad, *dil, *outpad, groups,
-                                      _code(in_dtype), _code(out_dtype), _ep_arg(ep), _stream(stream)))
+    st = (_native or _load_native()).tir_conv2d_transpose(x, w, y, N, H, W, C, K, R, S, *stride, *pad, *dil, *outpad, groups, in_dtype,
+                                                             out_dtype, ep, stream)
+    if st:
+        _check(st)
 
 
 def tir_attention_status(Q, K, V, O, batch, M, N, d, scale, in_dtype, out_dtype, stream=0) -> int:
@@ -331,7 +355,9 @@ def tir_attention_status(Q, K, V, O, batch, M, N, d, scale, in_dtype, out_dtype,
 
 def tir_attention(Q, K, V, O, batch, M, N, d, scale, in_dtype, out_dtype, stream=None) -> None:
     """O[b] = softmax(scale * Q[b] K[b]^T) V[b]; Q [batch, M, d], K and V [batch, N, d], d in (64, 128)."""
-    _check(tir_attention_status(Q, K, V, O, batch, M, N, d, scale, in_dtype, out_dtype, _stream(stream)))
+    st = (_native or _load_native()).tir_attention(Q, K, V, O, batch, M, N, d, scale, in_dtype, out_dtype, stream)
+    if st:
+        _check(st)
 
 
 def tir_tune_batch_matmul(A, B, C, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, c_bs, c_rs, c_cs,

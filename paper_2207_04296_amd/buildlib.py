@@ -1,13 +1,14 @@
 """Build libtir.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
 
-``python -m paper_2207_04296_amd.buildlib`` compiles every translation unit (in parallel) and
-links ``paper_2207_04296_amd/libtir.so``.  Nothing is compiled at import time or inside tests.
+``python -m paper_2207_04296_amd.buildlib`` compiles every translation unit (in parallel), links
+``paper_2207_04296_amd/libtir.so`` and builds the CPython extension ``_native.so`` over it.  Nothing is compiled at import time or inside tests.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -16,6 +17,7 @@ CSRC = PKG / "csrc"
 INCLUDE = PKG.parent / "include"
 OBJ = PKG / "_build"
 LIB = PKG / "libtir.so"
+NATIVE = PKG / "_native.so"
 N_UNITS = 6
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -66,14 +68,20 @@ def _compile(args):
 
 
 def sources():
-    return sorted(CSRC.glob("*.hip")) + sorted(CSRC.glob("*.h")) + sorted(CSRC.glob("*.def")) + [INCLUDE / "tir.h"]
+    return sorted(CSRC.glob("*.hip")) + sorted(CSRC.glob("*.cpp")) + sorted(CSRC.glob("*.h")) + sorted(CSRC.glob("*.def")) + [INCLUDE / "tir.h"]
 
 
 def is_stale() -> bool:
-    if not LIB.exists():
+    if not LIB.exists() or not NATIVE.exists():
         return True
-    t = LIB.stat().st_mtime
+    t = min(LIB.stat().st_mtime, NATIVE.stat().st_mtime)
     return any(s.stat().st_mtime > t for s in sources())
+
+
+def _build_native() -> None:
+    """The CPython extension (host code only); it finds libtir.so beside itself."""
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-fvisibility=hidden", f"-I{sysconfig.get_paths()['include']}", f"-I{INCLUDE}",
+                    str(CSRC / "native_binding.cpp"), "-o", str(NATIVE), f"-L{PKG}", "-l:libtir.so", "-Wl,-rpath,$ORIGIN"], check=True)
 
 
 def build(verbose: bool = True, jobs: int | None = None, defines=(), lib: Path = LIB, tag: str = "") -> Path:
@@ -90,8 +98,10 @@ def build(verbose: bool = True, jobs: int | None = None, defines=(), lib: Path =
             if verbose and warn.strip():
                 print(warn, file=sys.stderr)
     objs = [str(j[1]) for j in jobs_list]
-    cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(lib), *objs]
+    cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libtir.so", "-o", str(lib), *objs]
     subprocess.run(cmd, check=True)
+    if lib == LIB:
+        _build_native()
     if verbose:
         print(f"built {lib}")
     return lib

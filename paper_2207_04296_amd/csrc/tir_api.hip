@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <atomic>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -74,6 +75,34 @@ static const Variant kVariants[] = {
 #include "tir_variants.def"
 };
 static const int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
+
+// The variants of one (dt, out, amode, bmode), in table order: a call scores its candidates, not the whole table.
+struct VariantRange {
+    const Variant* const* first;
+    int n;
+};
+static const int kModes = 8, kDtypes = 5;
+static VariantRange variants_of(int dt, int out, int amode, int bmode) {
+    struct Index {
+        const Variant* order[kNumVariants];
+        VariantRange range[kDtypes][kDtypes][kModes][kModes] = {};
+        Index() {
+            int n = 0;
+            for (int d = 0; d < kDtypes; ++d)
+                for (int o = 0; o < kDtypes; ++o)
+                    for (int a = 0; a < kModes; ++a)
+                        for (int b = 0; b < kModes; ++b) {
+                            VariantRange& r = range[d][o][a][b];
+                            r.first = order + n;
+                            for (const Variant& v : kVariants)
+                                if (v.dt == d && v.out == o && v.amode == a && v.bmode == b) order[n++] = &v;
+                            r.n = (int)(order + n - r.first);
+                        }
+        }
+    };
+    static const Index index;
+    return index.range[dt][out][amode][bmode];
+}
 
 // The depth-wise kernel is not a tile variant: one entry per dtype pair, filled on first use.
 static const Variant* depthwise_variant(int dt, int out) {
@@ -147,10 +176,12 @@ struct Choice {
 static const Choice kNoChoice = {nullptr, 1};
 static std::mutex g_tune_mu;
 static std::map<TuneKey, Choice> g_tuned;
+static std::atomic<bool> g_any_tuned{false};      // g_tuned may hold records: without one, calls do not look
 // set by the tuner around its trial launches on the calling thread: the choice to plan with
 static thread_local Choice g_trial = {nullptr, 1};
 
 static Choice tuned_lookup(const TuneKey& k) {
+    if (!g_any_tuned.load(std::memory_order_acquire)) return kNoChoice;
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tuned.find(k);
     return it == g_tuned.end() ? kNoChoice : it->second;
@@ -169,6 +200,7 @@ struct Workspace {
 };
 static std::mutex g_ws_mu;
 static std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
+static std::atomic<bool> g_any_ws{false};         // likewise for g_ws
 
 // What a plan may use for split reductions: room for partial sums and counters (bytes = 0: none, never split),
 // and the slice count a caller insists on (force > 1: only variants that can split that way are considered,
@@ -201,6 +233,7 @@ static bool split_fits(const Variant* v, int ks, int64_t batch, int64_t tiles, i
 
 // The split a launch on `stream` of the current device may use: that of its registered workspace, or none.
 static SplitLimits stream_split_limits(hipStream_t stream) {
+    if (!g_any_ws.load(std::memory_order_acquire)) return kNoSplit;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
@@ -210,14 +243,15 @@ static SplitLimits stream_split_limits(hipStream_t stream) {
     return g_ws.count(std::make_pair(dev, stream)) ? kRegisteredSplit : kNoSplit;
 }
 
-// The kernels divide by these launch constants through multiply-and-shift (see Params).
-static void set_divisors(Params& p) {
+// The kernels divide by these launch constants through multiply-and-shift (see Params); a GEMM divides by one of them.
+static void set_divisors(Params& p, bool conv) {
     auto put = [](unsigned d, unsigned* magic, int* shift) {
         const FastDiv f = make_fastdiv(d < 1 ? 1u : d);
         *magic = f.magic;
         *shift = f.shift;
     };
     put((unsigned)(kGroupM * p.tiles_n), &p.div_gw_magic, &p.div_gw_shift);
+    if (!conv) return;
     put((unsigned)p.tiles_n, &p.div_tn_magic, &p.div_tn_shift);
     put((unsigned)p.tiles_m, &p.div_tm_magic, &p.div_tm_shift);
     put((unsigned)(p.PW / 8), &p.div_pw_magic, &p.div_pw_shift);      // copy units (8 pixels) per patch row
@@ -257,22 +291,25 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
     Choice best = kNoChoice;
     double best_score = -1.0;
     const int es = elem_size(dt);
-    for (int i = 0; i < kNumVariants; ++i) {
-        const Variant* v = &kVariants[i];
-        if (v->dt != dt || v->out != out || v->amode != amode || v->bmode != bmode || v->rowb > max_rowb) continue;
-        const int64_t tiles_1 = ((M + v->bm - 1) / v->bm) * ((N + v->bn - 1) / v->bn);
+    const VariantRange candidates = variants_of(dt, out, amode, bmode);
+    for (int i = 0; i < candidates.n; ++i) {
+        const Variant* v = candidates.first[i];
+        if (v->rowb > max_rowb) continue;
+        // (extents are below 2^31: 32-bit divisions, which take a third of the time of 64-bit ones)
+        const unsigned tm_1 = ((unsigned)M + (unsigned)v->bm - 1u) / (unsigned)v->bm, tn_1 = ((unsigned)N + (unsigned)v->bn - 1u) / (unsigned)v->bn;
+        const int64_t tiles_1 = (int64_t)tm_1 * tn_1;
         const int want_ks = sl.force > 1 ? sl.force : g_force_ksplit;
         const int forced_ks = (want_ks > 1 && split_fits(v, want_ks, batch, tiles_1, K, sl)) ? want_ks : 1;
         if (sl.force > 1 && forced_ks != sl.force) continue;          // the caller insists on this split
         if (g_force_name[0] && strstr(v->name, g_force_name)) return Choice{v, forced_ks};          // testing / tuning overrides
         if (g_force_bm && v->bm == g_force_bm && v->bn == g_force_bn && v->kw == 1 && v->cw == 0) return Choice{v, forced_ks};
-        const double tm = (double)((M + v->bm - 1) / v->bm), tn = (double)((N + v->bn - 1) / v->bn);
+        const double tm = (double)tm_1, tn = (double)tn_1;
         int ks = forced_ks;
         // (the partial sums' trip through memory costs about 4 us for a 64x64 tile and grows with the tile: it pays
         // only for small tiles whose wave groups face two dozen stages or more)
         if (!want_ks && sl.bytes > 0 && v->bm * v->bn <= 64 * 64) {
-            const int64_t stages = (K * es + v->rowb - 1) / v->rowb;
-            int64_t want = stages / v->kw >= 24 ? (int64_t)kCUs / (tiles_1 * batch) : 1;
+            const int64_t stages = (K * es + v->rowb - 1) >> __builtin_ctz((unsigned)v->rowb);
+            int64_t want = stages / v->kw >= 24 && tiles_1 * batch <= (int64_t)kCUs / 2 ? (int64_t)kCUs / (tiles_1 * batch) : 1;
             if (want > stages / (8 * v->kw)) want = stages / (8 * v->kw);
             if (want > 8) want = 8;
             while (want > 1 && !split_fits(v, (int)want, batch, tiles_1, K, sl)) --want;
@@ -287,7 +324,7 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
         double score = eff * fill * (0.25 + 0.75 * intensity);
         // ring depth: stages beyond the number of K-slabs are useless; with more than one
         // workgroup per CU prefer rings that let two of them be resident (LDS <= 80 KB)
-        const int64_t nslab = (K * es + v->rowb - 1) / v->rowb;
+        const int64_t nslab = (K * es + v->rowb - 1) >> __builtin_ctz((unsigned)v->rowb);       // (64, 128 or 256 bytes)
         const int lds = (v->bm + v->bn) * v->rowb * v->nstage * v->kw;
         double depth = 1.0;
         if (v->kw > 1) {
@@ -404,7 +441,7 @@ static tir_status plan_gemm(bool need_ptrs, const void* A, const void* B, void* 
     p.a_rs = a_rs; p.a_cs = a_cs; p.b_rs = b_rs; p.b_cs = b_cs; p.c_rs = c_rs; p.c_cs = c_cs;
     p.c_fast = (c_cs == 1 && (c_rs >= N || M == 1) && fits_tile_offsets(c_rs, N, elem_size(out))) ? 1 : 0;
     if (ep) { p.bias = ep->bias; p.bias_bs = 0; p.relu = ep->relu != 0; p.scale = ep->scale; p.store_nt = ep->streaming; }
-    set_divisors(p);
+    set_divisors(p, false);
     plan->v = v;
     return TIR_OK;
 }
@@ -561,7 +598,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         p.stride_h = g.stride_h; p.stride_w = g.stride_w; p.pad_h = g.pad_h; p.pad_w = g.pad_w;
         p.tap_sign = 1; p.up_h = 1; p.up_w = 1;
     }
-    set_divisors(p);
+    set_divisors(p, true);
     plan->v = v;
     return TIR_OK;
 }
@@ -783,6 +820,7 @@ static tir_status tune_problem(MakePlan make_plan, int reps, hipStream_t stream,
     if (best.v) {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         g_tuned[base.key] = best;
+        g_any_tuned.store(true, std::memory_order_release);
         if (best_us) *best_us = (double)best_ms * 1e3;
         if (best_name) *best_name = best.v->name;
     }
@@ -917,6 +955,7 @@ tir_status tir_set_workspace(tir_stream stream_, void* ws, uint64_t bytes) {
     e = hipGetLastError();
     if (e != hipSuccess) return fail(TIR_ERR_LAUNCH, "clearing the workspace counters failed: %s", hipGetErrorString(e));
     g_ws[key] = Workspace{ws, count};
+    g_any_ws.store(true, std::memory_order_release);
     return TIR_OK;
 }
 
@@ -1041,6 +1080,7 @@ tir_status tir_tune_load(const char* path) {
         // records of another build may name variants this one does not have, or that do not fit the key
         for (int i = 0; i < kNumVariants; ++i)
             if (strcmp(kVariants[i].name, name) == 0 && record_fits(k, &kVariants[i])) {
+                g_any_tuned.store(true, std::memory_order_release);
                 g_tuned[k] = Choice{&kVariants[i], ks};      // a split that does not fit the problem is dropped when planned
                 break;
             }

@@ -2,12 +2,12 @@
 // convolution) and the tables the dispatcher picks from.
 #include "tir_attention.h"
 #include "tir_depthwise.h"
+#include "tir_launch.h"
 
 namespace tir {
 
 template <int DT, int OUT, int DH> static hipError_t launch_attn(const AttnParams& p, hipStream_t stream) {
-    hipLaunchKernelGGL((attention_kernel<DT, OUT, DH>), dim3((unsigned)(p.batch * p.tiles_m)), dim3(256), 0, stream, p);
-    return hipGetLastError();
+    return launch_kernel(&attention_kernel<DT, OUT, DH>, dim3((unsigned)(p.batch * p.tiles_m)), dim3(256), stream, p);
 }
 
 attn_launch_fn attention_launcher(int dt, int out, int dh) {
@@ -19,7 +19,7 @@ attn_launch_fn attention_launcher(int dt, int out, int dh) {
     return nullptr;
 }
 
-template <int DT, int OUT, bool STREAM> static void launch_dw_as(const Params& p, hipStream_t stream) {
+template <int DT, int OUT, bool STREAM> static hipError_t launch_dw_as(const Params& p, hipStream_t stream) {
     constexpr int VEC = 16 / elem_size(DT);
     constexpr int PP = 256 / (kDwChannels / VEC);
     dim3 grid((unsigned)((p.M + kDwPixPerThread * PP - 1) / (kDwPixPerThread * PP)), (unsigned)((p.Cin + kDwChannels - 1) / kDwChannels));
@@ -27,16 +27,14 @@ template <int DT, int OUT, bool STREAM> static void launch_dw_as(const Params& p
         // four adjacent pixels per thread
         const long long groups = (long long)p.batch_imgs * p.P * ((p.Q + kDwBlockPix - 1) / kDwBlockPix);
         grid.x = (unsigned)((groups + PP - 1) / PP);
-        if (p.stride_w == 1) hipLaunchKernelGGL((depthwise3x3_blocked_kernel<DT, OUT, 1, STREAM>), grid, dim3(256), 0, stream, p);
-        else hipLaunchKernelGGL((depthwise3x3_blocked_kernel<DT, OUT, 2, STREAM>), grid, dim3(256), 0, stream, p);
-    } else if (p.R == 3 && p.S == 3) hipLaunchKernelGGL((depthwise_kernel<DT, OUT, true, STREAM>), grid, dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((depthwise_kernel<DT, OUT, false, STREAM>), grid, dim3(256), 0, stream, p);
+        return launch_kernel(p.stride_w == 1 ? &depthwise3x3_blocked_kernel<DT, OUT, 1, STREAM> : &depthwise3x3_blocked_kernel<DT, OUT, 2, STREAM>, grid,
+                             dim3(256), stream, p);
+    }
+    return launch_kernel(p.R == 3 && p.S == 3 ? &depthwise_kernel<DT, OUT, true, STREAM> : &depthwise_kernel<DT, OUT, false, STREAM>, grid, dim3(256), stream, p);
 }
 
 template <int DT, int OUT> static hipError_t launch_dw(const Params& p, hipStream_t stream) {
-    if (p.store_nt) launch_dw_as<DT, OUT, true>(p, stream);
-    else launch_dw_as<DT, OUT, false>(p, stream);
-    return hipGetLastError();
+    return p.store_nt ? launch_dw_as<DT, OUT, true>(p, stream) : launch_dw_as<DT, OUT, false>(p, stream);
 }
 
 dw_launch_fn depthwise_launcher(int dt, int out) {

@@ -102,8 +102,7 @@ struct FastDiv {
 inline FastDiv make_fastdiv(unsigned d) {
     FastDiv f = {0u, 0};
     if (d <= 1) return f;
-    int s = 0;
-    while ((1ull << s) < d) ++s;
+    const int s = 32 - __builtin_clz(d - 1);          // ceil(log2 d)
     f.magic = (unsigned)(((1ull << (32 + s)) / d) + 1ull - (1ull << 32));
     f.shift = s;
     return f;

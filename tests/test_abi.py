@@ -372,3 +372,20 @@ def test_variant_table_is_what_its_generator_writes():
     assert gen.render() == text, "run python paper_2207_04296_amd/csrc/gen_variants.py"
     names = re.findall(r'^V\d+\("([^"]+)"', text, flags=re.M)
     assert len(names) == len(set(names)) and len(names) > 600
+
+
+@pytest.mark.parametrize("args,exc", [
+    ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", None, 0), None),                    # zero-sized: TIR_OK
+    ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, B.TIR_F16, B.TIR_F32, B.Epilogue(), 0), None),    # codes, an epilogue
+    ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f17", "f32", None, 0), KeyError),
+    ((FAKE, "A", FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", None, 0), AttributeError),
+    ((FAKE, FAKE, FAKE, 0.5, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", None, 0), TypeError),
+    ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", 3, 0), TypeError),
+    ((FAKE, FAKE, FAKE, -1, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", None, 0), B.TirError),
+])
+def test_native_binding_converts_and_checks_its_arguments(args, exc):
+    if exc is None:
+        assert B.tir_gemm_fused(*args) is None
+    else:
+        with pytest.raises(exc):
+            B.tir_gemm_fused(*args)
