@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(256) clear_counters_kernel(unsigned* count, in
 static bool split_fits(const Variant* v, int ks, int64_t batch, int64_t tiles, int64_t K, const SplitLimits& sl) {
     if (ks == 1) return true;
     if (ks < 1 || ks > 64 || sl.bytes <= 0) return false;
-    if (v->amode != A_KMAJOR && v->amode != A_CONV && v->amode != A_CONVX) return false;      // the fast kernel only
+    if (v->amode != A_KMAJOR && v->amode != A_MMAJOR && v->amode != A_CONV && v->amode != A_CONVX) return false;      // the fast kernel only
     if (v->bm * v->bn > kSplitMaxTile) return false;
     const int64_t stages = (K * elem_size(v->dt) + v->rowb - 1) / v->rowb;
     const int64_t per = (stages + ks - 1) / ks;
@@ -417,6 +417,8 @@ static tir_status plan_gemm(bool need_ptrs, const void* A, const void* B, void* 
     // rows past the edge into out-of-range reads; byte offsets inside one tile must fit 31 bits)
     if (a_cs == 1 && k_vec && a_rs % vec == 0 && a_bs % vec == 0 && aligned(A, 16) && (a_rs >= K || M == 1) &&
         fits_tile_offsets(a_rs, K, es)) amode = A_KMAJOR;
+    else if (a_rs == 1 && M % vec == 0 && a_cs % vec == 0 && a_bs % vec == 0 && aligned(A, 16) && a_cs >= M &&
+             fits_tile_offsets(a_cs, M, es)) amode = A_MMAJOR;
     if (b_rs == 1 && k_vec && b_cs % vec == 0 && b_bs % vec == 0 && aligned(B, 16) && (b_cs >= K || N == 1) &&
         fits_tile_offsets(b_cs, K, es)) bmode = B_KMAJOR;
     else if (b_cs == 1 && N % vec == 0 && b_rs % vec == 0 && b_bs % vec == 0 && aligned(B, 16) && b_rs >= N &&
@@ -1193,7 +1195,7 @@ tir_status tir_gemm_split_static(const void* A, const void* B, void* C, int64_t 
     tir_status st = plan_gemm(true, A, B, C, 1, M, N, K, 0, a_rs, a_cs, 0, b_rs, b_cs, 0, c_rs, c_cs, (int)in, (int)out, ep, sl, &plan);
     if (st == TIR_ERR_UNSUPPORTED && plan.key.kind == 0 && !plan.v) {
         // no variant splits this problem `slices` ways inside the static scratch: say which limit it is
-        if (plan.key.amode != A_KMAJOR)
+        if (plan.key.amode != A_KMAJOR && plan.key.amode != A_MMAJOR)
             return fail(TIR_ERR_UNSUPPORTED, "tir_gemm_split_static: operand strides / alignment need the general kernel, which has no split reduction");
         const SplitLimits any = {(int64_t)1 << 60, (int64_t)1 << 40, slices};
         const Choice c = pick(plan.key.dt, plan.key.out, plan.key.amode, plan.key.bmode, 1, M, N, K, any);

@@ -161,8 +161,37 @@ template <int ROWB> __device__ __forceinline__ int kmajor_off(int row, int chunk
 
 // XOR applied to the byte offset inside k-row `k` of an N-major LDS tile so that the k-rows one
 // transposing read touches fall into different banks.
-template <class C> __device__ __forceinline__ int nmajor_xor(int k) { return ((k / C::RPW) % C::NSEG) * C::SEG; }
+template <class T> __device__ __forceinline__ int nmajor_xor(int k) { return ((k / T::RPW) % T::NSEG) * T::SEG; }
 
+// MFMA fragment of k-step kk for the 32 rows (of A) or columns (of B) starting at w0, from an N-major LDS tile T.
+template <class T, int ES> __device__ __forceinline__ uint4 read_nmajor(const char* tile, int kk, int w0, int blk, int s16) {
+    if constexpr (ES == 2) {
+        // The transposing read works on groups of 16 lanes.  Group `blk` covers columns 16*(blk&1).. of the 32-wide block
+        // and the k-group blk>>1; lane s fetches 4 values of k-row (s>>2) at columns 4*(s&3)..; afterwards lane s holds
+        // 4 consecutive k of column s.
+        const int w = w0 + 16 * (blk & 1) + 4 * (s16 & 3);
+        i16x4 h[2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            const int k = kk * 16 + 8 * (blk >> 1) + 4 * hh + (s16 >> 2);
+            const char* ptr = tile + k * T::ROW + ((w * 2) ^ nmajor_xor<T>(k));
+            h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(TIR_LDS_PTR(i16x4, ptr));
+        }
+        const i32x2 lo = __builtin_bit_cast(i32x2, h[0]), hi = __builtin_bit_cast(i32x2, h[1]);
+        return make_uint4((unsigned)lo[0], (unsigned)lo[1], (unsigned)hi[0], (unsigned)hi[1]);
+    } else {
+        // int8: lane s fetches 8 values of k-row (s>>1) at columns 8*(s&1)..
+        const int w = w0 + 16 * (blk & 1) + 8 * (s16 & 1);
+        i32x2 h[2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            const int k = kk * 32 + 16 * (blk >> 1) + 8 * hh + (s16 >> 1);
+            const char* ptr = tile + k * T::ROW + (w ^ nmajor_xor<T>(k));
+            h[hh] = __builtin_amdgcn_ds_read_tr8_b64_v2i32(TIR_LDS_PTR(i32x2, ptr));
+        }
+        return make_uint4((unsigned)h[0][0], (unsigned)h[0][1], (unsigned)h[1][0], (unsigned)h[1][1]);
+    }
+}
 
 constexpr unsigned kOutOfRange = 0x80000000u;   // buffer offset no descriptor of this library reaches
 
@@ -265,7 +294,7 @@ __device__ __forceinline__ void wait_vmcnt_upto(int n) {
 // MFMA stage: fragment addresses, fragment reads, accumulate.
 // ---------------------------------------------------------------------------------------------
 template <class C> struct Frag {
-    int a_base, b_base, sw, g, blk, s16, wn_off;
+    int a_base, b_base, sw, g, blk, s16, wm_off, wn_off;
     __device__ __forceinline__ Frag(int lane, int wm, int wn) {
         const int l31 = lane & 31;
         g = lane >> 5;
@@ -274,9 +303,11 @@ template <class C> struct Frag {
         sw = kmajor_swz<C::ROWB>(l31);   // the swizzle repeats every 16 rows: same for every 32-row block
         blk = lane >> 4;
         s16 = lane & 15;
+        wm_off = wm * C::TM;
         wn_off = wn * C::TN;
     }
     __device__ __forceinline__ uint4 read_a1(const char* sa, int kk, int i) const {
+        if constexpr (C::A_NM) return read_nmajor<typename C::ATile, C::ES>(sa, kk, wm_off + i * 32, blk, s16);
         const int col = ((2 * kk + g) ^ sw) << 4;
         return *(const uint4*)(sa + a_base + i * 32 * C::ROWB + col);
     }
@@ -289,42 +320,9 @@ template <class C> struct Frag {
         for (int j = 0; j < C::NI; ++j) bf[j] = read_b1(sb, kk, j);
     }
     __device__ __forceinline__ uint4 read_b1(const char* sb, int kk, int j) const {
-        uint4 out;
-        if constexpr (C::BMODE == B_NMAJOR) {
-            {
-                if constexpr (C::ES == 2) {
-                    // The transposing read works on groups of 16 lanes.  Group `blk` covers columns
-                    // 16*(blk&1).. of the 32-wide block and the k-group blk>>1; lane s fetches 4 values
-                    // of k-row (s>>2) at columns 4*(s&3)..; afterwards lane s holds 4 consecutive k of
-                    // column s.
-                    const int nloc = wn_off + j * 32 + 16 * (blk & 1) + 4 * (s16 & 3);
-                    i16x4 h[2];
-#pragma unroll
-                    for (int hh = 0; hh < 2; ++hh) {
-                        const int k = kk * 16 + 8 * (blk >> 1) + 4 * hh + (s16 >> 2);
-                        const char* ptr = sb + k * C::BROW + ((nloc * 2) ^ nmajor_xor<C>(k));
-                        h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(TIR_LDS_PTR(i16x4, ptr));
-                    }
-                    const i32x2 lo = __builtin_bit_cast(i32x2, h[0]), hi = __builtin_bit_cast(i32x2, h[1]);
-                    out = make_uint4((unsigned)lo[0], (unsigned)lo[1], (unsigned)hi[0], (unsigned)hi[1]);
-                } else {
-                    // int8: lane s fetches 8 values of k-row (s>>1) at columns 8*(s&1)..
-                    const int nloc = wn_off + j * 32 + 16 * (blk & 1) + 8 * (s16 & 1);
-                    i32x2 h[2];
-#pragma unroll
-                    for (int hh = 0; hh < 2; ++hh) {
-                        const int k = kk * 32 + 16 * (blk >> 1) + 8 * hh + (s16 >> 1);
-                        const char* ptr = sb + k * C::BROW + (nloc ^ nmajor_xor<C>(k));
-                        h[hh] = __builtin_amdgcn_ds_read_tr8_b64_v2i32(TIR_LDS_PTR(i32x2, ptr));
-                    }
-                    out = make_uint4((unsigned)h[0][0], (unsigned)h[0][1], (unsigned)h[1][0], (unsigned)h[1][1]);
-                }
-            }
-        } else {
-            const int col = ((2 * kk + g) ^ sw) << 4;
-            out = *(const uint4*)(sb + b_base + j * 32 * C::ROWB + col);
-        }
-        return out;
+        if constexpr (C::B_NM) return read_nmajor<typename C::BTile, C::ES>(sb, kk, wn_off + j * 32, blk, s16);
+        const int col = ((2 * kk + g) ^ sw) << 4;
+        return *(const uint4*)(sb + b_base + j * 32 * C::ROWB + col);
     }
 };
 
@@ -474,6 +472,29 @@ __device__ __forceinline__ void store_tile_phase(const Params& p, long long bz, 
     }
 }
 
+// Copy of an N-major tile (BK k-rows of the operand, `width` of them valid from the tile's first column, `ld` elements apart):
+// the copying threads' i-th pass covers 16-byte chunks i*CT .. of the tile (k-rows of RC chunks, any count).  Columns past the
+// operand's edge are switched off per lane; k-rows past K start beyond the stage's descriptor (ld >= extent: the host checks).
+template <class T, int IT, int CT, int ES>
+__device__ __forceinline__ void nmajor_offsets(unsigned (&off)[IT], int tid, int w0, int extent, long long ld) {
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const int chunk = i * CT + tid;
+        const int k = chunk / T::RC, pc = chunk - k * T::RC;
+        const int lb = (pc * 16) ^ nmajor_xor<T>(k);        // logical byte inside the k-row
+        off[i] = (w0 + lb / ES < extent) ? (unsigned)k * (unsigned)(ld * ES) + lb : kOutOfRange;
+    }
+}
+// Descriptor of one stage: it covers exactly the stage's BK k-rows (32-bit size, bounded by the host for 128 rows), or what
+// is left of the operand in the last stage, so that rows past K stay out of range.
+template <int ES, int BK>
+__device__ __forceinline__ i32x4 nmajor_rsrc(const char* base, long long bytes, long long ld, int width, int K, int stage, bool live) {
+    const long long step = (long long)BK * ld * ES;        // bytes the base advances per stage
+    const unsigned window = (unsigned)(((long long)(BK - 1) * ld + width) * ES);
+    const unsigned left = (stage + 1) * BK <= K ? window : (unsigned)(bytes - stage * step);
+    return make_rsrc32(base + stage * step, live ? left : 0u);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Fast kernel: vector copy modes, global -> LDS without a register hop, NSTAGE-deep copy ring.
 //
@@ -495,12 +516,12 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
     typedef typename InTraits<C::DT>::acc_t acc_t;
     constexpr int ES = C::ES, VEC = C::VEC, BK = C::BK, ROWB = C::ROWB, NSTAGE = C::NSTAGE, KSTEPS = C::KSTEPS;
     constexpr int L = C::A_IT + C::B_IT;      // copy instructions per wave and stage
-    static_assert(C::AMODE == A_KMAJOR || C::AMODE == A_CONV || C::AMODE == A_CONVX, "");
+    static_assert(C::AMODE == A_KMAJOR || C::AMODE == A_MMAJOR || C::AMODE == A_CONV || C::AMODE == A_CONVX, "");
     static_assert(C::BMODE == B_KMAJOR || C::BMODE == B_NMAJOR, "");
     static_assert((NSTAGE - 2) * L <= 63, "vmcnt range");
 
     __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
-    prefetch_args(p, C::AMODE != A_KMAJOR);
+    prefetch_args(p, C::AMODE == A_CONV || C::AMODE == A_CONVX);
 
     // reduction group kgrp owns the stages s with s % KW == kgrp; inside the group, thread tid of SUB.
     // With copy waves (CW > 0) the waves past the multiplying ones only copy: thread tid of CT, wave `wave` of CW.
@@ -575,6 +596,10 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
 #pragma unroll
         for (int i = 0; i < C::A_IT; ++i)
             a_off[i] = (unsigned)(a_r0 + i * C::K_RSTEP) * (unsigned)(p.a_rs * ES) + a_lc * 16;
+    } else if constexpr (C::AMODE == A_MMAJOR) {
+        nmajor_offsets<typename C::ATile, C::A_IT, C::CT, ES>(a_off, tid, m0, p.M, p.a_cs);
+        a_base = Ab + (long long)m0 * ES;
+        a_bytes = ((long long)(p.K - 1) * p.a_cs + (p.M - m0)) * ES;
     } else if constexpr (C::AMODE == A_CONVX) {
         // ReIndex with a depth axis: row m of A_t is output pixel (img, od, op, oq) = unfuse(m); keep the
         // pixel index of the image's first pixel and the (possibly up-sampled) coordinates of tap (0,0,0)
@@ -631,7 +656,6 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
     unsigned b_off[C::B_IT];
     const char* b_base = Bb;
     long long b_bytes = 0;
-    long long b_step = ROWB;    // bytes the base advances per stage
     if constexpr (C::BMODE == B_KMAJOR) {
         b_base = Bb + (long long)n0 * p.b_cs * ES;
         const int rows = p.N - n0 < C::BN ? p.N - n0 : C::BN;
@@ -640,19 +664,9 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
         for (int i = 0; i < C::B_IT; ++i)
             b_off[i] = (unsigned)(b_r0 + i * C::K_RSTEP) * (unsigned)(p.b_cs * ES) + b_lc * 16;
     } else {
-        // k-rows of the stage; rows past K start beyond the descriptor (b_rs >= N is checked by the
-        // host), columns past N are switched off per lane
+        nmajor_offsets<typename C::BTile, C::B_IT, C::CT, ES>(b_off, tid, n0, p.N, p.b_rs);
         b_base = Bb + (long long)n0 * ES;
         b_bytes = ((long long)(p.K - 1) * p.b_rs + (p.N - n0)) * ES;
-        b_step = (long long)BK * p.b_rs * ES;
-#pragma unroll
-        for (int i = 0; i < C::B_IT; ++i) {
-            // the copying threads' i-th pass covers 16-byte chunks i*CT .. of the tile (k-rows of B_RC chunks, any count)
-            const int chunk = i * C::CT + tid;
-            const int k = chunk / C::B_RC, pc = chunk - k * C::B_RC;
-            const int lb = (pc * 16) ^ nmajor_xor<C>(k);        // logical byte inside the k-row
-            b_off[i] = (n0 + lb / ES < p.N) ? (unsigned)k * (unsigned)(p.b_rs * ES) + lb : kOutOfRange;
-        }
     }
 
     // Per-stage copy state: descriptors (SGPRs) and, for the convolution, this stage's offsets and
@@ -722,6 +736,10 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
 #pragma unroll
                 for (int i = 0; i < C::A_IT; ++i) a_off[i] = kv ? a_off[i] : kOutOfRange;
             }
+#pragma unroll
+            for (int i = 0; i < C::A_IT; ++i) a_voff[i] = a_off[i];
+        } else if constexpr (C::AMODE == A_MMAJOR) {
+            ra = nmajor_rsrc<ES, BK>(a_base, a_bytes, p.a_cs, p.M - m0, p.K, stage, live);
 #pragma unroll
             for (int i = 0; i < C::A_IT; ++i) a_voff[i] = a_off[i];
         } else if constexpr (C::AMODE == A_CONVX) {
@@ -806,11 +824,7 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
                 for (int i = 0; i < C::B_IT; ++i) b_off[i] = kv ? b_off[i] : kOutOfRange;
             }
         } else {
-            // a stage reads BK k-rows: the descriptor covers exactly those (32-bit size, bounded by the host for
-            // 128 rows), or what is left of B in the last stage, so that rows past K stay out of range
-            const unsigned b_window = (unsigned)(((long long)(BK - 1) * p.b_rs + (p.N - n0)) * ES);
-            const unsigned b_left = (stage + 1) * BK <= p.K ? b_window : (unsigned)(b_bytes - stage * b_step);
-            rb = make_rsrc32(b_base + stage * b_step, live ? b_left : 0u);
+            rb = nmajor_rsrc<ES, BK>(b_base, b_bytes, p.b_rs, p.N - n0, p.K, stage, live);
         }
     };
     // u-th copy instruction of the prepared stage (u < L): A chunks first, then B chunks.

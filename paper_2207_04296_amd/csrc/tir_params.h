@@ -16,6 +16,9 @@ enum : int {
     A_CONV_GENERIC = 3,  // implicit im2col, element-wise (C/groups not a multiple of the vector)
     A_CONV_PATCH = 4,    // convolution reading its taps from an LDS-resident input patch (128 B per pixel)
     A_DEPTHWISE = 6,     // depth-wise 2-D convolution (one filter per channel): direct kernel, no matrix intrinsic
+    // A stored [k][x], x contiguous (a transposed A: weight gradients dW = X^T dY); transposed on the LDS read like B_NMAJOR.
+    // Before it existed such calls took the element-wise kernel: 768x3072x2048 bf16 175.6 us, now 15.0
+    A_MMAJOR = 7,
     A_CONVX = 5          // implicit im2col with the general coordinate decode: a depth axis (3-D convolution) and the
                          // transposed form (taps step backwards, only every up-th coordinate is an input pixel)
 };
@@ -153,6 +156,22 @@ __host__ __device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n,
 constexpr int const_gcd(int a, int b) { return b == 0 ? a : const_gcd(b, a % b); }
 constexpr int elem_size(int dt) { return dt == DT_I8 ? 1 : (dt == DT_F16 || dt == DT_BF16) ? 2 : 4; }
 
+// LDS tile of an operand whose non-reduction axis is contiguous ("N-major": BK k-rows of W elements).  A transposing read
+// touches 256 / SEG consecutive k-rows at one SEG-byte segment each (SEG: the bytes one half-wave reads per k-row); they must
+// fall into different SEG-byte groups of the 256-byte bank sweep.  Row r starts in group r * (ROW / SEG) mod (256 / SEG):
+// that visits 256 / SEG / NSEG groups, with period RPW, where NSEG = gcd(ROW / SEG, 256 / SEG); XORing (r / RPW) mod NSEG
+// into the segment index spreads the rows over the rest.  (ROW a multiple of 256: all rows start alike and the XOR does
+// everything; ROW / SEG odd, e.g. 96 fp16 columns: the stride alone does.)
+template <int W, int ES> struct NMajorTile {
+    static constexpr int ROW = W * ES;
+    static constexpr int RC = ROW / 16;             // 16-byte chunks per k-row
+    static constexpr int SEG = (ES == 2) ? 64 : 32;
+    static constexpr int SEGS_PER_SWEEP = 256 / SEG, SEGS_PER_ROW = ROW / SEG;
+    static constexpr int NSEG = const_gcd(SEGS_PER_ROW, SEGS_PER_SWEEP);
+    static constexpr int RPW = SEGS_PER_SWEEP / NSEG;
+    static constexpr bool OK = ROW % SEG == 0 && ROW % (NSEG * SEG) == 0;      // whole segments, XOR closed inside a row
+};
+
 // Compile-time shape of one kernel variant: BM x BN workgroup tile, WM x WN waves, ROWB bytes of k
 // per LDS row and stage (128 or 64), NSTAGE LDS stages in the copy ring, KW reduction groups: KW
 // sets of WM x WN waves share the output tile, group g reduces the stages s with s % KW == g through
@@ -183,23 +202,14 @@ struct Cfg {
     static constexpr int A_IT = BM * RCH / CT;    // 16-byte chunks per copying thread per stage
     static constexpr int B_IT = BN * RCH / CT;
     static constexpr int K_RSTEP = CT / RCH;          // K-major rows covered by one pass of the copying threads
-    // N-major B tile in LDS: BK k-rows of BN*ES bytes
-    static constexpr int BROW = BN * ES;
-    static constexpr int B_RC = BROW / 16;          // 16-byte chunks per k-row
-    static constexpr int SEG = (ES == 2) ? 64 : 32; // bytes one half-wave reads per k-row on the transposing read
-    // A transposing read touches 256 / SEG consecutive k-rows at one SEG-byte segment each; they must fall into
-    // different SEG-byte groups of the 256-byte bank sweep.  Row r starts in group r * (BROW / SEG) mod (256 / SEG):
-    // that visits 256 / SEG / NSEG groups, with period RPW, where NSEG = gcd(BROW / SEG, 256 / SEG); XORing
-    // (r / RPW) mod NSEG into the segment index spreads the rows over the rest.  (BROW a multiple of 256: all rows
-    // start alike and the XOR does everything; BROW / SEG odd, e.g. 96 fp16 columns: the stride alone does.)
-    static constexpr int SEGS_PER_SWEEP = 256 / SEG, SEGS_PER_ROW = BROW / SEG;
-    static constexpr int NSEG = const_gcd(SEGS_PER_ROW, SEGS_PER_SWEEP);
-    static constexpr int RPW = SEGS_PER_SWEEP / NSEG;
+    static constexpr bool A_NM = AMODE == A_MMAJOR, B_NM = BMODE == B_NMAJOR;      // N-major LDS tiles
+    typedef NMajorTile<BM, ES> ATile;
+    typedef NMajorTile<BN, ES> BTile;
     static_assert(ROWB == 256 || ROWB == 128 || ROWB == 64, "");
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be a multiple of the 32x32 MFMA block");
     static_assert((BM * RCH) % CT == 0 && (BN * RCH) % CT == 0, "copy must divide evenly");
     static_assert(K_RSTEP % 16 == 0, "the K-major swizzle must repeat with the copy's row step");
-    static_assert(BMODE != B_NMAJOR || (BROW % SEG == 0 && BROW % (NSEG * SEG) == 0), "N-major tile: whole segments, XOR closed inside a row");
+    static_assert((!A_NM || ATile::OK) && (!B_NM || BTile::OK), "N-major tile: whole segments, XOR closed inside a row");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of one CU");
     static_assert(KW >= 1 && KW <= 2 && THREADS <= 1024 && (CW == 0 || KW == 1), "");
     static_assert((KW - 1) * BM * BN * 4 <= LDS_BYTES, "the partial sums of the other groups must fit the rings");

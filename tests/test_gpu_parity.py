@@ -389,6 +389,42 @@ def test_every_variant_on_short_reductions(B, oracle, dtype, out):
         B.tir_debug_force_variant("")
 
 
+@pytest.mark.parametrize("dtype,out", [("f16", "f32"), ("bf16", "bf16"), ("i8", "i32")])
+def test_transposed_a_through_every_variant(B, oracle, dtype, out):
+    """A stored [K, M] (weight gradients): extents ragged against every tile, a K tail shorter than a stage, one stage,
+    reductions shorter and longer than the copy rings; B row-major and transposed."""
+    import torch
+    names = B.tir_debug_variant_names()
+    vec = 16 if dtype == "i8" else 8
+    dist = "i" if dtype == "i8" else "u"
+    try:
+        for (M, N, K) in [(39 * vec, 24 * vec, 49 * vec), (vec, 5 * vec, vec), (9 * vec, 70, 17 * vec), (17 * vec, vec, 200 * vec + 3)]:
+            for trans_b in (False, True):
+                ok = (K if trans_b else N) % vec == 0
+                a_bits = I.make_tensor(dtype, dist, 8600 + M, (K, M))
+                b_bits = I.make_tensor(dtype, dist, 8601 + N, (N, K) if trans_b else (K, N))
+                b_rs, b_cs = (1, K) if trans_b else (N, 1)
+                ref, S = oracle.gemm(dtype, a_bits, b_bits, M, N, K, 1, M, b_rs, b_cs)
+                if out == "bf16":
+                    S = S + 2.0 ** -8 * np.abs(ref) / 2e-3
+                a, b = B.to_device(a_bits, dtype), B.to_device(b_bits, dtype)
+                suffix = "_am_bk" if trans_b else "_am_bn"
+                todo = [n for n in names if n.startswith(f"{dtype}_{out}_") and n.endswith(suffix)] if ok else [""]
+                assert todo
+                for name in todo:
+                    B.tir_debug_force_variant(name)
+                    chosen = B.tir_gemm_variant(1, M, N, K, 1, M, b_rs, b_cs, N, 1, dtype, out)
+                    assert chosen.split("/")[0] == name or not ok
+                    _say(f"A^T {M}x{N}x{K} {chosen}")
+                    c = B.empty_out((M, N), out)
+                    c.fill_(float("nan")) if out != "i32" else c.fill_(-123456789)
+                    B.tir_gemm(a, b, c, M, N, K, 1, M, b_rs, b_cs, N, 1, dtype, out)
+                    torch.cuda.synchronize()
+                    PT.assert_close(PT.gpu_to_f64(c), ref, S, f"A^T {M}x{N}x{K} via {name or 'the automatic choice'}")
+    finally:
+        B.tir_debug_force_variant("")
+
+
 def test_prepared_calls_launch_what_run_workload_launches(B, oracle):
     """binding.prepare_workload marshals once and launches per call: a GEMM, a batched matmul and a fused convolution,
     each launched twice from its prepared call (the second time over a poisoned output), against the oracle."""
