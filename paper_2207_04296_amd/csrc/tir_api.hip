@@ -81,7 +81,7 @@ struct VariantRange {
     const Variant* const* first;
     int n;
 };
-static const int kModes = 8, kDtypes = 5;
+static const int kModes = 10, kDtypes = 5;
 static VariantRange variants_of(int dt, int out, int amode, int bmode) {
     struct Index {
         const Variant* order[kNumVariants];
@@ -291,6 +291,7 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
     Choice best = kNoChoice;
     double best_score = -1.0;
     const int es = elem_size(dt);
+    const bool staged = amode == A_UK || amode == A_UM;
     const VariantRange candidates = variants_of(dt, out, amode, bmode);
     for (int i = 0; i < candidates.n; ++i) {
         const Variant* v = candidates.first[i];
@@ -328,9 +329,10 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
         const int lds = (v->bm + v->bn) * v->rowb * v->nstage * v->kw;
         double depth = 1.0;
         if (v->kw > 1) {
-            // two reduction groups pay for the exchange of partial sums: only for small tiles in a single
-            // round of workgroups (nothing else on the CU hides the copy latency) facing a long reduction
-            if (tiles > kCUs || nslab < 4 * v->kw || v->bm * v->bn > 64 * 64) continue;
+            // reduction groups pay for the exchange of partial sums: only for small tiles in a single
+            // round of workgroups (nothing else on the CU hides the copy latency) facing a long reduction.  Operands staged
+            // through registers have less in flight and gain earlier (500x501x503 fp16: 6.9 us, 5.6 with four groups).
+            if (tiles > kCUs || nslab < (staged ? 2 : 4) * v->kw || v->bm * v->bn > 64 * 64) continue;
             depth += 0.05;
         }
         // copy waves pay off once a stage is worth the extra waves: measured -8 .. -17 % on 128x128 and larger
@@ -423,7 +425,14 @@ static tir_status plan_gemm(bool need_ptrs, const void* A, const void* B, void* 
         fits_tile_offsets(b_cs, K, es)) bmode = B_KMAJOR;
     else if (b_cs == 1 && N % vec == 0 && b_rs % vec == 0 && b_bs % vec == 0 && aligned(B, 16) && b_rs >= N &&
              fits_tile_offsets(b_rs, N, es)) bmode = B_NMAJOR;
-    if (amode == A_GENERIC || bmode == B_GENERIC) { amode = A_GENERIC; bmode = B_GENERIC; }
+    if (amode == A_GENERIC || bmode == B_GENERIC) {
+        // Unaligned rows: both operands through registers, each along its contiguous axis (k where both are), which must hold
+        // one vector.  Anything else - no unit stride, or fewer elements than a vector - is loaded element by element.
+        const int ua = a_cs == 1 && K >= vec && fits_tile_offsets(a_rs, K, es) ? A_UK : a_rs == 1 && M >= vec && fits_tile_offsets(a_cs, M, es) ? A_UM : A_GENERIC;
+        const int ub = b_rs == 1 && K >= vec && fits_tile_offsets(b_cs, K, es) ? B_UK : b_cs == 1 && N >= vec && fits_tile_offsets(b_rs, N, es) ? B_UN : B_GENERIC;
+        amode = ua != A_GENERIC && ub != B_GENERIC ? ua : A_GENERIC;
+        bmode = amode != A_GENERIC ? ub : B_GENERIC;
+    }
 
     plan->key = TuneKey{0, in, out, amode, bmode, batch, M, N, K, 0};
     plan->patch_ok = false;

@@ -17,6 +17,8 @@ template <class C> hipError_t launch_cfg(const Params& p, hipStream_t stream) {
         return launch_kernel(&conv_patch_kernel<C::DT, C::OUT>, grid, dim3(512), stream, p);
     } else if constexpr (C::AMODE == A_GENERIC || C::AMODE == A_CONV_GENERIC)
         return launch_kernel(&contract_staged_kernel<C>, grid, dim3(C::THREADS), stream, p);
+    else if constexpr (C::AMODE == A_UK || C::AMODE == A_UM)
+        return launch_kernel(&contract_unaligned_kernel<C>, grid, dim3(C::THREADS), stream, p);
     else {
         grid.z = (unsigned)p.ksplit;
         return launch_kernel(&contract_direct_kernel<C>, grid, dim3(C::THREADS), stream, p);

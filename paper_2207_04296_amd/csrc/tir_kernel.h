@@ -472,6 +472,52 @@ __device__ __forceinline__ void store_tile_phase(const Params& p, long long bz, 
     }
 }
 
+// Partial sums of the reduction groups (KW > 1) meet in LDS: every copy has landed and, after the barrier, every wave is past
+// its last fragment read; groups 1 .. KW-1 write their accumulators, group 0 adds them in order.  True for the waves that go on
+// to store the tile.
+template <class C, class acc_t>
+__device__ __forceinline__ bool sum_groups(char* smem, int wave, int lane, int kgrp, acc_t (&acc)[C::MI][C::NI]) {
+    if constexpr (C::KW > 1) {
+        typedef typename std::conditional<std::is_same<acc_t, f32x16>::value, float, int>::type acc_e;
+        typedef acc_e acc_e4 __attribute__((ext_vector_type(4)));
+        constexpr int WAVE_BYTES = C::MI * C::NI * 4096;
+        char* const mine = smem + wave * WAVE_BYTES;
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (kgrp != 0) {
+            acc_e4* xch = (acc_e4*)(mine + (kgrp - 1) * (C::WM * C::WN * WAVE_BYTES));
+#pragma unroll
+            for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+                for (int j = 0; j < C::NI; ++j)
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        acc_e4 v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][r4 * 4 + e];
+                        xch[((i * C::NI + j) * 4 + r4) * 64 + lane] = v;
+                    }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (kgrp != 0) return false;
+#pragma unroll
+        for (int k = 1; k < C::KW; ++k) {
+            const acc_e4* xch = (const acc_e4*)(mine + (k - 1) * (C::WM * C::WN * WAVE_BYTES));
+#pragma unroll
+            for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+                for (int j = 0; j < C::NI; ++j)
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        const acc_e4 v = xch[((i * C::NI + j) * 4 + r4) * 64 + lane];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][j][r4 * 4 + e] += v[e];
+                    }
+        }
+    }
+    return true;
+}
+
 // Copy of an N-major tile (BK k-rows of the operand, `width` of them valid from the tile's first column, `ld` elements apart):
 // the copying threads' i-th pass covers 16-byte chunks i*CT .. of the tile (k-rows of RC chunks, any count).  Columns past the
 // operand's edge are switched off per lane; k-rows past K start beyond the stage's descriptor (ld >= extent: the host checks).
@@ -973,41 +1019,7 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
         // (nothing is in flight any more: the last iterations waited for every copy)
     }
 
-    if constexpr (C::KW > 1) {
-        // The groups' partial sums meet in LDS (every copy has landed and, after the barrier, every
-        // wave is past its last fragment read): group 1 writes its accumulators, group 0 adds and stores.
-        typedef typename std::conditional<std::is_same<acc_t, f32x16>::value, float, int>::type acc_e;
-        typedef acc_e acc_e4 __attribute__((ext_vector_type(4)));
-        acc_e4* xch = (acc_e4*)(smem + wave * (C::MI * C::NI * 4096));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (kgrp != 0) {
-#pragma unroll
-            for (int i = 0; i < C::MI; ++i)
-#pragma unroll
-                for (int j = 0; j < C::NI; ++j)
-#pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        acc_e4 v;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][r4 * 4 + e];
-                        xch[((i * C::NI + j) * 4 + r4) * 64 + lane] = v;
-                    }
-        }
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (kgrp != 0) return;
-#pragma unroll
-        for (int i = 0; i < C::MI; ++i)
-#pragma unroll
-            for (int j = 0; j < C::NI; ++j)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const acc_e4 v = xch[((i * C::NI + j) * 4 + r4) * 64 + lane];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[i][j][r4 * 4 + e] += v[e];
-                }
-    }
+    if (!sum_groups<C>(smem, wave, lane, kgrp, acc)) return;
     // (Tiles above 128x128 have no split: their partial sums would be 256 KiB and more per slice, and the code below
     // would push the big tiles' register allocation into scratch memory.  The host plans accordingly.)
     if (C::BM * C::BN <= kSplitMaxTile && p.ksplit > 1) {
@@ -1444,6 +1456,207 @@ __global__ void __launch_bounds__(512) conv_patch_kernel(const Params p) {
             store_block<OUT>(acc[i][j], fused, bias_r[j], p.relu, p.scale, rc, (int)voff, row_bytes, p.store_nt != 0);
         }
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// GEMM on operands whose rows are contiguous but not 16-byte aligned (odd extents, odd strides, any base address).
+//
+// The global->LDS copy needs 16-byte rows, so these operands go through registers: 16-byte loads at element alignment (the
+// hardware splits a lane's access that straddles a line), two stages ahead of the MFMAs in two register sets, then one
+// linear LDS write per chunk into the same swizzled tiles the fast kernel reads.  Nothing outside an operand is touched: rows past
+// the edge are clamped (they are never stored), a chunk that would run past its row's end is loaded so that it ends there and
+// shifted into place, and k past K is zero on both sides.
+// One load per value, the form this replaces, was bound by load issue: 1001x1531x777 fp16 37.3 us, now 9.9.  A CU loads about
+// 47 KB/us this way (16-byte loads at 2-byte alignment cost 10 % over aligned ones; global->LDS copies reach 86), which
+// bounds the tiles: 192 of 128x64 move 312 KB each in that product.
+// ---------------------------------------------------------------------------------------------
+// 16 bytes moved down by n elements (0 <= n; everything is gone at n >= 16 / ES), zeros enter at the top.  Branch-free: n
+// differs from lane to lane.
+template <int ES> __device__ __forceinline__ uint4 shift_down(const uint4& v, int n) {
+    const int bytes = n * ES;
+    const bool by8 = bytes & 8, by4 = bytes & 4, none = bytes >= 16;
+    unsigned x = by8 ? v.z : v.x, y = by8 ? v.w : v.y, z = by8 ? 0u : v.z, w = by8 ? 0u : v.w;
+    x = by4 ? y : x; y = by4 ? z : y; z = by4 ? w : z; w = by4 ? 0u : w;
+    const unsigned b = (unsigned)(bytes & 3);
+    x = __builtin_amdgcn_alignbyte(y, x, b); y = __builtin_amdgcn_alignbyte(z, y, b); z = __builtin_amdgcn_alignbyte(w, z, b); w = __builtin_amdgcn_alignbyte(0u, w, b);
+    return make_uint4(none ? 0u : x, none ? 0u : y, none ? 0u : z, none ? 0u : w);
+}
+
+// One operand of the kernel: IT chunks per thread and stage of a tile of W rows (K-major) or W columns (N-major).
+// base0 / ld: the operand's first element and leading stride, w0 / extent: first row or column of the tile and their count.
+template <class C, bool NM, int W, int IT> struct UnalignedOperand {
+    static constexpr int ES = C::ES, VEC = C::VEC, BK = C::BK;
+    typedef NMajorTile<W, ES> T;
+    static constexpr int K_STEP = NM ? C::CT / T::RC : 0;      // N-major: k-rows from one of the thread's chunks to the next
+    const char* base;     // of stage 0, C::ROWB bytes before the tile: offsets stay non-negative when a chunk moves back
+    unsigned off[IT];
+    int shift;            // N-major: elements the thread's chunks are moved down by (the tile's last, partial chunk)
+    int k_first;          // k of the thread's (first) chunk inside a stage
+    long long step;       // bytes from one stage to the next
+    bool edge;            // uniform: N-major, some chunk of this tile must be shifted
+    __device__ __forceinline__ void init(const char* base0, long long ld, int w0, int extent, int tid) {
+        if constexpr (NM) {
+            static_assert(C::CT % T::RC == 0 && K_STEP % (T::RPW * T::NSEG) == 0, "a thread keeps its column and its swizzle over the passes");
+            const int k = tid / T::RC, lb = ((tid % T::RC) * 16) ^ nmajor_xor<T>(k);
+            const int col = w0 + lb / ES, start = col + VEC > extent ? extent - VEC : col;       // (extent >= VEC: the host checks)
+            shift = col - start;
+            edge = w0 + W > extent;
+            k_first = k;
+            base = base0 - C::ROWB;
+            step = (long long)BK * ld * ES;
+#pragma unroll
+            for (int i = 0; i < IT; ++i) off[i] = ((unsigned)(k + i * K_STEP) * (unsigned)ld + (unsigned)start) * ES + C::ROWB;
+        } else {
+            const int r0 = tid / C::RCH, lc = (tid % C::RCH) ^ kmajor_swz<C::ROWB>(r0);
+            shift = 0;
+            edge = false;
+            k_first = lc * VEC;
+            base = base0 + (long long)w0 * ld * ES - C::ROWB;
+            step = C::ROWB;
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const int r = r0 + i * C::K_RSTEP, rc = w0 + r < extent ? r : extent - 1 - w0;
+                off[i] = (unsigned)rc * (unsigned)(ld * ES) + (unsigned)lc * 16 + C::ROWB;
+            }
+        }
+    }
+    // Before the last stage is requested, if it reaches past K: k-rows past the last one re-read it (they become zeros), chunks of a
+    // row that would run past its end move back to end there (K >= VEC: the host checks).
+    __device__ __forceinline__ void to_tail(int stage, int K) {
+        const int left = K - stage * BK - k_first;          // elements from the (first) chunk on
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int past = NM ? k_first + i * K_STEP + stage * BK - (K - 1) : 0;
+            if (NM) off[i] -= past > 0 ? (unsigned)past * (unsigned)(step / BK) : 0u;
+            else off[i] -= left < VEC ? (unsigned)((VEC - left) * ES) : 0u;
+        }
+    }
+    __device__ __forceinline__ void load(int stage, uint4 (&v)[IT]) const {
+        const char* b = base + stage * step;
+#pragma unroll
+        for (int i = 0; i < IT; ++i) __builtin_memcpy(&v[i], b + off[i], 16);
+    }
+    // What has to happen to the loaded chunks before they go to LDS; `tail`: they are those of to_tail's stage.
+    __device__ __forceinline__ void finish(int stage, bool tail, int K, uint4 (&v)[IT]) const {
+        const int left = K - stage * BK - k_first;
+        if (NM ? edge : tail) {
+            const int n = NM ? shift : left < VEC ? VEC - left : 0;
+#pragma unroll
+            for (int i = 0; i < IT; ++i) v[i] = shift_down<ES>(v[i], n);
+        }
+        if (NM && tail) {
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const bool keep = i * K_STEP < left;
+                v[i] = make_uint4(keep ? v[i].x : 0u, keep ? v[i].y : 0u, keep ? v[i].z : 0u, keep ? v[i].w : 0u);
+            }
+        }
+    }
+};
+
+template <class C>
+__global__ void __launch_bounds__(C::THREADS, 2) contract_unaligned_kernel(const Params p) {
+    typedef typename InTraits<C::DT>::acc_t acc_t;
+    static_assert((C::AMODE == A_UK || C::AMODE == A_UM) && (C::BMODE == B_UK || C::BMODE == B_UN), "");
+    static_assert(C::NSTAGE == 2 && C::CW == 0, "");
+    __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+    prefetch_args(p, false);
+    // reduction group kgrp takes the stages s with s % KW == kgrp through buffers of its own; the groups meet at the barriers
+    const int lane = threadIdx.x & 63;
+    const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kgrp = C::KW == 1 ? 0 : wave_wg / (C::WM * C::WN);
+    const int wave = wave_wg - kgrp * (C::WM * C::WN), tid = (int)threadIdx.x - kgrp * C::SUB;
+    char* const ring = smem + kgrp * C::RING_BYTES;
+    const int wm = wave / C::WN, wn = wave % C::WN;
+    int tm, tn;
+    tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.div_gw_magic, p.div_gw_shift, &tm, &tn);
+    const int m0 = tm * C::BM, n0 = tn * C::BN;
+    const long long bz = blockIdx.y;
+
+    UnalignedOperand<C, C::A_NM, C::BM, C::A_IT> A;
+    UnalignedOperand<C, C::B_NM, C::BN, C::B_IT> B;
+    A.init((const char*)p.A + bz * p.a_bs * C::ES, C::A_NM ? p.a_cs : p.a_rs, m0, p.M, tid);
+    B.init((const char*)p.B + bz * p.b_bs * C::ES, C::B_NM ? p.b_rs : p.b_cs, n0, p.N, tid);
+
+    const Frag<C> frag(lane, wm, wn);
+    acc_t acc[C::MI][C::NI];
+#pragma unroll
+    for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < C::NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;   // reduction init
+    typedef typename std::conditional<std::is_same<acc_t, f32x16>::value, float, int>::type acc_e;
+    acc_e bias_r[C::NI];
+    load_bias<C>(p, bz, n0, wn, lane, bias_r);
+
+    const int nst_all = (p.K + C::BK - 1) / C::BK;
+    // Stages per group.  A group with a stage less than the others takes part in the barriers with a stage past the end: it
+    // loads the last one again and multiplies zeros.
+    const int nst = (nst_all + C::KW - 1) / C::KW;
+    uint4 va[2][C::A_IT], vb[2][C::B_IT];
+    // s counts the group's stages; stage s * KW + kgrp of the reduction reaches past K if it is the group's last or not at all
+    auto reaches_past = [&](int s) { return s == nst - 1 && (s * C::KW + kgrp + 1) * C::BK > p.K; };
+    auto load = [&](int s, int set) __attribute__((always_inline)) {
+        const int stage = C::KW > 1 && s * C::KW + kgrp > nst_all - 1 ? nst_all - 1 : s * C::KW + kgrp;
+        if (reaches_past(s)) {
+            A.to_tail(stage, p.K);
+            B.to_tail(stage, p.K);
+        }
+        A.load(stage, va[set]);
+        B.load(stage, vb[set]);
+    };
+    auto put = [&](int s, int set) __attribute__((always_inline)) {       // register set and LDS buffer s % 2 = set
+        const int stage = s * C::KW + kgrp;
+        const bool tail = reaches_past(s);
+        A.finish(stage, tail, p.K, va[set]);
+        B.finish(stage, tail, p.K, vb[set]);
+        char* dst = ring + set * C::STAGE_BYTES + tid * 16;
+#pragma unroll
+        for (int i = 0; i < C::A_IT; ++i) *(uint4*)(dst + i * C::CT * 16) = va[set][i];
+#pragma unroll
+        for (int i = 0; i < C::B_IT; ++i) *(uint4*)(dst + C::A_BYTES + i * C::CT * 16) = vb[set][i];
+    };
+    // Stage s sits in LDS buffer `set`, stage s + 1 in the other register set; this one is free for stage s + 2.  Whether
+    // those stages exist is a template flag: behind a branch around the loads the compiler would wait for all of them.
+    auto iteration = [&](int s, int set, auto load_flag, auto put_flag) __attribute__((always_inline)) {
+        if constexpr (decltype(load_flag)::value) load(s + 2, set);
+        const char* sa = ring + set * C::STAGE_BYTES;
+#pragma unroll
+        for (int kk = 0; kk < C::KSTEPS; ++kk) {
+            uint4 af[C::MI], bf[C::NI];
+            frag.read_a(sa, kk, af);
+            frag.read_b(sa + C::A_BYTES, kk, bf);
+            mfma_block<C>(af, bf, acc);
+        }
+        if constexpr (decltype(put_flag)::value) put(s + 1, set ^ 1);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // (the loads of stage s + 2 stay in flight)
+    };
+    if (nst > 0) {
+        const std::true_type yes;
+        const std::false_type no;
+        load(0, 0);
+        if (nst > 1) load(1, 1);
+        put(0, 0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        int s = 0;
+        for (; s + 3 < nst; s += 2) {
+            iteration(s, 0, yes, yes);
+            iteration(s + 1, 1, yes, yes);
+        }
+        if (s + 2 < nst) {
+            iteration(s, 0, yes, yes);
+            iteration(s + 1, 1, no, yes);
+            iteration(s + 2, 0, no, no);
+        } else if (s + 1 < nst) {
+            iteration(s, 0, no, yes);
+            iteration(s + 1, 1, no, no);
+        } else {
+            iteration(s, 0, no, no);
+        }
+    }
+    if (!sum_groups<C>(smem, wave, lane, kgrp, acc)) return;
+    store_tile<C>(p, bz, m0, n0, wm, wn, lane, acc, bias_r);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -19,13 +19,19 @@ enum : int {
     // A stored [k][x], x contiguous (a transposed A: weight gradients dW = X^T dY); transposed on the LDS read like B_NMAJOR.
     // Before it existed such calls took the element-wise kernel: 768x3072x2048 bf16 175.6 us, now 15.0
     A_MMAJOR = 7,
+    // Vector loads at element alignment, staged through registers: [x][k] rows (UK) or [k][x] rows (UM) of any length, stride
+    // and base address; the contiguous axis holds at least one 16-byte vector
+    A_UK = 8,
+    A_UM = 9,
     A_CONVX = 5          // implicit im2col with the general coordinate decode: a depth axis (3-D convolution) and the
                          // transposed form (taps step backwards, only every up-th coordinate is an input pixel)
 };
 enum : int {
     B_KMAJOR = 0,   // B stored [y][k], k contiguous (a "transposed" B, or a KRSC filter)
     B_NMAJOR = 1,   // B stored [k][y], y contiguous (row-major B); transposed on the LDS read
-    B_GENERIC = 2   // any strides, element-wise loads
+    B_GENERIC = 2,  // any strides, element-wise loads
+    B_UK = 3,       // as A_UK: [y][k] rows of any alignment
+    B_UN = 4        // as A_UM: [k][y] rows of any alignment
 };
 
 // Kernel arguments.  The block is fetched through the scalar cache 64 bytes at a time and a kernel's first copy waits
@@ -202,7 +208,7 @@ struct Cfg {
     static constexpr int A_IT = BM * RCH / CT;    // 16-byte chunks per copying thread per stage
     static constexpr int B_IT = BN * RCH / CT;
     static constexpr int K_RSTEP = CT / RCH;          // K-major rows covered by one pass of the copying threads
-    static constexpr bool A_NM = AMODE == A_MMAJOR, B_NM = BMODE == B_NMAJOR;      // N-major LDS tiles
+    static constexpr bool A_NM = AMODE == A_MMAJOR || AMODE == A_UM, B_NM = BMODE == B_NMAJOR || BMODE == B_UN;      // N-major LDS tiles
     typedef NMajorTile<BM, ES> ATile;
     typedef NMajorTile<BN, ES> BTile;
     static_assert(ROWB == 256 || ROWB == 128 || ROWB == 64, "");
@@ -211,7 +217,7 @@ struct Cfg {
     static_assert(K_RSTEP % 16 == 0, "the K-major swizzle must repeat with the copy's row step");
     static_assert((!A_NM || ATile::OK) && (!B_NM || BTile::OK), "N-major tile: whole segments, XOR closed inside a row");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of one CU");
-    static_assert(KW >= 1 && KW <= 2 && THREADS <= 1024 && (CW == 0 || KW == 1), "");
+    static_assert(KW >= 1 && KW <= 4 && THREADS <= 1024 && (CW == 0 || KW == 1), "");
     static_assert((KW - 1) * BM * BN * 4 <= LDS_BYTES, "the partial sums of the other groups must fit the rings");
 };
 

@@ -425,6 +425,45 @@ def test_transposed_a_through_every_variant(B, oracle, dtype, out):
         B.tir_debug_force_variant("")
 
 
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("bf16", "f32"), ("i8", "i32")])
+def test_unaligned_operands_through_every_variant(B, oracle, dtype, out):
+    """Rows of any length, stride and base address (staged through registers): extents of one vector, around a vector, a
+    stage and a tile; reductions of one element, around one stage and of several; A and B along either axis, batched."""
+    import torch
+    names = B.tir_debug_variant_names()
+    vec = 16 if dtype == "i8" else 8
+    bk = 16 * vec // 2
+    dist = "i" if dtype == "i8" else "u"
+    shapes = [(vec, vec, vec, 1, 0), (vec + 1, 3 * vec - 1, bk - 1, 1, 0), (65, 131, bk + 1, 1, 3), (129, 2 * vec + 1, 2 * bk + vec + 1, 2, 0),
+              (200, 257, 5 * bk - 3, 1, 1), (64, 2 * 64 + 4, vec + 3, 3, 5)]
+    try:
+        for (M, N, K, batch, pad) in shapes:
+            for ta in (False, True):
+                for tb in (False, True):
+                    lda, ldb = (M if ta else K) + pad, (K if tb else N) + pad
+                    # one element in front: the base address is aligned to nothing but the element
+                    a_bits = I.make_tensor(dtype, dist, 8700 + M, (1 + batch * (K if ta else M) * lda,))
+                    b_bits = I.make_tensor(dtype, dist, 8701 + N, (1 + batch * (N if tb else K) * ldb,))
+                    a_bs, b_bs = (K if ta else M) * lda, (N if tb else K) * ldb
+                    a_rs, a_cs = (1, lda) if ta else (lda, 1)
+                    b_rs, b_cs = (1, ldb) if tb else (ldb, 1)
+                    ref, S = oracle.batch_matmul(dtype, a_bits[1:].copy(), b_bits[1:].copy(), batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs)
+                    a, b = B.to_device(a_bits, dtype)[1:], B.to_device(b_bits, dtype)[1:]
+                    suffix = f"_{'um' if ta else 'uk'}_{'uk' if tb else 'un'}_generic"
+                    todo = [n for n in names if n.startswith(f"{dtype}_{out}_") and n.endswith(suffix)]
+                    assert len(todo) >= 3
+                    for name in todo:
+                        _say(f"unaligned {batch} x {M}x{N}x{K} pad {pad} {name}")
+                        B.tir_debug_force_variant(name)
+                        c = B.empty_out((batch, M, N), out)
+                        c.fill_(float("nan")) if out != "i32" else c.fill_(-123456789)
+                        B.tir_batch_matmul(a, b, c, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, M * N, N, 1, dtype, out)
+                        torch.cuda.synchronize()
+                        PT.assert_close(PT.gpu_to_f64(c), ref, S, f"{batch} x {M}x{N}x{K} via {name}")
+    finally:
+        B.tir_debug_force_variant("")
+
+
 def test_prepared_calls_launch_what_run_workload_launches(B, oracle):
     """binding.prepare_workload marshals once and launches per call: a GEMM, a batched matmul and a fused convolution,
     each launched twice from its prepared call (the second time over a poisoned output), against the oracle."""
