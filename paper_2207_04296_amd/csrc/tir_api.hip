@@ -81,7 +81,7 @@ struct VariantRange {
     const Variant* const* first;
     int n;
 };
-static const int kModes = 10, kDtypes = 5;
+static const int kModes = 11, kDtypes = 5;
 static VariantRange variants_of(int dt, int out, int amode, int bmode) {
     struct Index {
         const Variant* order[kNumVariants];
@@ -517,6 +517,16 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         amode = plain2d ? A_CONV : A_CONVX;
         bmode = B_KMAJOR;
     }
+    // Few channels (vectors of one tap are not whole): filter rows as the unit of the reduction.  A filter row must be contiguous in the
+    // input (one group, no dilation along the width), hold the loads' vectors inside the operands, and the filter and four waves' patches
+    // must fit 64 KiB of LDS.
+    const int64_t rows_cpr = (S * Cg + vec - 1) / vec;
+    const int64_t rows_rb = ((15 * (int64_t)g.stride_w * C + rows_cpr * vec) * es + 4 + 15) / 16 * 16;      // the last pixel's last chunk and one dword
+    const bool rows_ok = amode == A_CONV_GENERIC && plain2d && groups == 1 && (g.dil_w == 1 || S == 1) && C * es < 64 && W * C >= vec && K * Kd >= vec &&
+                         N * H * W * C * es < kMaxExtent && K * Kd * es < kMaxExtent && Mg * K * elem_size(out) < kMaxExtent &&
+                         R * rows_cpr < 4096 && rows_rb < 8192 && g.stride_h < 64 && conv_rows_lds(R, rows_cpr, g.stride_h, g.dil_h, rows_rb, 64, 4) <= 64 * 1024 &&
+                         N * ((P + 3) / 4) * ((Q + 15) / 16) * ((K + 31) / 32) <= kMaxExtent;
+    if (rows_ok && !(g_force_name[0] && !strstr(g_force_name, "rows"))) amode = A_CONV_ROWS;
     // A strided transposed convolution multiplies mostly structural zeros when read as one gather (only every
     // stride-th tap meets an input pixel).  Undilated, with whole stages per tap (one stage = 128 bytes of channels),
     // it is computed per output phase instead: stride_h*stride_w stride-1 convolutions with a tap subset each, all
@@ -576,6 +586,20 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
             const int64_t tt = t < R * S ? t : R * S - 1;
             p.tap_px[t] = R * S <= 9 ? (int)((tt / S) * g.dil_h * patch_w + (tt % S) * g.dil_w) : 0;
         }
+    }
+    if (amode == A_CONV_ROWS) {
+        p.rows_tiles_q = (int)((Q + 15) / 16);
+        p.tiles_m = (int)((P + 3) / 4) * p.rows_tiles_q;         // tiles of 4 x 16 pixels per image
+        p.PW = (int)rows_rb;
+        p.rows_cpr = (int)rows_cpr;
+        // As many waves per workgroup as put all tiles on the CUs at once (a wave's tile is its whole work: what does not fit
+        // waits for a second round), 4 to 16, within 128 KiB of LDS.
+        const int64_t waves_wanted = (N * p.tiles_m * p.tiles_n + (int64_t)kCUs - 1) / (int64_t)kCUs;
+        p.rows_waves = (int)(waves_wanted < 4 ? 4 : waves_wanted > 16 ? 16 : waves_wanted);
+        while (p.rows_waves > 4 && conv_rows_lds(R, rows_cpr, g.stride_h, g.dil_h, rows_rb, v->bn, p.rows_waves) > 128 * 1024) --p.rows_waves;
+        while (p.rows_lpr < 6 && (1 << p.rows_lpr) < rows_rb / 16) ++p.rows_lpr;
+        const FastDiv tq = make_fastdiv((unsigned)p.rows_tiles_q);
+        p.div_tq_magic = tq.magic; p.div_tq_shift = tq.shift;
     }
     p.batch_imgs = (int)N;
     p.a_bs = Cg;            // a group starts Cg channels further

@@ -2,6 +2,7 @@
 // build in parallel.  Each line of tir_variants.def owned by this unit becomes an explicit
 // instantiation of launch_cfg<Cfg<...>>, which the dispatcher references by address.
 #include "tir_kernel.h"
+#include "tir_conv_rows.h"
 #include "tir_launch.h"
 
 #ifndef TIR_UNIT
@@ -15,6 +16,11 @@ template <class C> hipError_t launch_cfg(const Params& p, hipStream_t stream) {
     if constexpr (C::AMODE == A_CONV_PATCH) {
         grid.x = (unsigned)(p.batch_imgs * p.tiles_m * p.tiles_n);
         return launch_kernel(&conv_patch_kernel<C::DT, C::OUT>, grid, dim3(512), stream, p);
+    } else if constexpr (C::AMODE == A_CONV_ROWS) {
+        grid.x = (unsigned)((p.batch_imgs * p.tiles_m + p.rows_waves - 1) / p.rows_waves * p.tiles_n);
+        const unsigned lds = (unsigned)conv_rows_lds(p.R, p.rows_cpr, p.stride_h, p.dil_h, p.PW, C::BN, p.rows_waves);
+        return launch_kernel((p.stride_w * p.Cin * C::ES) % 4 == 0 ? &conv_rows_kernel<C::DT, C::OUT, C::BN, false> : &conv_rows_kernel<C::DT, C::OUT, C::BN, true>, grid,
+                             dim3((unsigned)p.rows_waves * 64), stream, p, lds);
     } else if constexpr (C::AMODE == A_GENERIC || C::AMODE == A_CONV_GENERIC)
         return launch_kernel(&contract_staged_kernel<C>, grid, dim3(C::THREADS), stream, p);
     else if constexpr (C::AMODE == A_UK || C::AMODE == A_UM)

@@ -11,9 +11,9 @@ template <class C> hipError_t launch_cfg(const Params& p, hipStream_t stream);
 
 // Launch with the arguments where they are: the <<<>>> form copies them once more and keeps the launch configuration in
 // between (0.25 us of 2.6 us per launch with a 600-byte parameter block).
-template <class P> inline hipError_t launch_kernel(void (*kernel)(P), dim3 grid, dim3 block, hipStream_t stream, const P& p) {
+template <class P> inline hipError_t launch_kernel(void (*kernel)(P), dim3 grid, dim3 block, hipStream_t stream, const P& p, unsigned lds = 0) {
     void* args[] = {const_cast<typename std::remove_const<P>::type*>(&p)};
-    const hipError_t e = hipLaunchKernel((const void*)kernel, grid, block, args, 0, stream);
+    const hipError_t e = hipLaunchKernel((const void*)kernel, grid, block, args, lds, stream);
     if (e != hipSuccess) (void)hipGetLastError();          // reported through the return value
     return e;
 }

@@ -23,6 +23,7 @@ enum : int {
     // and base address; the contiguous axis holds at least one 16-byte vector
     A_UK = 8,
     A_UM = 9,
+    A_CONV_ROWS = 10,    // convolution of few channels: whole filter rows as the reduction's unit, patch and filter in LDS (tir_conv_rows.h)
     A_CONVX = 5          // implicit im2col with the general coordinate decode: a depth axis (3-D convolution) and the
                          // transposed form (taps step backwards, only every up-th coordinate is an input pixel)
 };
@@ -98,6 +99,11 @@ struct Params {
     int div_opq_shift;
     unsigned div_dwq_magic, div_dwpq_magic;                // depth-wise, pixel blocks: / ceil(Q / kDwBlockPix), / (P * that)
     int div_dwq_shift, div_dwpq_shift;
+    // few-channel kernel: tile columns per image row, 16-byte chunks per filter row, log2 of the lanes that copy one patch row,
+    // waves per workgroup; / tile columns
+    int rows_tiles_q, rows_cpr, rows_lpr, rows_waves;
+    unsigned div_tq_magic;
+    int div_tq_shift;
 };
 static_assert(offsetof(Params, a_bs) == 64 && offsetof(Params, c_cs) == 128 && offsetof(Params, H) == 192, "the lines described above");
 
@@ -126,6 +132,11 @@ __host__ __device__ inline unsigned fastdiv(unsigned m, unsigned magic, int shif
 
 // Adjacent output pixels one thread of the blocked depth-wise kernel owns.
 constexpr int kDwBlockPix = 4;      // measured 2, 4, 8: 8.5 / 7.2 / 6.9 us at stride 1 (16x56x56x128 fp16), 7.1 / 6.2 / 9.8 us at stride 2 (int8)
+
+// Few-channel convolution: LDS of a workgroup (filter of BN output channels; per wave a patch of rows of row_bytes and a row of zeros).
+inline int64_t conv_rows_lds(int64_t R, int64_t cpr, int64_t stride_h, int64_t dil_h, int64_t row_bytes, int64_t BN, int64_t waves) {
+    return ((R + 1) / 2 * 2 * cpr + 1) * BN * 16 + waves * (3 * stride_h + (R - 1) * dil_h + 2) * row_bytes;
+}
 
 // Largest workgroup tile (rows x columns) whose reduction may be split over workgroups.
 constexpr int kSplitMaxTile = 128 * 128;

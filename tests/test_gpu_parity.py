@@ -464,6 +464,38 @@ def test_unaligned_operands_through_every_variant(B, oracle, dtype, out):
         B.tir_debug_force_variant("")
 
 
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("f16", "f32"), ("bf16", "f32"), ("i8", "i32"), ("i8", "i8")])
+def test_few_channel_convolution(B, oracle, dtype, out):
+    """Filter rows as the reduction's unit: pixels at every alignment (1, 2, 3, 4, 5 channels at strides 1, 2, 3), filter rows
+    shorter than a vector, of whole vectors and with a remainder, one to several pixel tiles with remainders, images no wider than
+    a vector, padding wider than the filter's reach, dilation along the height, channel tiles with remainders, fused consumers."""
+    cases = [  # n, h, w, c, k, r, s, stride, pad, dil
+        (2, 30, 37, 3, 64, 7, 7, (2, 2), (3, 3), (1, 1)),
+        (1, 17, 16, 3, 40, 3, 3, (1, 1), (1, 1), (1, 1)),
+        (1, 33, 34, 1, 70, 5, 5, (1, 1), (2, 2), (1, 1)),
+        (2, 16, 32, 4, 32, 3, 3, (2, 2), (1, 1), (1, 1)),
+        (1, 9, 40, 2, 96, 4, 8, (1, 3), (2, 5), (2, 1)),
+        (1, 20, 19, 5, 33, 1, 1, (1, 1), (0, 0), (1, 1)),
+        (3, 5, 16, 1, 16, 2, 16, (1, 1), (3, 20), (1, 1)),
+        (1, 40, 21, 6, 24, 3, 5, (3, 1), (0, 2), (3, 1)),
+    ]
+    for i, (n, h, w, c, k, r, s, stride, pad, dil) in enumerate(cases):
+        scale = 1.0 / 300.0 if out == "i8" else 0.0
+        wl = I.Workload(f"rows_{dtype}_{out}_{i}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 8800 + i, n=n, h=h, w=w, c=c, k=k, r=r, s=s,
+                        stride=stride, pad=pad, dil=dil, ep_bias=i % 2 == 0, ep_relu=i % 3 == 0, ep_scale=scale)
+        assert "rows256x" in PT.variant_name(B, wl), PT.variant_name(B, wl)
+        a_bits, b_bits = wl.operands()
+        ref, S = PT.run_oracle(wl, a_bits, b_bits, oracle)
+        for force in ("rows256x64", "rows256x32"):
+            _say(f"{wl.name} {cases[i]} {force}")
+            B.tir_debug_force_variant(force)
+            try:
+                got = PT.run_gpu(wl, a_bits, b_bits, streaming=i % 2 == 1)
+            finally:
+                B.tir_debug_force_variant("")
+            PT.assert_close(got, ref, S, f"{wl.name} {cases[i]} {force}")
+
+
 def test_prepared_calls_launch_what_run_workload_launches(B, oracle):
     """binding.prepare_workload marshals once and launches per call: a GEMM, a batched matmul and a fused convolution,
     each launched twice from its prepared call (the second time over a poisoned output), against the oracle."""
