@@ -2,7 +2,7 @@
 // kernel.  Both contractions are tensorized blocks (Eq. 1 of the TensorIR paper, mapped onto the
 // 32x32x16 MFMA) that share the workgroup's tile instead of meeting in memory: the probabilities never
 // leave the registers (sec. 2 / 3.2: blocks isolate the two sub-problems, which does not prevent
-// cooperation across them).  The softmax is the textbook one, computed online over 128-key chunks.
+// cooperation across them).  The softmax is the textbook one, computed online over 64-key chunks.
 //
 // Both products are computed transposed, S^T = K Q^T and O^T = V^T P^T, so that the second MFMA
 // operand - whose row index is the lane - is the query in both: every lane then owns one query row,
@@ -46,27 +46,33 @@ template <> struct PackP<DT_BF16> {
 };
 
 // DT: f16 / bf16 inputs, OUT: same 16-bit type or f32, DH: head dimension (64 or 128) of Q, K and V.
+//
+// 64 keys per chunk: two stages of K and V and nothing else in LDS (64 KiB at d = 128), so that two workgroups share a CU and
+// one's softmax - vector work as long as the MFMAs of its chunk - runs under the other's MFMAs.  With 128-key chunks and the
+// queries in LDS as well (160 KiB) a SIMD had one wave and did one after the other: 16 x 4096 x 4096 x 128 bf16 took 208 us,
+// now 135 (1.02 PFLOP/s; this card's large bf16 matrix products reach 1.2).
 template <int DT, int OUT, int DH>
-__global__ void __launch_bounds__(256) attention_kernel(const AttnParams p) {
+__global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
     typedef OutTraits<OUT> OT;
     typedef typename OT::type out_t;
     constexpr int OS = (int)sizeof(out_t);
+    constexpr int KB = 64, JB = KB / 32;        // keys of a chunk, 32-key blocks of it
     constexpr int ROW = DH * 2;                 // bytes of one Q / K / V row
     constexpr int HALVES = DH / 64;             // 128-byte column groups of a K-major row
-    constexpr int TILE = 128 * ROW;             // one 128-row tile
+    constexpr int TILE = KB * ROW;              // one chunk of K or V
     constexpr int KSTEPS = DH / 16;             // MFMA k-steps over the head dimension
     constexpr int DB = DH / 32;                 // 32-wide blocks of the output's head dimension
     constexpr int VRC = ROW / 16;               // 16-byte chunks per V row
+    constexpr int COPIES = TILE / 4096;         // copy instructions per wave for one chunk of K or V
     // V tile [key][ROW] with the transposing-read swizzle: byte offset XOR ((key / RPW) % NSEG) * 64
     constexpr int WIN = ROW < 256 ? ROW : 256;
     constexpr int NSEG = WIN / 64, RPW = 256 / WIN;
     static_assert(DH == 64 || DH == 128, "head dimension");
-    static_assert(TILE * 5 <= 160 * 1024, "Q + two stages of K and V");
+    static_assert(128 * DH * OS <= 4 * TILE, "the output tile is staged where K and V were");
 
-    __shared__ __attribute__((aligned(1024))) char smem[5 * TILE];
-    char* const s_q = smem;
-    auto s_k = [&](int st) { return smem + TILE + st * 2 * TILE; };
-    auto s_v = [&](int st) { return smem + 2 * TILE + st * 2 * TILE; };
+    __shared__ __attribute__((aligned(1024))) char smem[4 * TILE];
+    auto s_k = [&](int st) { return smem + st * 2 * TILE; };
+    auto s_v = [&](int st) { return smem + TILE + st * 2 * TILE; };
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -74,71 +80,77 @@ __global__ void __launch_bounds__(256) attention_kernel(const AttnParams p) {
     const int l31 = lane & 31, g = lane >> 5;
     const int blk = lane >> 4, s16 = lane & 15;
 
-    const long long b = fastdiv(blockIdx.x, p.div_tm_magic, p.div_tm_shift);
-    const int tm = (int)blockIdx.x - (int)b * p.tiles_m;
+    // Workgroups go to the 8 L2 domains round-robin by launch index: each domain gets a run of consecutive tiles, i.e. whole heads,
+    // whose keys and values its L2 then holds once.
+    const int nwg = p.batch * p.tiles_m;
+    const int xq = nwg >> 3, xr = nwg & 7, xf = blockIdx.x & 7;
+    const int bid = xf * xq + (xf < xr ? xf : xr) + (blockIdx.x >> 3);
+    const long long b = fastdiv((unsigned)bid, p.div_tm_magic, p.div_tm_shift);
+    const int tm = bid - (int)b * p.tiles_m;
     const int m0 = tm * 128;
     const int rows_q = p.M - m0 < 128 ? p.M - m0 : 128;
-    const int nchunk = (p.N + 127) / 128;
+    const int nchunk = (p.N + KB - 1) / KB;
 
     // ------------------------------------------------------------ copy stage
-    // K-major tile (Q, K): slot q = tid + i*256 is row q / (8*HALVES)... kept as HALVES sub-tiles of
-    // [128 rows][128 B] so that the row swizzle of the GEMM kernels applies unchanged.
-    auto copy_kmajor = [&](const char* base, long long valid_bytes, char* dst, bool nt) {
-        const i32x4 r = make_rsrc(base, valid_bytes);
-#pragma unroll
-        for (int h = 0; h < HALVES; ++h)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int q = tid + i * 256;              // 1024 chunks of 16 B per sub-tile
-                const int row = q >> 3;
-                const int lc = (q & 7) ^ kmajor_swz<128>(row);
-                if (nt) load_to_lds_nt(r, dst + h * (128 * 128) + i * 4096 + wave * 1024, (unsigned)(row * ROW + h * 128 + lc * 16));
-                else load_to_lds(r, dst + h * (128 * 128) + i * 4096 + wave * 1024, (unsigned)(row * ROW + h * 128 + lc * 16));
-            }
-    };
-    auto copy_v = [&](const char* base, long long valid_bytes, char* dst, bool nt) {
-        const i32x4 r = make_rsrc(base, valid_bytes);
-#pragma unroll
-        for (int i = 0; i < 4 * HALVES; ++i) {
-            const int q = tid + i * 256;
-            const int key = q / VRC;
-            const int lb = ((q % VRC) * 16) ^ (((key / RPW) % NSEG) * 64);
-            if (nt) load_to_lds_nt(r, dst + i * 4096 + wave * 1024, (unsigned)(key * ROW + lb));
-            else load_to_lds(r, dst + i * 4096 + wave * 1024, (unsigned)(key * ROW + lb));
-        }
-    };
+    // K-major tile: HALVES sub-tiles of [KB rows][128 B] so that the row swizzle of the GEMM kernels applies unchanged.
+    unsigned k_off[2], v_off;                         // the lane's offsets of copy instruction i: a constant plus i times a scalar
+    {
+        const int row = tid >> 3;
+        k_off[0] = (unsigned)(row * ROW + (((tid & 7) ^ kmajor_swz<128>(row)) << 4));
+        k_off[1] = k_off[0] + 32 * ROW;               // rows 32 on: the swizzle repeats every 16
+        const int key = tid / VRC;                    // 256 threads: whole multiples of the swizzle's period
+        v_off = (unsigned)(key * ROW + (((tid % VRC) * 16) ^ (((key / RPW) % NSEG) * 64)));
+        static_assert((256 / VRC) % (RPW * NSEG) == 0, "the V swizzle repeats from one copy instruction to the next");
+    }
     const char* Qb = (const char*)p.Q + ((b * p.M + m0) * (long long)ROW);
     const char* Kb = (const char*)p.K + b * p.N * (long long)ROW;
     const char* Vb = (const char*)p.V + b * p.N * (long long)ROW;
-    // Non-temporal copies for what one workgroup alone reads - the queries always, keys and values when one tile holds all
-    // queries of a head: 7.05 -> 6.63 us on the benchmark's 192 heads with the operands coming from memory, no change from the caches.
+    // Non-temporal copies for what one workgroup alone reads (one tile holds all queries of a head): 7.05 -> 6.63 us on the
+    // benchmark's 192 heads with the operands coming from memory, no change from the caches.
     const bool kv_once = p.tiles_m == 1;
-    auto copy_chunk = [&](int c) {
-        const long long left = (long long)(p.N - c * 128) * ROW;      // rows past N lie outside the descriptor: zeros
-        copy_kmajor(Kb + (long long)c * TILE, left, s_k(c & 1), kv_once);
-        copy_v(Vb + (long long)c * TILE, left, s_v(c & 1), kv_once);
-    };
-    copy_kmajor(Qb, (long long)rows_q * ROW, s_q, true);
-    copy_chunk(0);
-    // Q and the first keys are enough to start on the scores: the first values (the newest 4*HALVES
-    // copies of this wave) may still be in flight, they are waited for before the second product
-    wait_vmcnt_upto(4 * HALVES);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-
-    // ------------------------------------------------------------ this wave's queries, as MFMA operands
-    const int swl = kmajor_swz<128>(l31);            // rows 32*w + l31 and 32*jb + l31 share it (period 16)
-    uint4 qf[KSTEPS];
+    auto copy_chunk = [&](int c) __attribute__((always_inline)) {
+        const long long left = (long long)(p.N - c * KB) * ROW;      // rows past N lie outside the descriptor: zeros
+        const i32x4 rk = make_rsrc(Kb + (long long)c * TILE, left), rv = make_rsrc(Vb + (long long)c * TILE, left);
+        char* const dk = s_k(c & 1) + wave * 1024;
+        char* const dv = s_v(c & 1) + wave * 1024;
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks)
-        qf[ks] = *(const uint4*)(s_q + (ks >> 2) * (128 * 128) + (wave * 32 + l31) * 128 + ((((ks & 3) * 2 + g) ^ swl) << 4));
+        for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (kv_once) load_to_lds_nt(rk, dk + h * (KB * 128) + i * 4096, k_off[i] + h * 128);
+                else load_to_lds(rk, dk + h * (KB * 128) + i * 4096, k_off[i] + h * 128);
+            }
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) {
+            if (kv_once) load_to_lds_nt(rv, dv + i * 4096, v_off + i * 4096);
+            else load_to_lds(rv, dv + i * 4096, v_off + i * 4096);
+        }
+    };
+    copy_chunk(0);
+
+    // ------------------------------------------------------------ this wave's queries, as MFMA operands (rows past M read zeros)
+    uint4 qf[KSTEPS];
+    {
+        const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void*)Qb, 0, rows_q * ROW, 0x00020000);
+        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+            qf[ks] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rq, (wave * 32 + l31) * ROW + ks * 32 + g * 16, 0, 2));
+    }
+    const int swl = kmajor_swz<128>(l31);            // rows 32*jb + l31 share it (period 16)
 
     f32x16 acc_o[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[db][r] = 0.f;          // reduction init
-    float m_run = -__builtin_inff(), l_run = 0.f;
+    // The reference the scores are taken relative to, in score units, and the sum of the probabilities relative to it.
+    float m_ref = 0.f, l_run = 0.f;
+    const float sc = p.scale_log2e;
+    // A row's reference only has to be close to its maximum: it is raised when some row of the wave has a score 2^8 above it
+    // (binary16 probabilities hold 2^15), which after the first chunk is rare, and the accumulators are rescaled only then.
+    constexpr float kSlack = 8.0f;
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 
     for (int c = 0; c < nchunk; ++c) {
         if (c + 1 < nchunk) copy_chunk(c + 1);        // its stage was last read before the previous barrier
@@ -146,64 +158,77 @@ __global__ void __launch_bounds__(256) attention_kernel(const AttnParams p) {
         const char* sv = s_v(c & 1);
 
         // S^T = K Q^T: rows = keys (registers), columns = queries (lanes)
-        f32x16 acc_s[4];
+        f32x16 acc_s[JB];
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
+        for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc_s[jb][r] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) {
-                const uint4 kf = *(const uint4*)(sk + (ks >> 2) * (128 * 128) + (jb * 32 + l31) * 128 + ((((ks & 3) * 2 + g) ^ swl) << 4));
+        for (int ks = 0; ks < KSTEPS; ++ks)
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb) {
+                const uint4 kf = *(const uint4*)(sk + (ks >> 2) * (KB * 128) + (jb * 32 + l31) * 128 + ((((ks & 3) * 2 + g) ^ swl) << 4));
                 acc_s[jb] = InTraits<DT>::mfma(kf, qf[ks], acc_s[jb]);
             }
+        if ((c + 1) * KB > p.N) {
+            // keys past N (only in the last chunk) drop out of the softmax
+            const float out = sc < 0.f ? __builtin_inff() : -__builtin_inff();
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (c * KB + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N) acc_s[jb][r] = out;
         }
-        // scores in base 2; keys past N (only in the last chunk) drop out of the softmax
-        const bool ragged = (c + 1) * 128 > p.N;
-        float mx = -__builtin_inff();
+        // the row's largest scaled score: that of its largest score, or of its smallest under a negative scale
+        float mx = acc_s[0][0];
+        if (sc >= 0.f) {
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb)
+            for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                float s = acc_s[jb][r] * p.scale_log2e;
-                if (ragged && c * 128 + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N) s = -__builtin_inff();
-                acc_s[jb][r] = s;
-                mx = __builtin_fmaxf(mx, s);
-            }
-        mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32));           // the other half-wave holds the query's other keys
-        const float m_new = __builtin_fmaxf(m_run, mx);          // finite: every chunk has at least one valid key
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        float lsum = 0.f;
-        uint4 pf[4][2];                                           // P^T fragments: key block jb, k-step s
+                for (int r = 0; r < 16; ++r) mx = __builtin_fmaxf(mx, acc_s[jb][r]);
+            mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32));           // the other half-wave holds the query's other keys
+        } else {
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
+            for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mx = __builtin_fminf(mx, acc_s[jb][r]);
+            mx = __builtin_fminf(mx, __shfl_xor(mx, 32));
+        }
+        if (c == 0) m_ref = mx;                                      // finite: every chunk has at least one valid key
+        else if (__builtin_amdgcn_ballot_w64((mx - m_ref) * sc > kSlack) != 0) {
+            const float alpha = __builtin_amdgcn_exp2f((m_ref - mx) * sc);
+            // (rows whose reference is already above keep it)
+            const bool up = (mx - m_ref) * sc > 0.f;
+            const float a = up ? alpha : 1.f;
+            m_ref = up ? mx : m_ref;
+            l_run *= a;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_o[db][r] *= a;
+        }
+        const float base = -m_ref * sc;
+        uint4 pf[JB][2];                                             // P^T fragments: key block jb, k-step s
+        float lsum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) {
             float pr[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                pr[r] = __builtin_amdgcn_exp2f(acc_s[jb][r] - m_new);
-                lsum += pr[r];
+                pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc_s[jb][r], sc, base));
+                lsum[r & 1] += pr[r];
             }
 #pragma unroll
             for (int s = 0; s < 2; ++s)
                 pf[jb][s] = make_uint4(PackP<DT>::two(pr[8 * s + 0], pr[8 * s + 1]), PackP<DT>::two(pr[8 * s + 2], pr[8 * s + 3]),
                                        PackP<DT>::two(pr[8 * s + 4], pr[8 * s + 5]), PackP<DT>::two(pr[8 * s + 6], pr[8 * s + 7]));
         }
-        l_run = l_run * alpha + lsum;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
+        l_run += lsum[0] + lsum[1];
 
-        if (c == 0) {
-            // the first values: everything but the next chunk's copies (issued after them) has landed
-            wait_vmcnt_upto(nchunk > 1 ? 8 * HALVES : 0);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
         // O^T += V^T P^T.  Position (g, 4*hh + e) of k-step s in key block jb is key
         // 32*jb + 16*s + 8*hh + 4*g + e - the order the probabilities sit in the registers above.
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb)
+        for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
             for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -230,7 +255,7 @@ __global__ void __launch_bounds__(256) attention_kernel(const AttnParams p) {
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     const float inv = 1.0f / l_tot;
     constexpr int ORB = DH * OS;                     // bytes of one output row
-    char* const s_o = smem + TILE;                   // the K / V stages are free now (ORB * 128 <= 4 * TILE)
+    char* const s_o = smem;                          // the K / V stages are free now
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -245,8 +270,7 @@ __global__ void __launch_bounds__(256) attention_kernel(const AttnParams p) {
             if constexpr (OS == 4) *(uint4*)dst = *(const uint4*)v;
             else *(uint2*)dst = *(const uint2*)v;
         }
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    __syncthreads();
     {
         char* Ob = (char*)p.O + (b * p.M + m0) * (long long)ORB;
         const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)Ob, 0, rows_q * ORB, 0x00020000);
