@@ -1140,13 +1140,11 @@ tir_status tir_attention(const void* Q, const void* K, const void* V, void* O, i
     if (M > kMaxExtent || N > kMaxExtent || batch * tiles_m > kMaxExtent) return fail(TIR_ERR_UNSUPPORTED, "extent beyond 2^31-1");
     attn_launch_fn fn = attention_launcher((int)in, (int)out, (int)d);
     if (!fn) return fail(TIR_ERR_UNSUPPORTED, "attention: no kernel for this dtype pair / head dimension");
-    AttnParams p;
+    AttnParams p = {};
     p.Q = Q; p.K = K; p.V = V; p.O = O;
-    p.M = (int)M; p.N = (int)N; p.batch = (int)batch; p.tiles_m = (int)tiles_m;
+    p.M = (int)M; p.N = (int)N; p.batch = (int)batch;
     p.scale_log2e = scale * 1.44269504088896340736f;
     if (p.scale_log2e == 0.f) p.scale_log2e = 1e-37f;      // every score counts alike, and the infinities that stand for keys past N keep their sign
-    const FastDiv dtm = make_fastdiv((unsigned)tiles_m);
-    p.div_tm_magic = dtm.magic; p.div_tm_shift = dtm.shift;
     hipError_t e = fn(p, (hipStream_t)stream);
     if (e != hipSuccess) return fail(TIR_ERR_LAUNCH, "attention launch failed: %s", hipGetErrorString(e));
     return TIR_OK;

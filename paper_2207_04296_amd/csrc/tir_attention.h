@@ -22,7 +22,7 @@ struct AttnParams {
     const void* V;   // [batch][N][D]
     void* O;         // [batch][M][D]
     int M, N, batch;
-    int tiles_m;     // ceil(M / 128)
+    int tiles_m;     // ceil(M / (32 * QW)), QW query waves per workgroup
     float scale_log2e;   // scale * log2(e): the softmax runs in base 2
     unsigned div_tm_magic;   // workgroup id / tiles_m as multiply-and-shift (make_fastdiv)
     int div_tm_shift;
@@ -51,34 +51,45 @@ template <> struct PackP<DT_BF16> {
 // one's softmax - vector work as long as the MFMAs of its chunk - runs under the other's MFMAs.  With 128-key chunks and the
 // queries in LDS as well (160 KiB) a SIMD had one wave and did one after the other: 16 x 4096 x 4096 x 128 bf16 took 208 us,
 // now 135 (1.02 PFLOP/s; this card's large bf16 matrix products reach 1.2).
-template <int DT, int OUT, int DH>
-__global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
+//
+// QW waves of 32 queries times KG key groups: group k takes the chunks c with c % KG == k through a ring of its own and the
+// groups' results are merged through LDS at the end.  Where the query tiles alone leave CUs or SIMDs idle, key groups put more waves
+// on the same tile (bf16, microseconds without and with: 8 heads of 64 x 4096 x 128 100 -> 59, 16 of 1024 x 1024 x 128 27 -> 18.4,
+// 24 of 686 x 686 x 64 13.5 -> 11.8).
+template <int DT, int OUT, int DH, int QW, int KG, int KB>
+__global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1) attention_kernel(const AttnParams p) {
     typedef OutTraits<OUT> OT;
     typedef typename OT::type out_t;
     constexpr int OS = (int)sizeof(out_t);
-    constexpr int KB = 64, JB = KB / 32;        // keys of a chunk, 32-key blocks of it
+    constexpr int TQ = QW * 32, GT = QW * 64;   // queries of a workgroup, threads of a key group
+    constexpr int JB = KB / 32;                 // 32-key blocks of a chunk of KB keys
     constexpr int ROW = DH * 2;                 // bytes of one Q / K / V row
     constexpr int HALVES = DH / 64;             // 128-byte column groups of a K-major row
     constexpr int TILE = KB * ROW;              // one chunk of K or V
     constexpr int KSTEPS = DH / 16;             // MFMA k-steps over the head dimension
     constexpr int DB = DH / 32;                 // 32-wide blocks of the output's head dimension
     constexpr int VRC = ROW / 16;               // 16-byte chunks per V row
-    constexpr int COPIES = TILE / 4096;         // copy instructions per wave for one chunk of K or V
+    constexpr int KROWS = GT / 8, KPASS = KB / KROWS;          // rows of K one copy instruction per wave covers (of one column group)
+    constexpr int COPIES = TILE / (GT * 16);    // copy instructions per wave for one chunk of V
+    constexpr int RING = 4 * TILE;              // one key group's two stages of K and V
     // V tile [key][ROW] with the transposing-read swizzle: byte offset XOR ((key / RPW) % NSEG) * 64
     constexpr int WIN = ROW < 256 ? ROW : 256;
     constexpr int NSEG = WIN / 64, RPW = 256 / WIN;
+    constexpr int MERGE = DB * 4096 + 512;      // what a wave hands over: its accumulators, sums and references
+    constexpr int LDS = RING * KG > TQ * DH * OS ? RING * KG : TQ * DH * OS;
     static_assert(DH == 64 || DH == 128, "head dimension");
-    static_assert(128 * DH * OS <= 4 * TILE, "the output tile is staged where K and V were");
+    static_assert(KROWS % 16 == 0 && KPASS >= 1 && COPIES >= 1, "the K swizzle repeats every 16 rows");
+    static_assert((KG - 1) * QW * MERGE <= LDS && LDS <= 160 * 1024, "");
 
-    __shared__ __attribute__((aligned(1024))) char smem[4 * TILE];
-    auto s_k = [&](int st) { return smem + st * 2 * TILE; };
-    auto s_v = [&](int st) { return smem + TILE + st * 2 * TILE; };
+    __shared__ __attribute__((aligned(1024))) char smem[LDS];
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kgrp = KG == 1 ? 0 : wave_wg / QW, wave = wave_wg - kgrp * QW;
+    const int tid = (int)threadIdx.x - kgrp * GT;                // thread of the key group
     const int l31 = lane & 31, g = lane >> 5;
     const int blk = lane >> 4, s16 = lane & 15;
+    char* const ring = smem + kgrp * RING;
 
     // Workgroups go to the 8 L2 domains round-robin by launch index: each domain gets a run of consecutive tiles, i.e. whole heads,
     // whose keys and values its L2 then holds once.
@@ -87,20 +98,21 @@ __global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
     const int bid = xf * xq + (xf < xr ? xf : xr) + (blockIdx.x >> 3);
     const long long b = fastdiv((unsigned)bid, p.div_tm_magic, p.div_tm_shift);
     const int tm = bid - (int)b * p.tiles_m;
-    const int m0 = tm * 128;
-    const int rows_q = p.M - m0 < 128 ? p.M - m0 : 128;
+    const int m0 = tm * TQ;
+    const int rows_q = p.M - m0 < TQ ? p.M - m0 : TQ;
     const int nchunk = (p.N + KB - 1) / KB;
+    const int nmine = (nchunk - kgrp + KG - 1) / KG;             // this group's chunks (chunk i of it is i * KG + kgrp)
+    const int nloop = (nchunk + KG - 1) / KG;                    // ... of the longest group: all take part in its barriers
 
     // ------------------------------------------------------------ copy stage
     // K-major tile: HALVES sub-tiles of [KB rows][128 B] so that the row swizzle of the GEMM kernels applies unchanged.
-    unsigned k_off[2], v_off;                         // the lane's offsets of copy instruction i: a constant plus i times a scalar
+    unsigned k_off, v_off;                            // the lane's offsets of the first copy instruction; the others are scalars further on
     {
         const int row = tid >> 3;
-        k_off[0] = (unsigned)(row * ROW + (((tid & 7) ^ kmajor_swz<128>(row)) << 4));
-        k_off[1] = k_off[0] + 32 * ROW;               // rows 32 on: the swizzle repeats every 16
-        const int key = tid / VRC;                    // 256 threads: whole multiples of the swizzle's period
+        k_off = (unsigned)(row * ROW + (((tid & 7) ^ kmajor_swz<128>(row)) << 4));
+        const int key = tid / VRC;
         v_off = (unsigned)(key * ROW + (((tid % VRC) * 16) ^ (((key / RPW) % NSEG) * 64)));
-        static_assert((256 / VRC) % (RPW * NSEG) == 0, "the V swizzle repeats from one copy instruction to the next");
+        static_assert((GT / VRC) % (RPW * NSEG) == 0, "the V swizzle repeats from one copy instruction to the next");
     }
     const char* Qb = (const char*)p.Q + ((b * p.M + m0) * (long long)ROW);
     const char* Kb = (const char*)p.K + b * p.N * (long long)ROW;
@@ -108,25 +120,27 @@ __global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
     // Non-temporal copies for what one workgroup alone reads (one tile holds all queries of a head): 7.05 -> 6.63 us on the
     // benchmark's 192 heads with the operands coming from memory, no change from the caches.
     const bool kv_once = p.tiles_m == 1;
-    auto copy_chunk = [&](int c) __attribute__((always_inline)) {
+    // (`st`, the ring stage of chunk i, is a constant in every call: worked out from i it costs an addition per LDS read)
+    auto copy_chunk = [&](int i, int st) __attribute__((always_inline)) {
+        const int c = i * KG + kgrp;
         const long long left = (long long)(p.N - c * KB) * ROW;      // rows past N lie outside the descriptor: zeros
         const i32x4 rk = make_rsrc(Kb + (long long)c * TILE, left), rv = make_rsrc(Vb + (long long)c * TILE, left);
-        char* const dk = s_k(c & 1) + wave * 1024;
-        char* const dv = s_v(c & 1) + wave * 1024;
+        char* const dk = ring + st * 2 * TILE + wave * 1024;
+        char* const dv = dk + TILE;
 #pragma unroll
         for (int h = 0; h < HALVES; ++h)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                if (kv_once) load_to_lds_nt(rk, dk + h * (KB * 128) + i * 4096, k_off[i] + h * 128);
-                else load_to_lds(rk, dk + h * (KB * 128) + i * 4096, k_off[i] + h * 128);
+            for (int u = 0; u < KPASS; ++u) {
+                if (kv_once) load_to_lds_nt(rk, dk + h * (KB * 128) + u * (GT * 16), k_off + u * (KROWS * ROW) + h * 128);
+                else load_to_lds(rk, dk + h * (KB * 128) + u * (GT * 16), k_off + u * (KROWS * ROW) + h * 128);
             }
 #pragma unroll
-        for (int i = 0; i < COPIES; ++i) {
-            if (kv_once) load_to_lds_nt(rv, dv + i * 4096, v_off + i * 4096);
-            else load_to_lds(rv, dv + i * 4096, v_off + i * 4096);
+        for (int u = 0; u < COPIES; ++u) {
+            if (kv_once) load_to_lds_nt(rv, dv + u * (GT * 16), v_off + u * (GT * 16));
+            else load_to_lds(rv, dv + u * (GT * 16), v_off + u * (GT * 16));
         }
     };
-    copy_chunk(0);
+    if (nmine > 0) copy_chunk(0, 0);
 
     // ------------------------------------------------------------ this wave's queries, as MFMA operands (rows past M read zeros)
     uint4 qf[KSTEPS];
@@ -150,12 +164,13 @@ __global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
     // A row's reference only has to be close to its maximum: it is raised when some row of the wave has a score 2^8 above it
     // (binary16 probabilities hold 2^15), which after the first chunk is rare, and the accumulators are rescaled only then.
     constexpr float kSlack = 8.0f;
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    copy_barrier<0>();                                // the queries and the first chunk
 
-    for (int c = 0; c < nchunk; ++c) {
-        if (c + 1 < nchunk) copy_chunk(c + 1);        // its stage was last read before the previous barrier
-        const char* sk = s_k(c & 1);
-        const char* sv = s_v(c & 1);
+    auto multiply_chunk = [&](int i, int st) __attribute__((always_inline)) {
+        const int c = i * KG + kgrp;
+        if (i + 1 < nmine) copy_chunk(i + 1, st ^ 1); // its stage was last read before the previous barrier
+        const char* sk = ring + st * 2 * TILE;
+        const char* sv = sk + TILE;
 
         // S^T = K Q^T: rows = keys (registers), columns = queries (lanes)
         f32x16 acc_s[JB];
@@ -194,7 +209,7 @@ __global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
                 for (int r = 0; r < 16; ++r) mx = __builtin_fminf(mx, acc_s[jb][r]);
             mx = __builtin_fminf(mx, __shfl_xor(mx, 32));
         }
-        if (c == 0) m_ref = mx;                                      // finite: every chunk has at least one valid key
+        if (i == 0) m_ref = mx;                                      // finite: every chunk has at least one valid key
         else if (__builtin_amdgcn_ballot_w64((mx - m_ref) * sc > kSlack) != 0) {
             const float alpha = __builtin_amdgcn_exp2f((m_ref - mx) * sc);
             // (rows whose reference is already above keep it)
@@ -246,9 +261,69 @@ __global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
                     acc_o[db] = InTraits<DT>::mfma(vf, pf[jb][s], acc_o[db]);
                 }
 
-        // the next chunk has landed (this wave's part); after the barrier everybody's has, and every
-        // wave is done reading this chunk's stage
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    auto step = [&](int i, int st) __attribute__((always_inline)) {
+        if (KG == 1 || i < nmine) multiply_chunk(i, st);
+        // the next chunk has landed (this wave's part); after the barrier everybody's has, and every wave is done reading
+        // this chunk's stage (a third stage, to wait for the chunk before last only, gained nothing: the copies are not late)
+        copy_barrier<0>();
+    };
+    for (int i = 0; i < nloop; i += 2) {
+        step(i, 0);
+        if (i + 1 < nloop) step(i + 1, 1);
+    }
+
+    if constexpr (KG > 1) {
+        // ------------------------------------------------------------ merge the key groups: sums and accumulators relative to the largest reference
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        const float ms = nmine > 0 ? m_ref * sc : -__builtin_inff();           // (a group without a chunk counts nothing)
+        auto area = [&](int k) { return smem + ((k - 1) * QW + wave) * MERGE; };      // the stages are free: everybody is past the last barrier
+        if (kgrp != 0) {
+            f32x4* const o = (f32x4*)area(kgrp);
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = acc_o[db][4 * q4 + e];
+                    o[(db * 4 + q4) * 64 + lane] = v;
+                }
+            float* const t = (float*)(area(kgrp) + DB * 4096);
+            t[lane] = l_run;
+            t[64 + lane] = ms;
+        }
+        __syncthreads();
+        if (kgrp == 0) {
+            float top = ms, mk[KG];
+            mk[0] = ms;
+#pragma unroll
+            for (int k = 1; k < KG; ++k) {
+                mk[k] = ((const float*)(area(k) + DB * 4096))[64 + lane];
+                top = __builtin_fmaxf(top, mk[k]);
+            }
+            const float own = __builtin_amdgcn_exp2f(mk[0] - top);             // (group 0 always has a chunk: top is finite)
+            l_run *= own;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_o[db][r] *= own;
+#pragma unroll
+            for (int k = 1; k < KG; ++k) {
+                const float f = __builtin_amdgcn_exp2f(mk[k] - top);
+                l_run += f * ((const float*)(area(k) + DB * 4096))[lane];
+                const f32x4* const o = (const f32x4*)area(k);
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const f32x4 v = o[(db * 4 + q4) * 64 + lane];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc_o[db][4 * q4 + e] += f * v[e];
+                    }
+            }
+        }
+        __syncthreads();                               // the output tile is staged where the handed-over values were
     }
 
     // ------------------------------------------------------------ normalise, stage through LDS, store rows
@@ -256,6 +331,7 @@ __global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
     const float inv = 1.0f / l_tot;
     constexpr int ORB = DH * OS;                     // bytes of one output row
     char* const s_o = smem;                          // the K / V stages are free now
+    if (KG == 1 || kgrp == 0)
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -276,8 +352,8 @@ __global__ void __launch_bounds__(256, 2) attention_kernel(const AttnParams p) {
         const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)Ob, 0, rows_q * ORB, 0x00020000);
         constexpr int ORC = ORB / 16;                // 16-byte chunks per output row
 #pragma unroll
-        for (int i = 0; i < 128 * ORC / 256; ++i) {
-            const int q = tid + i * 256;
+        for (int i = 0; i < TQ * ORC / (GT * KG); ++i) {
+            const int q = (int)threadIdx.x + i * GT * KG;
             const int row = q / ORC, pc = q % ORC;
             typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
             const u32x4 v = *(const u32x4*)(s_o + row * ORB + ((pc * 16) ^ ((row & 7) << 4)));

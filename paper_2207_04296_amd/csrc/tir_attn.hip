@@ -6,8 +6,23 @@
 
 namespace tir {
 
+template <int DT, int OUT, int DH, int QW, int KG, int KB> static hipError_t launch_attn_as(AttnParams p, hipStream_t stream) {
+    p.tiles_m = (p.M + 32 * QW - 1) / (32 * QW);
+    const FastDiv dtm = make_fastdiv((unsigned)p.tiles_m);
+    p.div_tm_magic = dtm.magic;
+    p.div_tm_shift = dtm.shift;
+    return launch_kernel(&attention_kernel<DT, OUT, DH, QW, KG, KB>, dim3((unsigned)(p.batch * p.tiles_m)), dim3(QW * KG * 64), stream, p);
+}
+
 template <int DT, int OUT, int DH> static hipError_t launch_attn(const AttnParams& p, hipStream_t stream) {
-    return launch_kernel(&attention_kernel<DT, OUT, DH>, dim3((unsigned)(p.batch * p.tiles_m)), dim3(256), stream, p);
+    const long long tiles = (long long)p.batch * ((p.M + 127) / 128);        // of 128 queries
+    // Two workgroups of four waves fill a CU.  Up to about one tile per CU a second key group takes the place of the second workgroup,
+    // up to half a tile four groups on half-tiles do; the merge costs about a chunk's time, so the groups need a few chunks each.  At
+    // d = 128 two groups take a CU's whole LDS, and from 160 tiles on (60 heads of 512 x 512: 240 tiles, 2 % slower) they gain nothing; at
+    // d = 64 two such workgroups share a CU (256 x 100 x 1000 20.3 us instead of 22.7, 96 x 300 x 3000 53.5 instead of 61).
+    if (tiles <= 128 && p.N > 256) return launch_attn_as<DT, OUT, DH, 2, 4, DH == 64 ? 64 : 32>(p, stream);
+    if (tiles <= (DH == 128 ? 144 : p.N >= 1024 ? 384 : 256) && p.N >= 384) return launch_attn_as<DT, OUT, DH, 4, 2, 64>(p, stream);
+    return launch_attn_as<DT, OUT, DH, 4, 1, 64>(p, stream);
 }
 
 attn_launch_fn attention_launcher(int dt, int out, int dh) {

@@ -718,6 +718,12 @@ ATTN_CASES = [
     (1, 300, 512, 128, 0.0884),      # head dimension 128, four chunks
     (2, 64, 384, 64, 3.0),           # peaked softmax
     (2, 40, 100, 128, 0.0),          # scale 0: uniform attention
+    (3, 70, 257, 64, 0.2),           # four key groups, the last one with a single key
+    (2, 65, 300, 128, -0.3),         # ... of 32-key chunks, a negative scale
+    (1, 33, 1200, 128, 4.0),         # ... several chunks each, references that rise late
+    (129, 20, 390, 64, 0.125),       # two key groups, an odd chunk count
+    (140, 1, 385, 128, 1.5),         # ... one key in the last chunk
+    (1, 200, 70, 64, -1.0),          # one group, two chunks, a negative scale
 ]
 
 
