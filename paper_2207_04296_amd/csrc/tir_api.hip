@@ -350,11 +350,6 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
     return best;
 }
 
-// by phase, a stage must hold channels of one tap
-static bool tuned_or_trial_mismatch(const Variant* v, int64_t group_channel_bytes) {
-    return v->amode == A_CONV && group_channel_bytes % v->rowb != 0 && !g_trial.v;
-}
-
 struct Plan {
     const Variant* v;
     Params p;
@@ -528,12 +523,16 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
                          N * ((P + 3) / 4) * ((Q + 15) / 16) * ((K + 31) / 32) <= kMaxExtent;
     if (rows_ok && !(g_force_name[0] && !strstr(g_force_name, "rows"))) amode = A_CONV_ROWS;
     // A strided transposed convolution multiplies mostly structural zeros when read as one gather (only every
-    // stride-th tap meets an input pixel).  Undilated, with whole stages per tap (one stage = 128 bytes of channels),
-    // it is computed per output phase instead: stride_h*stride_w stride-1 convolutions with a tap subset each, all
-    // in one launch of the 2-D kernels (a forced general-decode variant keeps the gather).
+    // stride-th tap meets an input pixel).  Undilated, it is computed per output phase instead: stride_h*stride_w stride-1
+    // convolutions with a tap subset each, all in one launch of the 2-D kernels (a forced general-decode variant keeps the
+    // gather).  A stage then holds channels of one tap, so channels are padded to whole stages (of 128 bytes in most tiles);
+    // where that padding leaves less than half of the work saved the gather, whose stages run across taps, stays.
+    // 4x4 stride 2 as a gather and by phase: 10 images 10x12, 416 -> 32 channels bf16 23.8 and 10.6 us; 3 of 14x43, 288 -> 32 fp16
+    // 23.8 and 8.9; 7 of 33x21, 32 -> 32 bf16 (half of every stage is padding) 11.9 and 5.7.
     const int64_t phases = (int64_t)g.stride_h * g.stride_w;
     const int64_t Pp = (P + g.stride_h - 1) / g.stride_h, Qp = (Q + g.stride_w - 1) / g.stride_w;      // pixel grid of one phase
-    const bool phased = g.transposed && amode == A_CONVX && phases > 1 && g.dil_h == 1 && g.dil_w == 1 && (Cg * es) % 128 == 0 &&
+    const int64_t tap_stages = (Cg * es + 127) / 128;
+    const bool phased = g.transposed && amode == A_CONVX && phases > 1 && g.dil_h == 1 && g.dil_w == 1 && tap_stages * 128 * 2 <= Cg * es * phases &&
                         groups * phases <= 65535 && N * P * Q * K * elem_size(out) < kMaxExtent && N * Pp * Qp <= kMaxExtent &&
                         !(g_force_name[0] && (strstr(g_force_name, "convx") || strstr(g_force_name, "generic")));
     if (phased) amode = A_CONV;
@@ -550,7 +549,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
                               g.transposed ? 1 : 0, g.transposed ? g.outpad_h : 0, g.transposed ? g.outpad_w : 0, 0};
     plan->key = TuneKey{1, in, out, amode, bmode, groups * N, OD * P * Q, Kg, Kd, hash_fields(geom, 21)};
     // the tile grid the variants are scored on: by phase, every phase is a batch entry of its own with a share of the taps
-    const int64_t sc_batch = phased ? groups * phases : groups, sc_M = phased ? N * Pp * Qp : Mg, sc_K = phased ? (Kd + phases - 1) / phases : Kd;
+    const int64_t sc_batch = phased ? groups * phases : groups, sc_M = phased ? N * Pp * Qp : Mg, sc_K = phased ? (T * R * S * tap_stages * (128 / es) + phases - 1) / phases : Kd;
     Choice ch = kNoChoice;
     // depth-wise (one input and one output channel per group): the direct kernel, unless a test forces a tile variant
     if (plain2d && Cg == 1 && Kg == 1 && C % vec == 0 && R * S <= kDwMaxTaps && aligned(x, 16) && aligned(w, 16) && aligned(y, 16) &&
@@ -565,9 +564,8 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     if (!ch.v) {
         const bool use_patch = patch_ok && !g_force_ksplit && (!g_force_name[0] || strstr(g_force_name, "patch"));
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);
-        else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
+        else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
     }
-    if (phased && ch.v && tuned_or_trial_mismatch(ch.v, Cg * es)) ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, sl, 128);
     const Variant* v = ch.v;
     if (v && v->amode == A_CONV_PATCH) amode = A_CONV_PATCH;
     if (!v) return fail(TIR_ERR_UNSUPPORTED, "no kernel variant for this dtype / forced tile");
@@ -615,8 +613,8 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     p.stride_d = g.stride_d; p.pad_d = g.pad_d; p.dil_d = g.dil_d;
     p.dil_h = g.dil_h; p.dil_w = g.dil_w;
     if (phased) {
-        if (v->amode != A_CONV || (Cg * es) % v->rowb != 0)
-            return fail(TIR_ERR_UNSUPPORTED, "transposed convolution by phase needs a 2-D implicit-GEMM variant whose stages hold one tap (got %s)", v->name);
+        if (v->amode != A_CONV)
+            return fail(TIR_ERR_UNSUPPORTED, "transposed convolution by phase needs a 2-D implicit-GEMM variant (got %s)", v->name);
         p.M = (int)(N * Pp * Qp);
         p.batch = (int)(groups * phases);
         p.tiles_m = (int)((p.M + v->bm - 1) / v->bm);

@@ -588,7 +588,9 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
 
     // Transposed convolution by output phase: this grid.y entry is (phase, group).  The phase's pixels are a
     // stride-1 convolution with every phases-th filter tap, taken backwards (cursor tap (fr, fs) is filter tap
-    // (f_r0 - phases_h*fr, f_s0 - phases_w*fs)); tap count, padding and with them K differ per phase.
+    // (f_r0 - phases_h*fr, f_s0 - phases_w*fs)); tap count, padding and with them K differ per phase.  A phase's taps are
+    // not neighbours in a filter row, so a stage never crosses from one to the next: channels that do not fill their last
+    // stage leave its other lanes switched off.
     int cS = p.S, cK = p.K, cpad_h = p.pad_h, cpad_w = p.pad_w;
     int f_r0 = 0, f_s0 = 0, ph = 0, pw = 0;
     bool phased = false;
@@ -609,7 +611,7 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
             cpad_w = (cS - 1) - qw;
             f_r0 = r0 + p.phases_h * (cR - 1);
             f_s0 = s0 + p.phases_w * (cS - 1);
-            cK = cR * cS * p.Cg;                          // 0 for a phase no tap reaches: its pixels get the empty sum
+            cK = cR * cS * ((p.Cg + BK - 1) / BK * BK);   // whole stages per tap; 0 for a phase no tap reaches: its pixels get the empty sum
         }
     }
 
@@ -717,12 +719,14 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
 
     // Per-stage copy state: descriptors (SGPRs) and, for the convolution, this stage's offsets and
     // the scalar tap cursor (filter row, filter column, channel offset of the next stage).
-    const bool conv_uniform_tap = (C::AMODE == A_CONV || C::AMODE == A_CONVX) && (p.Cg % BK == 0);
+    const bool conv_uniform_tap = (C::AMODE == A_CONV || C::AMODE == A_CONVX) && (p.Cg % BK == 0 || phased);
+    const bool ragged_tap = C::AMODE == A_CONV && phased && p.Cg % BK != 0;
+    const int conv_cg = (p.Cg + BK - 1) / BK * BK;       // channels of one tap in whole stages (= Cg unless ragged)
     int conv_ft = 0, conv_fr = 0, conv_fs = 0, conv_cc = 0;
     auto conv_advance = [&](int stages) {                // move the tap cursor `stages` stages ahead
         conv_cc += stages * BK;
-        while (conv_cc >= p.Cg) {
-            conv_cc -= p.Cg;
+        while (conv_cc >= conv_cg) {
+            conv_cc -= conv_cg;
             if (++conv_fs == cS) {
                 conv_fs = 0;
                 ++conv_fr;
@@ -733,7 +737,7 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
         }
     };
     if (conv_uniform_tap) conv_advance(s_begin + kgrp);
-    // One stage ahead, branch-free (Cg is a multiple of the stage's k extent: at most one tap boundary per stage).
+    // One stage ahead, branch-free (a tap is a whole number of stages: at most one tap boundary per stage).
     auto conv_step = [&]() {
         conv_cc += BK;
         const bool tap_end = conv_cc >= p.Cg;
@@ -834,14 +838,23 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
             // fuse(rh, rw, rc) -> (rh, rw, rc); a 16-byte vector never straddles a tap (Cg % VEC == 0)
             ra = make_rsrc32(Ab, live ? (unsigned)a_bytes : 0u);
             if (conv_uniform_tap) {
-                // Cg is a multiple of the stage's k extent: the whole stage belongs to one tap, so the tap
-                // decode is scalar and advances incrementally (stages are prepared in order)
+                // the whole stage belongs to one tap, so the tap decode is scalar and advances incrementally (stages are
+                // prepared in order)
                 const int dh = conv_fr * p.dil_h, dw = conv_fs * p.dil_w;
                 const unsigned delta = (unsigned)(((dh * p.W + dw) * p.Cin + conv_cc) * ES) + a_lc * 16;
-                // not live: the descriptor is empty (K = R*S*Cg is a multiple of the stage extent here)
+                // not live: the descriptor is empty (the reduction is a whole number of stages here)
                 const u16x2 d_hw = {(unsigned short)dw, (unsigned short)dh};
 #pragma unroll
                 for (int i = 0; i < C::A_IT; ++i) a_voff[i] = inside(a_hw[i], d_hw) ? a_off[i] + delta : kOutOfRange;
+                if (ragged_tap) {
+                    // the tap's last stage: vectors past its channels (the next pixel's, another tap's filter values) read as zeros
+                    const bool a_kv = conv_cc + a_lc * VEC < p.Cg, b_kv = conv_cc + b_lc * VEC < p.Cg;
+#pragma unroll
+                    for (int i = 0; i < C::A_IT; ++i) a_voff[i] = a_kv ? a_voff[i] : kOutOfRange;
+#pragma unroll
+                    for (int i = 0; i < C::B_IT; ++i)
+                        b_off[i] = b_kv ? (unsigned)(b_r0 + i * C::K_RSTEP) * (unsigned)(p.b_cs * ES) + b_lc * 16 : kOutOfRange;
+                }
 #pragma unroll
                 for (int kw = 0; kw < C::KW; ++kw) conv_step();
             } else {

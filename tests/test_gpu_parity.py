@@ -925,7 +925,7 @@ def test_conv2d_transpose_matches_oracle(B, oracle, dtype, out):
 
 @pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("f16", "f32"), ("bf16", "f32"), ("i8", "i32"), ("i8", "i8")])
 def test_conv2d_transpose_by_output_phase(B, oracle, dtype, out):
-    """Strided, undilated transposed convolutions whose channel blocks fill whole stages run as stride_h*stride_w
+    """Strided, undilated transposed convolutions (here with channel blocks that fill whole stages) run as stride_h*stride_w
     stride-1 convolutions (one per output phase, with that phase's taps) in one launch; same bar, and the gather
     form of the same problem (forced) must agree with the oracle as well."""
     import torch
@@ -966,6 +966,52 @@ def test_conv2d_transpose_by_output_phase(B, oracle, dtype, out):
                 PT.assert_close(PT.gpu_to_f64(y), ref, S, f"conv2d_transpose {'by phase' if not force else 'as a gather'}")
         finally:
             B.tir_debug_force_variant("")
+
+
+@pytest.mark.parametrize("dtype,out", [("f16", "f32"), ("bf16", "f32"), ("i8", "i8")])
+@pytest.mark.parametrize("vecs", [4, 7, 9, 15, 26])
+def test_conv2d_transpose_by_output_phase_pads_the_last_stage_of_a_tap(B, oracle, dtype, out, vecs):
+    """By phase with channels that are no multiple of a stage (vecs 16-byte vectors per pixel and group): through the default, copy-wave,
+    reduction-group, 64-byte- and 256-byte-stage variants.  An infinite filter value reaches exactly the outputs whose phase uses its tap (the
+    vectors past a tap's channels are another tap's values)."""
+    import torch
+    vec = 16 if dtype == "i8" else 8
+    N, H, W, K, stride, pad, outpad, groups = 2, 9, 7, 40, (2, 2), (1, 1), (1, 0), 2
+    R, S_ = 4, 3
+    C = groups * vecs * vec
+    xb = I.make_tensor(dtype, "i" if dtype == "i8" else "n0.1", 9940 + vecs, (N, H, W, C))
+    wb = I.make_tensor(dtype, "i" if dtype == "i8" else "n0.1", 9941 + vecs, (K, R, S_, C // groups))
+    scale = 1.0 / 700.0 if out == "i8" else 0.0
+    ep = B.make_epilogue(None, False, scale)
+    xd, wd = B.to_device(xb, dtype), B.to_device(wb, dtype)
+    ref, S = oracle.conv2d_transpose(dtype, xb, wb, stride, pad, (1, 1), outpad, groups)
+    if scale:
+        ref, S = oracle.epilogue(ref, S, bias=None, relu=False, scale=scale)
+    names = ["", "128x64w2x2s3c4_conv", "64x64w2x2s3k2_conv", "64x32w2x1s4_conv", "256x256w2x4s4r64_conv"] + (["64x64w2x2s3c4r256_conv"] if vecs == 26 else [])
+    _say(f"conv2d_transpose ragged stages {dtype}->{out} C={C}")
+    assert B.tir_conv2d_transpose_variant(N, H, W, C, K, R, S_, stride, pad, (1, 1), outpad, groups, dtype, out).endswith("/ph2x2")
+
+    def run(w):
+        y = _gpu_out(B, ref.shape, out)
+        B.tir_conv2d_transpose(xd, w, y, N, H, W, C, K, R, S_, stride, pad, (1, 1), outpad, groups, dtype, out, ep=ep)
+        torch.cuda.synchronize()
+        return PT.gpu_to_f64(y)
+
+    try:
+        for force in names:
+            B.tir_debug_force_variant(force)
+            PT.assert_close(run(wd), ref, S, f"ragged stages through {force or 'the default'}")
+            if dtype != "i8":
+                poisoned = wd.clone()
+                poisoned[3, 1, 1, 0] = float("inf")          # first channel of tap (1, 1): group 0's output channel 3
+                got = run(poisoned)
+                # y[n, oh, ow] meets tap (1, 1) where oh - (1 - pad) and ow - (1 - pad) are multiples of the stride (past the input: infinity x padding)
+                hit = np.zeros(ref.shape, dtype=bool)
+                hit[:, 0::2, 0::2, 3] = True
+                assert np.array_equal(~np.isfinite(got), hit), f"infinite filter value through {force or 'the default'}"
+                PT.assert_close(np.where(hit, 0.0, got), np.where(hit, 0.0, ref), S, "finite outputs")
+    finally:
+        B.tir_debug_force_variant("")
 
 
 # ------------------------------------------------------------------------------ depth-wise convolution
