@@ -73,6 +73,12 @@ AM_TILES = [(256, 256, 2, 4, 64, 3, 1), (256, 128, 4, 2, 128, 3, 1, 4), (128, 19
             (64, 64, 2, 2, 128, 3, 2), (64, 32, 2, 1, 128, 4, 1)]
 AM_MODES = [("am_bk", "A_MMAJOR", "B_KMAJOR"), ("am_bn", "A_MMAJOR", "B_NMAJOR")]
 
+# by output phase with a ragged last stage per tap: the tiles the scoring rule reaches
+RAGGED_TILES = [(256, 256, 2, 4, 64, 4, 1), (256, 128, 4, 2, 128, 3, 1, 4), (128, 192, 2, 2, 128, 3, 1, 4), (128, 128, 2, 2, 128, 4, 1, 4),
+                (128, 64, 2, 2, 128, 4, 1), (64, 64, 2, 2, 128, 4, 1), (64, 64, 2, 2, 128, 4, 2), (128, 32, 4, 1, 128, 3, 2),
+                (64, 32, 2, 1, 128, 4, 1), (64, 32, 2, 1, 128, 4, 2)]
+RAGGED_MODES = [("convr", "A_CONV_RAGGED", "B_KMAJOR")]
+
 # operands of any alignment, staged through registers (two stages ahead)
 U_TILES = [(128, 128, 2, 2, 128, 2, 1), (128, 64, 4, 2, 128, 2, 1), (64, 64, 2, 2, 128, 2, 1), (64, 64, 2, 2, 128, 2, 2), (64, 32, 2, 1, 128, 2, 1), (64, 32, 2, 1, 128, 2, 4)]
 U_MODES = [("uk_uk_generic", "A_UK", "B_UK"), ("uk_un_generic", "A_UK", "B_UN"), ("um_uk_generic", "A_UM", "B_UK"), ("um_un_generic", "A_UM", "B_UN")]
@@ -84,7 +90,7 @@ def render() -> str:
            "//   Vn(name, DT, OUT, BM, BN, WM, WN, AMODE, BMODE, ROWB, NSTAGE, KW, CW)   n = index of the translation unit that",
            "// instantiates the variant (tir_inst.hip is compiled once per unit with -DTIR_UNIT=n)."]
     for unit, (dt, od, tag) in enumerate(PAIRS):
-        for tile, modes in [(t, MODES) for t in TILES] + [(t, AM_MODES) for t in AM_TILES] + [(t, U_MODES) for t in U_TILES]:
+        for tile, modes in [(t, MODES) for t in TILES] + [(t, AM_MODES) for t in AM_TILES] + [(t, RAGGED_MODES) for t in RAGGED_TILES] + [(t, U_MODES) for t in U_TILES]:
             (bm, bn, wm, wn, rowb, ns, kw), cw = tile[:7], (tile[7] if len(tile) > 7 else 0)
             for (mname, am, bmo) in modes:
                 if bmo == "B_NMAJOR" and dt == "DT_I8" and bn * 1 < 32:

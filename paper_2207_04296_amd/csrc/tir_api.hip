@@ -81,7 +81,7 @@ struct VariantRange {
     const Variant* const* first;
     int n;
 };
-static const int kModes = 11, kDtypes = 5;
+static const int kModes = 12, kDtypes = 5;
 static VariantRange variants_of(int dt, int out, int amode, int bmode) {
     struct Index {
         const Variant* order[kNumVariants];
@@ -350,6 +350,11 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
     return best;
 }
 
+// by phase, a stage must hold channels of one tap
+static bool tuned_or_trial_mismatch(const Variant* v, int64_t group_channel_bytes) {
+    return v->amode == A_CONV && group_channel_bytes % v->rowb != 0 && !g_trial.v;
+}
+
 struct Plan {
     const Variant* v;
     Params p;
@@ -525,17 +530,18 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     // A strided transposed convolution multiplies mostly structural zeros when read as one gather (only every
     // stride-th tap meets an input pixel).  Undilated, it is computed per output phase instead: stride_h*stride_w stride-1
     // convolutions with a tap subset each, all in one launch of the 2-D kernels (a forced general-decode variant keeps the
-    // gather).  A stage then holds channels of one tap, so channels are padded to whole stages (of 128 bytes in most tiles);
-    // where that padding leaves less than half of the work saved the gather, whose stages run across taps, stays.
+    // gather).  A stage then holds channels of one tap, so channels are padded to whole 128-byte stages (A_CONV_RAGGED);
+    // where half of the saving or more would go into that padding the gather, whose stages run across taps, stays.
     // 4x4 stride 2 as a gather and by phase: 10 images 10x12, 416 -> 32 channels bf16 23.8 and 10.6 us; 3 of 14x43, 288 -> 32 fp16
-    // 23.8 and 8.9; 7 of 33x21, 32 -> 32 bf16 (half of every stage is padding) 11.9 and 5.7.
+    // 23.8 and 8.9.
     const int64_t phases = (int64_t)g.stride_h * g.stride_w;
     const int64_t Pp = (P + g.stride_h - 1) / g.stride_h, Qp = (Q + g.stride_w - 1) / g.stride_w;      // pixel grid of one phase
     const int64_t tap_stages = (Cg * es + 127) / 128;
-    const bool phased = g.transposed && amode == A_CONVX && phases > 1 && g.dil_h == 1 && g.dil_w == 1 && tap_stages * 128 * 2 <= Cg * es * phases &&
+    const bool ragged = (Cg * es) % 128 != 0;
+    const bool phased = g.transposed && amode == A_CONVX && phases > 1 && g.dil_h == 1 && g.dil_w == 1 && (!ragged || tap_stages * 128 * 2 < Cg * es * phases) &&
                         groups * phases <= 65535 && N * P * Q * K * elem_size(out) < kMaxExtent && N * Pp * Qp <= kMaxExtent &&
                         !(g_force_name[0] && (strstr(g_force_name, "convx") || strstr(g_force_name, "generic")));
-    if (phased) amode = A_CONV;
+    if (phased) amode = ragged ? A_CONV_RAGGED : A_CONV;
     // LDS-resident input patch: one pixel of one group is exactly one 128-byte LDS row, the input rows
     // that 256 consecutive output pixels touch (rows padded to 8 pixels, copied in passes of 32) fit beside the R*S filter slabs
     const int64_t span_out = (255 + Q - 1) / Q < P - 1 ? (255 + Q - 1) / Q : P - 1;   // output rows a tile can span, minus one
@@ -566,6 +572,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);
         else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
     }
+    if (phased && ch.v && tuned_or_trial_mismatch(ch.v, Cg * es)) ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, kNoSplit, 128);
     const Variant* v = ch.v;
     if (v && v->amode == A_CONV_PATCH) amode = A_CONV_PATCH;
     if (!v) return fail(TIR_ERR_UNSUPPORTED, "no kernel variant for this dtype / forced tile");
@@ -613,8 +620,8 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     p.stride_d = g.stride_d; p.pad_d = g.pad_d; p.dil_d = g.dil_d;
     p.dil_h = g.dil_h; p.dil_w = g.dil_w;
     if (phased) {
-        if (v->amode != A_CONV)
-            return fail(TIR_ERR_UNSUPPORTED, "transposed convolution by phase needs a 2-D implicit-GEMM variant (got %s)", v->name);
+        if (v->amode != A_CONV_RAGGED && (v->amode != A_CONV || (Cg * es) % v->rowb != 0))
+            return fail(TIR_ERR_UNSUPPORTED, "transposed convolution by phase needs a 2-D implicit-GEMM variant whose stages hold one tap (got %s)", v->name);
         p.M = (int)(N * Pp * Qp);
         p.batch = (int)(groups * phases);
         p.tiles_m = (int)((p.M + v->bm - 1) / v->bm);

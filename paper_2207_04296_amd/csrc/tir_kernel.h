@@ -589,8 +589,8 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
     // Transposed convolution by output phase: this grid.y entry is (phase, group).  The phase's pixels are a
     // stride-1 convolution with every phases-th filter tap, taken backwards (cursor tap (fr, fs) is filter tap
     // (f_r0 - phases_h*fr, f_s0 - phases_w*fs)); tap count, padding and with them K differ per phase.  A phase's taps are
-    // not neighbours in a filter row, so a stage never crosses from one to the next: channels that do not fill their last
-    // stage leave its other lanes switched off.
+    // not neighbours in a filter row, so a stage never crosses from one to the next: where channels do not fill their last
+    // stage (A_CONV_RAGGED variants) its other lanes are switched off.
     int cS = p.S, cK = p.K, cpad_h = p.pad_h, cpad_w = p.pad_w;
     int f_r0 = 0, f_s0 = 0, ph = 0, pw = 0;
     bool phased = false;
@@ -611,7 +611,7 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
             cpad_w = (cS - 1) - qw;
             f_r0 = r0 + p.phases_h * (cR - 1);
             f_s0 = s0 + p.phases_w * (cS - 1);
-            cK = cR * cS * ((p.Cg + BK - 1) / BK * BK);   // whole stages per tap; 0 for a phase no tap reaches: its pixels get the empty sum
+            cK = cR * cS * (C::RAGGED_TAP ? (p.Cg + BK - 1) / BK * BK : p.Cg);   // whole stages per tap; 0 for a phase no tap reaches: its pixels get the empty sum
         }
     }
 
@@ -719,9 +719,8 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
 
     // Per-stage copy state: descriptors (SGPRs) and, for the convolution, this stage's offsets and
     // the scalar tap cursor (filter row, filter column, channel offset of the next stage).
-    const bool conv_uniform_tap = (C::AMODE == A_CONV || C::AMODE == A_CONVX) && (p.Cg % BK == 0 || phased);
-    const bool ragged_tap = C::AMODE == A_CONV && phased && p.Cg % BK != 0;
-    const int conv_cg = (p.Cg + BK - 1) / BK * BK;       // channels of one tap in whole stages (= Cg unless ragged)
+    const bool conv_uniform_tap = (C::AMODE == A_CONV || C::AMODE == A_CONVX) && (C::RAGGED_TAP || p.Cg % BK == 0);
+    const int conv_cg = C::RAGGED_TAP ? (p.Cg + BK - 1) / BK * BK : p.Cg;       // channels of one tap in whole stages
     int conv_ft = 0, conv_fr = 0, conv_fs = 0, conv_cc = 0;
     auto conv_advance = [&](int stages) {                // move the tap cursor `stages` stages ahead
         conv_cc += stages * BK;
@@ -846,7 +845,7 @@ __global__ void __launch_bounds__(C::THREADS) contract_direct_kernel(const Param
                 const u16x2 d_hw = {(unsigned short)dw, (unsigned short)dh};
 #pragma unroll
                 for (int i = 0; i < C::A_IT; ++i) a_voff[i] = inside(a_hw[i], d_hw) ? a_off[i] + delta : kOutOfRange;
-                if (ragged_tap) {
+                if constexpr (C::RAGGED_TAP) {
                     // the tap's last stage: vectors past its channels (the next pixel's, another tap's filter values) read as zeros
                     const bool a_kv = conv_cc + a_lc * VEC < p.Cg, b_kv = conv_cc + b_lc * VEC < p.Cg;
 #pragma unroll

@@ -23,6 +23,9 @@ enum : int {
     // and base address; the contiguous axis holds at least one 16-byte vector
     A_UK = 8,
     A_UM = 9,
+    // A_CONV by output phase with channels that leave a tap's last stage ragged.  Its own kernels: as a branch in the A_CONV loop the masks
+    // cost the others 2 % (16x14x14x256 -> 128, 4x4 stride 2 by phase 10.80 us, 10.60 here; 16x28x28x128 -> 256, 3x3 stride 2 7.24, 7.11)
+    A_CONV_RAGGED = 11,
     A_CONV_ROWS = 10,    // convolution of few channels: whole filter rows as the reduction's unit, patch and filter in LDS (tir_conv_rows.h)
     A_CONVX = 5          // implicit im2col with the general coordinate decode: a depth axis (3-D convolution) and the
                          // transposed form (taps step backwards, only every up-th coordinate is an input pixel)
@@ -197,7 +200,8 @@ template <int W, int ES> struct NMajorTile {
 template <int DT_, int OUT_, int BM_, int BN_, int WM_, int WN_, int AMODE_, int BMODE_, int ROWB_ = 128, int NSTAGE_ = 2, int KW_ = 1, int CW_ = 0>
 struct Cfg {
     static constexpr int DT = DT_, OUT = OUT_, BM = BM_, BN = BN_, WM = WM_, WN = WN_;
-    static constexpr int AMODE = AMODE_, BMODE = BMODE_, ROWB = ROWB_, NSTAGE = NSTAGE_, KW = KW_, CW = CW_;
+    static constexpr bool RAGGED_TAP = AMODE_ == A_CONV_RAGGED;
+    static constexpr int AMODE = RAGGED_TAP ? (int)A_CONV : AMODE_, BMODE = BMODE_, ROWB = ROWB_, NSTAGE = NSTAGE_, KW = KW_, CW = CW_;
     static constexpr int SUB = WM * WN * 64;      // threads of one reduction group
     static constexpr int CT = CW ? CW * 64 : SUB; // threads that share the copy of a stage
     static constexpr int THREADS = SUB * KW + CW * 64;
