@@ -1149,7 +1149,6 @@ tir_status tir_attention(const void* Q, const void* K, const void* V, void* O, i
     p.Q = Q; p.K = K; p.V = V; p.O = O;
     p.M = (int)M; p.N = (int)N; p.batch = (int)batch;
     p.scale_log2e = scale * 1.44269504088896340736f;
-    if (p.scale_log2e == 0.f) p.scale_log2e = 1e-37f;      // every score counts alike, and the infinities that stand for keys past N keep their sign
     hipError_t e = fn(p, (hipStream_t)stream);
     if (e != hipSuccess) return fail(TIR_ERR_LAUNCH, "attention launch failed: %s", hipGetErrorString(e));
     return TIR_OK;

@@ -158,12 +158,16 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[db][r] = 0.f;          // reduction init
-    // The reference the scores are taken relative to, in score units, and the sum of the probabilities relative to it.
-    float m_ref = 0.f, l_run = 0.f;
+    // The reference the scores are taken relative to, in base-2 units, and the sum of the probabilities relative to it.
+    float m_run = 0.f, l_run = 0.f;
     const float sc = p.scale_log2e;
-    // A row's reference only has to be close to its maximum: it is raised when some row of the wave has a score 2^8 above it
-    // (binary16 probabilities hold 2^15), which after the first chunk is rare, and the accumulators are rescaled only then.
+    // A row's reference only has to be close to its maximum: it is raised when some row of the wave has a score 8 above it (a
+    // probability of 2^8; binary16 holds 2^15), which after the first chunk is rare, and the accumulators are rescaled only then.
     constexpr float kSlack = 8.0f;
+    // Up to this size a reference's own rounding moves an exponent by 2^-14 at most, and the exponent comes from one fused
+    // multiply-add per score.  Beyond it (scores of thousands, infinities, a scale of zero) score and reference are rounded alike first: the
+    // product inside the fused form is exact, so the row's largest score would keep the whole rounding error of its reference as exponent.
+    constexpr float kFused = 1024.0f;
     copy_barrier<0>();                                // the queries and the first chunk
 
     auto multiply_chunk = [&](int i, int st) __attribute__((always_inline)) {
@@ -209,20 +213,31 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
                 for (int r = 0; r < 16; ++r) mx = __builtin_fminf(mx, acc_s[jb][r]);
             mx = __builtin_fminf(mx, __shfl_xor(mx, 32));
         }
-        if (i == 0) m_ref = mx;                                      // finite: every chunk has at least one valid key
-        else if (__builtin_amdgcn_ballot_w64((mx - m_ref) * sc > kSlack) != 0) {
-            const float alpha = __builtin_amdgcn_exp2f((m_ref - mx) * sc);
-            // (rows whose reference is already above keep it)
-            const bool up = (mx - m_ref) * sc > 0.f;
-            const float a = up ? alpha : 1.f;
-            m_ref = up ? mx : m_ref;
-            l_run *= a;
+        const float m_chunk = mx * sc;
+        if (i == 0) m_run = m_chunk;
+        else if (__builtin_amdgcn_ballot_w64(m_chunk - m_run > kSlack) != 0) {
+            const float m_new = __builtin_fmaxf(m_run, m_chunk);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);          // 1 for rows whose reference stays
+            m_run = m_new;
+            l_run *= alpha;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc_o[db][r] *= a;
+                for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
         }
-        const float base = -m_ref * sc;
+        const bool fused = sc != 0.f && __builtin_amdgcn_ballot_w64(!(__builtin_fabsf(m_run) <= kFused)) == 0;
+        if (__builtin_expect(!fused, 0)) {
+#pragma clang fp contract(off)
+            // exponents in place of the scores; keys past N again, which a scale of zero would turn into NaN
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float s = acc_s[jb][r] * sc;
+                    acc_s[jb][r] = c * KB + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N ? -__builtin_inff() : s - m_run;
+                }
+        }
+        const float mul = fused ? sc : 1.f, base = fused ? -m_run : 0.f;
         uint4 pf[JB][2];                                             // P^T fragments: key block jb, k-step s
         float lsum[2] = {0.f, 0.f};
 #pragma unroll
@@ -230,7 +245,7 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
             float pr[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc_s[jb][r], sc, base));
+                pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc_s[jb][r], mul, base));
                 lsum[r & 1] += pr[r];
             }
 #pragma unroll
@@ -276,7 +291,7 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
     if constexpr (KG > 1) {
         // ------------------------------------------------------------ merge the key groups: sums and accumulators relative to the largest reference
         typedef float f32x4 __attribute__((ext_vector_type(4)));
-        const float ms = nmine > 0 ? m_ref * sc : -__builtin_inff();           // (a group without a chunk counts nothing)
+        const float ms = nmine > 0 ? m_run : -__builtin_inff();                // (a group without a chunk counts nothing)
         auto area = [&](int k) { return smem + ((k - 1) * QW + wave) * MERGE; };      // the stages are free: everybody is past the last barrier
         if (kgrp != 0) {
             f32x4* const o = (f32x4*)area(kgrp);

@@ -754,6 +754,60 @@ def test_attention_matches_oracle(B, oracle, dtype, out, rtol):
         _say(f"   max err/tol {ratio.max():.3g}")
 
 
+# one shape per kernel the attention dispatch has: (batch, M, N, d), every one with a last chunk of keys that is not whole
+ATTN_KERNELS = [
+    (3, 70, 300, 64),        # four key groups of 64-key chunks
+    (2, 65, 300, 128),       # ... of 32-key chunks
+    (129, 20, 390, 64),      # two key groups
+    (130, 17, 450, 128),
+    (260, 20, 500, 64),      # one group, eight chunks
+    (150, 33, 450, 128),
+    (2, 40, 130, 128),       # one group, three chunks
+]
+
+
+def _attention(B, dtype, out, q, k, v, scale):
+    """Output of tir_attention for raw bits, as float64."""
+    import torch
+    (batch, M, d), N = q.shape, k.shape[1]
+    o = B.empty_out((batch, M, d), out)
+    o.fill_(float("nan"))
+    B.tir_attention(B.to_device(q, dtype), B.to_device(k, dtype), B.to_device(v, dtype), o, batch, M, N, d, scale, dtype, out)
+    torch.cuda.synchronize()
+    return PT.gpu_to_f64(o)
+
+
+def _bits(values, dtype):
+    return I.to_f16_bits(values) if dtype == "f16" else I.to_bf16_bits(values)
+
+
+@pytest.mark.parametrize("dtype,rtol", [("f16", 2e-3), ("bf16", 6e-3)])
+@pytest.mark.parametrize("shape", ATTN_KERNELS, ids=str)
+def test_attention_of_large_scores(B, oracle, shape, dtype, rtol):
+    """Scores of 1e8 and more, where a score's or reference's last bit is many powers of two of probability: equal scores share the
+    row equally, keys masked through a channel of the type's lowest value (one or all of a chunk, of a group's first chunk) count
+    nothing, a scale of zero counts every key alike."""
+    batch, M, N, d = shape
+    vb = I.make_tensor(dtype, "u", 9850 + N, (batch, N, d))
+    lowest = -65504.0 if dtype == "f16" else -3.3895313892515355e38
+    q = I.uniform_pm1(9851 + M, batch * M * d).reshape(batch, M, d)
+    k = I.uniform_pm1(9852 + N, batch * N * d).reshape(batch, N, d)
+    cases = [(f"constant {a}", np.full(q.shape, a), np.full(k.shape, a), s) for a in (1000.0, 10000.0, 20011.0, 60000.0) for s in (0.125, -0.3)]
+    cases.append(("scale 0", q * 30000.0, k * 30000.0, 0.0))
+    for lo, hi in ((0, 32), (0, 64), (0, 128), (32, 64), (64, 128), (0, N - 1), (N - 3, N)):
+        qm, km = q.copy(), k.copy()
+        qm[..., 0], km[..., 0], km[:, lo:hi, 0] = 1.0, 0.0, lowest
+        cases.append((f"keys {lo}..{hi - 1} at the lowest value", qm, km, 0.125))
+    for what, qv, kv, scale in cases:
+        _say(f"attention {dtype} {shape} {what} scale {scale}")
+        qb, kb = _bits(qv, dtype), _bits(kv, dtype)
+        ref, T = oracle.attention(dtype, qb, kb, vb, scale)
+        got = _attention(B, dtype, "f32", qb, kb, vb, scale)
+        assert np.all(np.isfinite(got)), what
+        ratio = np.abs(got - ref) / (rtol * T + 1e-5)
+        assert ratio.max() <= 1.0, f"{what}: max err/tol {ratio.max():.3g}"
+
+
 def test_attention_argument_checks(B):
     import torch
     x = torch.zeros(128 * 64, dtype=torch.float16, device="cuda")
