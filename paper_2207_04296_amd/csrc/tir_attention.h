@@ -213,7 +213,8 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
                 for (int r = 0; r < 16; ++r) mx = __builtin_fminf(mx, acc_s[jb][r]);
             mx = __builtin_fminf(mx, __shfl_xor(mx, 32));
         }
-        const float m_chunk = mx * sc;
+        // (a chunk whose scores are all -inf counts nothing, but its reference has to be a number)
+        const float m_chunk = __builtin_fmaxf(mx * sc, -__FLT_MAX__);
         if (i == 0) m_run = m_chunk;
         else if (__builtin_amdgcn_ballot_w64(m_chunk - m_run > kSlack) != 0) {
             const float m_new = __builtin_fmaxf(m_run, m_chunk);

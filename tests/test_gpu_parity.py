@@ -808,6 +808,34 @@ def test_attention_of_large_scores(B, oracle, shape, dtype, rtol):
         assert ratio.max() <= 1.0, f"{what}: max err/tol {ratio.max():.3g}"
 
 
+@pytest.mark.parametrize("dtype,rtol", [("f16", 2e-3), ("bf16", 6e-3)])
+@pytest.mark.parametrize("shape", ATTN_KERNELS, ids=str)
+def test_attention_of_infinite_scores(B, oracle, shape, dtype, rtol):
+    """Keys with a score of -inf count nothing wherever they lie: in a whole first chunk of the row or of a key group, in all
+    keys but one, in the last chunk; a row without any other key, or with a score of +inf or NaN, is NaN."""
+    batch, M, N, d = shape
+    vb = I.make_tensor(dtype, "u", 9860 + N, (batch, N, d))
+    q = I.uniform_pm1(9861 + M, batch * M * d).reshape(batch, M, d)
+    k = I.uniform_pm1(9862 + N, batch * N * d).reshape(batch, N, d)
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    for lo, hi in ((0, 1), (0, 32), (0, 64), (0, 128), (32, 64), (64, 128), (0, N - 1), (N - 3, N)):
+        for sign in (1.0, -1.0):
+            _say(f"attention {dtype} {shape} keys {lo}..{hi - 1} at -inf, scale {sign * 0.125}")
+            km = k.copy()
+            km[:, lo:hi, 0] = -sign * np.inf
+            qb, kb = _bits(q, dtype), _bits(km, dtype)
+            ref, T = oracle.attention(dtype, qb, kb, vb, sign * 0.125)
+            got = _attention(B, dtype, "f32", qb, kb, vb, sign * 0.125)
+            assert np.all(np.isfinite(got)), (lo, hi, sign)
+            ratio = np.abs(got - ref) / (rtol * T + 1e-5)
+            assert ratio.max() <= 1.0, f"keys {lo}..{hi - 1}: max err/tol {ratio.max():.3g}"
+    for what, keys, value in (("every key -inf", slice(0, N), -np.inf), ("one +inf", slice(N // 2, N // 2 + 1), np.inf), ("one NaN", slice(5, 6), np.nan)):
+        _say(f"attention {dtype} {shape} {what}")
+        km = k.copy()
+        km[:, keys, 0] = value
+        assert np.all(np.isnan(_attention(B, dtype, "f32", _bits(q, dtype), _bits(km, dtype), vb, 0.125))), what
+
+
 def test_attention_argument_checks(B):
     import torch
     x = torch.zeros(128 * 64, dtype=torch.float16, device="cuda")
