@@ -158,12 +158,12 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[db][r] = 0.f;          // reduction init
-    // The reference the scores are taken relative to, in base-2 units, and the sum of the probabilities relative to it.
+    // The reference of the softmax, a row's largest score so far in base-2 units, and the sum of the probabilities relative to it.  Every
+    // row's own largest probability is then exactly 1 and loses nothing when the probabilities are rounded to 16 bits for the second
+    // product.  Letting references lag (up to 2^8, rescaling rarely) is 4 - 10 % faster and was measured less exact: bf16 against fp64,
+    // 2048 keys at d = 64, scale 1, N(0, 1) data 6.3e-4 instead of 1.7e-4, 4096 keys at d = 128, scale 1/sqrt(d) 1.67e-3 instead of 1.48e-3.
     float m_run = 0.f, l_run = 0.f;
     const float sc = p.scale_log2e;
-    // A row's reference only has to be close to its maximum: it is raised when some row of the wave has a score 8 above it (a
-    // probability of 2^8; binary16 holds 2^15), which after the first chunk is rare, and the accumulators are rescaled only then.
-    constexpr float kSlack = 8.0f;
     // Up to this size a reference's own rounding moves an exponent by 2^-14 at most, and the exponent comes from one fused
     // multiply-add per score.  Beyond it (scores of thousands, infinities, a scale of zero) score and reference are rounded alike first: the
     // product inside the fused form is exact, so the row's largest score would keep the whole rounding error of its reference as exponent.
@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
         // (a chunk whose scores are all -inf counts nothing, but its reference has to be a number)
         const float m_chunk = __builtin_fmaxf(mx * sc, -__FLT_MAX__);
         if (i == 0) m_run = m_chunk;
-        else if (__builtin_amdgcn_ballot_w64(m_chunk - m_run > kSlack) != 0) {
+        else if (__builtin_amdgcn_ballot_w64(m_chunk > m_run) != 0) {
             const float m_new = __builtin_fmaxf(m_run, m_chunk);
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);          // 1 for rows whose reference stays
             m_run = m_new;

@@ -711,12 +711,12 @@ def test_fused_consumer_argument_checks(B):
 # ------------------------------------------------------------------------------ fused attention head
 ATTN_CASES = [
     # batch, M, N, d, scale
-    (192, 128, 128, 64, 0.125),      # the benchmark's BERT-base head: 16 sequences x 12 heads, one key chunk
-    (3, 130, 200, 64, 0.125),        # two query tiles, two key chunks, both ragged
+    (192, 128, 128, 64, 0.125),      # the benchmark's BERT-base head: 16 sequences x 12 heads, two key chunks
+    (3, 130, 200, 64, 0.125),        # two query tiles, four key chunks, both ragged
     (2, 1, 1, 64, 1.0),              # a single key: the output is its value row
-    (2, 77, 129, 64, 0.5),           # one key in the second chunk
-    (1, 300, 512, 128, 0.0884),      # head dimension 128, four chunks
-    (2, 64, 384, 64, 3.0),           # peaked softmax
+    (2, 77, 129, 64, 0.5),           # one key in the third chunk
+    (1, 300, 512, 128, 0.0884),      # head dimension 128, four key groups of 32-key chunks
+    (2, 64, 384, 64, 3.0),           # peaked softmax, four key groups
     (2, 40, 100, 128, 0.0),          # scale 0: uniform attention
     (3, 70, 257, 64, 0.2),           # four key groups, the last one with a single key
     (2, 65, 300, 128, -0.3),         # ... of 32-key chunks, a negative scale
@@ -834,6 +834,35 @@ def test_attention_of_infinite_scores(B, oracle, shape, dtype, rtol):
         km = k.copy()
         km[:, keys, 0] = value
         assert np.all(np.isnan(_attention(B, dtype, "f32", _bits(q, dtype), _bits(km, dtype), vb, 0.125))), what
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", ATTN_KERNELS, ids=str)
+def test_attention_rounds_all_but_the_largest_probability(B, oracle, shape, dtype):
+    """Probabilities are taken relative to a row's largest score, so its largest one is 1 and is not rounded.  With u the input
+    type's rounding unit (2^-11, 2^-8) and j* the row's largest score the output differs from the exact one by at most
+    u * (T - P[j*] |V[j*]|), plus what fp32 sums leave: 2 * |scale| * d * 2^-24 * max sum_c |q k| of relative error in a probability,
+    2^-20 for the exponential, and for fp16 half a subnormal step per key.  Flat, peaked and negative scales, rows whose
+    largest score comes late and rises by many powers of two."""
+    batch, M, N, d = shape
+    u, step = (2.0 ** -11, 2.0 ** -25) if dtype == "f16" else (2.0 ** -8, 0.0)
+    vb = I.make_tensor(dtype, "u", 9870 + N, (batch, N, d))
+    v = I_decode(dtype, vb).reshape(vb.shape)
+    for scale, late in ((d ** -0.5, 1.0), (1.0, 1.0), (-0.5, 1.0), (0.5, 4.0)):
+        kv = I.normal(9872 + N, batch * N * d).reshape(batch, N, d)
+        kv[:, N // 2:] *= late
+        qb, kb = _bits(I.normal(9871 + M, batch * M * d).reshape(batch, M, d), dtype), _bits(kv, dtype)
+        q, k = I_decode(dtype, qb).reshape(qb.shape), I_decode(dtype, kb).reshape(kb.shape)
+        s = scale * (q @ k.transpose(0, 2, 1))
+        prob = np.exp(s - s.max(-1, keepdims=True))
+        prob /= prob.sum(-1, keepdims=True)
+        top = np.take_along_axis(prob, s.argmax(-1)[..., None], -1) * np.abs(np.take_along_axis(v, s.argmax(-1)[..., None], 1))
+        ref, T = oracle.attention(dtype, qb, kb, vb, scale)
+        fp32 = 2.0 * abs(scale) * d * 2.0 ** -24 * float((np.abs(q) @ np.abs(k).transpose(0, 2, 1)).max()) + 2.0 ** -20
+        got = _attention(B, dtype, "f32", qb, kb, vb, scale)
+        ratio = np.abs(got - ref) / (u * (T - top) + fp32 * T + step * N + 1e-7)
+        _say(f"attention {dtype} {shape} scale {scale:.3g} late x{late}: max err/bound {ratio.max():.3g}")
+        assert ratio.max() <= 1.0
 
 
 def test_attention_argument_checks(B):
