@@ -140,17 +140,22 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
             else load_to_lds(rv, dv + u * (GT * 16), v_off + u * (GT * 16));
         }
     };
+    // Both stages are filled up front: a head of 128 keys is these two chunks, and requesting the second only after the first had landed
+    // is one more trip to memory (192 heads of 128 x 128 x 64 fp16 from memory 6.59 us, 6.20 this way).
     if (nmine > 0) copy_chunk(0, 0);
 
     // ------------------------------------------------------------ this wave's queries, as MFMA operands (rows past M read zeros)
+    // (no non-temporal hint here, although nobody else reads them: a load takes 32 bytes of each of 32 rows, and lines that do not stay are
+    // fetched again by the next one - 6.76 us instead of 6.20 for the same heads)
     uint4 qf[KSTEPS];
     {
         const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void*)Qb, 0, rows_q * ROW, 0x00020000);
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks)
-            qf[ks] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rq, (wave * 32 + l31) * ROW + ks * 32 + g * 16, 0, 2));
+            qf[ks] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rq, (wave * 32 + l31) * ROW + ks * 32 + g * 16, 0, 0));
     }
+    if (nmine > 1) copy_chunk(1, 1);
     const int swl = kmajor_swz<128>(l31);            // rows 32*jb + l31 share it (period 16)
 
     f32x16 acc_o[DB];
@@ -168,11 +173,11 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
     // multiply-add per score.  Beyond it (scores of thousands, infinities, a scale of zero) score and reference are rounded alike first: the
     // product inside the fused form is exact, so the row's largest score would keep the whole rounding error of its reference as exponent.
     constexpr float kFused = 1024.0f;
-    copy_barrier<0>();                                // the queries and the first chunk
+    copy_barrier<0>();                                // the queries and the first two chunks
 
     auto multiply_chunk = [&](int i, int st) __attribute__((always_inline)) {
         const int c = i * KG + kgrp;
-        if (i + 1 < nmine) copy_chunk(i + 1, st ^ 1); // its stage was last read before the previous barrier
+        if (i > 0 && i + 1 < nmine) copy_chunk(i + 1, st ^ 1);      // its stage was last read before the previous barrier
         const char* sk = ring + st * 2 * TILE;
         const char* sv = sk + TILE;
 

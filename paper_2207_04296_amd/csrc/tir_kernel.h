@@ -239,7 +239,7 @@ __device__ __forceinline__ void load_to_lds(const i32x4& rsrc, const char* lds_b
 }
 // ... with the non-temporal hint, for operand bytes that (almost) no other workgroup of the launch reads again: they then do
 // not push the lines the workgroups share out of the caches.  Measured with the operands coming from memory: the headline
-// convolution's input 8.6 -> 8.2 us, the fused attention's Q, K, V 7.05 -> 6.63, no change with warm caches.  On operands
+// convolution's input 8.6 -> 8.2 us, the fused attention's K and V 7.05 -> 6.63, no change with warm caches.  On operands
 // that many workgroups re-read (a filter, the panels of a GEMM) it costs as much and more, and on the operands of batched
 // matmuls with one tile per batch entry it trades 10 % from memory against 8 % from the caches: those keep the plain copy.
 __device__ __forceinline__ void load_to_lds_nt(const i32x4& rsrc, const char* lds_base, unsigned voffset) {
