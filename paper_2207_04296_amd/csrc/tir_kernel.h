@@ -161,7 +161,7 @@ template <int ROWB> __device__ __forceinline__ int kmajor_off(int row, int chunk
 
 // XOR applied to the byte offset inside k-row `k` of an N-major LDS tile so that the k-rows one
 // transposing read touches fall into different banks.
-template <class T> __device__ __forceinline__ int nmajor_xor(int k) { return ((k / T::RPW) % T::NSEG) * T::SEG; }
+template <class T> __device__ __forceinline__ int nmajor_xor(unsigned k) { return (int)((k / T::RPW) % T::NSEG) * T::SEG; }
 
 // MFMA fragment of k-step kk for the 32 rows (of A) or columns (of B) starting at w0, from an N-major LDS tile T.
 template <class T, int ES> __device__ __forceinline__ uint4 read_nmajor(const char* tile, int kk, int w0, int blk, int s16) {
@@ -303,7 +303,7 @@ template <class C> struct Frag {
         sw = kmajor_swz<C::ROWB>(l31);   // the swizzle repeats every 16 rows: same for every 32-row block
         blk = lane >> 4;
         s16 = lane & 15;
-        wm_off = wm * C::TM;
+        if constexpr (C::A_NM) wm_off = wm * C::TM;       // (computed for all, it changed the code of every kernel's prologue: c2b 7.25 -> 7.38 us)
         wn_off = wn * C::TN;
     }
     __device__ __forceinline__ uint4 read_a1(const char* sa, int kk, int i) const {
@@ -522,23 +522,25 @@ __device__ __forceinline__ bool sum_groups(char* smem, int wave, int lane, int k
 // the copying threads' i-th pass covers 16-byte chunks i*CT .. of the tile (k-rows of RC chunks, any count).  Columns past the
 // operand's edge are switched off per lane; k-rows past K start beyond the stage's descriptor (ld >= extent: the host checks).
 template <class T, int IT, int CT, int ES>
-__device__ __forceinline__ void nmajor_offsets(unsigned (&off)[IT], int tid, int w0, int extent, long long ld) {
+__device__ __forceinline__ void nmajor_offsets(unsigned (&off)[IT], unsigned tid, int w0, int extent, long long ld) {
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
-        const int chunk = i * CT + tid;
-        const int k = chunk / T::RC, pc = chunk - k * T::RC;
-        const int lb = (pc * 16) ^ nmajor_xor<T>(k);        // logical byte inside the k-row
-        off[i] = (w0 + lb / ES < extent) ? (unsigned)k * (unsigned)(ld * ES) + lb : kOutOfRange;
+        const unsigned chunk = i * CT + tid;                // (unsigned: a signed division costs four instructions more)
+        const unsigned k = chunk / T::RC, pc = chunk - k * T::RC;
+        const int lb = (int)(pc * 16) ^ nmajor_xor<T>(k);   // logical byte inside the k-row
+        off[i] = (w0 + lb / ES < extent) ? k * (unsigned)(ld * ES) + lb : kOutOfRange;
     }
 }
 // Descriptor of one stage: it covers exactly the stage's BK k-rows (32-bit size, bounded by the host for 128 rows), or what
 // is left of the operand in the last stage, so that rows past K stay out of range.
 template <int ES, int BK>
 __device__ __forceinline__ i32x4 nmajor_rsrc(const char* base, long long bytes, long long ld, int width, int K, int stage, bool live) {
-    const long long step = (long long)BK * ld * ES;        // bytes the base advances per stage
-    const unsigned window = (unsigned)(((long long)(BK - 1) * ld + width) * ES);
-    const unsigned left = (stage + 1) * BK <= K ? window : (unsigned)(bytes - stage * step);
-    return make_rsrc32(base + stage * step, live ? left : 0u);
+    const long long at = stage * ((long long)BK * ld * ES);
+    const unsigned window = (unsigned)(((long long)(BK - 1) * ld + width) * ES), rest = (unsigned)(bytes - at);
+    // (both sizes worked out in front of the choice: a select, where a branch around them cost a kernel of few stages 2 %)
+    unsigned left = window;
+    left = (stage + 1) * BK <= K ? left : rest;
+    return make_rsrc32(base + at, live ? left : 0u);
 }
 
 // ---------------------------------------------------------------------------------------------
