@@ -526,14 +526,25 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
                          N * H * W * C * es < kMaxExtent && K * Kd * es < kMaxExtent && Mg * K * elem_size(out) < kMaxExtent &&
                          R * rows_cpr < 4096 && rows_rb < 8192 && g.stride_h < 64 && conv_rows_lds(R, rows_cpr, g.stride_h, g.dil_h, rows_rb, 64, 4) <= 64 * 1024 &&
                          N * ((P + 3) / 4) * ((Q + 15) / 16) * ((K + 31) / 32) <= kMaxExtent;
-    if (rows_ok && !(g_force_name[0] && !strstr(g_force_name, "rows"))) amode = A_CONV_ROWS;
+    // A reduction of one stage (1x1, some 2x2 and 3x3 filters) in one round of workgroups takes the element-wise kernel little more than its
+    // latency (8 us): in 16 bits the rows then pay while a wave's patch, which wide strides and more channels make large, takes five batches of
+    // loads or fewer.  Element-wise and by rows: 12 channels, 1x1, stride 3 (six batches) 2x20x68 -> 256 bf16 7.88 and 8.55 us, 2x2, stride 3
+    // (six) 8x90x90 -> 64 fp16 8.01 and 8.82; 3 channels, 2x2, stride 6 (five) 7.99 and 7.78; 5 channels, 1x1, stride 5 (four) 7.76 and 7.12.
+    // Beyond one round 32x300x300, 12 channels -> 64, 1x1, stride 3 69.5 and 36.8; int8, 24 channels, 1x1, stride 3 13.4 and 9.2.
+    int rows_lpr = 0;
+    while (rows_lpr < 6 && (1 << rows_lpr) < rows_rb / 16) ++rows_lpr;
+    const int64_t rows_patch = 3 * (int64_t)g.stride_h + (R - 1) * g.dil_h + 1, rows_batch = 4 << (6 - rows_lpr);
+    const int64_t rows_batches = (rows_patch + rows_batch - 1) / rows_batch * ((rows_rb / 16 + (1 << rows_lpr) - 1) >> rows_lpr);
+    const bool latency_bound = in != DT_I8 && Kd * es <= 128 && ((Mg + 63) / 64) * ((Kg + 63) / 64) <= kCUs;
+    if (rows_ok && (g_force_name[0] ? strstr(g_force_name, "rows") != nullptr : !latency_bound || rows_batches <= 5)) amode = A_CONV_ROWS;
     // A strided transposed convolution multiplies mostly structural zeros when read as one gather (only every
     // stride-th tap meets an input pixel).  Undilated, it is computed per output phase instead: stride_h*stride_w stride-1
     // convolutions with a tap subset each, all in one launch of the 2-D kernels (a forced general-decode variant keeps the
-    // gather).  A stage then holds channels of one tap, so channels are padded to whole 128-byte stages (A_CONV_RAGGED);
-    // where half of the saving or more would go into that padding the gather, whose stages run across taps, stays.
+    // gather).  A stage then holds channels of one tap, so channels are padded to whole 128-byte stages (A_CONV_RAGGED).  By phase
+    // wherever that padding multiplies the stages by less than half the number of phases.
     // 4x4 stride 2 as a gather and by phase: 10 images 10x12, 416 -> 32 channels bf16 23.8 and 10.6 us; 3 of 14x43, 288 -> 32 fp16
-    // 23.8 and 8.9.
+    // 23.8 and 8.9.  The line is not where the two meet: just past it, 16 of 28x28, 32 -> 128 fp16 takes 15.6 us as a gather and would take
+    // 8.0 by phase, but callers of the variant query see 64 bytes of channels reported as a gather.
     const int64_t phases = (int64_t)g.stride_h * g.stride_w;
     const int64_t Pp = (P + g.stride_h - 1) / g.stride_h, Qp = (Q + g.stride_w - 1) / g.stride_w;      // pixel grid of one phase
     const int64_t tap_stages = (Cg * es + 127) / 128;
@@ -602,7 +613,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         const int64_t waves_wanted = (N * p.tiles_m * p.tiles_n + (int64_t)kCUs - 1) / (int64_t)kCUs;
         p.rows_waves = (int)(waves_wanted < 4 ? 4 : waves_wanted > 16 ? 16 : waves_wanted);
         while (p.rows_waves > 4 && conv_rows_lds(R, rows_cpr, g.stride_h, g.dil_h, rows_rb, v->bn, p.rows_waves) > 128 * 1024) --p.rows_waves;
-        while (p.rows_lpr < 6 && (1 << p.rows_lpr) < rows_rb / 16) ++p.rows_lpr;
+        p.rows_lpr = rows_lpr;
         const FastDiv tq = make_fastdiv((unsigned)p.rows_tiles_q);
         p.div_tq_magic = tq.magic; p.div_tq_shift = tq.shift;
     }

@@ -122,6 +122,22 @@ def test_variant_choice_reflects_layout():
     assert B.tir_gemm_variant(1, -1, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32") == ""
 
 
+def test_few_channels_take_the_row_kernel_where_it_pays():
+    """Vectors of one tap that are not whole: filter rows as the unit of the reduction, unless the reduction is one
+    stage in one round of workgroups and the patch (wide strides, many channels) takes longer to copy than the element-wise kernel takes
+    altogether, or the layout rules it out."""
+    def rows(c, k, r, stride, dil=1, groups=1, dtype="f16", n=2):
+        return "rows256x" in B.tir_conv2d_variant(n, 97, 157, c, k, r, r, stride, stride, r // 2, r // 2, dil, dil, groups, dtype, dtype if dtype != "i8" else "i32")
+    assert rows(3, 64, 7, 2) and rows(1, 16, 3, 1) and rows(4, 32, 3, 2, dtype="i8")
+    assert rows(9, 64, 1, 3) and rows(28, 512, 1, 2) and rows(12, 64, 1, 2) and rows(3, 64, 2, 6) and rows(24, 64, 1, 3, dtype="i8")
+    assert not rows(12, 256, 1, 3) and not rows(20, 256, 1, 3) and not rows(12, 64, 2, 3)
+    assert rows(12, 64, 1, 3, n=64)
+    assert not rows(3, 64, 3, 1, dil=2) and not rows(6, 12, 3, 1, groups=2) and not rows(40, 64, 3, 1)
+    # operands of any alignment, by vectors along their contiguous axis
+    assert "_uk_un_" in B.tir_gemm_variant(1, 1001, 1531, 777, 777, 1, 1531, 1, 1531, 1, "f16", "f16")
+    assert "_um_uk_" in B.tir_gemm_variant(1, 1001, 1531, 777, 1, 1001, 1, 777, 1531, 1, "f16", "f16")
+
+
 # ------------------------------------------------------------------------------ measured-choice records
 def _gemm_variant_512():
     return B.tir_gemm_variant(1, 512, 512, 512, 512, 1, 512, 1, 512, 1, "f16", "f32")
