@@ -496,6 +496,51 @@ def test_few_channel_convolution(B, oracle, dtype, out):
             PT.assert_close(got, ref, S, f"{wl.name} {cases[i]} {force}")
 
 
+def _rows_waves(n, p, q, c, k, r, s, stride, dil_h, es, bn):
+    """Waves per workgroup of the few-channel kernel: what puts all tiles of 4 x 16 pixels on 256 CUs at once, 4 to 16, in 128 KiB of LDS."""
+    vec = 16 // es
+    cpr = -(-s * c // vec)
+    row = ((15 * stride[1] * c + cpr * vec) * es + 4 + 15) // 16 * 16
+    waves = max(4, min(16, -(-n * -(-p // 4) * -(-q // 16) * -(-k // bn) // 256)))
+    while waves > 4 and ((r + 1) // 2 * 2 * cpr + 1) * bn * 16 + waves * (3 * stride[0] + (r - 1) * dil_h + 2) * row > 128 * 1024:
+        waves -= 1
+    return waves
+
+
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("bf16", "f32"), ("i8", "i32")])
+def test_few_channel_convolution_with_many_waves_per_workgroup(B, oracle, dtype, out):
+    """More than four tiles per CU: up to 16 waves share one copy of the filter (counts that are no multiple of four copy with the first
+    fours only), the last workgroup has waves without a tile, LDS beyond 64 KiB, the bound of 128 KiB lowers the count; even and
+    odd filter heights, places aligned to four bytes or not."""
+    cases = [  # n, h, w, c, k, r, s, stride, pad
+        (5, 121, 130, 3, 16, 3, 3, (1, 1), (1, 1)),
+        (7, 128, 128, 1, 20, 2, 2, (1, 1), (0, 0)),
+        (8, 128, 128, 4, 16, 3, 3, (1, 1), (1, 1)),
+        (13, 128, 126, 2, 40, 4, 5, (1, 1), (1, 2)),
+        (17, 128, 128, 1, 16, 5, 5, (1, 1), (2, 2)),
+        (16, 384, 384, 5, 16, 5, 5, (3, 3), (2, 2)),
+    ]
+    seen = set()
+    for i, (n, h, w, c, k, r, s, stride, pad) in enumerate(cases):
+        wl = I.Workload(f"rows_waves_{dtype}_{out}_{i}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 8850 + i, n=n, h=h, w=w, c=c, k=k, r=r, s=s,
+                        stride=stride, pad=pad, dil=(1, 1), ep_bias=i % 2 == 0, ep_relu=i % 3 == 0)
+        p, q = (h + 2 * pad[0] - r) // stride[0] + 1, (w + 2 * pad[1] - s) // stride[1] + 1
+        a_bits, b_bits = wl.operands()
+        ref, S = PT.run_oracle(wl, a_bits, b_bits, oracle)
+        for bn in (64, 32):
+            waves = _rows_waves(n, p, q, c, k, r, s, stride, 1, 1 if dtype == "i8" else 2, bn)
+            seen.add(waves)
+            _say(f"{wl.name} {cases[i]} rows256x{bn}, {waves} waves")
+            B.tir_debug_force_variant(f"rows256x{bn}")
+            try:
+                assert f"rows256x{bn}" in PT.variant_name(B, wl)
+                got = PT.run_gpu(wl, a_bits, b_bits)
+            finally:
+                B.tir_debug_force_variant("")
+            PT.assert_close(got, ref, S, f"{wl.name} {cases[i]} rows256x{bn}")
+    assert min(seen) > 4 and seen >= ({6, 7, 8, 13, 16} if dtype == "i8" else {6, 7, 8, 13, 14, 16}), seen
+
+
 def test_prepared_calls_launch_what_run_workload_launches(B, oracle):
     """binding.prepare_workload marshals once and launches per call: a GEMM, a batched matmul and a fused convolution,
     each launched twice from its prepared call (the second time over a poisoned output), against the oracle."""
