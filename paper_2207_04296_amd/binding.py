@@ -55,6 +55,7 @@ def _load_native():
     global _native
     lib()
     from . import _native as module
+    module.set_epilogue_type(Epilogue)
     _native = module
     return module
 

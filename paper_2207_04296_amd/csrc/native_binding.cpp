@@ -6,7 +6,7 @@
 // (3.0 us for the same call, 2.3 of them the HIP launch).
 //
 // Conversions by C parameter type: pointers take a tensor (its data_ptr()), an integer address or None; tir_dtype a
-// code or a name ("f16", ...); const tir_epilogue* None or an object whose buffer is that struct; the last argument, the
+// code or a name ("f16", ...); const tir_epilogue* None or an instance of the binding's Epilogue (set_epilogue_type); the last argument, the
 // stream, None (torch's current stream), an integer handle or an object with .cuda_stream.  Every function returns the
 // tir_status as an int; wrong argument types raise.
 #define PY_SSIZE_T_CLEAN
@@ -26,6 +26,7 @@ PyObject* g_cuda_stream = nullptr;
 PyObject* g_current_stream = nullptr; // torch.cuda.current_stream: initialises the device, used for the first None
 PyObject* g_get_device = nullptr;     // torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 PyObject* g_raw_stream = nullptr;
+PyObject* g_epilogue_type = nullptr;  // the ctypes structure that mirrors tir_epilogue
 bool g_cuda_ready = false;
 
 bool to_address(PyObject* o, void** out) {
@@ -118,6 +119,13 @@ bool convert(PyObject* o, tir_dtype* out, Held& h) {
 bool convert(PyObject* o, const tir_epilogue** out, Held& h) {
     *out = nullptr;
     if (o == Py_None) return true;
+    // (any object has a buffer that could be read as the struct: a bias array's first values would become its address)
+    const int is = g_epilogue_type ? PyObject_IsInstance(o, g_epilogue_type) : 0;
+    if (is < 0) return false;
+    if (!is) {
+        PyErr_Format(PyExc_TypeError, "epilogue: expected an Epilogue or None, got %.200s", Py_TYPE(o)->tp_name);
+        return false;
+    }
     if (PyObject_GetBuffer(o, &h.view, PyBUF_SIMPLE) != 0) return false;
     h.used = true;
     if ((size_t)h.view.len < sizeof(tir_epilogue)) {
@@ -165,9 +173,21 @@ TIR_PY(tir_conv2d_transpose)
 TIR_PY(tir_attention)
 #undef TIR_PY
 
+// set_epilogue_type(cls): called once by the binding, before any operator.
+PyObject* py_set_epilogue_type(PyObject*, PyObject* cls) {
+    if (!PyType_Check(cls)) {
+        PyErr_SetString(PyExc_TypeError, "set_epilogue_type: expected a class");
+        return nullptr;
+    }
+    Py_INCREF(cls);
+    Py_XSETREF(g_epilogue_type, cls);
+    Py_RETURN_NONE;
+}
+
 #define TIR_METHOD(fn) {#fn, (PyCFunction)(void (*)(void))py_##fn, METH_FASTCALL, nullptr}
 PyMethodDef kMethods[] = {TIR_METHOD(tir_gemm_fused), TIR_METHOD(tir_batch_matmul_fused), TIR_METHOD(tir_conv2d_fused), TIR_METHOD(tir_conv1d),
-                          TIR_METHOD(tir_conv3d), TIR_METHOD(tir_conv2d_transpose), TIR_METHOD(tir_attention), {nullptr, nullptr, 0, nullptr}};
+                          TIR_METHOD(tir_conv3d), TIR_METHOD(tir_conv2d_transpose), TIR_METHOD(tir_attention),
+                          {"set_epilogue_type", py_set_epilogue_type, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 
 PyObject* attribute(const char* module, const char* name) {

@@ -1,6 +1,7 @@
 """Host-side checks of the C ABI that need no GPU: the library loads, exports every symbol the
 header declares, rejects bad arguments before touching the device, and maps workgroup ids to
 output tiles bijectively."""
+import ctypes
 import re
 from pathlib import Path
 
@@ -397,6 +398,10 @@ def test_variant_table_is_what_its_generator_writes():
     ((FAKE, "A", FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", None, 0), AttributeError),
     ((FAKE, FAKE, FAKE, 0.5, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", None, 0), TypeError),
     ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", 3, 0), TypeError),
+    # anything with a buffer of the struct's size is no epilogue: its first bytes would be taken for the bias pointer
+    ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", np.zeros(8, np.float32), 0), TypeError),
+    ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", bytes(64), 0), TypeError),
+    ((FAKE, FAKE, FAKE, 0, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", (ctypes.c_char * 64)(), 0), TypeError),
     ((FAKE, FAKE, FAKE, -1, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32", None, 0), B.TirError),
 ])
 def test_native_binding_converts_and_checks_its_arguments(args, exc):
