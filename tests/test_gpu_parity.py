@@ -389,24 +389,42 @@ def test_every_variant_on_short_reductions(B, oracle, dtype, out):
         B.tir_debug_force_variant("")
 
 
-@pytest.mark.parametrize("dtype,out", [("f16", "f32"), ("bf16", "bf16"), ("i8", "i32")])
+PAIRS = [("f16", "f32"), ("f16", "f16"), ("bf16", "f32"), ("bf16", "bf16"), ("i8", "i32"), ("i8", "i8")]
+
+
+def _consumer(B, oracle, dtype, out, channels, reduction, fused, ref, S):
+    """(epilogue or None, its bias tensor, expected result, S): bias and ReLU when `fused`, the scale int8 codes need, the rounding
+    of a bfloat16 output (2^-8 |c|) on top of the accumulation's bound."""
+    import torch
+    bias = None
+    scale = 1.0 / (64.0 * reduction ** 0.5) if out == "i8" else 0.0
+    if fused:
+        bias = (I.int8_uniform(8690 + channels, channels).astype(np.int32) * np.int32(64)) if dtype == "i8" else I.normal(8690 + channels, channels, 0.1).astype(np.float32)
+    bias_d = None if bias is None else torch.from_numpy(bias).cuda()
+    if fused or scale:
+        ref, S = oracle.epilogue(ref, S, bias=bias, relu=fused, scale=scale)
+    if out == "bf16":
+        S = S + 2.0 ** -8 * np.abs(ref) / PT.RTOL_S
+    return B.make_epilogue(bias_d, fused, scale), bias_d, ref, S
+
+
+@pytest.mark.parametrize("dtype,out", PAIRS)
 def test_transposed_a_through_every_variant(B, oracle, dtype, out):
     """A stored [K, M] (weight gradients): extents ragged against every tile, a K tail shorter than a stage, one stage,
-    reductions shorter and longer than the copy rings; B row-major and transposed."""
+    reductions shorter and longer than the copy rings; B row-major and transposed; every other shape with bias and ReLU."""
     import torch
     names = B.tir_debug_variant_names()
     vec = 16 if dtype == "i8" else 8
     dist = "i" if dtype == "i8" else "u"
     try:
-        for (M, N, K) in [(39 * vec, 24 * vec, 49 * vec), (vec, 5 * vec, vec), (9 * vec, 70, 17 * vec), (17 * vec, vec, 200 * vec + 3)]:
+        for i, (M, N, K) in enumerate([(39 * vec, 24 * vec, 49 * vec), (vec, 5 * vec, vec), (9 * vec, 70, 17 * vec), (17 * vec, vec, 200 * vec + 3)]):
             for trans_b in (False, True):
                 ok = (K if trans_b else N) % vec == 0
                 a_bits = I.make_tensor(dtype, dist, 8600 + M, (K, M))
                 b_bits = I.make_tensor(dtype, dist, 8601 + N, (N, K) if trans_b else (K, N))
                 b_rs, b_cs = (1, K) if trans_b else (N, 1)
                 ref, S = oracle.gemm(dtype, a_bits, b_bits, M, N, K, 1, M, b_rs, b_cs)
-                if out == "bf16":
-                    S = S + 2.0 ** -8 * np.abs(ref) / 2e-3
+                ep, bias, ref, S = _consumer(B, oracle, dtype, out, N, K, i % 2 == 1, ref, S)
                 a, b = B.to_device(a_bits, dtype), B.to_device(b_bits, dtype)
                 suffix = "_am_bk" if trans_b else "_am_bn"
                 todo = [n for n in names if n.startswith(f"{dtype}_{out}_") and n.endswith(suffix)] if ok else [""]
@@ -416,19 +434,19 @@ def test_transposed_a_through_every_variant(B, oracle, dtype, out):
                     chosen = B.tir_gemm_variant(1, M, N, K, 1, M, b_rs, b_cs, N, 1, dtype, out)
                     assert chosen.split("/")[0] == name or not ok
                     _say(f"A^T {M}x{N}x{K} {chosen}")
-                    c = B.empty_out((M, N), out)
-                    c.fill_(float("nan")) if out != "i32" else c.fill_(-123456789)
-                    B.tir_gemm(a, b, c, M, N, K, 1, M, b_rs, b_cs, N, 1, dtype, out)
+                    c = _gpu_out(B, (M, N), out)
+                    B.tir_gemm_fused(a, b, c, M, N, K, 1, M, b_rs, b_cs, N, 1, dtype, out, ep)
                     torch.cuda.synchronize()
                     PT.assert_close(PT.gpu_to_f64(c), ref, S, f"A^T {M}x{N}x{K} via {name or 'the automatic choice'}")
     finally:
         B.tir_debug_force_variant("")
 
 
-@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("bf16", "f32"), ("i8", "i32")])
+@pytest.mark.parametrize("dtype,out", PAIRS)
 def test_unaligned_operands_through_every_variant(B, oracle, dtype, out):
     """Rows of any length, stride and base address (staged through registers): extents of one vector, around a vector, a
-    stage and a tile; reductions of one element, around one stage and of several; A and B along either axis, batched."""
+    stage and a tile; reductions of one element, around one stage and of several; A and B along either axis, batched; every other shape with
+    bias and ReLU."""
     import torch
     names = B.tir_debug_variant_names()
     vec = 16 if dtype == "i8" else 8
@@ -437,7 +455,7 @@ def test_unaligned_operands_through_every_variant(B, oracle, dtype, out):
     shapes = [(vec, vec, vec, 1, 0), (vec + 1, 3 * vec - 1, bk - 1, 1, 0), (65, 131, bk + 1, 1, 3), (129, 2 * vec + 1, 2 * bk + vec + 1, 2, 0),
               (200, 257, 5 * bk - 3, 1, 1), (64, 2 * 64 + 4, vec + 3, 3, 5)]
     try:
-        for (M, N, K, batch, pad) in shapes:
+        for i, (M, N, K, batch, pad) in enumerate(shapes):
             for ta in (False, True):
                 for tb in (False, True):
                     lda, ldb = (M if ta else K) + pad, (K if tb else N) + pad
@@ -448,6 +466,7 @@ def test_unaligned_operands_through_every_variant(B, oracle, dtype, out):
                     a_rs, a_cs = (1, lda) if ta else (lda, 1)
                     b_rs, b_cs = (1, ldb) if tb else (ldb, 1)
                     ref, S = oracle.batch_matmul(dtype, a_bits[1:].copy(), b_bits[1:].copy(), batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs)
+                    ep, bias, ref, S = _consumer(B, oracle, dtype, out, N, K, i % 2 == 1, ref, S)
                     a, b = B.to_device(a_bits, dtype)[1:], B.to_device(b_bits, dtype)[1:]
                     suffix = f"_{'um' if ta else 'uk'}_{'uk' if tb else 'un'}_generic"
                     todo = [n for n in names if n.startswith(f"{dtype}_{out}_") and n.endswith(suffix)]
@@ -455,9 +474,8 @@ def test_unaligned_operands_through_every_variant(B, oracle, dtype, out):
                     for name in todo:
                         _say(f"unaligned {batch} x {M}x{N}x{K} pad {pad} {name}")
                         B.tir_debug_force_variant(name)
-                        c = B.empty_out((batch, M, N), out)
-                        c.fill_(float("nan")) if out != "i32" else c.fill_(-123456789)
-                        B.tir_batch_matmul(a, b, c, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, M * N, N, 1, dtype, out)
+                        c = _gpu_out(B, (batch, M, N), out)
+                        B.tir_batch_matmul_fused(a, b, c, batch, M, N, K, a_bs, a_rs, a_cs, b_bs, b_rs, b_cs, M * N, N, 1, dtype, out, ep)
                         torch.cuda.synchronize()
                         PT.assert_close(PT.gpu_to_f64(c), ref, S, f"{batch} x {M}x{N}x{K} via {name}")
     finally:
@@ -984,23 +1002,31 @@ def test_seeded_random_problems(B, oracle, seed):
 @pytest.mark.parametrize("seed", [4, 5, 6, 7])
 def test_seeded_random_problems_through_forced_variants(B, oracle, seed):
     """The same generator, each problem through one more variant of its dtype pair and copy mode drawn at random:
-    tile shapes, ring depths and copy-wave variants the scoring rule would never pick for such extents."""
+    tile shapes, ring depths and copy-wave variants the scoring rule would never pick for such extents, the unaligned kernels
+    (names ending in _generic: operands of any alignment) and the few-channel ones among them.  Left out are the kinds with one
+    kernel per dtype pair (element-wise, depth-wise, patch)."""
     names = B.tir_debug_variant_names()
     rng = np.random.default_rng(900 + seed)
+    kinds = set()
     try:
         for wl in _random_workloads(seed, 40):
             default = PT.variant_name(B, wl).split("/")[0]
-            if any(t in default for t in ("generic", "depthwise", "patch")):
-                continue
             parts = default.split("_")
-            cands = [n for n in names if n.startswith("_".join(parts[:2]) + "_") and n.endswith("_" + "_".join(parts[3:]))]
-            assert cands, default
+            cands = [n for n in names if n.split("_")[:2] == parts[:2] and n.split("_")[3:] == parts[3:] and "patch" not in n
+                     and ("rows256x" in n) == ("rows256x" in default)]
+            if "patch" in default or len(cands) <= 1:
+                assert any(t in default for t in ("s2_generic", "s2_conv_generic", "depthwise", "patch")), default
+                continue
             force = str(rng.choice(cands))
+            kinds.add("rows" if "rows256x" in force else "_".join(parts[3:]))
             _say(f"{wl.name}: {default} -> {force}")
             B.tir_debug_force_variant(force)
+            got = PT.variant_name(B, wl).split("/")[0]
+            assert got == force, (got, force)
             PT.check_workload(wl, oracle, f"{wl.name} via {force}")
     finally:
         B.tir_debug_force_variant("")
+    assert any(k.startswith("u") for k in kinds) and "conv" in kinds, kinds
 
 
 # ------------------------------------------------------------------------------ conv1d / conv3d / transposed conv2d
@@ -1124,7 +1150,7 @@ def test_conv2d_transpose_by_output_phase(B, oracle, dtype, out):
             B.tir_debug_force_variant("")
 
 
-@pytest.mark.parametrize("dtype,out", [("f16", "f32"), ("bf16", "f32"), ("i8", "i8")])
+@pytest.mark.parametrize("dtype,out", PAIRS)
 @pytest.mark.parametrize("vecs", [5, 7, 9, 15, 26])
 def test_conv2d_transpose_by_output_phase_pads_the_last_stage_of_a_tap(B, oracle, dtype, out, vecs):
     """By phase with channels that are no multiple of a stage (vecs 16-byte vectors per pixel and group): through the default and every
@@ -1137,12 +1163,9 @@ def test_conv2d_transpose_by_output_phase_pads_the_last_stage_of_a_tap(B, oracle
     C = groups * vecs * vec
     xb = I.make_tensor(dtype, "i" if dtype == "i8" else "n0.1", 9940 + vecs, (N, H, W, C))
     wb = I.make_tensor(dtype, "i" if dtype == "i8" else "n0.1", 9941 + vecs, (K, R, S_, C // groups))
-    scale = 1.0 / 700.0 if out == "i8" else 0.0
-    ep = B.make_epilogue(None, False, scale)
     xd, wd = B.to_device(xb, dtype), B.to_device(wb, dtype)
     ref, S = oracle.conv2d_transpose(dtype, xb, wb, stride, pad, (1, 1), outpad, groups)
-    if scale:
-        ref, S = oracle.epilogue(ref, S, bias=None, relu=False, scale=scale)
+    ep, bias, ref, S = _consumer(B, oracle, dtype, out, K, R * S_ * C // groups, dtype == "i8" and vecs in (5, 26), ref, S)
     names = [""] + [n for n in B.tir_debug_variant_names() if n.startswith(f"{dtype}_{out}_") and n.endswith("_convr")]
     assert len(names) > 5
     _say(f"conv2d_transpose ragged stages {dtype}->{out} C={C}")
@@ -1256,6 +1279,46 @@ def test_reduction_split_over_workgroups(B, oracle, ks, dtype, out):
                 PT.assert_close(PT.run_gpu(wl2, a2, b2), ref2, S2, f"{wl2.name} via {name}")
                 again = PT.run_gpu(wl, a_bits, b_bits)
                 assert np.array_equal(first, again), f"{wl.name}: two launches differ"
+    finally:
+        B.tir_debug_force_variant("")
+        B.tir_debug_force_ksplit(0)
+
+
+@pytest.mark.parametrize("ks", [2, 3, 8])
+@pytest.mark.parametrize("dtype,out", [("f16", "f32"), ("bf16", "bf16"), ("i8", "i32"), ("i8", "i8")])
+def test_reduction_split_of_a_transposed_a(B, oracle, ks, dtype, out):
+    """The same for A stored [K, M] (weight gradients: small outputs, a long reduction over the tokens): slices whose k-rows start inside
+    both operands, a tail of k-rows in the last slice, batches, B along either axis, plain tiles, two reduction groups, copy waves,
+    fused consumers; two launches in a row are bit-identical."""
+    import torch
+    vec = 16 if dtype == "i8" else 8
+    dist = "i" if dtype == "i8" else "u"
+    try:
+        for force in ("", "t64x64w2x2s3k2_", "t64x32w2x1s4_", "t128x128w2x2s3c4_"):
+            B.tir_debug_force_variant(force)
+            B.tir_debug_force_ksplit(ks)
+            for i, (batch, M, N, K) in enumerate([(1, 8 * vec, 5 * vec, 4096), (1, 13 * vec, 9 * vec, 1800 + vec // 2), (3, 3 * vec, 17 * vec, 3592), (1, 5 * vec, 4 * vec, 1024)]):
+                for trans_b in (False, True):
+                    if trans_b and K % vec:
+                        continue
+                    a_bits = I.make_tensor(dtype, dist, 9750 + M + K, (batch, K, M))
+                    b_bits = I.make_tensor(dtype, dist, 9751 + N + K, (batch, N, K) if trans_b else (batch, K, N))
+                    b_rs, b_cs = (1, K) if trans_b else (N, 1)
+                    shape = (batch, M, N, K, K * M, 1, M, N * K, b_rs, b_cs)
+                    ref, S = oracle.batch_matmul(dtype, a_bits, b_bits, *shape)
+                    ep, bias, ref, S = _consumer(B, oracle, dtype, out, N, K, i % 2 == 1, ref, S)
+                    name = B.tir_gemm_variant(batch, M, N, K, 1, M, b_rs, b_cs, N, 1, dtype, out)
+                    _say(f"A^T split {ks}: {batch} x {M}x{N}x{K} {'NT'[trans_b]} {dtype}->{out} {name}")
+                    assert "_am_b" in name and name.endswith(f"/z{ks}") and force in name, name
+                    a, b = B.to_device(a_bits, dtype), B.to_device(b_bits, dtype)
+                    got = []
+                    for _ in range(2):
+                        c = _gpu_out(B, (batch, M, N), out)
+                        B.tir_batch_matmul_fused(a, b, c, *shape, M * N, N, 1, dtype, out, ep)
+                        torch.cuda.synchronize()
+                        got.append(PT.gpu_to_f64(c))
+                    PT.assert_close(got[0], ref, S, name)
+                    assert np.array_equal(got[0], got[1]), f"{name}: two launches differ"
     finally:
         B.tir_debug_force_variant("")
         B.tir_debug_force_ksplit(0)

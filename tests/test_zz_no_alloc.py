@@ -59,3 +59,30 @@ def test_split_static_matches_the_allocating_entry_point_twice_in_a_row(oracle, 
         B.tir_gemm_split_static(a, b, c_again, M, N, K, K, 1, 1, K, N, 1, dtype, out, ep, slices)
         torch.cuda.synchronize()
         assert np.array_equal(PT.gpu_to_f64(c_again), got), f"{wl.name}: two identical calls differ"
+
+
+@pytest.mark.parametrize("dtype,out", [("f16", "f32"), ("bf16", "bf16"), ("i8", "i32")])
+def test_split_static_of_a_transposed_a(oracle, dtype, out):
+    """A stored [K, M]: the static scratch takes it like any operand the fast kernels take, B along either axis."""
+    import torch
+    from paper_2207_04296_amd import binding as B
+    B.lib()
+    dist = "i" if dtype == "i8" else "u"
+    for M, N, K, slices, trans_b in [(208, 176, 4112, 5, False), (96, 80, 1024, 2, True)]:
+        a_bits = I.make_tensor(dtype, dist, 9320 + M, (K, M))
+        b_bits = I.make_tensor(dtype, dist, 9321 + N, (N, K) if trans_b else (K, N))
+        b_rs, b_cs = (1, K) if trans_b else (N, 1)
+        ref, S = oracle.gemm(dtype, a_bits, b_bits, M, N, K, 1, M, b_rs, b_cs)
+        if out == "bf16":
+            S = S + 2.0 ** -8 * np.abs(ref) / PT.RTOL_S
+        a, b = B.to_device(a_bits, dtype), B.to_device(b_bits, dtype)
+        got = []
+        for _ in range(2):
+            c = B.empty_out((M, N), out)
+            _fill(c)
+            _say(f"tir_gemm_split_static, A^T {M}x{N}x{K} {dtype}->{out}, {slices} slices")
+            B.tir_gemm_split_static(a, b, c, M, N, K, 1, M, b_rs, b_cs, N, 1, dtype, out, None, slices)
+            torch.cuda.synchronize()
+            got.append(PT.gpu_to_f64(c))
+        PT.assert_close(got[0], ref, S, f"A^T {M}x{N}x{K} on the static scratch")
+        assert np.array_equal(got[0], got[1])
