@@ -18,10 +18,14 @@ template <int DT, int OUT, int DH> static hipError_t launch_attn(const AttnParam
     const long long tiles = (long long)p.batch * ((p.M + 127) / 128);        // of 128 queries
     // Two workgroups of four waves fill a CU.  Up to about one tile per CU a second key group takes the place of the second workgroup,
     // up to half a tile four groups on half-tiles do; the merge costs about a chunk's time, so the groups need a few chunks each.  At
-    // d = 128 two groups take a CU's whole LDS, and from 160 tiles on (60 heads of 512 x 512: 240 tiles, 2 % slower) they gain nothing; at
-    // d = 64 two such workgroups share a CU (256 x 100 x 1000 20.3 us instead of 22.7, 96 x 300 x 3000 53.5 instead of 61).
+    // d = 128 two groups take a CU's whole LDS, so that a second round of workgroups waits for the first; at d = 64 two such workgroups share a
+    // CU, and with many keys they pay up to a tile and a half per CU.
+    // One, two and four groups, bf16, us (tiles of 128 x 128 queries x keys):
+    //   d = 128: 128 tiles x 1000 keys 31.3 / 27.3 / 22.3, 144 x 1000 31.7 / 27.9 / 39.4, 160 x 2000 60.4 / 51.4, 200 x 400 16.5 / 16.2, 256 x 400
+    //            17.4 / 17.5, 256 x 600 23.1 / 22.8, 256 x 2000 64.6 / 58.5, 320 x 1000 43.9 / 59.7; 60 heads of 512 x 512 16.1 / 14.4
+    //   d = 64:  128 x 1000 21.4 / 16.8 / 12.2, 256 x 400 11.2 / 9.8, 384 x 1000 29.8 / 29.1, 384 x 400 15.0 / 15.3, 448 x 1000 31.4 / 32.4
     if (tiles <= 128 && p.N > 256) return launch_attn_as<DT, OUT, DH, 2, 4, DH == 64 ? 64 : 32>(p, stream);
-    if (tiles <= (DH == 128 ? 144 : p.N >= 1024 ? 384 : 256) && p.N >= 384) return launch_attn_as<DT, OUT, DH, 4, 2, 64>(p, stream);
+    if (tiles <= (DH == 64 && p.N >= 1024 ? 384 : 256) && p.N >= 384) return launch_attn_as<DT, OUT, DH, 4, 2, 64>(p, stream);
     return launch_attn_as<DT, OUT, DH, 4, 1, 64>(p, stream);
 }
 

@@ -822,9 +822,9 @@ ATTN_KERNELS = [
     (3, 70, 300, 64),        # four key groups of 64-key chunks
     (2, 65, 300, 128),       # ... of 32-key chunks
     (129, 20, 390, 64),      # two key groups
-    (130, 17, 450, 128),
+    (150, 17, 450, 128),
     (260, 20, 500, 64),      # one group, eight chunks
-    (150, 33, 450, 128),
+    (258, 9, 450, 128),
     (2, 40, 130, 128),       # one group, three chunks
 ]
 
