@@ -1,8 +1,8 @@
-// One attention head per (batch, 128-query tile): S = scale * Q K^T, row softmax, O = P V, in one
+// One workgroup per (batch, tile of 128 or 64 queries): S = scale * Q K^T, row softmax, O = P V, in one
 // kernel.  Both contractions are tensorized blocks (Eq. 1 of the TensorIR paper, mapped onto the
 // 32x32x16 MFMA) that share the workgroup's tile instead of meeting in memory: the probabilities never
 // leave the registers (sec. 2 / 3.2: blocks isolate the two sub-problems, which does not prevent
-// cooperation across them).  The softmax is the textbook one, computed online over 64-key chunks.
+// cooperation across them).  The softmax is the textbook one, computed online over chunks of 64 or 32 keys.
 //
 // Both products are computed transposed, S^T = K Q^T and O^T = V^T P^T, so that the second MFMA
 // operand - whose row index is the lane - is the query in both: every lane then owns one query row,
@@ -49,13 +49,12 @@ template <> struct PackP<DT_BF16> {
 //
 // 64 keys per chunk: two stages of K and V and nothing else in LDS (64 KiB at d = 128), so that two workgroups share a CU and
 // one's softmax - vector work as long as the MFMAs of its chunk - runs under the other's MFMAs.  With 128-key chunks and the
-// queries in LDS as well (160 KiB) a SIMD had one wave and did one after the other: 16 x 4096 x 4096 x 128 bf16 took 208 us,
-// now 135 (1.02 PFLOP/s; this card's large bf16 matrix products reach 1.2).
+// queries in LDS as well (160 KiB) a SIMD had one wave and did one after the other: 16 x 4096 x 4096 x 128 bf16 took 207 us,
+// now 141 (0.97 PFLOP/s; this card's large bf16 matrix products reach 1.2).
 //
 // QW waves of 32 queries times KG key groups: group k takes the chunks c with c % KG == k through a ring of its own and the
 // groups' results are merged through LDS at the end.  Where the query tiles alone leave CUs or SIMDs idle, key groups put more waves
-// on the same tile (bf16, microseconds without and with: 8 heads of 64 x 4096 x 128 100 -> 59, 16 of 1024 x 1024 x 128 27 -> 18.4,
-// 24 of 686 x 686 x 64 13.5 -> 11.8).
+// on the same tile (launch_attn gives the rule and both sides' times).
 template <int DT, int OUT, int DH, int QW, int KG, int KB>
 __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1) attention_kernel(const AttnParams p) {
     typedef OutTraits<OUT> OT;
@@ -164,15 +163,16 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[db][r] = 0.f;          // reduction init
     // The reference of the softmax, a row's largest score so far in base-2 units, and the sum of the probabilities relative to it.  Every
-    // row's own largest probability is then exactly 1 and loses nothing when the probabilities are rounded to 16 bits for the second
-    // product.  Letting references lag (up to 2^8, rescaling rarely) is 4 - 10 % faster and was measured less exact: bf16 against fp64,
+    // row's own largest probability is then 1 (to 2^-14 here, exactly once rounded to 16 bits) and loses nothing when the probabilities are
+    // rounded for the second product.  Letting references lag (up to 2^8, rescaling rarely) is 4 - 10 % faster and was measured less exact: bf16 against fp64,
     // 2048 keys at d = 64, scale 1, N(0, 1) data 6.3e-4 instead of 1.7e-4, 4096 keys at d = 128, scale 1/sqrt(d) 1.67e-3 instead of 1.48e-3.
     float m_run = 0.f, l_run = 0.f;
     const float sc = p.scale_log2e;
     // Up to this size a reference's own rounding moves an exponent by 2^-14 at most, and the exponent comes from one fused
     // multiply-add per score.  Beyond it (scores of thousands, infinities, a scale of zero) score and reference are rounded alike first: the
     // product inside the fused form is exact, so the row's largest score would keep the whole rounding error of its reference as exponent.
-    constexpr float kFused = 1024.0f;
+    // (The test costs a wave one comparison and one branch per chunk, 1 %; rounding every score first costs an instruction per score.)
+    const float fused_upto = sc != 0.f ? 1024.0f : -1.0f;
     copy_barrier<0>();                                // the queries and the first two chunks
 
     auto multiply_chunk = [&](int i, int st) __attribute__((always_inline)) {
@@ -231,8 +231,8 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
         }
-        const bool fused = sc != 0.f && __builtin_amdgcn_ballot_w64(!(__builtin_fabsf(m_run) <= kFused)) == 0;
-        if (__builtin_expect(!fused, 0)) {
+        float mul = sc, base = -m_run;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(__builtin_fabsf(m_run) <= fused_upto)) != 0, 0)) {
 #pragma clang fp contract(off)
             // exponents in place of the scores; keys past N again, which a scale of zero would turn into NaN
 #pragma unroll
@@ -242,8 +242,9 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
                     const float s = acc_s[jb][r] * sc;
                     acc_s[jb][r] = c * KB + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N ? -__builtin_inff() : s - m_run;
                 }
+            mul = 1.f;
+            base = 0.f;
         }
-        const float mul = fused ? sc : 1.f, base = fused ? -m_run : 0.f;
         uint4 pf[JB][2];                                             // P^T fragments: key block jb, k-step s
         float lsum[2] = {0.f, 0.f};
 #pragma unroll
