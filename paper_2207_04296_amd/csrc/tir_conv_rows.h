@@ -11,7 +11,11 @@
 // five dwords and shifted (SHIFT, 18 - 22 cycles).
 // 16x224x224x3 -> 64, 7x7, stride 2 in fp16 (5 MB in, 26 MB out: 6 us of HBM time): 113 us as element-wise gathers, 12.3 now.  A
 // wave's phases follow each other and each has its own bound - 16-byte loads at 2-byte alignment (46 cycles each in the CU's load
-// path: 4 600 cycles), MFMAs and LDS reads (7 000), stores (4 800).
+// path: 4 600 cycles), MFMAs and LDS reads (7 000), stores (4 800).  An image of height 1 leaves three of a tile's four rows empty and gains
+// all the same: 16x16000x1 -> 64, 10 taps, stride 5 17.4 us and 7.3, 4x3000x6 -> 80, 3 taps 10.7 and 5.2.
+//
+// The scoring rule sees tiles of 256 pixels x BN channels, not the kernel's 64 x BN per wave; of its two choices of BN it took the faster one, or one
+// within 4 %, for 43 of 44 calls drawn over image networks' stems and 1-D signals (worst 64x500x2 -> 128, 7 taps, stride 2: 6.5 us, 5.8 with BN = 64).
 #pragma once
 #include "tir_kernel.h"
 

@@ -1480,7 +1480,7 @@ __global__ void __launch_bounds__(512) conv_patch_kernel(const Params p) {
 // linear LDS write per chunk into the same swizzled tiles the fast kernel reads.  Nothing outside an operand is touched: rows past
 // the edge are clamped (they are never stored), a chunk that would run past its row's end is loaded so that it ends there and
 // shifted into place, and k past K is zero on both sides.
-// One load per value, the form this replaces, was bound by load issue: 1001x1531x777 fp16 37.3 us, now 9.9.  A CU loads about
+// One load per value, the form this replaces, was bound by load issue: 1001x1531x777 fp16 36.5 us, now 10.3.  A CU loads about
 // 47 KB/us this way (16-byte loads at 2-byte alignment cost 10 % over aligned ones; global->LDS copies reach 86), which
 // bounds the tiles: 192 of 128x64 move 312 KB each in that product.
 // ---------------------------------------------------------------------------------------------

@@ -17,7 +17,7 @@ enum : int {
     A_CONV_PATCH = 4,    // convolution reading its taps from an LDS-resident input patch (128 B per pixel)
     A_DEPTHWISE = 6,     // depth-wise 2-D convolution (one filter per channel): direct kernel, no matrix intrinsic
     // A stored [k][x], x contiguous (a transposed A: weight gradients dW = X^T dY); transposed on the LDS read like B_NMAJOR.
-    // Before it existed such calls took the element-wise kernel: 768x3072x2048 bf16 175.6 us, now 15.0
+    // Before it existed such calls took the element-wise kernel: 768x3072x2048 bf16 175.6 us, now 15.2
     A_MMAJOR = 7,
     // Vector loads at element alignment, staged through registers: [x][k] rows (UK) or [k][x] rows (UM) of any length, stride
     // and base address; the contiguous axis holds at least one 16-byte vector
