@@ -47,16 +47,24 @@ template <> struct PackP<DT_BF16> {
 
 // DT: f16 / bf16 inputs, OUT: same 16-bit type or f32, DH: head dimension (64 or 128) of Q, K and V.
 //
-// 64 keys per chunk: two stages of K and V and nothing else in LDS (64 KiB at d = 128), so that two workgroups share a CU and
-// one's softmax - vector work as long as the MFMAs of its chunk - runs under the other's MFMAs.  With 128-key chunks and the
-// queries in LDS as well (160 KiB) a SIMD had one wave and did one after the other: 16 x 4096 x 4096 x 128 bf16 took 207 us,
-// now 141 (0.97 PFLOP/s; this card's large bf16 matrix products reach 1.2).
+// 64 keys per chunk (KB): two stages of K and V and nothing else in LDS (64 KiB at d = 128), so that two workgroups share a CU.  A chunk's
+// softmax is vector work about as long as its MFMAs, and a wave runs the two under each other: the exponentials of chunk i stand between
+// the MFMAs of K Q^T of chunk i + 1, that chunk's row maxima between those of V^T P^T of chunk i, and the copy instructions of the chunk
+// after between the former (a copy instruction holds its wave for longer than an MFMA lasts; all in front of a chunk cost 10 %).  Measured
+// here: 32 MFMAs of 32 cycles with 128 multiply-adds and 32 exponentials between them take one wave 1 096 cycles, the MFMAs alone 1 038, the
+// vector work alone 840.  With each wave's phases in sequence, left to a second wave to cover, 16 x 4096 x 4096 x 128 bf16 took 143.8 us, now
+// 133.8; 160 x 128 x 2000 x 128 50.5 and 39.9, 52 x 376 x 376 x 64 9.3 and 7.7.  What bounds the long case is power: the same launch on constant data takes
+// 111 us instead of 155 (one warm card), with 14 % between the two forms of the loop.
 //
 // QW waves of 32 queries times KG key groups: group k takes the chunks c with c % KG == k through a ring of its own and the
 // groups' results are merged through LDS at the end.  Where the query tiles alone leave CUs or SIMDs idle, key groups put more waves
 // on the same tile (launch_attn gives the rule and both sides' times).
-template <int DT, int OUT, int DH, int QW, int KG, int KB>
-__global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1) attention_kernel(const AttnParams p) {
+//
+// FORM: the loop described above, plain or with non-temporal copies, or a chunk's phases in sequence.  The latter holds one chunk's scores instead of two: 120
+// registers instead of 165 at d = 64, four workgroups per CU instead of three.
+enum : int { ATTN_PIPED = 0, ATTN_PIPED_STREAM = 1, ATTN_SEQUENTIAL = 2 };
+template <int DT, int OUT, int DH, int QW, int KG, int KB, int FORM>
+__global__ void __launch_bounds__(QW * KG * 64, 2) attention_kernel(const AttnParams p) {
     typedef OutTraits<OUT> OT;
     typedef typename OT::type out_t;
     constexpr int OS = (int)sizeof(out_t);
@@ -116,32 +124,50 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
     const char* Qb = (const char*)p.Q + ((b * p.M + m0) * (long long)ROW);
     const char* Kb = (const char*)p.K + b * p.N * (long long)ROW;
     const char* Vb = (const char*)p.V + b * p.N * (long long)ROW;
-    // Non-temporal copies for what one workgroup alone reads (one tile holds all queries of a head): 7.05 -> 6.63 us on the
-    // benchmark's 192 heads with the operands coming from memory, no change from the caches.
+    // Non-temporal copies of the first two chunks for what one workgroup alone reads (one tile holds all queries of a head): 192 heads of
+    // 128 x 128 x 64 from memory 7.05 -> 6.63 us, no change from the caches.
     const bool kv_once = p.tiles_m == 1;
-    // (`st`, the ring stage of chunk i, is a constant in every call: worked out from i it costs an addition per LDS read)
-    auto copy_chunk = [&](int i, int st) __attribute__((always_inline)) {
+    // One copy instruction of a chunk's keys or values into ring stage st (a constant in every call: worked out from i it costs an
+    // addition per LDS read).
+    auto copy_key = [&](const i32x4& rk, int st, int u, bool once) __attribute__((always_inline)) {
+        char* const dst = ring + st * 2 * TILE + wave * 1024 + u / KPASS * (KB * 128) + u % KPASS * (GT * 16);
+        const unsigned off = k_off + u % KPASS * (KROWS * ROW) + u / KPASS * 128;
+        if (once) load_to_lds_nt(rk, dst, off);
+        else load_to_lds(rk, dst, off);
+    };
+    auto copy_value = [&](const i32x4& rv, int st, int u, bool once) __attribute__((always_inline)) {
+        char* const dst = ring + st * 2 * TILE + TILE + wave * 1024 + u * (GT * 16);
+        if (once) load_to_lds_nt(rv, dst, v_off + u * (GT * 16));
+        else load_to_lds(rv, dst, v_off + u * (GT * 16));
+    };
+    // Descriptor of chunk i of this group in K or V: rows past N lie outside it and read zeros; past the last chunk it is empty.
+    auto chunk_rsrc = [&](const char* base, int i) __attribute__((always_inline)) {
         const int c = i * KG + kgrp;
-        const long long left = (long long)(p.N - c * KB) * ROW;      // rows past N lie outside the descriptor: zeros
-        const i32x4 rk = make_rsrc(Kb + (long long)c * TILE, left), rv = make_rsrc(Vb + (long long)c * TILE, left);
-        char* const dk = ring + st * 2 * TILE + wave * 1024;
-        char* const dv = dk + TILE;
+        return make_rsrc(base + (long long)c * TILE, (long long)(p.N - c * KB) * ROW);
+    };
+    auto copy_keys = [&](int i, int st) __attribute__((always_inline)) {
+        const i32x4 rk = chunk_rsrc(Kb, i);
+        if (kv_once) {
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h)
+            for (int u = 0; u < COPIES; ++u) copy_key(rk, st, u, true);
+        } else {
 #pragma unroll
-            for (int u = 0; u < KPASS; ++u) {
-                if (kv_once) load_to_lds_nt(rk, dk + h * (KB * 128) + u * (GT * 16), k_off + u * (KROWS * ROW) + h * 128);
-                else load_to_lds(rk, dk + h * (KB * 128) + u * (GT * 16), k_off + u * (KROWS * ROW) + h * 128);
-            }
+            for (int u = 0; u < COPIES; ++u) copy_key(rk, st, u, false);
+        }
+    };
+    auto copy_values = [&](int i, int st) __attribute__((always_inline)) {
+        const i32x4 rv = chunk_rsrc(Vb, i);
+        if (kv_once) {
 #pragma unroll
-        for (int u = 0; u < COPIES; ++u) {
-            if (kv_once) load_to_lds_nt(rv, dv + u * (GT * 16), v_off + u * (GT * 16));
-            else load_to_lds(rv, dv + u * (GT * 16), v_off + u * (GT * 16));
+            for (int u = 0; u < COPIES; ++u) copy_value(rv, st, u, true);
+        } else {
+#pragma unroll
+            for (int u = 0; u < COPIES; ++u) copy_value(rv, st, u, false);
         }
     };
     // Both stages are filled up front: a head of 128 keys is these two chunks, and requesting the second only after the first had landed
     // is one more trip to memory (192 heads of 128 x 128 x 64 fp16 from memory 6.59 us, 6.20 this way).
-    if (nmine > 0) copy_chunk(0, 0);
+    if (nmine > 0) { copy_keys(0, 0); copy_values(0, 0); }
 
     // ------------------------------------------------------------ this wave's queries, as MFMA operands (rows past M read zeros)
     // (no non-temporal hint here, although nobody else reads them: a load takes 32 bytes of each of 32 rows, and lines that do not stay are
@@ -154,7 +180,8 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
         for (int ks = 0; ks < KSTEPS; ++ks)
             qf[ks] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rq, (wave * 32 + l31) * ROW + ks * 32 + g * 16, 0, 0));
     }
-    if (nmine > 1) copy_chunk(1, 1);
+    if (nmine > 1) copy_keys(1, 1);
+    if (nmine == 2 || (FORM == ATTN_SEQUENTIAL && nmine > 1)) copy_values(1, 1);      // (pipelined, with more chunks, the first step copies these values)
     const int swl = kmajor_swz<128>(l31);            // rows 32*jb + l31 share it (period 16)
 
     f32x16 acc_o[DB];
@@ -167,63 +194,63 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
     // rounded for the second product.  Letting references lag (up to 2^8, rescaling rarely) is 4 - 10 % faster and was measured less exact: bf16 against fp64,
     // 2048 keys at d = 64, scale 1, N(0, 1) data 6.3e-4 instead of 1.7e-4, 4096 keys at d = 128, scale 1/sqrt(d) 1.67e-3 instead of 1.48e-3.
     float m_run = 0.f, l_run = 0.f;
-    const float sc = p.scale_log2e;
+    // A negative scale is a positive one on negated queries (exact), so that the largest scaled score is that of the largest score.
+    const float sc = __builtin_fabsf(p.scale_log2e);
     // Up to this size a reference's own rounding moves an exponent by 2^-14 at most, and the exponent comes from one fused
     // multiply-add per score.  Beyond it (scores of thousands, infinities, a scale of zero) score and reference are rounded alike first: the
     // product inside the fused form is exact, so the row's largest score would keep the whole rounding error of its reference as exponent.
     // (The test costs a wave one comparison and one branch per chunk, 1 %; rounding every score first costs an instruction per score.)
     const float fused_upto = sc != 0.f ? 1024.0f : -1.0f;
     copy_barrier<0>();                                // the queries and the first two chunks
-
-    auto multiply_chunk = [&](int i, int st) __attribute__((always_inline)) {
-        const int c = i * KG + kgrp;
-        if (i > 0 && i + 1 < nmine) copy_chunk(i + 1, st ^ 1);      // its stage was last read before the previous barrier
-        const char* sk = ring + st * 2 * TILE;
-        const char* sv = sk + TILE;
-
-        // S^T = K Q^T: rows = keys (registers), columns = queries (lanes)
-        f32x16 acc_s[JB];
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc_s[jb][r] = 0.f;
+    if (p.scale_log2e < 0.f) {
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks)
+            qf[ks] = make_uint4(qf[ks].x ^ 0x80008000u, qf[ks].y ^ 0x80008000u, qf[ks].z ^ 0x80008000u, qf[ks].w ^ 0x80008000u);
+    }
+
+    // ------------------------------------------------------------ fragments of a chunk in ring stage st
+    auto k_frag = [&](int st, int ks, int jb) __attribute__((always_inline)) -> uint4 {
+        return *(const uint4*)(ring + st * 2 * TILE + (ks >> 2) * (KB * 128) + (jb * 32 + l31) * 128 + ((((ks & 3) * 2 + g) ^ swl) << 4));
+    };
+    // Position (g, 4*hh + e) of k-step s in key block jb is key 32*jb + 16*s + 8*hh + 4*g + e: the order in which the
+    // probabilities come out of the first product.
+    auto v_frag = [&](int st, int jb, int s, int db) __attribute__((always_inline)) -> uint4 {
+        i16x4 h[2];
 #pragma unroll
-            for (int jb = 0; jb < JB; ++jb) {
-                const uint4 kf = *(const uint4*)(sk + (ks >> 2) * (KB * 128) + (jb * 32 + l31) * 128 + ((((ks & 3) * 2 + g) ^ swl) << 4));
-                acc_s[jb] = InTraits<DT>::mfma(kf, qf[ks], acc_s[jb]);
-            }
+        for (int hh = 0; hh < 2; ++hh) {
+            const int key = jb * 32 + s * 16 + hh * 8 + 4 * (blk >> 1) + (s16 >> 2);
+            const int col = db * 32 + 16 * (blk & 1) + 4 * (s16 & 3);
+            const char* ptr = ring + st * 2 * TILE + TILE + key * ROW + ((col * 2) ^ (((key / RPW) % NSEG) * 64));
+            h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(TIR_LDS_PTR(i16x4, ptr));
+        }
+        const i32x2 lo = __builtin_bit_cast(i32x2, h[0]), hi = __builtin_bit_cast(i32x2, h[1]);
+        return make_uint4((unsigned)lo[0], (unsigned)lo[1], (unsigned)hi[0], (unsigned)hi[1]);
+    };
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // keys past N (only in the last chunk) drop out of the softmax
+    auto mask_chunk = [&](int i, f32x16 (&s)[JB]) __attribute__((always_inline)) {
+        const int c = i * KG + kgrp;
         if ((c + 1) * KB > p.N) {
-            // keys past N (only in the last chunk) drop out of the softmax
-            const float out = sc < 0.f ? __builtin_inff() : -__builtin_inff();
 #pragma unroll
             for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (c * KB + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N) acc_s[jb][r] = out;
+                    if (c * KB + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N) s[jb][r] = -__builtin_inff();
         }
-        // the row's largest scaled score: that of its largest score, or of its smallest under a negative scale
-        float mx = acc_s[0][0];
-        if (sc >= 0.f) {
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = __builtin_fmaxf(mx, acc_s[jb][r]);
-            mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32));           // the other half-wave holds the query's other keys
-        } else {
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = __builtin_fminf(mx, acc_s[jb][r]);
-            mx = __builtin_fminf(mx, __shfl_xor(mx, 32));
-        }
+    };
+    // A row's largest scaled score in a chunk from the lane's partial maxima.
+    auto chunk_reference = [&](float mx) __attribute__((always_inline)) -> float {
+        const auto both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, mx), __builtin_bit_cast(unsigned, mx), false, false);
+        const unsigned lo = both[0], hi = both[1];                   // the half-waves' values: each holds half of the query's keys
+        mx = __builtin_fmaxf(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
         // (a chunk whose scores are all -inf counts nothing, but its reference has to be a number)
-        const float m_chunk = __builtin_fmaxf(mx * sc, -__FLT_MAX__);
-        if (i == 0) m_run = m_chunk;
-        else if (__builtin_amdgcn_ballot_w64(m_chunk > m_run) != 0) {
+        return __builtin_fmaxf(mx * sc, -__FLT_MAX__);
+    };
+
+    auto raise_reference = [&](float m_chunk) __attribute__((always_inline)) {
+        if (__builtin_amdgcn_ballot_w64(m_chunk > m_run) != 0) {
             const float m_new = __builtin_fmaxf(m_run, m_chunk);
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);          // 1 for rows whose reference stays
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);              // 1 for rows whose reference stays
             m_run = m_new;
             l_run *= alpha;
 #pragma unroll
@@ -231,68 +258,155 @@ __global__ void __launch_bounds__(QW * KG * 64, QW * KG >= 8 || KG == 1 ? 2 : 1)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
         }
+    };
+
+    constexpr int NQK = KSTEPS * JB, NPV = JB * 2 * DB;      // MFMAs of the two products of a chunk
+    constexpr int EPM = JB * 16 / NQK;                       // exponentials per MFMA of the first product
+    // MFMAs by which a fragment's read runs ahead (2 and 2: 1 - 3 % slower on long sequences)
+    constexpr int LAK = 4, LAV = 3;
+
+    // Chunk i (ring stage st): its scores are in `cur` and m_run is its reference.  The first product of chunk i + 1 runs under the
+    // exponentials of chunk i, the maximum of its scores under the second product of chunk i.
+    auto chunk_step = [&](int i, int st, f32x16 (&cur)[JB], f32x16 (&nxt)[JB], auto last_flag, auto copy_flag) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last_flag)::value, COPY = decltype(copy_flag)::value;
         float mul = sc, base = -m_run;
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(__builtin_fabsf(m_run) <= fused_upto)) != 0, 0)) {
 #pragma clang fp contract(off)
             // exponents in place of the scores; keys past N again, which a scale of zero would turn into NaN
+            const int c = i * KG + kgrp;
 #pragma unroll
             for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const float s = acc_s[jb][r] * sc;
-                    acc_s[jb][r] = c * KB + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N ? -__builtin_inff() : s - m_run;
+                    const float s = cur[jb][r] * sc;
+                    cur[jb][r] = c * KB + jb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) >= p.N ? -__builtin_inff() : s - m_run;
                 }
             mul = 1.f;
             base = 0.f;
         }
-        uint4 pf[JB][2];                                             // P^T fragments: key block jb, k-step s
+        if constexpr (!LAST && !COPY) {
+            if (i > 0) copy_values(i + 1, st ^ 1);
+        }
+        const i32x4 rk = chunk_rsrc(Kb, i + 2), rv = chunk_rsrc(Vb, i + 1);
+        unsigned pw[JB * 8];                                         // P^T fragments: key block jb, k-step s at 8*jb + 4*s
         float lsum[2] = {0.f, 0.f};
+        uint4 kf[LAK], vf[LAV];
+        if constexpr (!LAST) {
 #pragma unroll
-        for (int jb = 0; jb < JB; ++jb) {
-            float pr[16];
+            for (int t = 0; t < LAK; ++t) kf[t] = k_frag(st ^ 1, t / JB, t % JB);
+        }
+        TIR_FENCE();
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc_s[jb][r], mul, base));
-                lsum[r & 1] += pr[r];
+        for (int t = 0; t < NQK; ++t) {
+            const int jb = t % JB, ks = t / JB;
+            if constexpr (!LAST) {
+                nxt[jb] = InTraits<DT>::mfma(kf[t % LAK], qf[ks], ks == 0 ? zero16 : nxt[jb]);
+                TIR_FENCE();
+                if constexpr (COPY) {
+#pragma unroll
+                    for (int u = t * 2 * COPIES / NQK; u < (t + 1) * 2 * COPIES / NQK; ++u) {
+                        if (u < COPIES) copy_key(rk, st, u, FORM == ATTN_PIPED_STREAM);
+                        else copy_value(rv, st ^ 1, u - COPIES, FORM == ATTN_PIPED_STREAM);
+                    }
+                }
+                if (t + LAK < NQK) kf[t % LAK] = k_frag(st ^ 1, (t + LAK) / JB, (t + LAK) % JB);
+            }
+            if (t >= NQK - LAV) {
+                const int v = t - (NQK - LAV);
+                vf[v] = v_frag(st, v / (2 * DB), v / DB % 2, v % DB);
             }
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-                pf[jb][s] = make_uint4(PackP<DT>::two(pr[8 * s + 0], pr[8 * s + 1]), PackP<DT>::two(pr[8 * s + 2], pr[8 * s + 3]),
-                                       PackP<DT>::two(pr[8 * s + 4], pr[8 * s + 5]), PackP<DT>::two(pr[8 * s + 6], pr[8 * s + 7]));
+            for (int e = t * EPM; e < (t + 1) * EPM; e += 2) {
+                float pr[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    pr[h] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[e / 16][e % 16 + h], mul, base));
+                    lsum[h] += pr[h];
+                }
+                pw[e / 2] = PackP<DT>::two(pr[0], pr[1]);
+            }
+            TIR_FENCE();
         }
         l_run += lsum[0] + lsum[1];
-
-        // O^T += V^T P^T.  Position (g, 4*hh + e) of k-step s in key block jb is key
-        // 32*jb + 16*s + 8*hh + 4*g + e - the order the probabilities sit in the registers above.
+        if constexpr (!LAST) mask_chunk(i + 1, nxt);
+        // O^T += V^T P^T
+        float mx[4];
+#pragma unroll
+        for (int t = 0; t < NPV; ++t) {
+            const int jb = t / (2 * DB), s = t / DB % 2, db = t % DB;
+            const uint4 pf = make_uint4(pw[8 * jb + 4 * s], pw[8 * jb + 4 * s + 1], pw[8 * jb + 4 * s + 2], pw[8 * jb + 4 * s + 3]);
+            acc_o[db] = InTraits<DT>::mfma(vf[t % LAV], pf, acc_o[db]);
+            TIR_FENCE();
+            if (t + LAV < NPV) vf[t % LAV] = v_frag(st, (t + LAV) / (2 * DB), (t + LAV) / DB % 2, (t + LAV) % DB);
+            if constexpr (!LAST) {
+                // the largest of chunk i + 1's scores, from the second MFMA on
+                constexpr int PER = (JB * 16 + NPV - 2) / (NPV - 1);
+#pragma unroll
+                for (int e = (t - 1) * PER; t > 0 && e < t * PER && e < JB * 16; ++e)
+                    mx[e & 3] = e < 4 ? nxt[e / 16][e % 16] : __builtin_fmaxf(mx[e & 3], nxt[e / 16][e % 16]);
+            }
+            TIR_FENCE();
+        }
+        if constexpr (!LAST) {
+            raise_reference(chunk_reference(__builtin_fmaxf(__builtin_fmaxf(mx[0], mx[1]), __builtin_fmaxf(mx[2], mx[3]))));
+        }
+    };
+    // The scores of chunk i on their own, and their reference.
+    auto scores = [&](int i, int st, f32x16 (&s)[JB]) __attribute__((always_inline)) -> float {
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb) s[jb] = InTraits<DT>::mfma(k_frag(st, ks, jb), qf[ks], ks == 0 ? zero16 : s[jb]);
+        mask_chunk(i, s);
+        float mx = s[0][0];
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    i16x4 h[2];
-#pragma unroll
-                    for (int hh = 0; hh < 2; ++hh) {
-                        const int key = jb * 32 + s * 16 + hh * 8 + 4 * (blk >> 1) + (s16 >> 2);
-                        const int col = db * 32 + 16 * (blk & 1) + 4 * (s16 & 3);
-                        const char* ptr = sv + key * ROW + ((col * 2) ^ (((key / RPW) % NSEG) * 64));
-                        h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(TIR_LDS_PTR(i16x4, ptr));
-                    }
-                    const i32x2 lo = __builtin_bit_cast(i32x2, h[0]), hi = __builtin_bit_cast(i32x2, h[1]);
-                    const uint4 vf = make_uint4((unsigned)lo[0], (unsigned)lo[1], (unsigned)hi[0], (unsigned)hi[1]);
-                    acc_o[db] = InTraits<DT>::mfma(vf, pf[jb][s], acc_o[db]);
-                }
+            for (int r = 0; r < 16; ++r) mx = __builtin_fmaxf(mx, s[jb][r]);
+        return chunk_reference(mx);
+    };
 
-    };
-    auto step = [&](int i, int st) __attribute__((always_inline)) {
-        if (KG == 1 || i < nmine) multiply_chunk(i, st);
-        // the next chunk has landed (this wave's part); after the barrier everybody's has, and every wave is done reading
-        // this chunk's stage (a third stage, to wait for the chunk before last only, gained nothing: the copies are not late)
-        copy_barrier<0>();
-    };
-    for (int i = 0; i < nloop; i += 2) {
-        step(i, 0);
-        if (i + 1 < nloop) step(i + 1, 1);
+    f32x16 s_even[JB], s_odd[JB];
+    if constexpr (FORM == ATTN_SEQUENTIAL) {
+        auto step = [&](int i, int st) __attribute__((always_inline)) {
+            if (i > 0 && i + 1 < nmine) {                // the stage was last read before the previous barrier
+                copy_keys(i + 1, st ^ 1);
+                copy_values(i + 1, st ^ 1);
+            }
+            const float m_chunk = scores(i, st, s_even);
+            if (i == 0) m_run = m_chunk;
+            else raise_reference(m_chunk);
+            chunk_step(i, st, s_even, s_odd, std::true_type(), std::false_type());
+            copy_barrier<0>();
+        };
+        static_assert(KG == 1, "");
+        for (int i = 0; i < nmine; i += 2) {
+            step(i, 0);
+            if (i + 1 < nmine) step(i + 1, 1);
+        }
+    } else {
+        if (KG == 1 || nmine > 0) m_run = scores(0, 0, s_even);
+        // A step overwrites the stage of the keys multiplied in the step before and of the values of that step; at its end the copies have
+        // landed (this wave's part) and, after the barrier, everybody's.  Up to two chunks nothing is copied any more and nobody waits.
+        const bool sync = nloop > 2;                      // (the same for all groups)
+        if (sync) copy_barrier<0>();
+        int i = 0;
+        for (; i + 2 < nmine; i += 2) {
+            chunk_step(i, 0, s_even, s_odd, std::false_type(), std::true_type());
+            copy_barrier<0>();
+            chunk_step(i + 1, 1, s_odd, s_even, std::false_type(), std::true_type());
+            copy_barrier<0>();
+        }
+        if (i + 1 < nmine) {
+            chunk_step(i, 0, s_even, s_odd, std::false_type(), std::false_type());
+            if (sync) copy_barrier<0>();
+            ++i;
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb) s_even[jb] = s_odd[jb];
+        }
+        if (KG == 1 || i < nmine) chunk_step(i, i & 1, s_even, s_odd, std::true_type(), std::false_type());
+        if (KG > 1 && sync && nmine < nloop) copy_barrier<0>();      // (the longer groups' last but one step)
+        copy_barrier<0>();                                // everybody is past its last read: the ring is free
     }
 
     if constexpr (KG > 1) {

@@ -6,27 +6,39 @@
 
 namespace tir {
 
-template <int DT, int OUT, int DH, int QW, int KG, int KB> static hipError_t launch_attn_as(AttnParams p, hipStream_t stream) {
+template <int DT, int OUT, int DH, int QW, int KG, int KB, int FORM> static hipError_t launch_attn_as(AttnParams p, hipStream_t stream) {
     p.tiles_m = (p.M + 32 * QW - 1) / (32 * QW);
     const FastDiv dtm = make_fastdiv((unsigned)p.tiles_m);
     p.div_tm_magic = dtm.magic;
     p.div_tm_shift = dtm.shift;
-    return launch_kernel(&attention_kernel<DT, OUT, DH, QW, KG, KB>, dim3((unsigned)(p.batch * p.tiles_m)), dim3(QW * KG * 64), stream, p);
+    return launch_kernel(&attention_kernel<DT, OUT, DH, QW, KG, KB, FORM>, dim3((unsigned)(p.batch * p.tiles_m)), dim3(QW * KG * 64), stream, p);
 }
 
 template <int DT, int OUT, int DH> static hipError_t launch_attn(const AttnParams& p, hipStream_t stream) {
     const long long tiles = (long long)p.batch * ((p.M + 127) / 128);        // of 128 queries
-    // Two workgroups of four waves fill a CU.  Up to about one tile per CU a second key group takes the place of the second workgroup,
-    // up to half a tile four groups on half-tiles do; the merge costs about a chunk's time, so the groups need a few chunks each.  At
-    // d = 128 two groups take a CU's whole LDS, so that a second round of workgroups waits for the first; at d = 64 two such workgroups share a
-    // CU, and with many keys they pay up to a tile and a half per CU.
-    // One, two and four groups, bf16, us (tiles of 128 x 128 queries x keys):
-    //   d = 128: 128 tiles x 1000 keys 31.3 / 27.3 / 22.3, 144 x 1000 31.7 / 27.9 / 39.4, 160 x 2000 60.4 / 51.4, 200 x 400 16.5 / 16.2, 256 x 400
-    //            17.4 / 17.5, 256 x 600 23.1 / 22.8, 256 x 2000 64.6 / 58.5, 320 x 1000 43.9 / 59.7; 60 heads of 512 x 512 16.1 / 14.4
-    //   d = 64:  128 x 1000 21.4 / 16.8 / 12.2, 256 x 400 11.2 / 9.8, 384 x 1000 29.8 / 29.1, 384 x 400 15.0 / 15.3, 448 x 1000 31.4 / 32.4
-    if (tiles <= 128 && p.N > 256) return launch_attn_as<DT, OUT, DH, 2, 4, DH == 64 ? 64 : 32>(p, stream);
-    if (tiles <= (DH == 64 && p.N >= 1024 ? 384 : 256) && p.N >= 384) return launch_attn_as<DT, OUT, DH, 4, 2, 64>(p, stream);
-    return launch_attn_as<DT, OUT, DH, 4, 1, 64>(p, stream);
+    // Two workgroups of four waves fill a CU.  Up to half a tile per CU four key groups on tiles of 64 queries put eight waves on a CU instead
+    // of four; the merge costs about a chunk's time, so that every group needs more than one chunk.  (Two groups on 128 queries, up to one tile
+    // per CU, pay no more since a wave runs its softmax under its own MFMAs.)
+    // One, two and four groups, bf16, us (tiles of 128 queries x keys):
+    //   d = 128: 64 x 320 9.0 / 10.6 / 9.4, 64 x 400 11.3 / 12.2 / 10.7, 128 x 400 11.8 / 12.8 / 11.4, 128 x 1000 22.0 / 23.6 / 20.3,
+    //            144 x 1000 22.3 / 24.0 / 36.2, 256 x 1000 29.6 / 29.9 / 39.2
+    //   d = 64:  64 x 256 5.91 / 6.46 / 5.75, 128 x 256 5.97 / 6.63 / 6.06, 64 x 320 6.60 / 7.38 / 6.31, 128 x 1000 15.4 / 15.8 / 11.8,
+    //            144 x 1000 15.8 / 16.5 / 22.0, 384 x 1000 29.5 / 33.9 / 34.5
+    if (tiles <= 128 && p.N >= (DH == 64 ? 257 : 384)) return launch_attn_as<DT, OUT, DH, 2, 4, DH == 64 ? 64 : 32, ATTN_PIPED>(p, stream);
+    // Few keys that leave the last chunk of 64 half empty: chunks of 32.  64 and 32 keys per chunk, us:
+    //   d = 64:  100 x 77 4.74 / 4.38, 100 x 160 5.54 / 5.21, 384 x 77 6.04 / 5.72, 800 x 77 9.33 / 8.17, 2000 x 150 28.3 / 26.5
+    //   d = 128: 100 x 77 6.26 / 5.76, 320 x 160 11.7 / 10.8, 512 x 160 15.4 / 15.5, 1024 x 96 22.8 / 20.4
+    if ((p.N - 1) % 64 < 32 && p.N <= 160) return launch_attn_as<DT, OUT, DH, 4, 1, 32, ATTN_PIPED>(p, stream);
+    // Two to four workgroups per CU at d = 64 and few keys: four of the sequential form fit a CU, three of the other, and what does not fit is a
+    // second round.  Pipelined and sequential, us: 512 x 320 14.3 / 12.6, 640 x 320 17.0 / 16.1, 800 x 192 16.6 / 14.2, 1024 x 64 8.8 / 7.0; beyond either
+    // end 400 x 320 10.4 / 11.8, 800 x 600 33.7 / 35.1, 1300 x 128 16.6 / 16.9.
+    if constexpr (DH == 64) {
+        if (tiles >= 512 && tiles <= 1024 && p.N <= 400) return launch_attn_as<DT, OUT, DH, 4, 1, 64, ATTN_SEQUENTIAL>(p, stream);
+    }
+    // Keys and values that nobody reads twice and that do not fit the 256 MB memory-side cache go past it: 3000 x 192 at d = 128 92.9 us, 81.6 with non-temporal
+    // copies; within it they cost as much (800 x 320 34.3 / 40.5).
+    if (p.M <= 128 && (long long)p.batch * p.N * DH * 4 > (256ll << 20)) return launch_attn_as<DT, OUT, DH, 4, 1, 64, ATTN_PIPED_STREAM>(p, stream);
+    return launch_attn_as<DT, OUT, DH, 4, 1, 64, ATTN_PIPED>(p, stream);
 }
 
 attn_launch_fn attention_launcher(int dt, int out, int dh) {

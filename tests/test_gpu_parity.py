@@ -821,7 +821,7 @@ def test_attention_matches_oracle(B, oracle, dtype, out, rtol):
 ATTN_KERNELS = [
     (3, 70, 300, 64),        # four key groups of 64-key chunks
     (2, 65, 300, 128),       # ... of 32-key chunks
-    (129, 20, 390, 64),      # two key groups
+    (129, 20, 390, 64),      # one group, seven and eight chunks
     (150, 17, 450, 128),
     (260, 20, 500, 64),      # one group, eight chunks
     (258, 9, 450, 128),
@@ -926,6 +926,44 @@ def test_attention_rounds_all_but_the_largest_probability(B, oracle, shape, dtyp
         ratio = np.abs(got - ref) / (u * (T - top) + fp32 * T + step * N + 1e-7)
         _say(f"attention {dtype} {shape} scale {scale:.3g} late x{late}: max err/bound {ratio.max():.3g}")
         assert ratio.max() <= 1.0
+
+
+@pytest.mark.parametrize("dtype,rtol", [("f16", 2e-3), ("bf16", 6e-3)])
+@pytest.mark.parametrize("batch,M,d,keys", [
+    (3, 33, 64, (1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256)),      # 32- and 64-key chunks, one to five of them
+    (3, 33, 128, (1, 32, 33, 64, 65, 96, 97, 129, 160, 161, 193, 256, 321, 383)),
+    (2, 65, 64, (257, 320, 321, 449, 512, 513, 577)),                                         # four key groups: one to three chunks each
+    (2, 65, 128, (384, 385, 417, 513)),
+    (600, 3, 64, (64, 65, 97, 128, 192, 193, 256, 400)),                                      # two to four workgroups per CU: a chunk's phases in sequence
+])
+def test_attention_by_number_of_chunks(B, oracle, batch, M, d, keys, dtype, rtol):
+    """Every chunk count at which the loop over the keys changes form (no step, one step, the two-step loop and what it leaves over), whole
+    and ragged last chunks; tolerances as in test_attention_matches_oracle.  The values of the last key are large, so that a key
+    dropped or counted twice shows; a negative scale takes the same path on negated queries."""
+    for N in keys:
+        q = I.make_tensor(dtype, "u", 31 + N, (batch, M, d))
+        k = I.make_tensor(dtype, "u", 32 + N, (batch, N, d))
+        values = I.uniform_pm1(33 + N, batch * N * d).reshape(batch, N, d)
+        values[:, -1] *= 16.0
+        v = _bits(values, dtype)
+        for scale in (0.7, -0.7):
+            _say(f"attention {dtype} {batch}x{M}x{N}x{d} scale {scale}")
+            ref, T = oracle.attention(dtype, q, k, v, scale)
+            got = _attention(B, dtype, "f32", q, k, v, scale)
+            ratio = np.abs(got - ref) / (rtol * T + 1e-5)
+            assert np.all(ratio <= 1.0), f"{N} keys, scale {scale}: max err/tol {np.max(ratio):.3g}"
+
+
+def test_attention_of_keys_beyond_the_memory_side_cache(B, oracle):
+    """More than 256 MB of keys and values with one tile of queries per head: the loop's copies are non-temporal.  Keys and values repeat
+    every eight heads (the queries do not), two heads of every eight are compared."""
+    heads, N, d = 2056, 520, 64
+    q = I.make_tensor("f16", "u", 71, (heads, 2, d))
+    k, v = (I.make_tensor("f16", "u", 72 + i, (8, N, d)) for i in range(2))
+    got = _attention(B, "f16", "f32", q, np.tile(k, (heads // 8, 1, 1)), np.tile(v, (heads // 8, 1, 1)), 0.5)
+    pick = np.flatnonzero(np.arange(heads) % 8 % 5 == 1)
+    ref, T = oracle.attention("f16", q[pick], k[pick % 8], v[pick % 8], 0.5)
+    assert np.all(np.abs(got[pick] - ref) <= 2e-3 * T + 1e-5)
 
 
 def test_attention_argument_checks(B):
