@@ -59,6 +59,12 @@ TILES = [
     # two reduction groups over 64-byte stages measured slower)
     (256, 96, 4, 1, 128, 3, 1, 4),
     (128, 192, 2, 2, 128, 3, 1, 4),
+    # one 96-column block row per wave: outputs whose extents are multiples of 96 or 192 rather than 128 or 256 (network widths of 768, 1152, 1536,
+    # 2304 ...), which 128-wide tiles cut into a number that leaves CUs idle (the rule in pick() finds them by fill and padding).  us, before -> now:
+    # 1536x1536x1024 fp16 9.2 -> 8.0 (144 tiles -> 256), 1152x1152x4096 A^T 32.3 -> 23.6, 1024x2304x768 8.3 -> 7.1, 700x1700x1024 7.85 -> 7.1;
+    # nine waves of 32x32 are 5 - 10 % slower, and so are 96x128 tiles of six waves
+    (96, 96, 3, 1, 128, 4, 1, 4),
+    (128, 96, 4, 1, 128, 3, 1, 4),
 ]
 PAIRS = [("DT_F16", "DT_F32", "f16_f32"), ("DT_F16", "DT_F16", "f16_f16"), ("DT_BF16", "DT_F32", "bf16_f32"),
          ("DT_BF16", "DT_BF16", "bf16_bf16"), ("DT_I8", "DT_I32", "i8_i32"), ("DT_I8", "DT_I8", "i8_i8")]
@@ -68,7 +74,7 @@ CONVX_TILES = [(256, 128, 4, 2, 128, 3, 1), (128, 128, 2, 2, 128, 3, 1), (128, 6
                (64, 64, 2, 2, 128, 3, 2), (128, 32, 4, 1, 128, 3, 1)]
 
 # A transposed A (stored [k][x]: weight gradients, dW = X^T dY): the tiles the scoring rule reaches
-AM_TILES = [(256, 256, 2, 4, 64, 3, 1), (256, 128, 4, 2, 128, 3, 1, 4), (128, 192, 2, 2, 128, 3, 1, 4), (128, 128, 2, 2, 128, 3, 1, 4),
+AM_TILES = [(96, 96, 3, 1, 128, 4, 1, 4), (128, 96, 4, 1, 128, 3, 1, 4), (256, 256, 2, 4, 64, 3, 1), (256, 128, 4, 2, 128, 3, 1, 4), (128, 192, 2, 2, 128, 3, 1, 4), (128, 128, 2, 2, 128, 3, 1, 4),
             (128, 128, 2, 2, 128, 3, 1), (128, 64, 2, 2, 128, 3, 1), (64, 64, 2, 2, 128, 3, 1), (64, 64, 2, 2, 128, 4, 1),
             (64, 64, 2, 2, 128, 3, 2), (64, 32, 2, 1, 128, 4, 1)]
 AM_MODES = [("am_bk", "A_MMAJOR", "B_KMAJOR"), ("am_bn", "A_MMAJOR", "B_NMAJOR")]

@@ -335,6 +335,11 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
             if (tiles > kCUs || nslab < (staged ? 2 : 4) * v->kw || v->bm * v->bn > 64 * 64) continue;
             depth += 0.05;
         }
+        // 96-row tiles for one round of workgroups only: their ring leaves room for one workgroup per CU, and what they save in padding short
+        // reductions of many rounds do not gain (237 x 272x384x96 fp16 41.9 us in 128x128 tiles, 45.7 in these; 160 x 288x768x128 int8 47.4 and 52.3)
+        if (v->bm == 96 && tiles > kCUs) continue;
+        // (nor do the 128x96 ones pay for short convolutions of many rounds: 12x36x42, 16 -> 288 channels in each of 8 groups, 3x3 stride 2 16.3 and 17.8)
+        if (v->bm == 128 && v->bn == 96 && amode == A_CONV && tiles > kCUs && nslab < 8) continue;
         // copy waves pay off once a stage is worth the extra waves: measured -8 .. -17 % on 128x128 and larger
         // tiles of mid-size GEMMs, a loss on the narrow ones
         // (and -13 % on a 64x64-tile convolution with 18 stages once the stages are 256 bytes)
