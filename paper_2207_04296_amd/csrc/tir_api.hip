@@ -281,9 +281,11 @@ static uint64_t hash_fields(const int64_t* f, int n) {
 // search over tilings (sec. 4.4): every listed tile is scored by
 //   padding efficiency  x  how evenly its workgroups fill the 256 CUs  x  bytes-per-flop factor,
 // where the last term favours tiles that need fewer global->LDS bytes per MFMA (bm*bn/(bm+bn),
-// saturating at the 256x256 tile).  Among equal tiles the ring depth is chosen by occupancy:
-// deep rings when one workgroup per CU must hide the global latency alone, shallow ones when
-// several workgroups share a CU (their LDS must fit side by side) or the reduction is short.
+// saturating at the 256x256 tile), times a term for how the copies of such a workgroup are hidden (`depth` below: waves, ring, rounds).
+//
+// The constants are fitted to the time of every variant on 491 calls of more than 0.12 GFLOP (GEMM, batched, convolutions, transposed ones by phase;
+// the extents of image and language networks, a quarter of the GEMMs odd): a pick takes 1.017 of the fastest variant's time in the geometric mean, 1.043 with the
+// constants before.  Each constant's comment gives calls that it moves, in us with the choice before and now.
 //
 // A reduction much longer than the tile grid is wide (few small tiles, many stages) is split over several
 // workgroups per tile, as many as fill the CUs once while each keeps at least eight stages.
@@ -322,34 +324,53 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
         const double fill = tiles / (rounds * kCUs);
         double intensity = (double)v->bm * v->bn / (double)(v->bm + v->bn) / 128.0;
         if (intensity > 1.0) intensity = 1.0;
-        double score = eff * fill * (0.25 + 0.75 * intensity);
-        // ring depth: stages beyond the number of K-slabs are useless; with more than one
-        // workgroup per CU prefer rings that let two of them be resident (LDS <= 80 KB)
+        // (the few-channel kernel's two widths by constants of their own: 25x133x120x1 -> 80, 5x5 fp16 33.9 us in 32 columns, 37.6 in 64)
+        double score = eff * fill * (amode == A_CONV_ROWS ? 0.25 + 0.75 * intensity : 0.2 + 0.8 * intensity);
         const int64_t nslab = (K * es + v->rowb - 1) >> __builtin_ctz((unsigned)v->rowb);       // (64, 128 or 256 bytes)
         const int lds = (v->bm + v->bn) * v->rowb * v->nstage * v->kw;
         double depth = 1.0;
+        const bool one_round = tiles <= kCUs, small = v->bm * v->bn <= 64 * 64;
         if (v->kw > 1) {
-            // reduction groups pay for the exchange of partial sums: only for small tiles in a single
-            // round of workgroups (nothing else on the CU hides the copy latency) facing a long reduction.  Operands staged
-            // through registers have less in flight and gain earlier (500x501x503 fp16: 6.9 us, 5.6 with four groups).
-            if (tiles > kCUs || nslab < (staged ? 2 : 4) * v->kw || v->bm * v->bn > 64 * 64) continue;
-            depth += 0.05;
+            // Reduction groups pay for the exchange of partial sums.  Small tiles: in a single round of workgroups (nothing else on the CU hides the
+            // copy latency), from two stages per group on (3x3 over 32 channels, 245 tiles of 64x32 5.3 -> 4.8).  Operands staged through
+            // registers have less in flight (500x501x503 fp16: 6.9, 5.6 with four groups).
+            // Convolutions: larger tiles as well, because the waves share the arithmetic of the copies' addresses, and a long reduction pays for it in any number of
+            // rounds (18x88x13, 176 -> 192 channels, 5x5 stride 2 bf16 38.9 -> 24.0; 17x36x39, 864 -> 64 in two groups fp16 73 -> 43.5).
+            if (one_round ? nslab < (small ? 2 * v->kw : 16) || (!small && amode != A_CONV) : amode != A_CONV || nslab < 40 || v->bm < 128) continue;
+            depth += !one_round ? 0.08 : !small ? 0.05 : amode == A_CONV ? 0.02 : 0.01;
         }
         // 96-row tiles for one round of workgroups only: their ring leaves room for one workgroup per CU, and what they save in padding short
-        // reductions of many rounds do not gain (237 x 272x384x96 fp16 41.9 us in 128x128 tiles, 45.7 in these; 160 x 288x768x128 int8 47.4 and 52.3)
-        if (v->bm == 96 && tiles > kCUs) continue;
+        // reductions of many rounds do not gain (237 x 272x384x96 fp16 41.9 in 128x128 tiles, 45.7 in these; 160 x 288x768x128 int8 47.4 and 52.3)
+        if (v->bm == 96 && !one_round) continue;
         // (nor do the 128x96 ones pay for short convolutions of many rounds: 12x36x42, 16 -> 288 channels in each of 8 groups, 3x3 stride 2 16.3 and 17.8)
-        if (v->bm == 128 && v->bn == 96 && amode == A_CONV && tiles > kCUs && nslab < 8) continue;
-        // copy waves pay off once a stage is worth the extra waves: measured -8 .. -17 % on 128x128 and larger
-        // tiles of mid-size GEMMs, a loss on the narrow ones
-        // (and -13 % on a 64x64-tile convolution with 18 stages once the stages are 256 bytes)
-        if (v->cw) depth += ((v->bm * v->bn >= 128 * 128 && nslab >= 8) ? 0.04 : (v->rowb == 256 && tiles <= kCUs && nslab >= 8) ? 0.07 : -0.04);
-        else if (v->rowb == 256) depth -= 0.04;
-        if (nslab < v->nstage) depth -= 0.02 * (v->nstage - (int)nslab);
-        if (tiles > kCUs && lds > 80 * 1024) depth -= 0.03;
-        else if (tiles <= kCUs) depth += 0.01 * v->nstage;
-        else depth += 0.005 * v->nstage;
-        score *= depth * (1.0 - 0.03 * (ks - 1));       // the partial sums' round trip
+        if (v->bm == 128 && v->bn == 96 && amode == A_CONV && !one_round && nslab < 8) continue;
+        // Copy waves take the copies' issue off the multiplying ones.  Tiles of 128x128 and more behind four waves gain from four stages on (1664x1888x256 bf16
+        // 6.6 -> 6.0), behind eight from eight; 64x64 and more from three and four (transposed 16x14x14, 256 -> 128 by phase 11.1 -> 9.7; 43x37, 64 -> 304
+        // channels 5x5 15.2 -> 12.1; 3776x512x896 fp16 8.1 -> 7.1; long GEMMs do not: 3952x448x1728 fp16 11.6 without, 12.4 with), the small ones, and those
+        // with 256-byte stages, in one round only.
+        if (v->cw) {
+            const int area = v->bm * v->bn;
+            const bool big = area >= 128 * 128, eight = v->wm * v->wn == 8;
+            const int64_t from = v->rowb == 256 ? 3 : big ? (eight ? 8 : 4) : small ? 4 : 3;
+            const bool pays = nslab >= from && (one_round || !(small || v->rowb == 256));
+            depth += !pays ? -0.04 : v->rowb == 256 ? 0.07 : small ? 0.06 : big ? (eight || !one_round ? 0.04 : 0.1) : amode != A_CONV && v->bm != 96 && nslab > 20 ? 0.0 : 0.05;
+        } else if (v->rowb == 256) depth -= 0.04;
+        if (!one_round) {
+            // 64x32 tiles have two waves; many rounds of them are slower than of wider tiles (38110 pixels, 48 channels -> 48, 3x3, 1192 tiles 12.4 -> 8.6; but
+            // 15x17x18, 16 -> 16 channels in 8 groups, 3x3, 576 tiles 4.7, and 5.3 in 256x32 tiles)
+            if (v->bm == 64 && v->bn == 32 && tiles > 4 * kCUs) depth -= 0.12;
+            // Many rounds of one stage or two: nothing but latency and stores, which five 64x64 workgroups per CU cover for each other (209 x 320x80x64 fp16
+            // 10.1 -> 7.9, 244 x 118x285x32 bf16 13.5 -> 11.2, 58x81 1x1 16 -> 128 channels 13.9 -> 10.9)
+            const int64_t kbytes = K * es;
+            if (tiles > 5 * kCUs && small && v->bn == 64 && v->nstage == 2 && v->kw == 1 && !staged) depth += kbytes <= 128 ? 0.4 : kbytes <= 256 ? 0.05 : 0.0;
+        }
+        // Ring depth: stages beyond the number of K-slabs are useless; with more than one
+        // workgroup per CU prefer rings that let two of them be resident (LDS <= 80 KB)
+        if (nslab < v->nstage) depth -= 0.04 * (v->nstage - (int)nslab);
+        if (!one_round && lds > 80 * 1024) depth -= 0.04;
+        else depth += (one_round ? 0.015 : 0.0025) * v->nstage;
+        // the partial sums' round trip (25x14x43, 96 -> 32 channels 5x5 fp16 in two slices 13.6, in two groups of one workgroup 11.0)
+        score *= depth * (ks > 1 ? 0.95 - 0.03 * (ks - 1) : 1.0);
         if (score > best_score) { best_score = score; best = Choice{v, ks}; }
     }
     return best;
@@ -584,7 +605,9 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     else if (!g_force_name[0] && !g_force_bm && !g_force_ksplit) ch = tuned_lookup(plan->key);
     if (ch.v && ch.v->amode == A_CONV_PATCH && !patch_ok) ch = kNoChoice;
     if (!ch.v) {
-        const bool use_patch = patch_ok && !g_force_ksplit && (!g_force_name[0] || strstr(g_force_name, "patch"));
+        // A filter of one tap reads no pixel twice, and the patch kernel would copy the pixels again for every 64 output channels: 1x1, 64 -> 256 channels,
+        // 20x56x56 fp16 18.1 us, 8.9 in 256x256 tiles; 64 -> 64, 8x56x56 4.6 and 4.0
+        const bool use_patch = patch_ok && !g_force_ksplit && (g_force_name[0] ? strstr(g_force_name, "patch") != nullptr : R * S > 1);
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);
         else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
     }
