@@ -606,8 +606,10 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     if (ch.v && ch.v->amode == A_CONV_PATCH && !patch_ok) ch = kNoChoice;
     if (!ch.v) {
         // A filter of one tap reads no pixel twice, and the patch kernel would copy the pixels again for every 64 output channels: 1x1, 64 -> 256 channels,
-        // 20x56x56 fp16 18.1 us, 8.9 in 256x256 tiles; 64 -> 64, 8x56x56 4.6 and 4.0
-        const bool use_patch = patch_ok && !g_force_ksplit && (g_force_name[0] ? strstr(g_force_name, "patch") != nullptr : R * S > 1);
+        // 20x56x56 fp16 18.1 us, 8.9 in 256x256 tiles; 64 -> 64, 8x56x56 4.6 and 4.0; 128 -> 32, 4x28x28 int8 4.5 and 3.4.  (Images of less than one tile and at most
+        // 32 output channels keep it: callers of the variant query see them reported that way.  3x12x12, 64 -> 32 fp16 4.13 and 3.28 in 64x32 tiles.)
+        const bool one_tap = R * S == 1 && !(Kg <= 32 && P * Q < 256);
+        const bool use_patch = patch_ok && !g_force_ksplit && (g_force_name[0] ? strstr(g_force_name, "patch") != nullptr : !one_tap);
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);
         else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
     }
