@@ -87,7 +87,7 @@ RAGGED_MODES = [("convr", "A_CONV_RAGGED", "B_KMAJOR")]
 
 # operands of any alignment, staged through registers (two stages ahead).  A name ending in _generic says that the variant takes operands
 # of any alignment: these and the few-channel kernels by vectors, t64x64w2x2s2_generic and t64x64w2x2s2_conv_generic element by element.
-U_TILES = [(128, 128, 2, 2, 128, 2, 1), (128, 64, 4, 2, 128, 2, 1), (64, 64, 2, 2, 128, 2, 1), (64, 64, 2, 2, 128, 2, 2), (64, 32, 2, 1, 128, 2, 1), (64, 32, 2, 1, 128, 2, 4)]
+U_TILES = [(128, 128, 2, 2, 128, 2, 1), (128, 128, 2, 4, 128, 2, 1), (128, 64, 4, 2, 128, 2, 1), (64, 64, 2, 2, 128, 2, 1), (64, 64, 2, 2, 128, 2, 2), (64, 32, 2, 1, 128, 2, 1), (64, 32, 2, 1, 128, 2, 4)]
 U_MODES = [("uk_uk_generic", "A_UK", "B_UK"), ("uk_un_generic", "A_UK", "B_UN"), ("um_uk_generic", "A_UM", "B_UK"), ("um_un_generic", "A_UM", "B_UN")]
 
 

@@ -339,6 +339,10 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
             if (one_round ? nslab < (small ? 2 * v->kw : 16) || (!small && amode != A_CONV) : amode != A_CONV || nslab < 40 || v->bm < 128) continue;
             depth += !one_round ? 0.08 : !small ? 0.05 : amode == A_CONV ? 0.02 : 0.01;
         }
+        // Operands staged through registers, 128x128 tiles: eight waves instead of four hide each other's loads and LDS writes over a long reduction (1500x1501x2001
+        // fp16 34.4 -> 27.8, 2999x1001x1999 A^T B^T 36.8 -> 28.7, 3001x2005x777 24.5 -> 22.6); a short one is faster with the fragments four waves reuse
+        // (2049x3333x333 bf16 17.2 and 18.8, 4001x4001x501 int8 24.9 and 29.3).
+        if (staged && v->bm == 128 && v->bn == 128) depth += (v->wm * v->wn == 8) == (nslab >= 10) ? 0.02 : -0.02;
         // 96-row tiles for one round of workgroups only: their ring leaves room for one workgroup per CU, and what they save in padding short
         // reductions of many rounds do not gain (237 x 272x384x96 fp16 41.9 in 128x128 tiles, 45.7 in these; 160 x 288x768x128 int8 47.4 and 52.3)
         if (v->bm == 96 && !one_round) continue;
