@@ -146,15 +146,15 @@ __global__ void __launch_bounds__(256) depthwise_kernel(const Params p) {
     }
 }
 
-// 3x3 filter, undilated along the width, stride 1 or 2 there (SW): a thread owns four horizontally adjacent output
-// pixels x one 16-byte channel vector.  Their taps touch 3 rows x NC = 3*SW + 3 consecutive input columns, loaded
-// once (18 vectors for 4 pixels at stride 1 instead of 36) and all requested before the first multiply; row and
+// 3x3 filter, undilated along the width, stride 1 or 2 there (SW): a thread owns NP (four or eight) horizontally adjacent output
+// pixels x one 16-byte channel vector.  Their taps touch 3 rows x NC = (NP - 1)*SW + 3 consecutive input columns, loaded
+// once (18 vectors for 4 pixels at stride 1 instead of 36, 30 for 8) and all requested before the first multiply; row and
 // column validity are decided once per row / column, so a tap's address costs three vector instructions instead
 // of a dozen.  The one-pixel kernel above spent twice as many instructions on addresses as on multiply-adds.
 // STREAM (the output policy) is a template parameter, not a branch: a branch around each store splits the pixel loop
 // into blocks, and the compiler then waits for the previous pixel's stores before the next pixel's arithmetic
 // (measured: 6.9 -> 8.8 us).
-template <int DT, int OUT, int SW, bool STREAM>
+template <int DT, int OUT, int SW, int NP, bool STREAM>
 __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params p) {
     typedef typename DwIn<DT>::acc_e acc_e;
     typedef OutTraits<OUT> OT;
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params 
     constexpr int ES = elem_size(DT), VEC = 16 / ES;
     constexpr int CV = kDwChannels / VEC;            // channel vectors per workgroup
     constexpr int PP = 256 / CV;                     // pixel groups per workgroup
-    constexpr int NP = kDwBlockPix, NC = (NP - 1) * SW + 3;
+    constexpr int NC = (NP - 1) * SW + 3;
 
     // every argument the kernel reads, fetched in one batch
     asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.C), "s"(p.M), "s"(p.bias), "s"(p.relu), "s"(p.scale), "s"(p.batch_imgs), "s"(p.H), "s"(p.W), "s"(p.Cin),

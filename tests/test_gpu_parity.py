@@ -1264,6 +1264,26 @@ def test_depthwise_convolution(B, oracle, case):
         PT.assert_close(got, ref, S, wl.name)
 
 
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("f16", "f32"), ("bf16", "f32"), ("i8", "i8"), ("i8", "i32")])
+@pytest.mark.parametrize("w,c,stride_h,dil_h", [(9, 8, 1, 1), (16, 24, 1, 2), (12, 72, 2, 1)])
+def test_depthwise_convolution_of_eight_pixels_per_thread(B, oracle, dtype, out, w, c, stride_h, dil_h):
+    """352 to 512 workgroups of eight pixels per thread (that of a launch of one round): rows of one group and a pixel, of two whole groups and of one and a half,
+    part of a channel block and two blocks."""
+    vec = 16 if dtype == "i8" else 8
+    c = c * vec // 8
+    blocks, groups, threads = (c + 63) // 64, (w + 7) // 8, 256 * vec // 64
+    n = 3
+    rows = (400 * threads // (blocks * groups * n)) * stride_h
+    p = (rows - 1) // stride_h + 1
+    assert 352 <= -(-n * p * groups // threads) * blocks <= 512
+    wl = I.Workload(f"dw8_{dtype}_{out}_w{w}c{c}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 9970 + c, n=n, h=rows, w=w, c=c, k=c, r=3, s=3,
+                    stride=(stride_h, 1), pad=(dil_h, 1), dil=(dil_h, 1), groups=c, ep_bias=True, ep_relu=out != "f32", ep_scale=1.0 / 300.0 if out == "i8" else 0.0)
+    name = PT.variant_name(B, wl)
+    _say(f"{wl.name} h={rows} -> {name}")
+    assert "depthwise" in name, name
+    PT.check_workload(wl, oracle)
+
+
 # ------------------------------------------------------------------------------ more batches than one grid dimension holds
 @pytest.mark.parametrize("K,bias", [(16, False), (24, True), (5, True)])
 def test_batch_count_beyond_one_launch(B, oracle, K, bias):
