@@ -35,6 +35,14 @@ template <int DT, int OUT, int DH> static hipError_t launch_attn(const AttnParam
     if constexpr (DH == 64) {
         if (tiles >= 512 && tiles <= 1024 && p.N <= 400) return launch_attn_as<DT, OUT, DH, 4, 1, 64, ATTN_SEQUENTIAL>(p, stream);
     }
+    // Tiles of 256 queries at d = 128: one workgroup of eight waves in the place of two of four, which copies keys and values once instead of twice (and the long launches
+    // are bound by power).  Where they pad no more rows, and where the CUs of the last round would hold two of the smaller workgroups anyway.  128 and 256 queries, us:
+    // 16 x 4096 x 4096 145.4 / 140.1, 75 x 512 x 2000 57.9 / 52.5, 24 x 1536 x 1536 43.5 / 40.1, 130 x 256 x 1000 30.8 / 29.9, 100 x 900 x 700 47.5 / 46.7;
+    // 64 x 1024 x 512 20.9 / 20.9, x 256 12.4 / 13.2; one small workgroup per CU in the last round: 16 x 2048 x 4096 77.5 / 95.7, 40 x 2048 x 300 20.5 / 26.5.
+    // At d = 64 32 x 4096 x 4096 177 / 187.
+    if constexpr (DH == 128) {
+        if (p.N >= 512 && (p.M + 127) / 128 % 2 == 0 && (tiles - 1) % 512 >= 256) return launch_attn_as<DT, OUT, DH, 8, 1, 64, ATTN_PIPED>(p, stream);
+    }
     // Keys and values that nobody reads twice and that do not fit the 256 MB memory-side cache go past it: 3000 x 192 at d = 128 92.9 us, 81.6 with non-temporal
     // copies; within it they cost as much (800 x 320 34.3 / 40.5).
     if (p.M <= 128 && (long long)p.batch * p.N * DH * 4 > (256ll << 20)) return launch_attn_as<DT, OUT, DH, 4, 1, 64, ATTN_PIPED_STREAM>(p, stream);

@@ -934,6 +934,7 @@ def test_attention_rounds_all_but_the_largest_probability(B, oracle, shape, dtyp
     (3, 33, 128, (1, 32, 33, 64, 65, 96, 97, 129, 160, 161, 193, 256, 321, 383)),
     (2, 65, 64, (257, 320, 321, 449, 512, 513, 577)),                                         # four key groups: one to three chunks each
     (2, 65, 128, (384, 385, 417, 513)),
+    (65, 400, 128, (512, 513, 577, 641)),                                                     # tiles of 256 queries, the second one of a head not whole
     (600, 3, 64, (64, 65, 97, 128, 192, 193, 256, 400)),                                      # two to four workgroups per CU: a chunk's phases in sequence
 ])
 def test_attention_by_number_of_chunks(B, oracle, batch, M, d, keys, dtype, rtol):
