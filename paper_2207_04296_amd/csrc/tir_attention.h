@@ -1,4 +1,4 @@
-// One workgroup per (batch, tile of 128 or 64 queries): S = scale * Q K^T, row softmax, O = P V, in one
+// One workgroup per (batch, tile of 256, 128 or 64 queries): S = scale * Q K^T, row softmax, O = P V, in one
 // kernel.  Both contractions are tensorized blocks (Eq. 1 of the TensorIR paper, mapped onto the
 // 32x32x16 MFMA) that share the workgroup's tile instead of meeting in memory: the probabilities never
 // leave the registers (sec. 2 / 3.2: blocks isolate the two sub-problems, which does not prevent
@@ -296,8 +296,10 @@ __global__ void __launch_bounds__(QW * KG * 64, 2) attention_kernel(const AttnPa
             for (int t = 0; t < LAK; ++t) kf[t] = k_frag(st ^ 1, t / JB, t % JB);
         }
         // At d = 128 a wave between its MFMAs goes before one that rescales or waits at a barrier (16 x 4096 x 4096 x 128 bf16 150.3 -> 147.3 us; with eight waves in a
-        // workgroup 144.9 -> 138.8); at d = 64, where the vector work is the longer half, it costs 8 %.
-        if constexpr (DH == 128) __builtin_amdgcn_s_setprio(1);
+        // workgroup 144.9 -> 138.8); at d = 64, where the vector work is the longer half, it costs 8 %.  There a wave of the sequential form goes first while it
+        // takes exponentials, and the SIMD's other three have their MFMAs under them (32 x 4096 x 4096 x 64 bf16 160.7 -> 158.5 us, eight waves in a workgroup 158.3 -> 155.5,
+        // 26 x 3841 x 2500 89.5 -> 86.7; first from the row maxima on: 4 % slower again).
+        if constexpr (DH == 128 || FORM == ATTN_SEQUENTIAL) __builtin_amdgcn_s_setprio(1);
         TIR_FENCE();
 #pragma unroll
         for (int t = 0; t < NQK; ++t) {
@@ -332,6 +334,7 @@ __global__ void __launch_bounds__(QW * KG * 64, 2) attention_kernel(const AttnPa
         }
         l_run += lsum[0] + lsum[1];
         if constexpr (!LAST) mask_chunk(i + 1, nxt);
+        if constexpr (FORM == ATTN_SEQUENTIAL) __builtin_amdgcn_s_setprio(0);
         // O^T += V^T P^T
         float mx[4];
 #pragma unroll
@@ -350,7 +353,7 @@ __global__ void __launch_bounds__(QW * KG * 64, 2) attention_kernel(const AttnPa
             }
             TIR_FENCE();
         }
-        if constexpr (DH == 128) __builtin_amdgcn_s_setprio(0);
+        if constexpr (DH == 128 && FORM != ATTN_SEQUENTIAL) __builtin_amdgcn_s_setprio(0);
         if constexpr (!LAST) {
             raise_reference(chunk_reference(__builtin_fmaxf(__builtin_fmaxf(mx[0], mx[1]), __builtin_fmaxf(mx[2], mx[3]))));
         }

@@ -29,17 +29,25 @@ template <int DT, int OUT, int DH> static hipError_t launch_attn(const AttnParam
     //   d = 64:  100 x 77 4.74 / 4.38, 100 x 160 5.54 / 5.21, 384 x 77 6.04 / 5.72, 800 x 77 9.33 / 8.17, 2000 x 150 28.3 / 26.5
     //   d = 128: 100 x 77 6.26 / 5.76, 320 x 160 11.7 / 10.8, 512 x 160 15.4 / 15.5, 1024 x 96 22.8 / 20.4
     if ((p.N - 1) % 64 < 32 && p.N <= 160) return launch_attn_as<DT, OUT, DH, 4, 1, 32, ATTN_PIPED>(p, stream);
-    // Two to four workgroups per CU at d = 64 and few keys: four of the sequential form fit a CU, three of the other, and what does not fit is a
-    // second round.  Pipelined and sequential, us: 512 x 320 14.3 / 12.6, 640 x 320 17.0 / 16.1, 800 x 192 16.6 / 14.2, 1024 x 64 8.8 / 7.0; beyond either
-    // end 400 x 320 10.4 / 11.8, 800 x 600 33.7 / 35.1, 1300 x 128 16.6 / 16.9.
+    // More than two workgroups per CU at d = 64: four of the sequential form fit a CU, three of the other.  Pipelined and sequential, us: 20 x 4096 x 4096
+    // 112 / 108, 75 x 1024 x 600 22.2 / 21.5, 750 x 512 x 1000 131 / 120, 60 x 4096 x 1000 79.9 / 77.3, 600 x 512 x 128 22.1 / 20.3, 2000 x 197 x 197 52.5 / 49.0; at
+    // two per CU 16 x 4096 x 4096 81.0 / 82.5, and where long heads leave a sliver for a second round of four 203 x 738 x 1818 88.7 / 90.3, 99 x 1372 x 833 43.9 / 44.7
+    // (short ones 300 x 512 x 192 15.2 / 14.7, 150 x 1024 x 600 37.5 / 37.1).  Heads of one tile, where each workgroup reads its own keys: up to four per CU and few keys only
+    // (640 x 320 17.0 / 16.1, 800 x 192 16.6 / 14.2, 1024 x 64 8.8 / 7.0, 700 x 200 13.3 / 12.4; 600 x 600 23.2 / 24.8, 1100 x 64 9.5 / 10.4, 1500 x 256 27.3 / 29.2).
+    //
+    // Its tiles of 256 queries, eight waves that copy keys and values once instead of twice: where three or four of the smaller workgroups per CU would be one
+    // round, pad no more rows and the keys are not few.  Sequential with 128 and 256 queries, us: 32 x 4096 x 4096 158 / 152, 390 x 256 x 1000 39.1 / 37.7,
+    // 450 x 256 x 512 22.7 / 21.9, 512 x 256 x 320 16.9 / 15.8, 450 x 256 x 256 13.6 / 13.5; fewer keys 390 x 256 x 192 10.2 / 10.6, fewer tiles 24 x 4096 x 4096
+    // 116 / 126, more 750 x 512 x 1000 120 / 124, 40 x 4096 x 2000 99.6 / 110.
     if constexpr (DH == 64) {
-        if (tiles >= 512 && tiles <= 1024 && p.N <= 400) return launch_attn_as<DT, OUT, DH, 4, 1, 64, ATTN_SEQUENTIAL>(p, stream);
+        if (tiles > 768 && tiles <= 1024 && p.N >= 256 && (p.M + 127) / 128 % 2 == 0) return launch_attn_as<DT, OUT, DH, 8, 1, 64, ATTN_SEQUENTIAL>(p, stream);
+        const bool sliver = tiles > 1024 && tiles <= 1280 && p.N > 600;
+        if ((p.M > 128 && tiles > 512 && !sliver) || (tiles >= 512 && tiles <= 1024 && p.N <= 400)) return launch_attn_as<DT, OUT, DH, 4, 1, 64, ATTN_SEQUENTIAL>(p, stream);
     }
     // Tiles of 256 queries at d = 128: one workgroup of eight waves in the place of two of four, which copies keys and values once instead of twice (and the long launches
     // are bound by power).  Where they pad no more rows, and where the CUs of the last round would hold two of the smaller workgroups anyway.  128 and 256 queries, us:
     // 16 x 4096 x 4096 145.4 / 140.1, 75 x 512 x 2000 57.9 / 52.5, 24 x 1536 x 1536 43.5 / 40.1, 130 x 256 x 1000 30.8 / 29.9, 100 x 900 x 700 47.5 / 46.7;
     // 64 x 1024 x 512 20.9 / 20.9, x 256 12.4 / 13.2; one small workgroup per CU in the last round: 16 x 2048 x 4096 77.5 / 95.7, 40 x 2048 x 300 20.5 / 26.5.
-    // At d = 64 32 x 4096 x 4096 177 / 187.
     if constexpr (DH == 128) {
         if (p.N >= 512 && (p.M + 127) / 128 % 2 == 0 && (tiles - 1) % 512 >= 256) return launch_attn_as<DT, OUT, DH, 8, 1, 64, ATTN_PIPED>(p, stream);
     }

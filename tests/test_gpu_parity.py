@@ -936,6 +936,8 @@ def test_attention_rounds_all_but_the_largest_probability(B, oracle, shape, dtyp
     (2, 65, 128, (384, 385, 417, 513)),
     (65, 400, 128, (512, 513, 577, 641)),                                                     # tiles of 256 queries, the second one of a head not whole
     (600, 3, 64, (64, 65, 97, 128, 192, 193, 256, 400)),                                      # two to four workgroups per CU: a chunk's phases in sequence
+    (172, 260, 64, (401,)),                                                                   # ... more than 128 queries: of any number of keys
+    (385, 129, 64, (256, 257)),                                                               # ... in tiles of 256 queries, half empty
 ])
 def test_attention_by_number_of_chunks(B, oracle, batch, M, d, keys, dtype, rtol):
     """Every chunk count at which the loop over the keys changes form (no step, one step, the two-step loop and what it leaves over), whole
