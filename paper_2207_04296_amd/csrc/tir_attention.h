@@ -53,7 +53,7 @@ template <> struct PackP<DT_BF16> {
 // after between the former (a copy instruction holds its wave for longer than an MFMA lasts; all in front of a chunk cost 10 %).  Measured
 // here: 32 MFMAs of 32 cycles with 128 multiply-adds and 32 exponentials between them take one wave 1 096 cycles, the MFMAs alone 1 038, the
 // vector work alone 840.  With each wave's phases in sequence, left to a second wave to cover, 16 x 4096 x 4096 x 128 bf16 took 143.8 us, now
-// 133.8; 160 x 128 x 2000 x 128 50.5 and 39.9, 52 x 376 x 376 x 64 9.3 and 7.7.  What bounds the long case is power: the same launch on constant data takes
+// 133.8 (128.3 with priorities and tiles of 256 queries); 160 x 128 x 2000 x 128 50.5 and 39.9, 52 x 376 x 376 x 64 9.3 and 7.7.  What bounds the long case is power: the same launch on constant data takes
 // 111 us instead of 155 (one warm card), with 14 % between the two forms of the loop.
 //
 // QW waves of 32 queries times KG key groups: group k takes the chunks c with c % KG == k through a ring of its own and the
