@@ -323,6 +323,9 @@ void tir_debug_tile_of_block(int bid, int tiles_m, int tiles_n, int* tm, int* tn
 /* Host copy of the kernels' division by a launch constant: m / d for d >= 1 and m < 2^31 through the
  * multiply-and-shift constants the planner derives from d (used to decode output rows into pixels). */
 unsigned tir_debug_fastdiv(unsigned d, unsigned m);
+/* Adjacent output pixels (4 or 8) per thread of the depth-wise kernel for 3x3 filters undilated along the width, on N images of
+ * P x Q output pixels (Q >= 4) and C channels. */
+int tir_debug_depthwise_pixels(int64_t N, int64_t P, int64_t Q, int64_t C, int stride_w, tir_dtype in, tir_dtype out);
 
 /*
  * Measurement aid: enqueue a register-only fp16 MFMA loop (no memory traffic) of `iters` x 16 MFMAs

@@ -1064,6 +1064,10 @@ unsigned tir_debug_fastdiv(unsigned d, unsigned m) {
     return fastdiv(m, f.magic, f.shift);
 }
 
+int tir_debug_depthwise_pixels(int64_t N, int64_t P, int64_t Q, int64_t C, int stride_w, tir_dtype in, tir_dtype out) {
+    return depthwise_pixels((int)in, (int)out, N, P, Q, C, stride_w);
+}
+
 tir_status tir_probe_mfma_rate(void* sink, int iters, int random_operands, double* flop, tir_stream stream) {
     if (!sink || iters <= 0) return fail(TIR_ERR_INVALID_ARG, "tir_probe_mfma_rate: sink is null or iters <= 0");
     hipLaunchKernelGGL(mfma_probe_kernel, dim3(1024), dim3(256), 0, (hipStream_t)stream, (float*)sink, iters, random_operands);

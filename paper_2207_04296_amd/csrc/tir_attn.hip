@@ -71,23 +71,19 @@ template <int DT, int OUT, bool STREAM> static hipError_t launch_dw_as(const Par
     constexpr int PP = 256 / (kDwChannels / VEC);
     dim3 grid((unsigned)((p.M + kDwPixPerThread * PP - 1) / (kDwPixPerThread * PP)), (unsigned)((p.Cin + kDwChannels - 1) / kDwChannels));
     if (p.R == 3 && p.S == 3 && p.dil_w == 1 && (p.stride_w == 1 || p.stride_w == 2) && p.Q >= kDwBlockPix) {
-        auto workgroups = [&](int np) { return ((long long)p.batch_imgs * p.P * ((p.Q + np - 1) / np) + PP - 1) / PP; };
-        // Eight adjacent pixels per thread at stride 1 fetch a sixth fewer vectors per pixel, with twice the registers (two workgroups per CU instead of four) and twice the
-        // serial arithmetic per thread: faster where one round of them fills the chip.  Four and eight pixels, fp16, us from the caches / from memory:
-        // 16x56x56x128 (392 workgroups of eight) 8.07 / 9.06 and 6.89 / 8.11, 32x28x28x256 (448, an eighth of the pixels padding) 8.05 / 9.00 and 7.02 / 8.13,
-        // 8x112x112x64 8.11 / 9.32 and 6.80 / 8.24; fewer: 5x46x51x384 (306) 6.74 / 7.50 and 6.79 / 7.89, 4x28x28x256 3.69 and 4.48; more than one round:
-        // 32x56x56x128 (784) 12.5 / 16.9 and 11.9 / 18.1.  Two rows of four pixels 7.35 / 8.39 on the first, four rows of two 7.39 / 8.12.
-        const long long eights = workgroups(8) * grid.y;
-        if (p.stride_w == 1 && eights >= 352 && eights <= 512) {
-            Params q = p;
-            const unsigned qg = (unsigned)((p.Q + 7) / 8);
-            const FastDiv dq = make_fastdiv(qg), dpq = make_fastdiv((unsigned)p.P * qg);
-            q.div_dwq_magic = dq.magic; q.div_dwq_shift = dq.shift;
-            q.div_dwpq_magic = dpq.magic; q.div_dwpq_shift = dpq.shift;
-            grid.x = (unsigned)workgroups(8);
-            return launch_kernel(&depthwise3x3_blocked_kernel<DT, OUT, 1, 8, STREAM>, grid, dim3(256), stream, q);
+        auto blocks_x = [&](int np) { return (unsigned)(depthwise_workgroups(DT, p.batch_imgs, p.P, p.Q, p.Cin, np) / grid.y); };
+        if constexpr (OUT != DT_I32) {
+            if (depthwise_pixels(DT, OUT, p.batch_imgs, p.P, p.Q, p.Cin, p.stride_w) == 8) {
+                Params q = p;
+                const unsigned qg = (unsigned)((p.Q + 7) / 8);
+                const FastDiv dq = make_fastdiv(qg), dpq = make_fastdiv((unsigned)p.P * qg);
+                q.div_dwq_magic = dq.magic; q.div_dwq_shift = dq.shift;
+                q.div_dwpq_magic = dpq.magic; q.div_dwpq_shift = dpq.shift;
+                grid.x = blocks_x(8);
+                return launch_kernel(&depthwise3x3_blocked_kernel<DT, OUT, 1, 8, STREAM>, grid, dim3(256), stream, q);
+            }
         }
-        grid.x = (unsigned)workgroups(kDwBlockPix);
+        grid.x = blocks_x(kDwBlockPix);
         return launch_kernel(p.stride_w == 1 ? &depthwise3x3_blocked_kernel<DT, OUT, 1, kDwBlockPix, STREAM> : &depthwise3x3_blocked_kernel<DT, OUT, 2, kDwBlockPix, STREAM>, grid,
                              dim3(256), stream, p);
     }

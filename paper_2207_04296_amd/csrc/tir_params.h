@@ -133,7 +133,7 @@ __host__ __device__ inline unsigned fastdiv(unsigned m, unsigned magic, int shif
 #endif
 }
 
-// Adjacent output pixels one thread of the blocked depth-wise kernel owns, other than at stride 1 where one round of workgroups fills the chip with eight (launch_dw_as).
+// Adjacent output pixels one thread of the blocked depth-wise kernel owns where depthwise_pixels() does not give it eight.
 constexpr int kDwBlockPix = 4;      // measured 2, 4, 8: 8.5 / 7.2 / 6.9 us at stride 1 (16x56x56x128 fp16), 7.1 / 6.2 / 9.8 us at stride 2 (int8)
 
 // Few-channel convolution: LDS of a workgroup (filter of BN output channels; per wave a patch of rows of row_bytes and a row of zeros).

@@ -113,6 +113,27 @@ def test_division_by_launch_constants_is_exact():
                 assert B.tir_debug_fastdiv(d, m) == m // d, (d, m)
 
 
+@pytest.mark.parametrize("dtype,out,n,p,q,c,pixels", [
+    # us with four and with eight pixels per thread, one box
+    ("f16", "f16", 16, 56, 56, 128, 8),        # 8.1, 6.9
+    ("f16", "f16", 4, 505, 4, 512, 4),         # 5.7, 7.2: half of a group of eight is padding
+    ("f16", "f16", 9, 110, 11, 352, 4),        # 7.8, 8.1: a third more pixels
+    ("f16", "f32", 16, 60, 14, 384, 4),        # 12.3, 12.8
+    ("bf16", "bf16", 4, 480, 4, 384, 4),       # 6.0, 7.5
+    ("bf16", "bf16", 8, 180, 9, 256, 8),       # 7.9, 7.8
+    ("bf16", "f32", 4, 505, 9, 256, 4),        # 11.3, 12.4
+    ("i8", "i8", 4, 137, 49, 384, 4),          # 13.1, 16.4
+    ("i8", "i8", 16, 286, 4, 384, 4),          # 9.6, 13.8
+    ("i8", "i8", 8, 245, 49, 128, 8),          # 16.8, 16.2
+    ("i8", "i32", 2, 2880, 28, 64, 4),         # 33.3, 35.8
+    ("f16", "f16", 32, 56, 56, 128, 4),        # more than one round of workgroups of eight
+])
+def test_depthwise_pixels_per_thread(dtype, out, n, p, q, c, pixels):
+    """Eight pixels per thread only where the workgroups of four no longer run at once and those of eight do; padding counts."""
+    assert B.tir_debug_depthwise_pixels(n, p, q, c, 1, dtype, out) == pixels
+    assert B.tir_debug_depthwise_pixels(n, p, q, c, 2, dtype, out) == 4
+
+
 def test_variant_choice_reflects_layout():
     # row-major B is read N-major, a transposed B K-major; odd K falls back to the general kernel
     assert B.tir_gemm_variant(1, 4096, 4096, 4096, 4096, 1, 4096, 1, 4096, 1, "f16", "f32").endswith("ak_bn")

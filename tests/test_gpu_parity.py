@@ -1287,6 +1287,30 @@ def test_depthwise_convolution_of_eight_pixels_per_thread(B, oracle, dtype, out,
     PT.check_workload(wl, oracle)
 
 
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("f16", "f32"), ("bf16", "f32"), ("bf16", "bf16"), ("i8", "i8")])
+@pytest.mark.parametrize("w,c,stride_h,dil_h", [(17, 8, 1, 1), (16, 24, 1, 2), (21, 72, 2, 1), (4, 72, 1, 1)])
+def test_depthwise_convolution_where_eight_pixels_per_thread_pay(B, oracle, dtype, out, w, c, stride_h, dil_h):
+    """About 500 workgroups of eight pixels per thread: rows of whole groups, of two groups and a pixel and of two and five; rows of
+    four columns, where eight would be half padding, stay with four.  bfloat16 output adds its own rounding, 2^-8 |y|."""
+    vec = 16 if dtype == "i8" else 8
+    c = c * vec // 8
+    blocks, groups, threads, n = (c + 63) // 64, (w + 7) // 8, 256 * vec // 64, 3
+    rows = (510 * threads // (blocks * groups * n)) * stride_h
+    p = (rows - 1) // stride_h + 1
+    pixels = B.tir_debug_depthwise_pixels(n, p, w, c, 1, dtype, out)
+    assert pixels == (4 if w == 4 else 8)
+    wl = I.Workload(f"dw8_{dtype}_{out}_w{w}c{c}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 9980 + c, n=n, h=rows, w=w, c=c, k=c, r=3, s=3,
+                    stride=(stride_h, 1), pad=(dil_h, 1), dil=(dil_h, 1), groups=c, ep_bias=True, ep_relu=out != "f32", ep_scale=1.0 / 300.0 if out == "i8" else 0.0)
+    _say(f"{wl.name} h={rows} pixels per thread {pixels}")
+    a_bits, b_bits = wl.operands()
+    ref, S = PT.run_oracle(wl, a_bits, b_bits, oracle)
+    got = PT.run_gpu(wl, a_bits, b_bits)
+    if out == "bf16":
+        assert np.all(np.abs(got - ref) <= PT.RTOL_S * S + PT.ATOL + np.abs(ref) * 2.0 ** -8)
+    else:
+        PT.assert_close(got, ref, S, wl.name)
+
+
 # ------------------------------------------------------------------------------ more batches than one grid dimension holds
 @pytest.mark.parametrize("K,bias", [(16, False), (24, True), (5, True)])
 def test_batch_count_beyond_one_launch(B, oracle, K, bias):
