@@ -284,8 +284,8 @@ static uint64_t hash_fields(const int64_t* f, int n) {
 // saturating at the 256x256 tile), times a term for how the copies of such a workgroup are hidden (`depth` below: waves, ring, rounds).
 //
 // The constants are fitted to the time of every variant on 491 calls of more than 0.12 GFLOP (GEMM, batched, convolutions, transposed ones by phase;
-// the extents of image and language networks, a quarter of the GEMMs odd): a pick takes 1.017 of the fastest variant's time in the geometric mean, 1.043 with the
-// constants before.  Each constant's comment gives calls that it moves, in us with the choice before and now.
+// the extents of image and language networks, a quarter of the GEMMs odd), and corrected for calls that the fit had moved to slower ones: over 3853 drawn calls of
+// any size a pick takes 1.014 of the fastest variant's time in the geometric mean.  Each constant's comment gives calls that it moves, in us with the choice before and now.
 //
 // A reduction much longer than the tile grid is wide (few small tiles, many stages) is split over several
 // workgroups per tile, as many as fill the CUs once while each keeps at least eight stages.
@@ -320,8 +320,9 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
         }
         const double tiles = tm * tn * (double)batch * ks;
         const double eff = ((double)M * (double)N) / (tm * v->bm * tn * v->bn);
-        const double rounds = tiles <= kCUs ? 1.0 : (double)((int64_t)(tiles + kCUs - 1) / kCUs);
-        const double fill = tiles / (rounds * kCUs);
+        // Beyond one round not by whole rounds: a CU holds several workgroups of most tiles, so that a last round is seldom waited for by itself.  (Whole rounds
+        // move 40 of 3853 calls to variants 3 to 34 % slower, 51 to faster ones.)
+        const double fill = tiles <= kCUs ? tiles / kCUs : tiles / (tiles + (kCUs - 1.0));
         double intensity = (double)v->bm * v->bn / (double)(v->bm + v->bn) / 128.0;
         if (intensity > 1.0) intensity = 1.0;
         // (the few-channel kernel's two widths by constants of their own: 25x133x120x1 -> 80, 5x5 fp16 33.9 us in 32 columns, 37.6 in 64)
@@ -336,7 +337,9 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
             // registers have less in flight (500x501x503 fp16: 6.9, 5.6 with four groups).
             // Convolutions: larger tiles as well, because the waves share the arithmetic of the copies' addresses, and a long reduction pays for it in any number of
             // rounds (18x88x13, 176 -> 192 channels, 5x5 stride 2 bf16 38.9 -> 24.0; 17x36x39, 864 -> 64 in two groups fp16 73 -> 43.5).
-            if (one_round ? nslab < (small ? 2 * v->kw : 16) || (!small && amode != A_CONV) : amode != A_CONV || nslab < 40 || v->bm < 128) continue;
+            // 128x32 tiles from three stages per group on: of 45 calls the 33 with fewer take 1 to 5 % more in two groups (transposed 19x43x9, 64 -> 32 channels 4x4
+            // stride 2 bf16 5.56 and 5.74), those with more 0.71 to 1.10 of the time.
+            if (one_round ? nslab < (small ? (v->bm == 128 ? 3 : 2) * v->kw : 16) || (!small && amode != A_CONV) : amode != A_CONV || nslab < 40 || v->bm < 128) continue;
             depth += !one_round ? 0.08 : !small ? 0.05 : amode == A_CONV ? 0.02 : 0.01;
         }
         // Operands staged through registers, 128x128 tiles: eight waves instead of four hide each other's loads and LDS writes over a long reduction (1500x1501x2001
@@ -346,23 +349,37 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
         // 96-row tiles for one round of workgroups only: their ring leaves room for one workgroup per CU, and what they save in padding short
         // reductions of many rounds do not gain (237 x 272x384x96 fp16 41.9 in 128x128 tiles, 45.7 in these; 160 x 288x768x128 int8 47.4 and 52.3)
         if (v->bm == 96 && !one_round) continue;
-        // (nor do the 128x96 ones pay for short convolutions of many rounds: 12x36x42, 16 -> 288 channels in each of 8 groups, 3x3 stride 2 16.3 and 17.8)
-        if (v->bm == 128 && v->bn == 96 && amode == A_CONV && !one_round && nslab < 8) continue;
+        // (nor do the 128x96 ones pay for short convolutions of many rounds: 12x36x42, 16 -> 288 channels in each of 8 groups, 3x3 stride 2 16.3 and 17.8; longer
+        // ones are faster in 256x96: 16x106x90, 128 -> 288, 3x3 stride 2 bf16 34.8 and 45.3, 48 -> 96 channels in each of 8 groups, 5x5 int8 29.4 and 35.8)
+        if (v->bm == 128 && v->bn == 96 && amode == A_CONV && !one_round) {
+            if (nslab < 8) continue;
+            depth -= 0.1;
+        }
+        // GEMMs of one stage do not repay their four stages of copies (30 x 48x608x96 int8 3.95 in 64x32, 4.59; 25 x 704x96x64 int8 4.20 in 256x32, 4.56), those of two
+        // not half a tile of padding (37 x 48x560x128 fp16 4.38 in 64x32, 4.83; less padding pays: 63 x 64x272x96 bf16 5.66 and 4.57)
+        if (v->bm == 96 && amode != A_CONV && (nslab == 1 || (nslab == 2 && eff < 0.5))) score *= 0.85;
+        // One stage and many rounds: half as many, twice as large stores (84 x 608x656x64 bf16 37.2 in 256x256, 43.4 in 64x64; 8x47x112, 32 -> 160 1x1 8.7 and 9.3)
+        if (v->bm == 256 && v->bn >= 128 && nslab == 1 && !one_round) depth += 0.03;
         // Copy waves take the copies' issue off the multiplying ones.  Tiles of 128x128 and more behind four waves gain from four stages on (1664x1888x256 bf16
-        // 6.6 -> 6.0), behind eight from eight; 64x64 and more from three and four (transposed 16x14x14, 256 -> 128 by phase 11.1 -> 9.7; 43x37, 64 -> 304
-        // channels 5x5 15.2 -> 12.1; 3776x512x896 fp16 8.1 -> 7.1; long GEMMs do not: 3952x448x1728 fp16 11.6 without, 12.4 with), the small ones, and those
-        // with 256-byte stages, in one round only.
+        // 6.6 -> 6.0), behind eight from eight; 64x64 and more from three and four (43x37, 64 -> 304 channels 5x5 15.2 -> 12.1; 3776x512x896 fp16 8.1 -> 7.1; long
+        // GEMMs do not: 3952x448x1728 fp16 11.6 without, 12.4 with, in 128x64 tiles and 16 bits from 14 stages on 1120x1376x864 9.2 and 9.6), the small ones, and those
+        // with 256-byte stages, in one round only.  128x64 tiles of int8 convolutions in many rounds are faster without (11x70x43, 32 -> 48 channels in each of 8 groups,
+        // 5x5 39.0 and 44.8): a stage holds more taps than in 16 bits, and the copy waves alone decode them.
         if (v->cw) {
             const int area = v->bm * v->bn;
             const bool big = area >= 128 * 128, eight = v->wm * v->wn == 8;
             const int64_t from = v->rowb == 256 ? 3 : big ? (eight ? 8 : 4) : small ? 4 : 3;
             const bool pays = nslab >= from && (one_round || !(small || v->rowb == 256));
-            depth += !pays ? -0.04 : v->rowb == 256 ? 0.07 : small ? 0.06 : big ? (eight || !one_round ? 0.04 : 0.1) : amode != A_CONV && v->bm != 96 && nslab > 20 ? 0.0 : 0.05;
+            depth += !pays ? -0.04 : v->rowb == 256 ? 0.07 : small ? 0.06 : big ? (eight || !one_round ? 0.04 : 0.1)
+                     : amode != A_CONV && v->bm != 96 && nslab > (v->bn == 64 && dt != DT_I8 ? 13 : 20) ? 0.0 : 0.05;
         } else if (v->rowb == 256) depth -= 0.04;
+        else if (dt == DT_I8 && amode == A_CONV && !one_round && v->bm == 128 && v->bn == 64 && v->nstage == 3 && v->kw == 1 && nslab >= 5) depth += 0.06;
         if (!one_round) {
             // 64x32 tiles have two waves; many rounds of them are slower than of wider tiles (38110 pixels, 48 channels -> 48, 3x3, 1192 tiles 12.4 -> 8.6; but
-            // 15x17x18, 16 -> 16 channels in 8 groups, 3x3, 576 tiles 4.7, and 5.3 in 256x32 tiles)
+            // 15x17x18, 16 -> 16 channels in 8 groups, 3x3, 576 tiles 4.7, and 5.3 in 256x32 tiles).  Three per CU of a convolution run at once, which the fill does
+            // not see (5236 pixels, 112 -> 16 channels in each of 8 groups, 5x5, 656 tiles 29.0, and 33.1 in 256x32; 37840 pixels, 80 -> 32 1x1, 592 tiles 4.9 and 5.4).
             if (v->bm == 64 && v->bn == 32 && tiles > 4 * kCUs) depth -= 0.12;
+            if (v->bm == 64 && v->bn == 32 && amode == A_CONV && v->kw == 1 && tiles > 2 * kCUs && tiles <= 3 * kCUs) depth += 0.12;
             // Many rounds of one stage or two: nothing but latency and stores, which five 64x64 workgroups per CU cover for each other (209 x 320x80x64 fp16
             // 10.1 -> 7.9, 244 x 118x285x32 bf16 13.5 -> 11.2, 58x81 1x1 16 -> 128 channels 13.9 -> 10.9)
             const int64_t kbytes = K * es;
@@ -373,8 +390,9 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
         if (nslab < v->nstage) depth -= 0.04 * (v->nstage - (int)nslab);
         if (!one_round && lds > 80 * 1024) depth -= 0.04;
         else depth += (one_round ? 0.015 : 0.0025) * v->nstage;
-        // the partial sums' round trip (25x14x43, 96 -> 32 channels 5x5 fp16 in two slices 13.6, in two groups of one workgroup 11.0)
-        score *= depth * (ks > 1 ? 0.95 - 0.03 * (ks - 1) : 1.0);
+        // the partial sums' round trip (25x14x43, 96 -> 32 channels 5x5 fp16 in two slices 13.6, in two groups of one workgroup 11.0); a reduction of 8 KB and
+        // more per row covers its fixed part (464 -> 160 channels 5x5 over 3078 pixels 34.8 in two slices, 44.8 in one; 192 -> 16, 11700 pixels 18.1 and 20.4)
+        score *= depth * (ks > 1 ? (K * es >= 8192 ? 1.0 : 0.95) - 0.03 * (ks - 1) : 1.0);
         if (score > best_score) { best_score = score; best = Choice{v, ks}; }
     }
     return best;

@@ -144,6 +144,37 @@ def test_variant_choice_reflects_layout():
     assert B.tir_gemm_variant(1, -1, 8, 8, 8, 1, 8, 1, 8, 1, "f16", "f32") == ""
 
 
+@pytest.mark.parametrize("call,variant", [
+    # the variant that was measured faster, us with it and with the one the score preferred
+    (("gemm", 21, 32, 896, 64, "n", "bf16", "f32"), "t64x32w2x1s4_ak_bn"),                    # 3.91, 4.45 in 96x96 tiles
+    (("gemm", 25, 704, 96, 64, "t", "i8", "i8"), "t256x32w4x1s3_ak_bk"),                      # 4.20, 4.56 in 96x96
+    (("gemm", 63, 64, 272, 96, "t", "bf16", "f32"), "t96x96w3x1s4c4_ak_bk"),                  # 4.57, 5.66 in 64x32
+    (("gemm", 1, 576, 3040, 1024, "n", "f16", "f32"), "t128x64w2x2s4_ak_bn"),                 # 9.61, 10.25 with copy waves
+    (("gemm", 84, 608, 656, 64, "t", "bf16", "f32"), "t256x256w2x4s2_ak_bk"),                 # 36.7, 43.2 in 64x64
+    (("conv", 16, 106, 90, 128, 288, 3, 2, 1, 1, "bf16", "bf16"), "t256x96w4x1s3c4_conv"),    # 34.8, 45.3 in 128x96
+    (("conv", 3, 18, 57, 464, 160, 5, 1, 2, 1, "f16", "f16"), "t128x32w4x1s3k2_conv/z2"),     # 34.8, 44.8 in one slice
+    (("conv", 25, 14, 43, 96, 32, 5, 1, 1, 1, "f16", "f16"), "t64x32w2x1s4k2_conv"),          # 11.0, 13.6 in two slices
+    (("conv", 11, 70, 43, 256, 384, 5, 1, 1, 8, "i8", "i32"), "t128x64w2x2s3_conv"),          # 39.1, 44.8 with copy waves
+    (("conv", 3, 70, 100, 672, 576, 1, 1, 1, 2, "i8", "i8"), "t256x96w4x1s3c4_conv"),        # three stages: 16.7, 20.5 in 128x64
+    (("conv", 14, 11, 34, 896, 128, 5, 1, 1, 8, "f16", "f16"), "t64x32w2x1s4_conv"),          # 29.0, 33.1 in 256x32
+    (("conv", 4, 110, 86, 80, 32, 1, 1, 1, 1, "f16", "f16"), "t64x32w2x1s4_conv"),            # 4.94, 5.39 in 256x32
+    (("tconv", 31, 7, 34, 64, 32, "bf16", "bf16"), "t128x32w4x1s4_conv/ph2x2"),               # 5.50, 5.70 in two reduction groups
+])
+def test_variant_choice_of_measured_calls(call, variant):
+    """One call per rule of the scoring that corrects a slower choice, and calls just beyond."""
+    if call[0] == "gemm":
+        _, batch, m, n, k, b, dtype, out = call
+        name = B.tir_gemm_variant(batch, m, n, k, k, 1, *((1, k) if b == "t" else (n, 1)), n, 1, dtype, out)
+    elif call[0] == "conv":
+        _, n, h, w, c, k, r, stride, dil, groups, dtype, out = call
+        pad = dil * (r - 1) // 2
+        name = B.tir_conv2d_variant(n, h, w, c, k, r, r, stride, stride, pad, pad, dil, dil, groups, dtype, out)
+    else:
+        _, n, h, w, c, k, dtype, out = call
+        name = B.tir_conv2d_transpose_variant(n, h, w, c, k, 4, 4, (2, 2), (1, 1), (1, 1), (0, 0), 1, dtype, out)
+    assert name == f"{dtype}_{out}_{variant}"
+
+
 def test_few_channels_take_the_row_kernel_where_it_pays():
     """Vectors of one tap that are not whole: filter rows as the unit of the reduction, unless the reduction is one
     stage in one round of workgroups and the patch (wide strides, many channels) takes longer to copy than the element-wise kernel takes
