@@ -63,8 +63,12 @@ __global__ void __launch_bounds__(256) mfma_probe_kernel(float* sink, int iters,
 }
 
 // ------------------------------------------------------------------------------- variant table
+template <int E> constexpr int tile_extent() {
+    static_assert(E >= 32 && E <= 256 && E % 32 == 0, "tile extents are multiples of 32 up to 256");
+    return E;
+}
 #define TIR_ROW(name, DT, OUT, BM, BN, WM, WN, AM, BMO, RB, NS, KW, CW) \
-    {name, DT, OUT, BM, BN, WM, WN, AM, BMO, RB, NS, KW, CW, &launch_cfg<Cfg<DT, OUT, BM, BN, WM, WN, AM, BMO, RB, NS, KW, CW>>},
+    {name, DT, OUT, tile_extent<BM>(), tile_extent<BN>(), WM, WN, AM, BMO, RB, NS, KW, CW, &launch_cfg<Cfg<DT, OUT, BM, BN, WM, WN, AM, BMO, RB, NS, KW, CW>>},
 #define V0 TIR_ROW
 #define V1 TIR_ROW
 #define V2 TIR_ROW
@@ -76,18 +80,34 @@ static const Variant kVariants[] = {
 };
 static const int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
-// The variants of one (dt, out, amode, bmode), in table order: a call scores its candidates, not the whole table.
+// The variants of one (dt, out, amode, bmode), in table order: a call scores its candidates, not the whole table.  What pick() needs of a
+// variant and does not depend on the call is worked out once.
+struct Candidate {
+    const Variant* v;
+    int shape;              // number of its tile shape, below kShapes
+    int row_shift;          // log2 of rowb
+    double bytes_factor;    // grows with bm * bn / (bm + bn), up to the 256x256 tile
+};
 struct VariantRange {
-    const Variant* const* first;
+    const Candidate* first;
     int n;
 };
+// Tile shapes by number (tile_extent() above sees to their range).
+static const int kShapes = 64;
+static constexpr int shape_of(int bm, int bn) { return (bm / 32 - 1) * 8 + (bn / 32 - 1); }
 static const int kModes = 12, kDtypes = 5;
 static VariantRange variants_of(int dt, int out, int amode, int bmode) {
     struct Index {
-        const Variant* order[kNumVariants];
+        Candidate order[kNumVariants];
         VariantRange range[kDtypes][kDtypes][kModes][kModes] = {};
         Index() {
             int n = 0;
+            auto candidate = [](const Variant& v) {
+                double intensity = (double)v.bm * v.bn / (double)(v.bm + v.bn) / 128.0;
+                if (intensity > 1.0) intensity = 1.0;
+                // (the few-channel kernel's two widths by constants of their own: 25x133x120x1 -> 80, 5x5 fp16 33.9 us in 32 columns, 37.6 in 64)
+                return Candidate{&v, shape_of(v.bm, v.bn), __builtin_ctz((unsigned)v.rowb), v.amode == A_CONV_ROWS ? 0.25 + 0.75 * intensity : 0.2 + 0.8 * intensity};
+            };
             for (int d = 0; d < kDtypes; ++d)
                 for (int o = 0; o < kDtypes; ++o)
                     for (int a = 0; a < kModes; ++a)
@@ -95,7 +115,7 @@ static VariantRange variants_of(int dt, int out, int amode, int bmode) {
                             VariantRange& r = range[d][o][a][b];
                             r.first = order + n;
                             for (const Variant& v : kVariants)
-                                if (v.dt == d && v.out == o && v.amode == a && v.bmode == b) order[n++] = &v;
+                                if (v.dt == d && v.out == o && v.amode == a && v.bmode == b) order[n++] = candidate(v);
                             r.n = (int)(order + n - r.first);
                         }
         }
@@ -295,42 +315,55 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
     const int es = elem_size(dt);
     const bool staged = amode == A_UK || amode == A_UM;
     const VariantRange candidates = variants_of(dt, out, amode, bmode);
+    const bool overrides = sl.force > 1 || g_force_ksplit || g_force_name[0] || g_force_bm;
+    struct Shape {
+        int64_t tiles;
+        double eff, fit;      // padding efficiency, alone and times fill
+    } shapes[kShapes];
+    uint64_t have = 0;        // shapes that are filled in
+    // Beyond one round fill is not counted by whole rounds: a CU holds several workgroups of most tiles, so that a last round is seldom waited for by itself.
+    // (Whole rounds move 40 of 3853 calls to variants 3 to 34 % slower, 51 to faster ones.)
+    auto fill = [](double tiles) { return tiles <= kCUs ? tiles / kCUs : tiles / (tiles + (kCUs - 1.0)); };
     for (int i = 0; i < candidates.n; ++i) {
-        const Variant* v = candidates.first[i];
+        const Candidate& c = candidates.first[i];
+        const Variant* v = c.v;
         if (v->rowb > max_rowb) continue;
-        // (extents are below 2^31: 32-bit divisions, which take a third of the time of 64-bit ones)
-        const unsigned tm_1 = ((unsigned)M + (unsigned)v->bm - 1u) / (unsigned)v->bm, tn_1 = ((unsigned)N + (unsigned)v->bn - 1u) / (unsigned)v->bn;
-        const int64_t tiles_1 = (int64_t)tm_1 * tn_1;
-        const int want_ks = sl.force > 1 ? sl.force : g_force_ksplit;
-        const int forced_ks = (want_ks > 1 && split_fits(v, want_ks, batch, tiles_1, K, sl)) ? want_ks : 1;
-        if (sl.force > 1 && forced_ks != sl.force) continue;          // the caller insists on this split
-        if (g_force_name[0] && strstr(v->name, g_force_name)) return Choice{v, forced_ks};          // testing / tuning overrides
-        if (g_force_bm && v->bm == g_force_bm && v->bn == g_force_bn && v->kw == 1 && v->cw == 0) return Choice{v, forced_ks};
-        const double tm = (double)tm_1, tn = (double)tn_1;
-        int ks = forced_ks;
+        Shape& shape = shapes[c.shape];
+        if (!(have >> c.shape & 1)) {
+            have |= 1ull << c.shape;
+            // (extents are below 2^31: 32-bit divisions, which take a third of the time of 64-bit ones)
+            const unsigned tm = ((unsigned)M + (unsigned)v->bm - 1u) / (unsigned)v->bm, tn = ((unsigned)N + (unsigned)v->bn - 1u) / (unsigned)v->bn;
+            shape.tiles = (int64_t)tm * tn;
+            shape.eff = ((double)M * (double)N) / ((double)tm * v->bm * (double)tn * v->bn);
+            shape.fit = shape.eff * fill((double)tm * (double)tn * (double)batch);
+        }
+        int ks = 1;
+        if (overrides) {
+            const int want_ks = sl.force > 1 ? sl.force : g_force_ksplit;
+            if (want_ks > 1 && split_fits(v, want_ks, batch, shape.tiles, K, sl)) ks = want_ks;
+            if (sl.force > 1 && ks != sl.force) continue;          // the caller insists on this split
+            if (g_force_name[0] && strstr(v->name, g_force_name)) return Choice{v, ks};          // testing / tuning overrides
+            if (g_force_bm && v->bm == g_force_bm && v->bn == g_force_bn && v->kw == 1 && v->cw == 0) return Choice{v, ks};
+        }
+        const int64_t nslab = (K * es + v->rowb - 1) >> c.row_shift;       // stages (of 64, 128 or 256 bytes)
+        const bool small = v->bm * v->bn <= 64 * 64;
         // (the partial sums' trip through memory costs about 4 us for a 64x64 tile and grows with the tile: it pays
         // only for small tiles whose wave groups face two dozen stages or more)
-        if (!want_ks && sl.bytes > 0 && v->bm * v->bn <= 64 * 64) {
-            const int64_t stages = (K * es + v->rowb - 1) >> __builtin_ctz((unsigned)v->rowb);
-            int64_t want = stages / v->kw >= 24 && tiles_1 * batch <= (int64_t)kCUs / 2 ? (int64_t)kCUs / (tiles_1 * batch) : 1;
-            if (want > stages / (8 * v->kw)) want = stages / (8 * v->kw);
+        if (small && sl.bytes > 0 && !(sl.force > 1 || g_force_ksplit) && nslab >= 24 * v->kw && shape.tiles * batch <= (int64_t)kCUs / 2) {
+            int64_t want = (int64_t)kCUs / (shape.tiles * batch);
+            if (want > nslab / (8 * v->kw)) want = nslab / (8 * v->kw);
             if (want > 8) want = 8;
-            while (want > 1 && !split_fits(v, (int)want, batch, tiles_1, K, sl)) --want;
+            while (want > 1 && !split_fits(v, (int)want, batch, shape.tiles, K, sl)) --want;
             if (want > 1) ks = (int)want;
         }
-        const double tiles = tm * tn * (double)batch * ks;
-        const double eff = ((double)M * (double)N) / (tm * v->bm * tn * v->bn);
-        // Beyond one round not by whole rounds: a CU holds several workgroups of most tiles, so that a last round is seldom waited for by itself.  (Whole rounds
-        // move 40 of 3853 calls to variants 3 to 34 % slower, 51 to faster ones.)
-        const double fill = tiles <= kCUs ? tiles / kCUs : tiles / (tiles + (kCUs - 1.0));
-        double intensity = (double)v->bm * v->bn / (double)(v->bm + v->bn) / 128.0;
-        if (intensity > 1.0) intensity = 1.0;
-        // (the few-channel kernel's two widths by constants of their own: 25x133x120x1 -> 80, 5x5 fp16 33.9 us in 32 columns, 37.6 in 64)
-        double score = eff * fill * (amode == A_CONV_ROWS ? 0.25 + 0.75 * intensity : 0.2 + 0.8 * intensity);
-        const int64_t nslab = (K * es + v->rowb - 1) >> __builtin_ctz((unsigned)v->rowb);       // (64, 128 or 256 bytes)
+        const double eff = shape.eff, tiles = (double)shape.tiles * (double)batch * ks;
+        double score = (ks == 1 ? shape.fit : eff * fill(tiles)) * c.bytes_factor;
+        const bool one_round = tiles <= kCUs;
+        // `depth` is at most 1.3, 1.7 for small tiles in several rounds: most candidates end here.  With the
+        // shared terms of a tile shape a query of 128x128x128 fp16, 37 candidates, takes 1.13 us through the binding instead of 1.20 (an eager call 3.89 instead of 3.99)
+        if (score * (small && !one_round ? 1.7 : 1.3) <= best_score) continue;
         const int lds = (v->bm + v->bn) * v->rowb * v->nstage * v->kw;
         double depth = 1.0;
-        const bool one_round = tiles <= kCUs, small = v->bm * v->bn <= 64 * 64;
         if (v->kw > 1) {
             // Reduction groups pay for the exchange of partial sums.  Small tiles: in a single round of workgroups (nothing else on the CU hides the
             // copy latency), from two stages per group on (3x3 over 32 channels, 245 tiles of 64x32 5.3 -> 4.8).  Operands staged through
