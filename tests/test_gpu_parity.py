@@ -782,9 +782,9 @@ ATTN_CASES = [
     (2, 64, 384, 64, 3.0),           # peaked softmax, four key groups
     (2, 40, 100, 128, 0.0),          # scale 0: uniform attention
     (3, 70, 257, 64, 0.2),           # four key groups, the last one with a single key
-    (2, 65, 300, 128, -0.3),         # ... of 32-key chunks, a negative scale
-    (1, 33, 1200, 128, 4.0),         # ... several chunks each, references that rise late
-    (129, 20, 390, 64, 0.125),       # two key groups, an odd chunk count
+    (2, 65, 300, 128, -0.3),         # one group, five chunks, a negative scale
+    (1, 33, 1200, 128, 4.0),         # four key groups of 32-key chunks, several chunks each, references that rise late
+    (129, 20, 390, 64, 0.125),       # one group, an odd chunk count
     (140, 1, 385, 128, 1.5),         # ... one key in the last chunk
     (1, 200, 70, 64, -1.0),          # one group, two chunks, a negative scale
 ]
@@ -817,27 +817,41 @@ def test_attention_matches_oracle(B, oracle, dtype, out, rtol):
         _say(f"   max err/tol {ratio.max():.3g}")
 
 
-# one shape per kernel the attention dispatch has: (batch, M, N, d), every one with a last chunk of keys that is not whole
+# shapes for every kernel the attention dispatch has: (batch, M, N, d), every one with a last chunk of keys that is not whole
 ATTN_KERNELS = [
     (3, 70, 300, 64),        # four key groups of 64-key chunks
-    (2, 65, 300, 128),       # ... of 32-key chunks
+    (2, 65, 300, 128),       # below the four groups at this head dimension: one group, five chunks
     (129, 20, 390, 64),      # one group, seven and eight chunks
     (150, 17, 450, 128),
     (260, 20, 500, 64),      # one group, eight chunks
     (258, 9, 450, 128),
-    (2, 40, 130, 128),       # one group, three chunks
+    (2, 40, 130, 128),       # one group, five chunks of 32 keys
+    (3, 33, 150, 64),        # ... at the other head dimension
+    (2, 65, 450, 128),       # four key groups of 32-key chunks
+    (4, 3, 390, 64),         # (with the copies below) a chunk's phases in sequence, four waves
+    (2, 129, 257, 64),       # ... eight waves, the second tile a single row
+    (2, 129, 513, 128),      # eight waves, pipelined
+    (4, 33, 250, 128),       # non-temporal copies, an even chunk count
+    (4, 33, 530, 64),        # ... an odd one
 ]
+# copies of the heads that take a shape to its kernel by the number of tiles (the last two: by more than 256 MB of keys and values)
+ATTN_COPIES = {(4, 3, 390, 64): 130, (2, 129, 257, 64): 193, (2, 129, 513, 128): 65, (4, 33, 250, 128): 526, (4, 33, 530, 64): 500}
 
 
 def _attention(B, dtype, out, q, k, v, scale):
-    """Output of tir_attention for raw bits, as float64."""
+    """Output of tir_attention for raw bits, as float64.  Shapes of ATTN_COPIES are launched on copies of the heads, which must agree to the bit."""
     import torch
     (batch, M, d), N = q.shape, k.shape[1]
-    o = B.empty_out((batch, M, d), out)
+    copies = ATTN_COPIES.get((batch, M, N, d), 1)
+    o = B.empty_out((batch * copies, M, d), out)
     o.fill_(float("nan"))
-    B.tir_attention(B.to_device(q, dtype), B.to_device(k, dtype), B.to_device(v, dtype), o, batch, M, N, d, scale, dtype, out)
+    qd, kd, vd = (B.to_device(t, dtype).repeat(copies, 1, 1) for t in (q, k, v))
+    B.tir_attention(qd, kd, vd, o, batch * copies, M, N, d, scale, dtype, out)
     torch.cuda.synchronize()
-    return PT.gpu_to_f64(o)
+    if copies > 1:
+        bits = o.view(torch.int32 if out == "f32" else torch.int16).reshape(copies, batch, M, d)
+        assert bool((bits == bits[:1]).all()), "heads of equal operands differ"
+    return PT.gpu_to_f64(o[:batch])
 
 
 def _bits(values, dtype):
@@ -955,6 +969,24 @@ def test_attention_by_number_of_chunks(B, oracle, batch, M, d, keys, dtype, rtol
             got = _attention(B, dtype, "f32", q, k, v, scale)
             ratio = np.abs(got - ref) / (rtol * T + 1e-5)
             assert np.all(ratio <= 1.0), f"{N} keys, scale {scale}: max err/tol {np.max(ratio):.3g}"
+
+
+@pytest.mark.parametrize("dtype,rtol", [("f16", 2e-3), ("bf16", 6e-3)])
+@pytest.mark.parametrize("shape", ATTN_KERNELS, ids=str)
+def test_attention_with_output_of_the_input_type(B, oracle, shape, dtype, rtol):
+    """Every kernel of the dispatch with 16-bit output, whose tile in LDS and stores are half as wide; tolerances as in test_attention_matches_oracle, the
+    values of the last key large."""
+    batch, M, N, d = shape
+    qb, kb = I.make_tensor(dtype, "u", 41 + N, (batch, M, d)), I.make_tensor(dtype, "u", 42 + N, (batch, N, d))
+    values = I.uniform_pm1(43 + N, batch * N * d).reshape(batch, N, d)
+    values[:, -1] *= 16.0
+    vb = _bits(values, dtype)
+    for scale in (0.7, -0.7):
+        ref, T = oracle.attention(dtype, qb, kb, vb, scale)
+        got = _attention(B, dtype, dtype, qb, kb, vb, scale)
+        ratio = np.abs(got - ref) / (rtol * T + 1e-5 + (np.abs(ref) * 2.0 ** -8 if dtype == "bf16" else 0.0))
+        _say(f"attention {dtype} {shape} scale {scale}: max err/tol {ratio.max():.3g}")
+        assert ratio.max() <= 1.0
 
 
 def test_attention_of_keys_beyond_the_memory_side_cache(B, oracle):
@@ -1189,6 +1221,33 @@ def test_conv2d_transpose_by_output_phase(B, oracle, dtype, out):
                 PT.assert_close(PT.gpu_to_f64(y), ref, S, f"conv2d_transpose {'by phase' if not force else 'as a gather'}")
         finally:
             B.tir_debug_force_variant("")
+
+
+@pytest.mark.parametrize("dtype,out", PAIRS)
+@pytest.mark.parametrize("force", ["t96x96w3x1s4c4_conv", "t128x96w4x1s3c4_conv"])
+def test_conv2d_transpose_by_output_phase_on_the_96_column_tiles(B, oracle, force, dtype, out):
+    """Workgroups of three multiplying waves and four rows of 32: pixels of a phase and channels ragged against 96 and 128, phases of one, two and four
+    taps of one stage, and of one to nine taps of three."""
+    import torch
+    vec = 16 if dtype == "i8" else 8
+    for (N, H, W, C, K, R, pad, outpad) in ((2, 9, 11, 8 * vec, 104, 3, 1, 1), (1, 10, 12, 24 * vec, 200, 5, 2, 0)):
+        xb = I.make_tensor(dtype, "i" if dtype == "i8" else "u", 9940 + H, (N, H, W, C))
+        wb = I.make_tensor(dtype, "i" if dtype == "i8" else "u", 9941 + K, (K, R, R, C))
+        ref, S = oracle.conv2d_transpose(dtype, xb, wb, (2, 2), (pad, pad), (1, 1), (outpad, outpad), 1)
+        ep, bias, ref, S = _consumer(B, oracle, dtype, out, K, R * R * C // 4, True, ref, S)
+        xd, wd = B.to_device(xb, dtype), B.to_device(wb, dtype)
+        args = (N, H, W, C, K, R, R, (2, 2), (pad, pad), (1, 1), (outpad, outpad), 1, dtype, out)
+        B.tir_debug_force_variant(force)
+        try:
+            name = B.tir_conv2d_transpose_variant(*args)
+            _say(f"conv2d_transpose {N}x{H}x{W} {C} -> {K} {R}x{R} via {name}")
+            assert name == f"{dtype}_{out}_{force}/ph2x2", name
+            y = _gpu_out(B, ref.shape, out)
+            B.tir_conv2d_transpose(xd, wd, y, *args, ep=ep)
+            torch.cuda.synchronize()
+        finally:
+            B.tir_debug_force_variant("")
+        PT.assert_close(PT.gpu_to_f64(y), ref, S, name)
 
 
 @pytest.mark.parametrize("dtype,out", PAIRS)
