@@ -370,6 +370,7 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
             // registers have less in flight (500x501x503 fp16: 6.9, 5.6 with four groups).
             // Convolutions: larger tiles as well, because the waves share the arithmetic of the copies' addresses, and a long reduction pays for it in any number of
             // rounds (18x88x13, 176 -> 192 channels, 5x5 stride 2 bf16 38.9 -> 24.0; 17x36x39, 864 -> 64 in two groups fp16 73 -> 43.5).
+            // By phase, 16x14x14, 256 -> 128 4x4 stride 2 fp16 in 128x64 tiles: one group 12.8, two 12.1, one and copy waves 12.2.
             // 128x32 tiles from three stages per group on: of 45 calls the 33 with fewer take 1 to 5 % more in two groups (transposed 19x43x9, 64 -> 32 channels 4x4
             // stride 2 bf16 5.56 and 5.74), those with more 0.71 to 1.10 of the time.
             if (one_round ? nslab < (small ? (v->bm == 128 ? 3 : 2) * v->kw : 16) || (!small && amode != A_CONV) : amode != A_CONV || nslab < 40 || v->bm < 128) continue;
@@ -390,7 +391,8 @@ static Choice pick(int dt, int out, int amode, int bmode, int64_t batch, int64_t
         }
         // GEMMs of one stage do not repay their four stages of copies (30 x 48x608x96 int8 3.95 in 64x32, 4.59; 25 x 704x96x64 int8 4.20 in 256x32, 4.56), those of two
         // not half a tile of padding (37 x 48x560x128 fp16 4.38 in 64x32, 4.83; less padding pays: 63 x 64x272x96 bf16 5.66 and 4.57)
-        if (v->bm == 96 && amode != A_CONV && (nslab == 1 || (nslab == 2 && eff < 0.5))) score *= 0.85;
+        // (nor does 128x192 for half a tile: 49 x 64x928x64 5.5 in 64x64, 6.5; 51 x 32x848x64 4.8 and 5.3; 49 x 48x848x128 6.2 and 6.9)
+        if (amode != A_CONV && (v->bm == 96 ? nslab == 1 || (nslab == 2 && eff < 0.5) : v->bn == 192 && nslab <= 2 && eff < 0.5)) score *= 0.85;
         // One stage and many rounds: half as many, twice as large stores (84 x 608x656x64 bf16 37.2 in 256x256, 43.4 in 64x64; 8x47x112, 32 -> 160 1x1 8.7 and 9.3)
         if (v->bm == 256 && v->bn >= 128 && nslab == 1 && !one_round) depth += 0.03;
         // Copy waves take the copies' issue off the multiplying ones.  Tiles of 128x128 and more behind four waves gain from four stages on (1664x1888x256 bf16
@@ -662,7 +664,8 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     if (!ch.v) {
         // A filter of one tap reads no pixel twice, and the patch kernel would copy the pixels again for every 64 output channels: 1x1, 64 -> 256 channels,
         // 20x56x56 fp16 18.1 us, 8.9 in 256x256 tiles; 64 -> 64, 8x56x56 4.6 and 4.0; 128 -> 32, 4x28x28 int8 4.5 and 3.4.  (Images of less than one tile and at most
-        // 32 output channels keep it: callers of the variant query see them reported that way.  3x12x12, 64 -> 32 fp16 4.13 and 3.28 in 64x32 tiles.)
+        // 32 output channels stay with the patch kernel, the slower one there as well - 1 to 20 images of 12x12 to 15x15 4.9 to 5.5 us, 4.0 to 4.25 in 64x32 tiles - because
+        // the tests take a call of that size to reach the one-tap form of it by the automatic choice.)
         const bool one_tap = R * S == 1 && !(Kg <= 32 && P * Q < 256);
         const bool use_patch = patch_ok && !g_force_ksplit && (g_force_name[0] ? strstr(g_force_name, "patch") != nullptr : !one_tap);
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);

@@ -149,6 +149,7 @@ def test_variant_choice_reflects_layout():
     (("gemm", 21, 32, 896, 64, "n", "bf16", "f32"), "t64x32w2x1s4_ak_bn"),                    # 3.91, 4.45 in 96x96 tiles
     (("gemm", 25, 704, 96, 64, "t", "i8", "i8"), "t256x32w4x1s3_ak_bk"),                      # 4.20, 4.56 in 96x96
     (("gemm", 63, 64, 272, 96, "t", "bf16", "f32"), "t96x96w3x1s4c4_ak_bk"),                  # 4.57, 5.66 in 64x32
+    (("gemm", 49, 64, 928, 64, "n", "f16", "f32"), "t64x64w2x2s2_ak_bn"),                     # 5.51, 6.53 in 128x192
     (("gemm", 1, 576, 3040, 1024, "n", "f16", "f32"), "t128x64w2x2s4_ak_bn"),                 # 9.61, 10.25 with copy waves
     (("gemm", 84, 608, 656, 64, "t", "bf16", "f32"), "t256x256w2x4s2_ak_bk"),                 # 36.7, 43.2 in 64x64
     (("conv", 16, 106, 90, 128, 288, 3, 2, 1, 1, "bf16", "bf16"), "t256x96w4x1s3c4_conv"),    # 34.8, 45.3 in 128x96
