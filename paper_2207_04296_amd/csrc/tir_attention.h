@@ -54,14 +54,14 @@ template <> struct PackP<DT_BF16> {
 // here: 32 MFMAs of 32 cycles with 128 multiply-adds and 32 exponentials between them take one wave 1 096 cycles, the MFMAs alone 1 038, the
 // vector work alone 840.  With each wave's phases in sequence, left to a second wave to cover, 16 x 4096 x 4096 x 128 bf16 took 143.8 us, now
 // 133.8 (128.3 with priorities and tiles of 256 queries); 160 x 128 x 2000 x 128 50.5 and 39.9, 52 x 376 x 376 x 64 9.3 and 7.7.  What bounds the long case is power: the same launch on constant data takes
-// 111 us instead of 155 (one warm card), with 14 % between the two forms of the loop.
+// 103.5 us instead of 141.5 under the profiler, at 1.99 GHz instead of 1.68 and 8 % fewer cycles.
 //
 // QW waves of 32 queries times KG key groups: group k takes the chunks c with c % KG == k through a ring of its own and the
 // groups' results are merged through LDS at the end.  Where the query tiles alone leave CUs or SIMDs idle, key groups put more waves
 // on the same tile (launch_attn gives the rule and both sides' times).
 //
-// FORM: the loop described above, plain or with non-temporal copies, or a chunk's phases in sequence.  The latter holds one chunk's scores instead of two: 120
-// registers instead of 165 at d = 64, four workgroups per CU instead of three.
+// FORM: the loop described above, plain or with non-temporal copies, or a chunk's phases in sequence.  The latter holds one chunk's scores instead of two: 109 to 112
+// registers instead of 161 to 163 at d = 64, four workgroups per CU instead of three.
 enum : int { ATTN_PIPED = 0, ATTN_PIPED_STREAM = 1, ATTN_SEQUENTIAL = 2 };
 template <int DT, int OUT, int DH, int QW, int KG, int KB, int FORM>
 __global__ void __launch_bounds__(QW * KG * 64, 2) attention_kernel(const AttnParams p) {

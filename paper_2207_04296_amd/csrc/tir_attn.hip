@@ -17,7 +17,8 @@ template <int DT, int OUT, int DH, int QW, int KG, int KB, int FORM> static hipE
 template <int DT, int OUT, int DH> static hipError_t launch_attn(const AttnParams& p, hipStream_t stream) {
     const long long tiles = (long long)p.batch * ((p.M + 127) / 128);        // of 128 queries
     // Two workgroups of four waves fill a CU.  Up to half a tile per CU four key groups on tiles of 64 queries put eight waves on a CU instead
-    // of four; the merge costs about a chunk's time, so that every group needs more than one chunk.  (Two groups on 128 queries, up to one tile
+    // of four.  The merge costs about a chunk's time: from five chunks in all on at d = 64 (four groups of 64 keys), at d = 128 from three
+    // chunks of 32 per group.  (Two groups on 128 queries, up to one tile
     // per CU, pay no more since a wave runs its softmax under its own MFMAs.)
     // One, two and four groups, bf16, us (tiles of 128 queries x keys):
     //   d = 128: 64 x 320 9.0 / 10.6 / 9.4, 64 x 400 11.3 / 12.2 / 10.7, 128 x 400 11.8 / 12.8 / 11.4, 128 x 1000 22.0 / 23.6 / 20.3,

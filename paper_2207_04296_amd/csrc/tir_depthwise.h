@@ -241,9 +241,9 @@ inline long long depthwise_workgroups(int dt, long long N, long long P, long lon
 }
 
 // Pixels per thread of the blocked kernel.  Eight at stride 1 fetch a sixth fewer vectors per pixel than four, with twice the registers and twice the serial
-// arithmetic per thread.  One round of them (two workgroups per CU) takes the same time however full it is, so they pay where the workgroups of four no longer run at
-// once: more than three per CU, in bf16 -> bf16 more than two.  That counts the padding of both forms: at widths of 4 or 9 to 12 eight pixels make a third to
-// twice as many.  int8 -> int32 writes 64 bytes per pixel and thread and does not gain.  Four and eight pixels, us, same buffers:
+// arithmetic per thread.  One round of them (two workgroups per CU) takes the same time however full it is; workgroups of four step up in time at the fourth per
+// CU, in bf16 -> bf16 (196 registers, two per CU; fp16 122) at the third, and from there on eight pay.  That counts the padding of both forms: at widths of 4 or 9 to 12
+// eight pixels make a third to twice as many.  int8 -> int32 writes 64 bytes per pixel and thread and does not gain.  Four and eight pixels, us, same buffers:
 //   fp16: 16x56x56x128 (784 workgroups of four) 8.1 / 6.9, 16x60x14x384 -> fp32 (720) 12.3 / 12.8, 9x110x11x352 (558) 7.8 / 8.1, 4x505x4x512 (512) 5.7 / 7.2
 //   bf16: 360 to 512 workgroups of four 6.0 / 7.6, 513 to 768 8.2 / 8.1, 769 to 1024 10.4 / 9.2 (medians); -> fp32 4x505x9x256 (760) 11.3 / 12.4
 //   int8: 4x960x4x384 (360) 10.3 / 14.5, 4x137x49x384 (672) 13.1 / 16.4, 8x245x49x128 (800) 16.8 / 16.2; -> int32 2x2880x28x64 (630) 33.3 / 35.8, 8x288x56x128 (1008) 52.3 / 55.5
