@@ -1122,6 +1122,11 @@ int tir_debug_depthwise_pixels(int64_t N, int64_t P, int64_t Q, int64_t C, int s
     return depthwise_pixels((int)in, (int)out, N, P, Q, C, stride_w);
 }
 
+const char* tir_debug_attention_kernel(int64_t batch, int64_t M, int64_t N, int64_t d, tir_dtype out) {
+    static const char* const names[] = {"t64_groups4", "t128_chunks32", "t128", "t128_stream", "t128_sequential", "t256", "t256_sequential"};
+    return names[attention_kernel_of(batch, M, N, (int)d, (int)out)];
+}
+
 tir_status tir_probe_mfma_rate(void* sink, int iters, int random_operands, double* flop, tir_stream stream) {
     if (!sink || iters <= 0) return fail(TIR_ERR_INVALID_ARG, "tir_probe_mfma_rate: sink is null or iters <= 0");
     hipLaunchKernelGGL(mfma_probe_kernel, dim3(1024), dim3(256), 0, (hipStream_t)stream, (float*)sink, iters, random_operands);

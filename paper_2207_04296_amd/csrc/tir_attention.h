@@ -58,7 +58,7 @@ template <> struct PackP<DT_BF16> {
 //
 // QW waves of 32 queries times KG key groups: group k takes the chunks c with c % KG == k through a ring of its own and the
 // groups' results are merged through LDS at the end.  Where the query tiles alone leave CUs or SIMDs idle, key groups put more waves
-// on the same tile (launch_attn gives the rule and both sides' times).
+// on the same tile (attention_kernel_of gives the rule and both sides' times).
 //
 // FORM: the loop described above, plain or with non-temporal copies, or a chunk's phases in sequence.  The latter holds one chunk's scores instead of two: 109 to 112
 // registers instead of 161 to 163 at d = 64, four workgroups per CU instead of three.
@@ -505,6 +505,10 @@ __global__ void __launch_bounds__(QW * KG * 64, 2) attention_kernel(const AttnPa
         }
     }
 }
+
+// The kernels of the dispatch: tiles of 64, 128 or 256 queries; four key groups; chunks of 32 keys; the forms above.
+enum AttnKernel : int { ATTN_T64_GROUPS, ATTN_T128_C32, ATTN_T128, ATTN_T128_STREAM, ATTN_T128_SEQUENTIAL, ATTN_T256, ATTN_T256_SEQUENTIAL };
+AttnKernel attention_kernel_of(long long batch, long long M, long long N, int DH, int OUT);
 
 typedef hipError_t (*attn_launch_fn)(const AttnParams&, hipStream_t);
 // (dt, out, head dimension) -> launcher, or null when the combination is not compiled

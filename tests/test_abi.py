@@ -134,6 +134,26 @@ def test_depthwise_pixels_per_thread(dtype, out, n, p, q, c, pixels):
     assert B.tir_debug_depthwise_pixels(n, p, q, c, 2, dtype, out) == 4
 
 
+@pytest.mark.parametrize("batch,m,n,d,out,kernel", [
+    # us with this kernel and with another, the same operands again / three sets of operands in turn
+    (512, 256, 256, 64, "bf16", "t128_sequential"),       # 15.7 / 16.1, in tiles of 256 15.7 / 18.7
+    (512, 256, 256, 64, "f32", "t128_sequential"),        # 17.2 / 17.2, 17.6 / 21.1
+    (256, 512, 320, 64, "f32", "t128_sequential"),        # 17.3 / 17.7, 18.3 / 18.6
+    (256, 512, 768, 64, "bf16", "t256_sequential"),       # 32.2 / 33.0, in tiles of 128 33.5 / 33.9
+    (800, 128, 600, 64, "bf16", "t128_sequential"),       # 31.9 / 33.2, pipelined 32.0 / 38.5
+    (2000, 40, 64, 64, "bf16", "t128_sequential"),        # 11.0 / 12.6, 12.3 / 13.8
+    (2000, 128, 160, 64, "bf16", "t128_sequential"),      # 27.1 / 27.3, in chunks of 32 25.1 / 31.7
+    (500, 128, 1000, 64, "bf16", "t128_stream"),          # 28.8 / 30.1, plain 26.9 / 32.2
+    (1024, 128, 400, 128, "bf16", "t128_stream"),         # 49.8 / 49.3, plain 44.9 / 58.8
+    (200, 128, 2000, 128, "bf16", "t128"),                # 38.7 / 52.2, non-temporal 47.9 / 49.6
+    (390, 256, 512, 128, "f32", "t128"),                  # 40.1 / 48.4, in tiles of 256 45.6 / 50.4
+    (16, 4096, 4096, 128, "bf16", "t256"),
+    (192, 128, 128, 64, "f16", "t128"),
+])
+def test_attention_kernel_of_measured_calls(batch, m, n, d, out, kernel):
+    assert B.tir_debug_attention_kernel(batch, m, n, d, out) == kernel
+
+
 def test_variant_choice_reflects_layout():
     # row-major B is read N-major, a transposed B K-major; odd K falls back to the general kernel
     assert B.tir_gemm_variant(1, 4096, 4096, 4096, 4096, 1, 4096, 1, 4096, 1, "f16", "f32").endswith("ak_bn")

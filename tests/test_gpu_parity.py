@@ -829,13 +829,27 @@ ATTN_KERNELS = [
     (3, 33, 150, 64),        # ... at the other head dimension
     (2, 65, 450, 128),       # four key groups of 32-key chunks
     (4, 3, 390, 64),         # (with the copies below) a chunk's phases in sequence, four waves
-    (2, 129, 257, 64),       # ... eight waves, the second tile a single row
-    (2, 129, 513, 128),      # eight waves, pipelined
+    (2, 129, 257, 64),       # ... heads of two tiles, the second a single row
+    (2, 390, 513, 64),       # ... eight waves, the last of 128 rows empty but for six
+    (2, 129, 513, 128),      # eight waves, pipelined, with 16-bit output
+    (2, 129, 833, 128),      # ... and with any
     (4, 33, 250, 128),       # non-temporal copies, an even chunk count
-    (4, 33, 530, 64),        # ... an odd one
+    (4, 33, 1210, 64),       # ... at the other head dimension
+    (4, 33, 530, 64),        # a chunk's phases in sequence for more than four workgroups per CU
 ]
-# copies of the heads that take a shape to its kernel by the number of tiles (the last two: by more than 256 MB of keys and values)
-ATTN_COPIES = {(4, 3, 390, 64): 130, (2, 129, 257, 64): 193, (2, 129, 513, 128): 65, (4, 33, 250, 128): 526, (4, 33, 530, 64): 500}
+# copies of the heads that take a shape to its kernel by the number of tiles and the size of keys and values
+ATTN_COPIES = {(4, 3, 390, 64): 130, (2, 129, 257, 64): 193, (2, 129, 513, 128): 65, (2, 129, 833, 128): 65, (4, 33, 250, 128): 526,
+               (4, 33, 1210, 64): 125, (4, 33, 530, 64): 500}
+ATTN_COPIES.update({(2, 390, n, 64): 97 for n in (512, 513, 577, 640)})            # tiles of 256 queries by number of chunks
+ATTN_COPIES.update({(2, 129, n, 128): 65 for n in (768, 769, 897, 960)})
+
+
+def test_the_attention_shapes_reach_every_kernel(B):
+    """... with either width of the output, at both head dimensions where both have the kernel."""
+    for out in ("f32", "f16"):
+        reached = {(d, B.tir_debug_attention_kernel(batch * ATTN_COPIES.get((batch, M, N, d), 1), M, N, d, out)) for batch, M, N, d in ATTN_KERNELS}
+        both = {(d, k) for d in (64, 128) for k in ("t64_groups4", "t128_chunks32", "t128", "t128_stream")}
+        assert reached == both | {(64, "t128_sequential"), (64, "t256_sequential"), (128, "t256")}
 
 
 def _attention(B, dtype, out, q, k, v, scale):
@@ -951,7 +965,9 @@ def test_attention_rounds_all_but_the_largest_probability(B, oracle, shape, dtyp
     (65, 400, 128, (512, 513, 577, 641)),                                                     # tiles of 256 queries, the second one of a head not whole
     (600, 3, 64, (64, 65, 97, 128, 192, 193, 256, 400)),                                      # two to four workgroups per CU: a chunk's phases in sequence
     (172, 260, 64, (401,)),                                                                   # ... more than 128 queries: of any number of keys
-    (385, 129, 64, (256, 257)),                                                               # ... in tiles of 256 queries, half empty
+    (385, 129, 64, (256, 257)),                                                               # ... heads of one tile of 128 queries and a row
+    (2, 390, 64, (512, 513, 577, 640)),                                                       # ... in tiles of 256 queries (on copies of the heads)
+    (2, 129, 128, (768, 769, 833, 897, 960)),                                                 # tiles of 256 queries, whatever the output type
 ])
 def test_attention_by_number_of_chunks(B, oracle, batch, M, d, keys, dtype, rtol):
     """Every chunk count at which the loop over the keys changes form (no step, one step, the two-step loop and what it leaves over), whole
