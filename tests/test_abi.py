@@ -114,7 +114,7 @@ def test_division_by_launch_constants_is_exact():
 
 
 @pytest.mark.parametrize("dtype,out,n,p,q,c,pixels", [
-    # us with four and with eight pixels per thread, one box
+    # us with four and with eight pixels per thread
     ("f16", "f16", 16, 56, 56, 128, 8),        # 8.1, 6.9
     ("f16", "f16", 4, 505, 4, 512, 4),         # 5.7, 7.2: half of a group of eight is padding
     ("f16", "f16", 9, 110, 11, 352, 4),        # 7.8, 8.1: a third more pixels
