@@ -1345,8 +1345,9 @@ def test_depthwise_convolution(B, oracle, case):
 @pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("f16", "f32"), ("bf16", "f32"), ("i8", "i8"), ("i8", "i32")])
 @pytest.mark.parametrize("w,c,stride_h,dil_h", [(9, 8, 1, 1), (16, 24, 1, 2), (12, 72, 2, 1)])
 def test_depthwise_convolution_of_eight_pixels_per_thread(B, oracle, dtype, out, w, c, stride_h, dil_h):
-    """352 to 512 workgroups of eight pixels per thread (that of a launch of one round): rows of one group and a pixel, of two whole groups and of one and a half,
-    part of a channel block and two blocks."""
+    """400 workgroups of eight pixels per thread (a launch of one round): rows of one group and a pixel, of two whole groups and of one and a half,
+    part of a channel block and two blocks.  Rows of whole groups take eight, the others, a third of padding, and int8 -> int32 four (the test after this one
+    has the sizes where they take eight as well)."""
     vec = 16 if dtype == "i8" else 8
     c = c * vec // 8
     blocks, groups, threads = (c + 63) // 64, (w + 7) // 8, 256 * vec // 64
