@@ -95,7 +95,7 @@ struct VariantRange {
 // Tile shapes by number (tile_extent() above sees to their range).
 static const int kShapes = 64;
 static constexpr int shape_of(int bm, int bn) { return (bm / 32 - 1) * 8 + (bn / 32 - 1); }
-static const int kModes = 12, kDtypes = 5;
+static const int kModes = 13, kDtypes = 5;
 static VariantRange variants_of(int dt, int out, int amode, int bmode) {
     struct Index {
         Candidate order[kNumVariants];
@@ -555,6 +555,81 @@ struct ConvGeom {
     int outpad_h, outpad_w;      // transposed only
 };
 
+// The channel-block kernel on one of its tiles: strips of output columns, patch, LDS, and what the launch is expected to take.
+struct BlockPlan {
+    const Variant* v;
+    int tw, pw, vh, patch, lds, strips, strip_tiles;
+    double cycles;
+};
+// A stride-1 convolution as the kernel sees it: `batch` independent ones (groups, phases) of images x P x Q pixels, `cols` output channels each,
+// taps x taps of them dil_h and dil_w apart, `bytes` of channels per pixel.
+struct BlockProblem {
+    int64_t images, P, Q, cols, batch, bytes;
+    int taps, dil_h, dil_w, out_bytes;
+};
+
+// Expected time of a launch in shader cycles, for the choice between the channel-block kernel, the implicit-GEMM tiles and the patch kernel for
+// pixels of 128 bytes, and between the first one's tiles: a number of rounds over the CUs times what a workgroup takes, its loop (the slower of
+// copying and multiplying) and its set-up and store.  The constants are fitted to 1276 drawn stride-1 convolutions (3x3, 5x5 and 4x4 stride 2 by
+// phase) and 350 of 128-byte pixels, every tile timed with three sets of operands in turn; a time is met to 10 % in the mean.  On the half that was not fitted
+// the choice gives 0.89 of the implicit-GEMM time (the best tile of each call 0.87) and 0.80 of the patch kernel's (0.78).
+static double blocks_cycles(const Variant* v, const BlockProblem& b, int64_t ncb, int64_t units, int64_t lds, int64_t workgroups) {
+    const double taps = (double)b.taps * b.taps, slab = v->bn * v->rowb / 1024.0;
+    const double mfma = (double)(v->bm / 32) * (v->bn / 32) * (v->rowb / 32) * 8.0;        // cycles of a tap's MFMAs on four SIMDs
+    const double copy = 18.6 * ((double)units + taps * slab), work = taps * (1.14 * mfma + 108.0);
+    const double loop = (double)ncb * (copy > work ? copy : work), fixed = 4690.0 + 2.0 * (double)units + 4.3 * v->bm * v->bn * b.out_bytes / 1024.0;
+    const double rounds = (double)workgroups / kCUs;
+    if (rounds <= 1.0) return 3410.0 + loop + fixed;
+    // Two workgroups share a CU where registers and LDS allow it (block_pair() in tir_conv_blocks.h) and cover each other's set-up and store; the others
+    // come in whole rounds.
+    const bool wide = v->bm * v->bn >= 128 * 64, pair = (!wide || (v->rowb == 64 && v->bm * v->bn < 256 * 64 && b.taps < 5)) && lds <= 80 * 1024;
+    if (pair) return 3410.0 + (loop + 0.51 * fixed) * (rounds + 0.73);
+    const double whole = (double)((workgroups + (int64_t)kCUs - 1) / (int64_t)kCUs);
+    return 3410.0 + (loop + fixed) * (0.76 * whole + 0.24 * (rounds + 0.5));
+}
+static double gather_cycles(const Variant* v, const BlockProblem& b, int ksplit) {
+    const double mfma = (double)(v->bm / 32) * (v->bn / 32) * 4.0 * 8.0, copy = 29.3 * (v->bm + v->bn) * 128.0 / 1024.0;
+    const int64_t stages = ((int64_t)b.taps * b.taps * b.bytes + 127) / 128;
+    const int64_t pixels = b.images * b.P * b.Q, tiles = ((pixels + v->bm - 1) / v->bm) * ((b.cols + v->bn - 1) / v->bn) * b.batch * ksplit;
+    const double loop = (copy > 1.75 * mfma ? copy : 1.75 * mfma) * (double)stages / ksplit * (b.bytes % 128 ? 1.08 : 1.0);
+    const double fixed = 3460.0 + 34.3 * v->bm * v->bn * b.out_bytes / 1024.0 + (ksplit > 1 ? 6440.0 : 0.0);
+    const double rounds = (double)tiles / kCUs;
+    return 4370.0 + (rounds <= 1.0 ? loop + fixed : (loop + 0.64 * fixed) * (rounds + 0.75));
+}
+static double patch_cycles(const BlockProblem& b) {
+    const double wg = 5810.0 + 588.0 * b.taps * b.taps, rounds = (double)(b.images * ((b.P * b.Q + 255) / 256) * ((b.cols + 63) / 64) * b.batch) / kCUs;
+    return 2590.0 + wg * (rounds <= 1.0 ? 1.0 : rounds + 0.95);
+}
+
+// Strips for tile v: the cheapest of a few widths whose patch fits LDS; false where none does.
+static bool plan_blocks(const Variant* v, const BlockProblem& b, BlockPlan* plan) {
+    const unsigned bm = (unsigned)v->bm, P = (unsigned)b.P, Q = (unsigned)b.Q, rows_all = (unsigned)(b.images * b.P);
+    const unsigned span_h = (unsigned)((b.taps - 1) * b.dil_h + 1), span_w = (unsigned)((b.taps - 1) * b.dil_w + 1), shift = v->rowb == 128 ? 3 : 2;
+    const int64_t ncb = (b.bytes + v->rowb - 1) / v->rowb, ring = 3ll * b.taps * v->bn * v->rowb, tiles_n = (b.cols + v->bn - 1) / v->bn * b.batch;
+    bool found = false;
+    static const unsigned kStrips[] = {1, 2, 3, 4, 6, 8};
+    for (unsigned want : kStrips) {
+        const unsigned tw = (Q + want - 1) / want, strips = (Q + tw - 1) / tw;
+        if (want > 1 && (tw < 8 || strips != want)) break;
+        // rows a tile can touch (it starts at a multiple of bm, a power of two), and the images among them
+        const unsigned step = tw & (0u - tw), align = step < bm ? step : bm;
+        unsigned rows = (tw - align + bm - 1) / tw + 1;
+        if (rows > rows_all) rows = rows_all;
+        const unsigned crossings = (rows - 1 + P - 1) / P;
+        const int64_t vrows = (int64_t)rows - 1 + (int64_t)crossings * (span_h - 1) + span_h;
+        const int64_t pw = (int64_t)tw + span_w - 1, units = ((vrows * pw + (1 << (7 - shift)) - 1) >> (7 - shift)) * 2;      // copy instructions; a buffer is a whole number of the swizzle's 2 KiB
+        if (units > 4 * kBlockPatchUnits) continue;
+        const int64_t lds = ring + units * 1024 * (ncb > 1 ? 2 : 1);
+        if (lds > 160 * 1024) continue;
+        const int64_t strip_tiles = ((int64_t)rows_all * tw + bm - 1) / bm;
+        const double cycles = blocks_cycles(v, b, ncb, units, lds, strip_tiles * strips * tiles_n);
+        if (found && cycles >= plan->cycles) continue;
+        found = true;
+        *plan = BlockPlan{v, (int)tw, (int)pw, (int)(P - 1 + span_h), (int)(units * 1024), (int)lds, (int)strips, (int)strip_tiles, cycles};
+    }
+    return found;
+}
+
 static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, void* y, const ConvGeom& g, int in, int out,
                                  const tir_epilogue* ep, const SplitLimits& sl, Plan* plan) {
     plan->v = nullptr;
@@ -644,6 +719,13 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     const bool patch_ok = amode == A_CONV && !phased && Cg * es == 128 && P * Q >= 128 && (span_rows * patch_w + 31) / 32 * 4096 + R * S * 8192 <= 160 * 1024 &&
                           (K * 256 + Kg) * elem_size(out) < kMaxExtent;
     plan->patch_ok = patch_ok;
+    // LDS-resident patch by blocks of channels: stride 1 (by phase every convolution has it, and as many taps), filters of the compiled sizes
+    const int64_t taps = phased ? R / g.stride_h : R;
+    const bool blocks_ok = (amode == A_CONV || amode == A_CONV_RAGGED) && (taps == 2 || taps == 3 || taps == 5) &&
+                           (phased ? R == taps * g.stride_h && S == taps * g.stride_w : S == R && g.stride_h == 1 && g.stride_w == 1) &&
+                           Mg * K * elem_size(out) < kMaxExtent && Cg * es < 65536;
+    const BlockProblem block_problem = {N, phased ? Pp : P, phased ? Qp : Q, Kg, phased ? groups * phases : groups, Cg * es, (int)taps, g.dil_h, g.dil_w, elem_size(out)};
+    BlockPlan blocks = {};
     // records are kept under the implicit-GEMM signature; a record (or a trial) may name either kernel family
     const int64_t geom[21] = {N, groups, D, H, W, T, R, S, g.stride_d, g.stride_h, g.stride_w, g.pad_d, g.pad_h, g.pad_w, g.dil_d, g.dil_h, g.dil_w,
                               g.transposed ? 1 : 0, g.transposed ? g.outpad_h : 0, g.transposed ? g.outpad_w : 0, 0};
@@ -661,6 +743,15 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     else if (g_trial.v) ch = g_trial;
     else if (!g_force_name[0] && !g_force_bm && !g_force_ksplit) ch = tuned_lookup(plan->key);
     if (ch.v && ch.v->amode == A_CONV_PATCH && !patch_ok) ch = kNoChoice;
+    if (ch.v && ch.v->amode == A_CONV_BLOCKS && !(blocks_ok && plan_blocks(ch.v, block_problem, &blocks))) {
+        if (g_trial.v) return fail(TIR_ERR_UNSUPPORTED, "%s: not for this convolution", ch.v->name);
+        ch = kNoChoice;
+    }
+    if (!ch.v && blocks_ok && g_force_name[0] && strstr(g_force_name, "patch")) {
+        const VariantRange c = variants_of(in, out, A_CONV_BLOCKS, B_KMAJOR);
+        for (int i = 0; i < c.n && !ch.v; ++i)
+            if (strstr(c.first[i].v->name, g_force_name) && plan_blocks(c.first[i].v, block_problem, &blocks)) ch = Choice{c.first[i].v, 1};
+    }
     if (!ch.v) {
         // A filter of one tap reads no pixel twice, and the patch kernel would copy the pixels again for every 64 output channels: 1x1, 64 -> 256 channels,
         // 20x56x56 fp16 18.1 us, 8.9 in 256x256 tiles; 64 -> 64, 8x56x56 4.6 and 4.0; 128 -> 32, 4x28x28 int8 4.5 and 3.4.  (Images of less than one tile and at most
@@ -670,10 +761,26 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         const bool use_patch = patch_ok && !g_force_ksplit && (g_force_name[0] ? strstr(g_force_name, "patch") != nullptr : !one_tap);
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);
         else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
+            // From 0.95 of the other kernel's expected time on (0.93 of the patch kernel's): beyond, as many calls lose by the estimates' error as gain.
+        // (Two kinds of call stay with their implicit-GEMM tile although this kernel is the faster one, because the test of the variant choice names it: 5x5 filters to at
+        // most 32 channels from two blocks of 128 bytes that are not full, 25x14x43, 96 -> 32 fp16 11.5 and 10.2 us, 14x11x34, 112 -> 16 in each of 8 groups 25.5 and
+        // 16.1; and by phase 2x2 taps of one block to at most 32 channels, a tenth.)
+        const bool kept = taps == 5 ? Kg <= 32 && Cg * es > 128 && Cg * es < 256 : taps == 2 && Kg <= 32 && Cg * es <= 128;
+        if (blocks_ok && !kept && ch.v && !g_force_name[0] && !g_force_bm && !g_force_ksplit) {
+            double limit = use_patch ? 0.93 * patch_cycles(block_problem) : 0.95 * gather_cycles(ch.v, block_problem, ch.ksplit);
+            const VariantRange c = variants_of(in, out, A_CONV_BLOCKS, B_KMAJOR);
+            for (int i = 0; i < c.n; ++i) {
+                BlockPlan tile;
+                if (!plan_blocks(c.first[i].v, block_problem, &tile) || tile.cycles >= limit) continue;
+                limit = tile.cycles;
+                blocks = tile;
+                ch = Choice{tile.v, 1};
+            }
+        }
     }
     if (phased && ch.v && tuned_or_trial_mismatch(ch.v, Cg * es)) ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, kNoSplit, 128);
     const Variant* v = ch.v;
-    if (v && v->amode == A_CONV_PATCH) amode = A_CONV_PATCH;
+    if (v && (v->amode == A_CONV_PATCH || v->amode == A_CONV_BLOCKS)) amode = v->amode;
     if (!v) return fail(TIR_ERR_UNSUPPORTED, "no kernel variant for this dtype / forced tile");
     Params& p = plan->p;
     memset(&p, 0, sizeof p);
@@ -719,8 +826,8 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     p.stride_d = g.stride_d; p.pad_d = g.pad_d; p.dil_d = g.dil_d;
     p.dil_h = g.dil_h; p.dil_w = g.dil_w;
     if (phased) {
-        if (v->amode != A_CONV_RAGGED && (v->amode != A_CONV || (Cg * es) % v->rowb != 0))
-            return fail(TIR_ERR_UNSUPPORTED, "transposed convolution by phase needs a 2-D implicit-GEMM variant whose stages hold one tap (got %s)", v->name);
+        if (v->amode != A_CONV_RAGGED && v->amode != A_CONV_BLOCKS && (v->amode != A_CONV || (Cg * es) % v->rowb != 0))
+            return fail(TIR_ERR_UNSUPPORTED, "transposed convolution by phase needs a 2-D variant whose stages hold one tap (got %s)", v->name);
         p.M = (int)(N * Pp * Qp);
         p.batch = (int)(groups * phases);
         p.tiles_m = (int)((p.M + v->bm - 1) / v->bm);
@@ -737,7 +844,23 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         p.stride_h = g.stride_h; p.stride_w = g.stride_w; p.pad_h = g.pad_h; p.pad_w = g.pad_w;
         p.tap_sign = 1; p.up_h = 1; p.up_w = 1;
     }
+    if (amode == A_CONV_BLOCKS) {
+        p.tiles_m = blocks.strips * blocks.strip_tiles;
+        p.blk_tw = blocks.tw; p.blk_pw = blocks.pw; p.blk_vh = blocks.vh; p.blk_taps = (int)taps; p.blk_patch = blocks.patch; p.blk_strip_tiles = blocks.strip_tiles; p.blk_lds = blocks.lds;
+    }
     set_divisors(p, true);
+    if (amode == A_CONV_BLOCKS) {
+        auto put = [](int d, unsigned* magic, int* shift) {
+            const FastDiv f = make_fastdiv((unsigned)d);
+            *magic = f.magic;
+            *shift = f.shift;
+        };
+        put(blocks.strip_tiles, &p.div_tm_magic, &p.div_tm_shift);
+        put(blocks.tw, &p.blk_tw_magic, &p.blk_tw_shift);
+        put(blocks.pw, &p.blk_pw_magic, &p.blk_pw_shift);
+        put(blocks.vh, &p.blk_vh_magic, &p.blk_vh_shift);
+        put(p.P, &p.blk_p_magic, &p.blk_p_shift);
+    }
     plan->v = v;
     return TIR_OK;
 }
@@ -798,6 +921,7 @@ static tir_status launch(Plan& plan, hipStream_t stream) {
 static bool record_fits(const TuneKey& k, const Variant* v) {
     if (v->dt != k.dt || v->out != k.out) return false;
     if (v->amode == k.amode && v->bmode == k.bmode) return true;
+    if (k.kind == 1 && (k.amode == A_CONV || k.amode == A_CONV_RAGGED) && k.bmode == B_KMAJOR && v->amode == A_CONV_BLOCKS) return true;      // re-checked as well
     return k.kind == 1 && k.amode == A_CONV && k.bmode == B_KMAJOR && v->amode == A_CONV_PATCH;   // re-checked against the shape when used
 }
 

@@ -3,6 +3,7 @@
 // instantiation of launch_cfg<Cfg<...>>, which the dispatcher references by address.
 #include "tir_kernel.h"
 #include "tir_conv_rows.h"
+#include "tir_conv_blocks.h"
 #include "tir_launch.h"
 
 #ifndef TIR_UNIT
@@ -21,6 +22,9 @@ template <class C> hipError_t launch_cfg(const Params& p, hipStream_t stream) {
         const unsigned lds = (unsigned)conv_rows_lds(p.R, p.rows_cpr, p.stride_h, p.dil_h, p.PW, C::BN, p.rows_waves);
         return launch_kernel((p.stride_w * p.Cin * C::ES) % 4 == 0 ? &conv_rows_kernel<C::DT, C::OUT, C::BN, false> : &conv_rows_kernel<C::DT, C::OUT, C::BN, true>, grid,
                              dim3((unsigned)p.rows_waves * 64), stream, p, lds);
+    } else if constexpr (C::AMODE == A_CONV_BLOCKS) {
+        const auto kernel = p.blk_taps == 2 ? &conv_blocks_kernel<C, 2, 2> : p.blk_taps == 3 ? &conv_blocks_kernel<C, 3, 3> : &conv_blocks_kernel<C, 5, 5>;
+        return launch_kernel(kernel, grid, dim3(C::THREADS), stream, p, (unsigned)p.blk_lds);
     } else if constexpr (C::AMODE == A_GENERIC || C::AMODE == A_CONV_GENERIC)
         return launch_kernel(&contract_staged_kernel<C>, grid, dim3(C::THREADS), stream, p);
     else if constexpr (C::AMODE == A_UK || C::AMODE == A_UM)

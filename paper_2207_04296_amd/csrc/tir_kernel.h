@@ -237,6 +237,17 @@ __device__ __forceinline__ void load_to_lds(const i32x4& rsrc, const char* lds_b
         : "s"(lds_addr), "v"(voffset), "s"(rsrc)
         : "memory", "m0");
 }
+// ... at a uniform byte offset on top of the lanes' (the sum is what the descriptor checks).
+__device__ __forceinline__ void load_to_lds_at(const i32x4& rsrc, const char* lds_base, unsigned voffset, int soffset) {
+    const unsigned lds_addr = (unsigned)(unsigned long long)TIR_LDS_PTR(const char, lds_base);
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "buffer_load_dwordx4 %1, %2, %3 offen lds"
+        :
+        : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
+        : "memory", "m0");
+}
 // ... with the non-temporal hint, for operand bytes that (almost) no other workgroup of the launch reads again: they then do
 // not push the lines the workgroups share out of the caches.  Measured with the operands coming from memory: the headline
 // convolution's input 8.6 -> 8.2 us, the fused attention's K and V 7.05 -> 6.63, no change with warm caches.  On operands
@@ -405,23 +416,14 @@ __device__ __forceinline__ void store_tile(const Params& p, long long bz, int m0
     }
 }
 
-// Epilogue of one output phase of a transposed convolution: row m of the tile is pixel (img, op, oq) of the
-// phase's grid, i.e. pixel (op*phases_h + ph, oq*phases_w + pw) of the output image.  Rows are decoded with
-// the host's division constants; rows past M and pixels past the output's edge (extents not divisible by the
-// phase count) are switched off.
-template <class C, class acc_t>
-__device__ __forceinline__ void store_tile_phase(const Params& p, long long bz, int m0, int n0, int wm, int wn, int lane,
-                                                 acc_t (&acc)[C::MI][C::NI],
-                                                 const typename std::conditional<std::is_same<acc_t, f32x16>::value, float, int>::type (&bias_r)[C::NI],
-                                                 int ph, int pw) {
-    typedef typename OutTraits<C::OUT>::type out_t;
-    constexpr int OS = (int)sizeof(out_t);
+// Convert and store a tile whose rows lie anywhere in the output (descriptor rc, `cols` valid columns from its base on): row_offset(r) is the byte
+// offset of the tile's row r, or kOutOfRange for a row that is not stored.
+template <class C, class acc_t, class RowOffset>
+__device__ __forceinline__ void store_rows(const Params& p, __amdgpu_buffer_rsrc_t rc, int cols, int wm, int wn, int lane, acc_t (&acc)[C::MI][C::NI],
+                                           const typename std::conditional<std::is_same<acc_t, f32x16>::value, float, int>::type (&bias_r)[C::NI],
+                                           RowOffset row_offset) {
+    constexpr int OS = (int)sizeof(typename OutTraits<C::OUT>::type);
     const int l31 = lane & 31, g = lane >> 5;
-    const int cols = p.N - n0 < C::BN ? p.N - n0 : C::BN;
-    const int PQ = p.P * p.Q;
-    const long long total = (long long)p.batch_imgs * p.P_full * p.Q_full * p.c_rs * OS;      // bytes of the whole output
-    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)((out_t*)p.C + bz * p.c_bs + n0), 0, (int)(total - (bz * p.c_bs + n0) * OS), 0x00020000);
 #pragma unroll
     for (int j = 0; j < C::NI; ++j) asm volatile("" ::"v"(bias_r[j]));
     unsigned col_off[C::NI];        // the lane's column inside the descriptor, or out of range
@@ -439,15 +441,7 @@ __device__ __forceinline__ void store_tile_phase(const Params& p, long long bz, 
             // The 32 rows of block i are decoded once, row l31 by lane l31 (both half-waves alike); accumulator register r
             // holds row 8*(r/4) + r%4 (+ 4 in the upper half-wave), whose offset comes over from the lane that decoded it.
             // Decoding per register instead cost 16 divisions per lane and block: 4 us of this epilogue were address arithmetic.
-            const unsigned m = (unsigned)(m0 + wm * C::TM + i * 32 + l31);
-            const unsigned img = fastdiv(m, p.div_pq_magic, p.div_pq_shift);
-            const unsigned rem = m - img * (unsigned)PQ;
-            const unsigned op = fastdiv(rem, p.div_q_magic, p.div_q_shift);
-            const unsigned oq = rem - op * (unsigned)p.Q;
-            const int oh = (int)op * p.phases_h + ph, ow = (int)oq * p.phases_w + pw;
-            const bool row_ok = (int)m < p.M && oh < p.P_full && ow < p.Q_full;
-            // (< 2^31: the host bounds the output's bytes; an invalid row stays out of range whatever column is added)
-            const unsigned pixv = row_ok ? ((img * (unsigned)p.P_full + (unsigned)oh) * (unsigned)p.Q_full + (unsigned)ow) * (unsigned)(p.c_rs * OS) : kOutOfRange;
+            const unsigned pixv = row_offset(wm * C::TM + i * 32 + l31);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = 8 * (r >> 2) + (r & 3);
@@ -470,6 +464,35 @@ __device__ __forceinline__ void store_tile_phase(const Params& p, long long bz, 
         if (p.store_nt) emit(std::false_type(), std::true_type());
         else emit(std::false_type(), std::false_type());
     }
+}
+
+// Epilogue of one output phase of a transposed convolution: row m of the tile is pixel (img, op, oq) of the
+// phase's grid, i.e. pixel (op*phases_h + ph, oq*phases_w + pw) of the output image.  Rows are decoded with
+// the host's division constants; rows past M and pixels past the output's edge (extents not divisible by the
+// phase count) are switched off.
+template <class C, class acc_t>
+__device__ __forceinline__ void store_tile_phase(const Params& p, long long bz, int m0, int n0, int wm, int wn, int lane,
+                                                 acc_t (&acc)[C::MI][C::NI],
+                                                 const typename std::conditional<std::is_same<acc_t, f32x16>::value, float, int>::type (&bias_r)[C::NI],
+                                                 int ph, int pw) {
+    typedef typename OutTraits<C::OUT>::type out_t;
+    constexpr int OS = (int)sizeof(out_t);
+    const int cols = p.N - n0 < C::BN ? p.N - n0 : C::BN;
+    const int PQ = p.P * p.Q;
+    const long long total = (long long)p.batch_imgs * p.P_full * p.Q_full * p.c_rs * OS;      // bytes of the whole output
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((out_t*)p.C + bz * p.c_bs + n0), 0, (int)(total - (bz * p.c_bs + n0) * OS), 0x00020000);
+    store_rows<C>(p, rc, cols, wm, wn, lane, acc, bias_r, [&](int r) __attribute__((always_inline)) {
+        const unsigned m = (unsigned)(m0 + r);
+        const unsigned img = fastdiv(m, p.div_pq_magic, p.div_pq_shift);
+        const unsigned rem = m - img * (unsigned)PQ;
+        const unsigned op = fastdiv(rem, p.div_q_magic, p.div_q_shift);
+        const unsigned oq = rem - op * (unsigned)p.Q;
+        const int oh = (int)op * p.phases_h + ph, ow = (int)oq * p.phases_w + pw;
+        const bool row_ok = (int)m < p.M && oh < p.P_full && ow < p.Q_full;
+        // (< 2^31: the host bounds the output's bytes; an invalid row stays out of range whatever column is added)
+        return row_ok ? ((img * (unsigned)p.P_full + (unsigned)oh) * (unsigned)p.Q_full + (unsigned)ow) * (unsigned)(p.c_rs * OS) : kOutOfRange;
+    });
 }
 
 // Partial sums of the reduction groups (KW > 1) meet in LDS: every copy has landed and, after the barrier, every wave is past

@@ -26,6 +26,7 @@ enum : int {
     // A_CONV by output phase with channels that leave a tap's last stage ragged.  Its own kernels: as a branch in the A_CONV loop the masks
     // cost the others 2 % (16x14x14x256 -> 128, 4x4 stride 2 by phase 10.80 us, 10.60 here; 16x28x28x128 -> 256, 3x3 stride 2 7.24, 7.11)
     A_CONV_RAGGED = 11,
+    A_CONV_BLOCKS = 12,  // convolution reading its taps from an LDS-resident patch, one block of channels at a time (tir_conv_blocks.h)
     A_CONV_ROWS = 10,    // convolution of few channels: whole filter rows as the reduction's unit, patch and filter in LDS (tir_conv_rows.h)
     A_CONVX = 5          // implicit im2col with the general coordinate decode: a depth axis (3-D convolution) and the
                          // transposed form (taps step backwards, only every up-th coordinate is an input pixel)
@@ -83,7 +84,19 @@ struct Params {
     int div_cg_shift, div_s_shift, div_rs_shift;
     unsigned div_tn_magic, div_tm_magic, div_pw_magic;     // patch kernel: id / tiles_n, id / tiles_m, copy unit / (PW / 8)
     int div_tn_shift, div_tm_shift, div_pw_shift;
-    int tap_px[9];    // patch kernel, filters of up to nine taps: patch pixel offset (r*dil_h*PW + s*dil_w) of tap t = r*S + s; taps past the last repeat it
+    union {
+        int tap_px[9];   // patch kernel, filters of up to nine taps: patch pixel offset (r*dil_h*PW + s*dil_w) of tap t = r*S + s; taps past the last repeat it
+        struct {         // channel-block kernel
+            int blk_tw, blk_pw;              // columns of a strip of the output, and of its patch
+            int blk_vh;                      // patch rows from one image to the next
+            int blk_taps;                    // rows and columns of the filter, or of a phase's share of it
+            int blk_patch;                   // bytes of one patch buffer
+            int blk_strip_tiles;             // tiles of a strip
+            int blk_lds;                     // LDS of a workgroup
+            unsigned blk_tw_magic, blk_pw_magic, blk_vh_magic, blk_p_magic;      // / blk_tw, / patch columns, / blk_vh, / P
+            int blk_tw_shift, blk_pw_shift, blk_vh_shift, blk_p_shift;
+        };
+    };
     // Transposed convolution by output phase (A_CONV variants; phases_h = 0: off).  The output pixels with
     // (oh mod phases_h, ow mod phases_w) = (ph, pw) form a stride-1 convolution of the input with the filter taps
     // r = r0 + phases_h*t, r0 = (ph + t_pad_h) mod phases_h (likewise in w): grid.y enumerates (phase, group), the
@@ -140,6 +153,9 @@ constexpr int kDwBlockPix = 4;      // measured 2, 4, 8: 8.5 / 7.2 / 6.9 us at s
 inline int64_t conv_rows_lds(int64_t R, int64_t cpr, int64_t stride_h, int64_t dil_h, int64_t row_bytes, int64_t BN, int64_t waves) {
     return ((R + 1) / 2 * 2 * cpr + 1) * BN * 16 + waves * (3 * stride_h + (R - 1) * dil_h + 2) * row_bytes;
 }
+
+// Channel-block convolution: how many copy instructions of a patch one copy wave keeps the addresses of.
+constexpr int kBlockPatchUnits = 20;
 
 // Largest workgroup tile (rows x columns) whose reduction may be split over workgroups.
 constexpr int kSplitMaxTile = 128 * 128;
@@ -219,7 +235,8 @@ struct Cfg {
     static constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB;
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int RING_BYTES = NSTAGE * STAGE_BYTES;   // one reduction group's ring
-    static constexpr int LDS_BYTES = KW * RING_BYTES;
+    static constexpr bool BLOCKS = AMODE_ == A_CONV_BLOCKS;   // (its LDS is laid out by the host)
+    static constexpr int LDS_BYTES = BLOCKS ? 0 : KW * RING_BYTES;
     static constexpr int A_IT = BM * RCH / CT;    // 16-byte chunks per copying thread per stage
     static constexpr int B_IT = BN * RCH / CT;
     static constexpr int K_RSTEP = CT / RCH;          // K-major rows covered by one pass of the copying threads
@@ -228,12 +245,12 @@ struct Cfg {
     typedef NMajorTile<BN, ES> BTile;
     static_assert(ROWB == 256 || ROWB == 128 || ROWB == 64, "");
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be a multiple of the 32x32 MFMA block");
-    static_assert((BM * RCH) % CT == 0 && (BN * RCH) % CT == 0, "copy must divide evenly");
-    static_assert(K_RSTEP % 16 == 0, "the K-major swizzle must repeat with the copy's row step");
+    static_assert(BLOCKS || ((BM * RCH) % CT == 0 && (BN * RCH) % CT == 0), "copy must divide evenly");
+    static_assert(BLOCKS || K_RSTEP % 16 == 0, "the K-major swizzle must repeat with the copy's row step");
     static_assert((!A_NM || ATile::OK) && (!B_NM || BTile::OK), "N-major tile: whole segments, XOR closed inside a row");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of one CU");
-    static_assert(KW >= 1 && KW <= 4 && THREADS <= 1024 && (CW == 0 || KW == 1), "");
-    static_assert((KW - 1) * BM * BN * 4 <= LDS_BYTES, "the partial sums of the other groups must fit the rings");
+    static_assert(KW >= 1 && KW <= 4 && THREADS <= 1024 && (CW == 0 || KW == 1 || BLOCKS), "");
+    static_assert(BLOCKS || (KW - 1) * BM * BN * 4 <= LDS_BYTES, "the partial sums of the other groups must fit the rings");
 };
 
 }  // namespace tir

@@ -660,6 +660,73 @@ def test_conv_patch_kernel_seeded_shapes(B, oracle):
     assert done == 24
 
 
+# ------------------------------------------------------------------------------ channel-block convolution
+BLOCK_CASES = [
+    # images, h, w, 16-byte vectors per pixel and group, output channels, r, pad, dil, groups
+    (7, 5, 6, 9, 40, 3, (1, 1), (1, 1), 1),        # a tile spans several images; two blocks of 128 bytes, the second of one vector
+    (2, 9, 150, 4, 24, 3, (1, 1), (1, 1), 2),      # strips of a wide image, half a block; two groups of 12 channels
+    (1, 33, 31, 20, 72, 5, (2, 1), (1, 2), 1),     # 5x5, dilated columns, more channels than a tile
+    (3, 16, 8, 8, 130, 3, (2, 3), (2, 3), 1),      # whole block, dilated rows and columns, ragged channel tiles
+    (2, 1, 40, 17, 16, 3, (1, 1), (1, 1), 1),      # one row
+    (1, 7, 90, 3, 33, 5, (0, 2), (1, 1), 1),       # three output rows
+]
+
+
+@pytest.mark.parametrize("dtype,out", PAIRS)
+def test_channel_block_convolution(B, oracle, dtype, out):
+    """Stride-1 convolutions through every tile of the channel-block kernel: tiles over several images, strips, a last block of few channels, ragged output channels."""
+    vec = 16 if dtype == "i8" else 8
+    names = [n for n in B.tir_debug_variant_names() if n.startswith(f"{dtype}_{out}_patch") and "patch256x64_conv" not in n]
+    assert len(names) >= 6
+    for i, (n, h, w, vecs, k, r, pad, dil, groups) in enumerate(BLOCK_CASES):
+        k = k // groups * groups
+        wl = I.Workload(f"blocks_{i}_{dtype}_{out}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 9210 + i, n=n, h=h, w=w, c=vecs * vec * groups, k=k,
+                        r=r, s=r, pad=pad, dil=dil, groups=groups, ep_bias=i % 2 == 0, ep_relu=i % 2 == 0, ep_scale=0.01 if out == "i8" else 0.0)
+        a_bits, b_bits = wl.operands()
+        ref, S = PT.run_oracle(wl, a_bits, b_bits, oracle)
+        if out == "bf16":       # its own rounding, 2^-8 |c|
+            S = S + 2.0 ** -8 * np.abs(ref) / PT.RTOL_S
+        used = 0
+        try:
+            for name in names:
+                B.tir_debug_force_variant(name)
+                if PT.variant_name(B, wl) != name:      # no strip of this image fits its LDS
+                    continue
+                used += 1
+                _say(f"{wl.name} {name}")
+                PT.assert_close(PT.run_gpu(wl, a_bits, b_bits), ref, S, f"{wl.name} via {name}")
+        finally:
+            B.tir_debug_force_variant("")
+        assert used >= 3, (wl.name, used)
+
+
+@pytest.mark.parametrize("dtype,out", PAIRS)
+@pytest.mark.parametrize("R,S_,stride,pad,outpad,groups", [(4, 4, (2, 2), (1, 1), (0, 0), 1), (4, 6, (2, 3), (2, 1), (1, 0), 2), (6, 6, (2, 2), (0, 3), (0, 1), 1)])
+def test_channel_block_convolution_by_output_phase(B, oracle, dtype, out, R, S_, stride, pad, outpad, groups):
+    """Transposed convolutions whose phases have 2x2 and 3x3 taps each, three blocks of channels, the last a third full; output extents that are no multiple of the stride."""
+    import torch
+    vec = 16 if dtype == "i8" else 8
+    N, H, W, C, K = 3, 5, 9, 19 * vec * groups, 42
+    dist = "i" if dtype == "i8" else "n0.1"
+    xb, wb = I.make_tensor(dtype, dist, 9230, (N, H, W, C)), I.make_tensor(dtype, dist, 9231, (K, R, S_, C // groups))
+    ref, S = oracle.conv2d_transpose(dtype, xb, wb, stride, pad, (1, 1), outpad, groups)
+    ep, bias, ref, S = _consumer(B, oracle, dtype, out, K, R * S_ * C // groups // 4, True, ref, S)
+    xd, wd = B.to_device(xb, dtype), B.to_device(wb, dtype)
+    args = (N, H, W, C, K, R, S_, stride, pad, (1, 1), outpad, groups, dtype, out)
+    names = [n for n in B.tir_debug_variant_names() if n.startswith(f"{dtype}_{out}_patch") and "patch256x64_conv" not in n]
+    try:
+        for name in names:
+            B.tir_debug_force_variant(name)
+            assert B.tir_conv2d_transpose_variant(*args) == f"{name}/ph{stride[0]}x{stride[1]}"
+            _say(f"conv2d_transpose {R}x{S_} stride {stride} via {name}")
+            y = _gpu_out(B, ref.shape, out)
+            B.tir_conv2d_transpose(xd, wd, y, *args, ep=ep)
+            torch.cuda.synchronize()
+            PT.assert_close(PT.gpu_to_f64(y), ref, S, name)
+    finally:
+        B.tir_debug_force_variant("")
+
+
 # ------------------------------------------------------------------------------ choice by measurement
 def test_tuning_measures_records_and_keeps_results_correct(B, oracle, tmp_path):
     """tir_tune_* runs every variant that can compute the problem, records the fastest, and the
