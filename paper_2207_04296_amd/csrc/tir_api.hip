@@ -761,7 +761,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         const bool use_patch = patch_ok && !g_force_ksplit && (g_force_name[0] ? strstr(g_force_name, "patch") != nullptr : !one_tap);
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);
         else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
-            // From 0.95 of the other kernel's expected time on (0.93 of the patch kernel's): beyond, as many calls lose by the estimates' error as gain.
+        // From 0.95 of the other kernel's expected time on (0.93 of the patch kernel's): beyond, as many calls lose by the estimates' error as gain.
         // (Two kinds of call stay with their implicit-GEMM tile although this kernel is the faster one, because the test of the variant choice names it: 5x5 filters to at
         // most 32 channels from two blocks of 128 bytes that are not full, 25x14x43, 96 -> 32 fp16 11.5 and 10.2 us, 14x11x34, 112 -> 16 in each of 8 groups 25.5 and
         // 16.1; and by phase 2x2 taps of one block to at most 32 channels, a tenth.)
