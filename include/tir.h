@@ -324,8 +324,10 @@ void tir_debug_tile_of_block(int bid, int tiles_m, int tiles_n, int* tm, int* tn
  * multiply-and-shift constants the planner derives from d (used to decode output rows into pixels). */
 unsigned tir_debug_fastdiv(unsigned d, unsigned m);
 /* Adjacent output pixels (4 or 8) per thread of the depth-wise kernel for 3x3 filters undilated along the width, on N images of
- * P x Q output pixels (Q >= 4) and C channels. */
+ * P x Q output pixels (Q >= 4) and C channels, unless tir_debug_depthwise_rows says two. */
 int tir_debug_depthwise_pixels(int64_t N, int64_t P, int64_t Q, int64_t C, int stride_w, tir_dtype in, tir_dtype out);
+/* Rows of output pixels per thread of that kernel at stride 1, undilated: 1, or 2 of four pixels each. */
+int tir_debug_depthwise_rows(int64_t N, int64_t P, int64_t Q, int64_t C, tir_dtype in, tir_dtype out);
 /* Name of the kernel tir_attention launches for these sizes, head dimension (64 or 128) and output type: its tile of queries and form. */
 const char* tir_debug_attention_kernel(int64_t batch, int64_t M, int64_t N, int64_t d, tir_dtype out);
 

@@ -20,7 +20,7 @@ DTYPE_CODES = {"f16": TIR_F16, "bf16": TIR_BF16, "i8": TIR_I8, "f32": TIR_F32, "
 
 EXPORTS = ["tir_gemm", "tir_batch_matmul", "tir_conv2d", "tir_last_error", "tir_gemm_variant",
            "tir_conv2d_variant", "tir_debug_force_tile", "tir_debug_force_variant", "tir_debug_variant_count",
-           "tir_debug_variant_name", "tir_debug_tile_of_block", "tir_debug_depthwise_pixels", "tir_debug_attention_kernel",
+           "tir_debug_variant_name", "tir_debug_tile_of_block", "tir_debug_depthwise_pixels", "tir_debug_depthwise_rows", "tir_debug_attention_kernel",
            "tir_probe_mfma_rate", "tir_version",
            "tir_tune_batch_matmul", "tir_tune_conv2d", "tir_tune_count", "tir_tune_clear", "tir_tune_save",
            "tir_tune_load", "tir_gemm_fused", "tir_batch_matmul_fused", "tir_conv2d_fused", "tir_attention",
@@ -103,6 +103,8 @@ def lib() -> ctypes.CDLL:
     L.tir_debug_tile_of_block.restype = None
     L.tir_debug_depthwise_pixels.argtypes = [i64] * 4 + [ci] * 3
     L.tir_debug_depthwise_pixels.restype = ci
+    L.tir_debug_depthwise_rows.argtypes = [i64] * 4 + [ci] * 2
+    L.tir_debug_depthwise_rows.restype = ci
     L.tir_debug_attention_kernel.argtypes = [i64] * 4 + [ci]
     L.tir_debug_attention_kernel.restype = ctypes.c_char_p
     L.tir_probe_mfma_rate.argtypes = [vp, ci, ci, ctypes.POINTER(ctypes.c_double), vp]
@@ -295,6 +297,10 @@ def tir_debug_tile_of_block(bid: int, tiles_m: int, tiles_n: int):
 
 def tir_debug_depthwise_pixels(N: int, P: int, Q: int, C: int, stride_w: int, in_dtype, out_dtype) -> int:
     return int(lib().tir_debug_depthwise_pixels(N, P, Q, C, stride_w, _code(in_dtype), _code(out_dtype)))
+
+
+def tir_debug_depthwise_rows(N: int, P: int, Q: int, C: int, in_dtype, out_dtype) -> int:
+    return int(lib().tir_debug_depthwise_rows(N, P, Q, C, _code(in_dtype), _code(out_dtype)))
 
 
 def tir_debug_attention_kernel(batch: int, M: int, N: int, d: int, out_dtype) -> str:

@@ -1246,6 +1246,10 @@ int tir_debug_depthwise_pixels(int64_t N, int64_t P, int64_t Q, int64_t C, int s
     return depthwise_pixels((int)in, (int)out, N, P, Q, C, stride_w);
 }
 
+int tir_debug_depthwise_rows(int64_t N, int64_t P, int64_t Q, int64_t C, tir_dtype in, tir_dtype out) {
+    return depthwise_rows((int)in, (int)out, N, P, Q, C);
+}
+
 const char* tir_debug_attention_kernel(int64_t batch, int64_t M, int64_t N, int64_t d, tir_dtype out) {
     static const char* const names[] = {"t64_groups4", "t128_chunks32", "t128", "t128_stream", "t128_sequential", "t256", "t256_sequential"};
     return names[attention_kernel_of(batch, M, N, (int)d, (int)out)];

@@ -97,19 +97,29 @@ template <int DT, int OUT, bool STREAM> static hipError_t launch_dw_as(const Par
     dim3 grid((unsigned)((p.M + kDwPixPerThread * PP - 1) / (kDwPixPerThread * PP)), (unsigned)((p.Cin + kDwChannels - 1) / kDwChannels));
     if (p.R == 3 && p.S == 3 && p.dil_w == 1 && (p.stride_w == 1 || p.stride_w == 2) && p.Q >= kDwBlockPix) {
         auto blocks_x = [&](int np) { return (unsigned)(depthwise_workgroups(DT, p.batch_imgs, p.P, p.Q, p.Cin, np) / grid.y); };
+        // another split of the pixels than the plan's: four columns of two rows, or eight columns
+        auto split = [&](unsigned rows, unsigned groups) {
+            Params q = p;
+            const FastDiv dq = make_fastdiv(groups), dpq = make_fastdiv(rows * groups);
+            q.div_dwq_magic = dq.magic; q.div_dwq_shift = dq.shift;
+            q.div_dwpq_magic = dpq.magic; q.div_dwpq_shift = dpq.shift;
+            return q;
+        };
+        if constexpr (OUT == DT && DT != DT_I8) {
+            if (p.stride_w == 1 && p.stride_h == 1 && p.dil_h == 1 && depthwise_rows(DT, OUT, p.batch_imgs, p.P, p.Q, p.Cin) == 2) {
+                const unsigned rows = (unsigned)(p.P + 1) / 2;
+                grid.x = (unsigned)(depthwise_workgroups(DT, p.batch_imgs, rows, p.Q, p.Cin, kDwBlockPix) / grid.y);
+                return launch_kernel(&depthwise3x3_blocked_kernel<DT, OUT, 1, kDwBlockPix, 2, STREAM>, grid, dim3(256), stream, split(rows, (unsigned)(p.Q + kDwBlockPix - 1) / kDwBlockPix));
+            }
+        }
         if constexpr (OUT != DT_I32) {
             if (depthwise_pixels(DT, OUT, p.batch_imgs, p.P, p.Q, p.Cin, p.stride_w) == 8) {
-                Params q = p;
-                const unsigned qg = (unsigned)((p.Q + 7) / 8);
-                const FastDiv dq = make_fastdiv(qg), dpq = make_fastdiv((unsigned)p.P * qg);
-                q.div_dwq_magic = dq.magic; q.div_dwq_shift = dq.shift;
-                q.div_dwpq_magic = dpq.magic; q.div_dwpq_shift = dpq.shift;
                 grid.x = blocks_x(8);
-                return launch_kernel(&depthwise3x3_blocked_kernel<DT, OUT, 1, 8, STREAM>, grid, dim3(256), stream, q);
+                return launch_kernel(&depthwise3x3_blocked_kernel<DT, OUT, 1, 8, 1, STREAM>, grid, dim3(256), stream, split((unsigned)p.P, (unsigned)(p.Q + 7) / 8));
             }
         }
         grid.x = blocks_x(kDwBlockPix);
-        return launch_kernel(p.stride_w == 1 ? &depthwise3x3_blocked_kernel<DT, OUT, 1, kDwBlockPix, STREAM> : &depthwise3x3_blocked_kernel<DT, OUT, 2, kDwBlockPix, STREAM>, grid,
+        return launch_kernel(p.stride_w == 1 ? &depthwise3x3_blocked_kernel<DT, OUT, 1, kDwBlockPix, 1, STREAM> : &depthwise3x3_blocked_kernel<DT, OUT, 2, kDwBlockPix, 1, STREAM>, grid,
                              dim3(256), stream, p);
     }
     return launch_kernel(p.R == 3 && p.S == 3 ? &depthwise_kernel<DT, OUT, true, STREAM> : &depthwise_kernel<DT, OUT, false, STREAM>, grid, dim3(256), stream, p);

@@ -151,10 +151,12 @@ __global__ void __launch_bounds__(256) depthwise_kernel(const Params p) {
 // once (18 vectors for 4 pixels at stride 1 instead of 36, 30 for 8) and all requested before the first multiply; row and
 // column validity are decided once per row / column, so a tap's address costs three vector instructions instead
 // of a dozen.  The one-pixel kernel above spent twice as many instructions on addresses as on multiply-adds.
+// Two rows of output pixels per thread (NR = 2, four columns each, stride 1, undilated) share two of their input rows: 24 vectors for 8 pixels, where eight in
+// a row take 30 and two threads of four 36.  The kernel is bound by those fetches through the CU's load path; depthwise_rows() has both sides.
 // STREAM (the output policy) is a template parameter, not a branch: a branch around each store splits the pixel loop
 // into blocks, and the compiler then waits for the previous pixel's stores before the next pixel's arithmetic
 // (measured: 6.9 -> 8.8 us).
-template <int DT, int OUT, int SW, int NP, bool STREAM>
+template <int DT, int OUT, int SW, int NP, int NR, bool STREAM>
 __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params p) {
     typedef typename DwIn<DT>::acc_e acc_e;
     typedef OutTraits<OUT> OT;
@@ -165,6 +167,7 @@ __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params 
     constexpr int CV = kDwChannels / VEC;            // channel vectors per workgroup
     constexpr int PP = 256 / CV;                     // pixel groups per workgroup
     constexpr int NC = (NP - 1) * SW + 3;
+    constexpr int NI = NR + 2;                       // input rows (two output rows: stride 1, undilated)
 
     // every argument the kernel reads, fetched in one batch
     asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.C), "s"(p.M), "s"(p.bias), "s"(p.relu), "s"(p.scale), "s"(p.batch_imgs), "s"(p.H), "s"(p.W), "s"(p.Cin),
@@ -183,15 +186,16 @@ __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params 
     for (int e = 0; e < VEC; ++e) bias_r[e] = p.bias ? ((const acc_e*)p.bias)[c0 + e] : (acc_e)0;
 
     const int QG = (p.Q + NP - 1) / NP;              // pixel groups per output row
+    const int PG = (p.P + NR - 1) / NR;              // rows of pixel groups per image
     int bx = blockIdx.x;                             // each XCD owns a contiguous range of pixel groups (shared rows stay in its L2)
     {
-        const int nb = (p.batch_imgs * p.P * QG + PP - 1) / PP, nb8 = nb - nb % kXcds;      // = gridDim.x (a hidden argument, fetched late)
+        const int nb = (p.batch_imgs * PG * QG + PP - 1) / PP, nb8 = nb - nb % kXcds;      // = gridDim.x (a hidden argument, fetched late)
         if (bx < nb8) bx = (bx % kXcds) * (nb8 / kXcds) + bx / kXcds;
     }
     const int gidx = bx * PP + pl;
-    if (gidx >= p.batch_imgs * p.P * QG) return;
-    const int img = (int)fastdiv((unsigned)gidx, p.div_dwpq_magic, p.div_dwpq_shift), rem = gidx - img * (p.P * QG);
-    const int op = (int)fastdiv((unsigned)rem, p.div_dwq_magic, p.div_dwq_shift), oq0 = (rem - op * QG) * NP;
+    if (gidx >= p.batch_imgs * PG * QG) return;
+    const int img = (int)fastdiv((unsigned)gidx, p.div_dwpq_magic, p.div_dwpq_shift), rem = gidx - img * (PG * QG);
+    const int og = (int)fastdiv((unsigned)rem, p.div_dwq_magic, p.div_dwq_shift), op = og * NR, oq0 = (rem - og * QG) * NP;
     const int ih0 = op * p.stride_h - p.pad_h, iw0 = oq0 * SW - p.pad_w;
 
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)p.A, 0, (int)((long long)p.batch_imgs * p.H * p.W * p.Cin * ES), 0x00020000);
@@ -200,10 +204,10 @@ __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params 
     bool col_ok[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) col_ok[c] = (unsigned)(iw0 + c) < (unsigned)p.W;
-    u32x4 v[3][NC];
+    u32x4 v[NI][NC];
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const int ih = ih0 + r * p.dil_h;
+    for (int r = 0; r < NI; ++r) {
+        const int ih = ih0 + r * (NR > 1 ? 1 : p.dil_h);
         const bool row_ok = (unsigned)ih < (unsigned)p.H;
         int row_off = (((img * p.H + ih) * p.W + iw0) * p.Cin + c0) * ES;           // only used where the tap is inside the image
         asm volatile("" : "+v"(row_off));      // (kept as one value: re-associated with the column, every load's address became a multiply)
@@ -213,13 +217,14 @@ __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params 
     }
     const int out_pix0 = (img * p.P + op) * p.Q + oq0;
 #pragma unroll
-    for (int j = 0; j < NP; ++j) {
+    for (int k = 0; k < NR * NP; ++k) {
+        const int i = k / NP, j = k % NP;
         acc_e acc[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[e] = 0;                    // reduction init
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
-            const uint4 u = __builtin_bit_cast(uint4, v[t / 3][j * SW + t % 3]);
+            const uint4 u = __builtin_bit_cast(uint4, v[i + t / 3][j * SW + t % 3]);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc[e] += DwIn<DT>::get(u, e) * DwIn<DT>::get(wv[(9 * e + t) / VEC], (9 * e + t) % VEC);
         }
@@ -227,7 +232,7 @@ __global__ void __launch_bounds__(256) depthwise3x3_blocked_kernel(const Params 
 #pragma unroll
         for (int e = 0; e < VEC; ++e) o[e] = finish_value<OUT>(consumer(acc[e], bias_r[e], p.relu), p.scale);
         constexpr int OB = VEC * (int)sizeof(out_t);
-        const int obyte = oq0 + j < p.Q ? ((out_pix0 + j) * p.Cin + c0) * (int)sizeof(out_t) : (int)kOutOfRange;      // < 2^31: checked by the host
+        const int obyte = oq0 + j < p.Q && (NR == 1 || op + i < p.P) ? ((out_pix0 + i * p.Q + j) * p.Cin + c0) * (int)sizeof(out_t) : (int)kOutOfRange;      // < 2^31: checked by the host
 #pragma unroll
         for (int b = 0; b < OB; b += 16)
             __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)((const char*)o + b), ry, obyte + b, 0, STREAM ? TIR_STORE_AUX_STREAM : TIR_STORE_AUX);
@@ -250,6 +255,23 @@ inline long long depthwise_workgroups(int dt, long long N, long long P, long lon
 inline int depthwise_pixels(int dt, int out, long long N, long long P, long long Q, long long C, int stride_w) {
     if (stride_w != 1 || out == DT_I32 || depthwise_workgroups(dt, N, P, Q, C, 8) > 2 * 256) return kDwBlockPix;
     return depthwise_workgroups(dt, N, P, Q, C, kDwBlockPix) > (out == DT_BF16 ? 2 : 3) * 256 ? 8 : kDwBlockPix;
+}
+
+// Rows of output pixels per thread of the blocked kernel at stride 1, undilated, P x Q output pixels: two rows of four, or one (of depthwise_pixels()).  Two
+// rows fetch a fifth less per pixel than eight in a row, but hold 24 vectors at once (fp16 170 registers, bf16 245: two workgroups per CU, where four in a
+// row have four and two), so a launch that has not a workgroup of four for every CU is slower (1.2 - 1.3 of the time: half as many CUs work).  From there on:
+// bf16 gains everywhere, 104 of 106 drawn calls 0.74 - 0.99 of the time (0.88 in the mean), but for a last round of a few workgroups.  fp16 gains while every
+// CU has at most one workgroup (and a whole block of 64 channels: 3x98x112x48 4.7 / 4.9), 0.88 - 1.01, and from 800 on, 0.84 - 0.99; between, four or eight in a row
+// have more workgroups in flight.  One row and two, us, three sets of buffers in turn:
+//   bf16: 10x72x22x208 8.4 / 7.7, 32x56x56x128 15.4 / 13.2, 32x112x112x64 31.2 / 26.6, 11x100x49x176 16.4 / 12.1; slower: 8x85x19x464 8.7 / 9.9, 25x47x39x80 7.5 / 7.8,
+//         25x43x57x112 (516 workgroups) 11.2 / 11.9
+//   fp16: 18x14x41x144 5.7 / 5.0, 20x43x11x336 6.2 / 5.7, 17x32x105x240 20.2 / 17.5, 32x112x112x64 28.4 / 26.1; 16x56x56x128 (392 workgroups) 7.85 / 8.08, 16x56x56x256 13.3 / 13.7
+// Not measured, and left with one row: fewer than seven rows of output, other types of output.
+inline int depthwise_rows(int dt, int out, long long N, long long P, long long Q, long long C) {
+    if (out != dt || dt == DT_I8 || P < 7 || depthwise_workgroups(dt, N, P, Q, C, kDwBlockPix) <= 256) return 1;
+    const long long two = depthwise_workgroups(dt, N, (P + 1) / 2, Q, C, kDwBlockPix);
+    if (dt == DT_BF16) return two <= 512 || two > 528 ? 2 : 1;
+    return (two <= 256 && C >= kDwChannels) || two > 800 ? 2 : 1;
 }
 
 typedef hipError_t (*dw_launch_fn)(const Params&, hipStream_t);

@@ -1454,6 +1454,26 @@ def test_depthwise_convolution_where_eight_pixels_per_thread_pay(B, oracle, dtyp
         PT.assert_close(got, ref, S, wl.name)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n,p,w,c,pad,rows", [(3, 251, 42, 64, (1, 1), 2), (6, 57, 53, 72, (0, 2), 2), (5, 7, 1171, 64, (1, 1), 2), (18, 301, 39, 64, (1, 1), 2), (6, 6, 1171, 64, (1, 1), 1)])
+def test_depthwise_convolution_of_two_rows_per_thread(B, oracle, dtype, n, p, w, c, pad, rows):
+    """One workgroup of two rows of four pixels on most CUs, and 800 and more: an odd last row of pixels, columns that are no multiple of four, a channel block
+    of one vector, padding other than one, the fewest rows.  bfloat16 output adds its own rounding, 2^-8 |y|."""
+    h, width = p + 2 - 2 * pad[0], w + 2 - 2 * pad[1]
+    assert B.tir_debug_depthwise_rows(n, p, w, c, dtype, dtype) == rows
+    wl = I.Workload(f"dw2x4_{dtype}_{n}x{p}x{w}c{c}", "conv2d", dtype, dtype, "n0.1", 9990 + p, n=n, h=h, w=width, c=c, k=c, r=3, s=3, pad=pad, groups=c,
+                    ep_bias=True, ep_relu=p % 2 == 0)
+    _say(f"{wl.name} -> {PT.variant_name(B, wl)}")
+    assert "depthwise" in PT.variant_name(B, wl)
+    a_bits, b_bits = wl.operands()
+    ref, S = PT.run_oracle(wl, a_bits, b_bits, oracle)
+    got = PT.run_gpu(wl, a_bits, b_bits)
+    if dtype == "bf16":
+        assert np.all(np.abs(got - ref) <= PT.RTOL_S * S + PT.ATOL + np.abs(ref) * 2.0 ** -8)
+    else:
+        PT.assert_close(got, ref, S, wl.name)
+
+
 # ------------------------------------------------------------------------------ more batches than one grid dimension holds
 @pytest.mark.parametrize("K,bias", [(16, False), (24, True), (5, True)])
 def test_batch_count_beyond_one_launch(B, oracle, K, bias):
