@@ -260,12 +260,12 @@ inline int depthwise_pixels(int dt, int out, long long N, long long P, long long
 // Rows of output pixels per thread of the blocked kernel at stride 1, undilated, P x Q output pixels: two rows of four, or one (of depthwise_pixels()).  Two
 // rows fetch a fifth less per pixel than eight in a row, but hold 24 vectors at once (fp16 170 registers, bf16 245: two workgroups per CU, where four in a
 // row have four and two), so a launch that has not a workgroup of four for every CU is slower (1.2 - 1.3 of the time: half as many CUs work).  From there on:
-// bf16 gains everywhere, 104 of 106 drawn calls 0.74 - 0.99 of the time (0.88 in the mean), but for a last round of a few workgroups.  fp16 gains while every
+// bf16 gains everywhere, 103 of 105 drawn calls 0.74 - 0.99 of the time (0.89 in the mean), but for a last round of a few workgroups.  fp16 gains while every
 // CU has at most one workgroup (and a whole block of 64 channels: 3x98x112x48 4.7 / 4.9), 0.88 - 1.01, and from 800 on, 0.84 - 0.99; between, four or eight in a row
 // have more workgroups in flight.  One row and two, us, three sets of buffers in turn:
 //   bf16: 10x72x22x208 8.4 / 7.7, 32x56x56x128 15.4 / 13.2, 32x112x112x64 31.2 / 26.6, 11x100x49x176 16.4 / 12.1; slower: 8x85x19x464 8.7 / 9.9, 25x47x39x80 7.5 / 7.8,
-//         25x43x57x112 (516 workgroups) 11.2 / 11.9
-//   fp16: 18x14x41x144 5.7 / 5.0, 20x43x11x336 6.2 / 5.7, 17x32x105x240 20.2 / 17.5, 32x112x112x64 28.4 / 26.1; 16x56x56x128 (392 workgroups) 7.85 / 8.08, 16x56x56x256 13.3 / 13.7
+//         25x43x57x112 (516 workgroups, one row by the rule) 11.2 / 11.9
+//   fp16: 18x14x41x144 5.7 / 5.0, 20x43x11x336 6.2 / 5.7, 17x32x105x240 20.2 / 17.5, 32x112x112x64 28.4 / 26.1; one row by the rule: 16x56x56x128 (392 workgroups) 7.85 / 8.08, 16x56x56x256 (784) 13.3 / 13.7
 // Not measured, and left with one row: fewer than seven rows of output, other types of output.
 inline int depthwise_rows(int dt, int out, long long N, long long P, long long Q, long long C) {
     if (out != dt || dt == DT_I8 || P < 7 || depthwise_workgroups(dt, N, P, Q, C, kDwBlockPix) <= 256) return 1;
