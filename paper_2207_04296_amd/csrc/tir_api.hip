@@ -566,39 +566,56 @@ struct BlockPlan {
 struct BlockProblem {
     int64_t images, P, Q, cols, batch, bytes;
     int taps, dil_h, dil_w, out_bytes;
+    bool phased;
 };
 
 // Expected time of a launch in shader cycles, for the choice between the channel-block kernel, the implicit-GEMM tiles and the patch kernel for
-// pixels of 128 bytes, and between the first one's tiles: a number of rounds over the CUs times what a workgroup takes, its loop (the slower of
-// copying and multiplying) and its set-up and store.  The constants are fitted to 1276 drawn stride-1 convolutions (3x3, 5x5 and 4x4 stride 2 by
-// phase) and 350 of 128-byte pixels, every tile timed with three sets of operands in turn; a time is met to 10 % in the mean.  On the half that was not fitted
-// the choice gives 0.89 of the implicit-GEMM time (the best tile of each call 0.87) and 0.80 of the patch kernel's (0.78).
-static double blocks_cycles(const Variant* v, const BlockProblem& b, int64_t ncb, int64_t units, int64_t lds, int64_t workgroups) {
+// pixels of 128 bytes, and between the first one's tiles and strips: a number of rounds over the CUs times what a workgroup takes, its loop (the slower of
+// copying and multiplying) and its set-up and store.  Fitted to half of 8623 drawn stride-1 convolutions (3x3, 5x5 and 4x4 stride 2 by
+// phase), every tile timed in every number of strips with three sets of operands in turn, first to the times and then to the choice that follows.  On the other
+// half: times met to 7 % (root mean square; implicit GEMM 8), the choice at 0.85 of the other kernels' time in the geometric mean (the best tile of each call 0.84), and
+// 17 of 4312 calls more than 5 % slower than there, 5 more than 10 %.  Known ones, that time and this kernel's: 30x22x78, 272 -> 144, dilation 2 fp16 to fp32 61.8 and
+// 70.9 us, 2x58x63, 64 -> 480 in each of 8 groups, 5x5 int8 to int32 69.2 and 74, 20x20x26, 16 -> 160 in each of 4 groups fp16 to fp32 9.9 and 11.2, 7x19x80, 64 -> 96 in
+// each of 2 groups, dilation 2 6.8 and 7.5, 3x12x36, 496 -> 272, dilation 2 13.7 and 15.2, 1x106x15, 160 -> 16 in each of 4 groups, 5x5 12.1 and 12.9.
+static double whole_rounds(double rounds, double n) { return n * (double)(int64_t)((rounds + n) / n - 1e-9); }      // up to a multiple of n
+static double blocks_cycles(const Variant* v, const BlockProblem& b, int64_t ncb, int64_t units, int64_t lds, int64_t workgroups, int64_t strips) {
     const double taps = (double)b.taps * b.taps, slab = v->bn * v->rowb / 1024.0;
     const double mfma = (double)(v->bm / 32) * (v->bn / 32) * (v->rowb / 32) * 8.0;        // cycles of a tap's MFMAs on four SIMDs
-    const double copy = 18.6 * ((double)units + taps * slab), work = taps * (1.14 * mfma + 108.0);
-    const double loop = (double)ncb * (copy > work ? copy : work), fixed = 4690.0 + 2.0 * (double)units + 4.3 * v->bm * v->bn * b.out_bytes / 1024.0;
-    const double rounds = (double)workgroups / kCUs;
-    if (rounds <= 1.0) return 3410.0 + loop + fixed;
-    // Two workgroups share a CU where registers and LDS allow it (block_pair() in tir_conv_blocks.h) and cover each other's set-up and store; the others
-    // come in whole rounds.
+    const double copy = 16.5 * ((double)units + taps * slab), work = taps * (1.125 * mfma + 60.0);
+    // (the store of a phase or of more than one strip decodes its rows: 8x28x28, 32 -> 32 in each of 8 groups, dilation 2 int8 4.95 in one strip, 5.35 in two)
+    const double fixed = 4590.0 + 10.2 * (double)units + 10.4 * v->bm * v->bn * b.out_bytes / 1024.0 + (b.phased || strips > 1 ? 3.7 * v->bm : 0.0);
+    const double loop = (double)ncb * ((copy > work ? copy : work) + 590.0), rounds = (double)workgroups / kCUs;
+    if (rounds <= 1.0) return 2010.0 + loop + fixed;
+    // A last round that is partly filled takes most of a whole one's time, which matters against 256x256 and 256x128 tiles of one round: 6x33x45, 192 -> 128
+    // transposed fp16 in 560 workgroups, two per CU, 17.9 us and 14.1.  Two share a CU where registers and LDS allow it
+    // (block_pair() in tir_conv_blocks.h) and cover each other's set-up and store.
     const bool wide = v->bm * v->bn >= 128 * 64, pair = (!wide || (v->rowb == 64 && v->bm * v->bn < 256 * 64 && b.taps < 5)) && lds <= 80 * 1024;
-    if (pair) return 3410.0 + (loop + 0.51 * fixed) * (rounds + 0.73);
-    const double whole = (double)((workgroups + (int64_t)kCUs - 1) / (int64_t)kCUs);
-    return 3410.0 + (loop + fixed) * (0.76 * whole + 0.24 * (rounds + 0.5));
+    if (pair) return 2010.0 + (loop + 0.36 * fixed) * 0.5 * (whole_rounds(rounds, 2.0) + rounds) + 0.5 * fixed;
+    return 2010.0 + (loop + fixed) * (0.85 * whole_rounds(rounds, 1.0) + 0.15 * (rounds + 0.5));
 }
 static double gather_cycles(const Variant* v, const BlockProblem& b, int ksplit) {
-    const double mfma = (double)(v->bm / 32) * (v->bn / 32) * 4.0 * 8.0, copy = 29.3 * (v->bm + v->bn) * 128.0 / 1024.0;
-    const int64_t stages = ((int64_t)b.taps * b.taps * b.bytes + 127) / 128;
+    const bool ragged = v->amode == A_CONV_RAGGED;
+    const int64_t taps = (int64_t)b.taps * b.taps;
+    const int64_t stages = b.phased ? taps * ((b.bytes + v->rowb - 1) / v->rowb) : (taps * b.bytes + v->rowb - 1) / v->rowb;        // by phase a stage holds channels of one tap
     const int64_t pixels = b.images * b.P * b.Q, tiles = ((pixels + v->bm - 1) / v->bm) * ((b.cols + v->bn - 1) / v->bn) * b.batch * ksplit;
-    const double loop = (copy > 1.75 * mfma ? copy : 1.75 * mfma) * (double)stages / ksplit * (b.bytes % 128 ? 1.08 : 1.0);
-    const double fixed = 3460.0 + 34.3 * v->bm * v->bn * b.out_bytes / 1024.0 + (ksplit > 1 ? 6440.0 : 0.0);
-    const double rounds = (double)tiles / kCUs;
-    return 4370.0 + (rounds <= 1.0 ? loop + fixed : (loop + 0.64 * fixed) * (rounds + 0.75));
+    const double rounds = (double)tiles / kCUs, area = v->bm * v->bn, busy = rounds < 1.0 ? rounds : 1.0;
+    // Pixels that straddle 128-byte lines cost large tiles a fifth more copy time (11x38x24, 416 -> 240 in 128x96 tiles 30.2 us, 16 us of MFMAs).
+    const bool straddle = !b.phased && b.bytes > 128 && b.bytes % 128 != 0 && v->rowb == 128 && v->kw == 1 && area >= 128 * 64;
+    const double copy = (straddle ? 35.9 : 30.4) * (v->bm + v->bn) * v->rowb / 1024.0;
+    const double work = 1.667 * (v->bm / 32) * (v->bn / 32) * (v->rowb / 32) * 8.0 * (0.373 + 0.627 * busy);      // (a chip that is partly idle clocks higher)
+    const double issue = v->cw ? 0.0 : 95.0 * v->rowb / 128.0 / v->kw;    // the copies' addresses, unless copy waves work them out
+    const double loop = ((copy > work ? copy : work) + issue) * (double)stages / ksplit * (ragged ? 1.064 : 1.0);
+    const double fixed = 6550.0 + 37.9 * area * b.out_bytes / 1024.0 + (ksplit > 1 ? 6690.0 : 0.0);
+    if (rounds <= 1.0) return 786.0 + loop + fixed;
+    // workgroups per CU: LDS, four waves per SIMD, registers
+    const int waves = v->wm * v->wn, by_lds = 160 * 1024 / ((v->bm + v->bn) * v->rowb * v->nstage * v->kw), by_waves = 16 / (waves * v->kw + v->cw);
+    const int resident = v->bm * v->bn >= 4096 * waves ? 1 : by_lds < by_waves ? by_lds : by_waves;
+    if (resident > 1) return 786.0 + (loop + 0.215 * fixed) * (0.825 * whole_rounds(rounds, resident) + 0.175 * rounds) + 0.195 * fixed;
+    return 786.0 + (loop + fixed) * (0.6 * whole_rounds(rounds, 1.0) + 0.4 * (rounds + 0.5));
 }
-static double patch_cycles(const BlockProblem& b) {
-    const double wg = 5810.0 + 588.0 * b.taps * b.taps, rounds = (double)(b.images * ((b.P * b.Q + 255) / 256) * ((b.cols + 63) / 64) * b.batch) / kCUs;
-    return 2590.0 + wg * (rounds <= 1.0 ? 1.0 : rounds + 0.95);
+static double patch_cycles(const BlockProblem& b) {        // (2x2 or 3x3: the slabs of 25 taps do not fit LDS)
+    const double rounds = (double)(b.images * ((b.P * b.Q + 255) / 256) * ((b.cols + 63) / 64) * b.batch) / kCUs;
+    return 560.0 + (8180.0 + 588.0 * b.taps * b.taps) * whole_rounds(rounds, 1.0);
 }
 
 // Strips for tile v: the cheapest of a few widths whose patch fits LDS; false where none does.
@@ -622,7 +639,7 @@ static bool plan_blocks(const Variant* v, const BlockProblem& b, BlockPlan* plan
         const int64_t lds = ring + units * 1024 * (ncb > 1 ? 2 : 1);
         if (lds > 160 * 1024) continue;
         const int64_t strip_tiles = ((int64_t)rows_all * tw + bm - 1) / bm;
-        const double cycles = blocks_cycles(v, b, ncb, units, lds, strip_tiles * strips * tiles_n);
+        const double cycles = blocks_cycles(v, b, ncb, units, lds, strip_tiles * strips * tiles_n, strips);
         if (found && cycles >= plan->cycles) continue;
         found = true;
         *plan = BlockPlan{v, (int)tw, (int)pw, (int)(P - 1 + span_h), (int)(units * 1024), (int)lds, (int)strips, (int)strip_tiles, cycles};
@@ -724,7 +741,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     const bool blocks_ok = (amode == A_CONV || amode == A_CONV_RAGGED) && (taps == 2 || taps == 3 || taps == 5) &&
                            (phased ? R == taps * g.stride_h && S == taps * g.stride_w : S == R && g.stride_h == 1 && g.stride_w == 1) &&
                            Mg * K * elem_size(out) < kMaxExtent && Cg * es < 65536;
-    const BlockProblem block_problem = {N, phased ? Pp : P, phased ? Qp : Q, Kg, phased ? groups * phases : groups, Cg * es, (int)taps, g.dil_h, g.dil_w, elem_size(out)};
+    const BlockProblem block_problem = {N, phased ? Pp : P, phased ? Qp : Q, Kg, phased ? groups * phases : groups, Cg * es, (int)taps, g.dil_h, g.dil_w, elem_size(out), phased};
     BlockPlan blocks = {};
     // records are kept under the implicit-GEMM signature; a record (or a trial) may name either kernel family
     const int64_t geom[21] = {N, groups, D, H, W, T, R, S, g.stride_d, g.stride_h, g.stride_w, g.pad_d, g.pad_h, g.pad_w, g.dil_d, g.dil_h, g.dil_w,
@@ -761,13 +778,14 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         const bool use_patch = patch_ok && !g_force_ksplit && (g_force_name[0] ? strstr(g_force_name, "patch") != nullptr : !one_tap);
         if (use_patch) ch = pick(in, out, A_CONV_PATCH, bmode, groups * N, P * Q, Kg, Kd, sl);
         else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
-        // From 0.95 of the other kernel's expected time on (0.93 of the patch kernel's): beyond, as many calls lose by the estimates' error as gain.
+        // From 0.94 of the other kernel's expected time on: beyond, calls are lost to the estimates' error that gain nothing in the mean (at 0.97 three times as many
+        // are more than 5 % slower).
         // (Two kinds of call stay with their implicit-GEMM tile although this kernel is the faster one, because the test of the variant choice names it: 5x5 filters to at
         // most 32 channels from two blocks of 128 bytes that are not full, 25x14x43, 96 -> 32 fp16 11.5 and 10.2 us, 14x11x34, 112 -> 16 in each of 8 groups 25.5 and
         // 16.1; and by phase 2x2 taps of one block to at most 32 channels, a tenth.)
         const bool kept = taps == 5 ? Kg <= 32 && Cg * es > 128 && Cg * es < 256 : taps == 2 && Kg <= 32 && Cg * es <= 128;
         if (blocks_ok && !kept && ch.v && !g_force_name[0] && !g_force_bm && !g_force_ksplit) {
-            double limit = use_patch ? 0.93 * patch_cycles(block_problem) : 0.95 * gather_cycles(ch.v, block_problem, ch.ksplit);
+            double limit = 0.94 * (use_patch ? patch_cycles(block_problem) : gather_cycles(ch.v, block_problem, ch.ksplit));
             const VariantRange c = variants_of(in, out, A_CONV_BLOCKS, B_KMAJOR);
             for (int i = 0; i < c.n; ++i) {
                 BlockPlan tile;

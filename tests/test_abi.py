@@ -196,6 +196,28 @@ def test_variant_choice_of_measured_calls(call, variant):
     assert name == f"{dtype}_{out}_{variant}"
 
 
+@pytest.mark.parametrize("call,variant", [
+    # us with this kernel and with the other one: the implicit GEMM or the patch kernel of 128-byte pixels, and the channel-block kernel
+    (("tconv", 6, 33, 45, 192, 128, "f16", "f16"), "t256x128w4x2s3c4_conv/ph2x2"),                # 14.9, 18.4: 560 workgroups of blocks, two per CU
+    (("tconv", 5, 48, 40, 96, 224, "f16", "f16"), "t256x256w2x4s4r64_convr/ph2x2"),               # 15.8, 19.5
+    (("tconv", 17, 19, 29, 64, 224, "bf16", "bf16"), "t256x256w2x4s4r64_conv/ph2x2"),             # 12.9, 15.4
+    (("conv", 29, 21, 39, 112, 144, 3, 1, 2, 1, "bf16", "f32"), "t128x192w2x2s3c4_conv"),         # 13.5, 18.3
+    (("conv", 5, 40, 29, 256, 2048, 3, 1, 1, 8, "f16", "f16"), "t256x256w2x4s4r64_conv"),         # 13.8, 15.4
+    (("conv", 7, 50, 49, 128, 224, 5, 1, 1, 2, "bf16", "bf16"), "t256x128w4x2s3c4_conv"),         # 20.5, 27.8
+    (("conv", 1, 21, 109, 256, 3328, 3, 1, 2, 8, "i8", "i32"), "t256x256w2x4s4r64_conv"),         # 10.8, 14.2
+    (("conv", 5, 96, 71, 16, 192, 3, 1, 1, 1, "i8", "i32"), "t256x256w2x4s3r64_conv"),            # 8.9, 11.0
+    (("tconv", 16, 14, 14, 256, 128, "f16", "f16"), "patch128x64w2x2r128_conv/ph2x2"),            # 10.7, 8.6
+    (("tconv", 31, 38, 15, 192, 128, "bf16", "bf16"), "patch256x64w4x1r64_conv/ph2x2"),           # 42.6, 27.2: 128x128 tiles of two stages, three rounds
+    (("conv", 8, 28, 28, 256, 256, 3, 1, 2, 8, "i8", "i8"), "patch256x32w4x1r64_conv"),           # 5.6, 4.9
+    (("conv", 7, 88, 42, 704, 512, 3, 1, 1, 4, "i8", "i8"), "patch256x64w4x1r64_conv"),           # 62.7, 35.6
+    (("conv", 14, 88, 55, 64, 112, 5, 1, 2, 1, "f16", "f16"), "patch256x64w4x1r64_conv"),         # 66.0, 38.2
+    (("conv", 3, 42, 48, 64, 16, 3, 1, 1, 1, "f16", "f16"), "patch64x64w2x2r128_conv"),           # 6.4, 4.4
+])
+def test_channel_block_choice_of_measured_calls(call, variant):
+    """Stride-1 convolutions on both sides of the line between the channel-block kernel and the others."""
+    test_variant_choice_of_measured_calls(call, variant)
+
+
 def test_few_channels_take_the_row_kernel_where_it_pays():
     """Vectors of one tap that are not whole: filter rows as the unit of the reduction, unless the reduction is one
     stage in one round of workgroups and the patch (wide strides, many channels) takes longer to copy than the element-wise kernel takes
