@@ -780,11 +780,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         else ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, phased ? kNoSplit : sl, phased ? (int)(Cg * es >= 256 && (Cg * es) % 256 == 0 ? 256 : 128) : 256);
         // From 0.94 of the other kernel's expected time on: beyond, calls are lost to the estimates' error that gain nothing in the mean (at 0.97 three times as many
         // are more than 5 % slower).
-        // (Two kinds of call stay with their implicit-GEMM tile although this kernel is the faster one, because the test of the variant choice names it: 5x5 filters to at
-        // most 32 channels from two blocks of 128 bytes that are not full, 25x14x43, 96 -> 32 fp16 11.5 and 10.2 us, 14x11x34, 112 -> 16 in each of 8 groups 25.5 and
-        // 16.1; and by phase 2x2 taps of one block to at most 32 channels, a tenth.)
-        const bool kept = taps == 5 ? Kg <= 32 && Cg * es > 128 && Cg * es < 256 : taps == 2 && Kg <= 32 && Cg * es <= 128;
-        if (blocks_ok && !kept && ch.v && !g_force_name[0] && !g_force_bm && !g_force_ksplit) {
+        if (blocks_ok && ch.v && !g_force_name[0] && !g_force_bm && !g_force_ksplit) {
             double limit = 0.94 * (use_patch ? patch_cycles(block_problem) : gather_cycles(ch.v, block_problem, ch.ksplit));
             const VariantRange c = variants_of(in, out, A_CONV_BLOCKS, B_KMAJOR);
             for (int i = 0; i < c.n; ++i) {

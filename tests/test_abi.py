@@ -174,12 +174,16 @@ def test_variant_choice_reflects_layout():
     (("gemm", 84, 608, 656, 64, "t", "bf16", "f32"), "t256x256w2x4s2_ak_bk"),                 # 36.7, 43.2 in 64x64
     (("conv", 16, 106, 90, 128, 288, 3, 2, 1, 1, "bf16", "bf16"), "t256x96w4x1s3c4_conv"),    # 34.8, 45.3 in 128x96
     (("conv", 3, 18, 57, 464, 160, 5, 1, 2, 1, "f16", "f16"), "t128x32w4x1s3k2_conv/z2"),     # 34.8, 44.8 in one slice
-    (("conv", 25, 14, 43, 96, 32, 5, 1, 1, 1, "f16", "f16"), "t64x32w2x1s4k2_conv"),          # 11.0, 13.6 in two slices
+    (("conv", 25, 14, 43, 96, 32, 5, 1, 1, 1, "f16", "f16"), "patch128x32w4x1r128_conv"),     # 10.1; 11.1 in 64x32 tiles of two reduction groups
     (("conv", 11, 70, 43, 256, 384, 5, 1, 1, 8, "i8", "i32"), "t128x64w2x2s3_conv"),          # 39.1, 44.8 with copy waves
     (("conv", 3, 70, 100, 672, 576, 1, 1, 1, 2, "i8", "i8"), "t256x96w4x1s3c4_conv"),        # three stages: 16.7, 20.5 in 128x64
-    (("conv", 14, 11, 34, 896, 128, 5, 1, 1, 8, "f16", "f16"), "t64x32w2x1s4_conv"),          # 29.0, 33.1 in 256x32
+    (("conv", 14, 11, 34, 896, 128, 5, 1, 1, 8, "f16", "f16"), "patch256x32w4x1r64_conv"),    # 14.6; 25.8 in 64x32
     (("conv", 4, 110, 86, 80, 32, 1, 1, 1, 1, "f16", "f16"), "t64x32w2x1s4_conv"),            # 4.94, 5.39 in 256x32
-    (("tconv", 31, 7, 34, 64, 32, "bf16", "bf16"), "t128x32w4x1s4_conv/ph2x2"),               # 5.50, 5.70 in two reduction groups
+    (("tconv", 31, 7, 34, 64, 32, "bf16", "bf16"), "patch128x32w4x1r128_conv/ph2x2"),         # 4.2 - 4.5; 5.0 in 128x32
+    # as many pixels, columns and products for the score as these three, strided or of one tap: the channel-block kernel does not take them
+    (("conv", 25, 28, 86, 96, 32, 5, 2, 1, 1, "f16", "f16"), "t64x32w2x1s4k2_conv"),          # 11.2, 14.7 in two slices
+    (("conv", 14, 22, 68, 896, 128, 5, 2, 1, 8, "f16", "f16"), "t64x32w2x1s4_conv"),          # 31.5, 39.8 in 256x32
+    (("conv", 31, 7, 34, 1024, 128, 1, 1, 1, 4, "bf16", "bf16"), "t128x32w4x1s4_conv"),       # 5.40, 5.76 in two reduction groups
 ])
 def test_variant_choice_of_measured_calls(call, variant):
     """One call per rule of the scoring that corrects a slower choice, and calls just beyond."""
@@ -206,12 +210,15 @@ def test_variant_choice_of_measured_calls(call, variant):
     (("conv", 7, 50, 49, 128, 224, 5, 1, 1, 2, "bf16", "bf16"), "t256x128w4x2s3c4_conv"),         # 20.5, 27.8
     (("conv", 1, 21, 109, 256, 3328, 3, 1, 2, 8, "i8", "i32"), "t256x256w2x4s4r64_conv"),         # 10.8, 14.2
     (("conv", 5, 96, 71, 16, 192, 3, 1, 1, 1, "i8", "i32"), "t256x256w2x4s3r64_conv"),            # 8.9, 11.0
+    (("conv", 16, 56, 56, 64, 64, 3, 1, 1, 1, "f16", "f16"), "patch256x64_conv"),                 # 7.2, 7.4
     (("tconv", 16, 14, 14, 256, 128, "f16", "f16"), "patch128x64w2x2r128_conv/ph2x2"),            # 10.7, 8.6
     (("tconv", 31, 38, 15, 192, 128, "bf16", "bf16"), "patch256x64w4x1r64_conv/ph2x2"),           # 42.6, 27.2: 128x128 tiles of two stages, three rounds
     (("conv", 8, 28, 28, 256, 256, 3, 1, 2, 8, "i8", "i8"), "patch256x32w4x1r64_conv"),           # 5.6, 4.9
     (("conv", 7, 88, 42, 704, 512, 3, 1, 1, 4, "i8", "i8"), "patch256x64w4x1r64_conv"),           # 62.7, 35.6
     (("conv", 14, 88, 55, 64, 112, 5, 1, 2, 1, "f16", "f16"), "patch256x64w4x1r64_conv"),         # 66.0, 38.2
     (("conv", 3, 42, 48, 64, 16, 3, 1, 1, 1, "f16", "f16"), "patch64x64w2x2r128_conv"),           # 6.4, 4.4
+    (("conv", 2, 57, 59, 896, 128, 5, 1, 1, 8, "bf16", "f32"), "patch256x32w4x1r64_conv"),        # 46.9, 15.7
+    (("tconv", 29, 17, 54, 64, 32, "bf16", "bf16"), "patch256x32w4x1r64_conv/ph2x2"),             # 10.4, 7.1
 ])
 def test_channel_block_choice_of_measured_calls(call, variant):
     """Stride-1 convolutions on both sides of the line between the channel-block kernel and the others."""
