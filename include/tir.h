@@ -328,6 +328,9 @@ unsigned tir_debug_fastdiv(unsigned d, unsigned m);
 int tir_debug_depthwise_pixels(int64_t N, int64_t P, int64_t Q, int64_t C, int stride_w, tir_dtype in, tir_dtype out);
 /* Rows of output pixels per thread of that kernel at stride 1, undilated: 1, or 2 of four pixels each. */
 int tir_debug_depthwise_rows(int64_t N, int64_t P, int64_t Q, int64_t C, tir_dtype in, tir_dtype out);
+/* Of the calling thread's last convolution call or variant query: tiles and strip widths of the channel-block kernel that were planned, and the strips of output
+ * columns it runs in (0: another kernel). */
+void tir_debug_block_plan(int* planned, int* strips);
 /* Name of the kernel tir_attention launches for these sizes, head dimension (64 or 128) and output type: its tile of queries and form. */
 const char* tir_debug_attention_kernel(int64_t batch, int64_t M, int64_t N, int64_t d, tir_dtype out);
 

@@ -20,7 +20,7 @@ DTYPE_CODES = {"f16": TIR_F16, "bf16": TIR_BF16, "i8": TIR_I8, "f32": TIR_F32, "
 
 EXPORTS = ["tir_gemm", "tir_batch_matmul", "tir_conv2d", "tir_last_error", "tir_gemm_variant",
            "tir_conv2d_variant", "tir_debug_force_tile", "tir_debug_force_variant", "tir_debug_variant_count",
-           "tir_debug_variant_name", "tir_debug_tile_of_block", "tir_debug_depthwise_pixels", "tir_debug_depthwise_rows", "tir_debug_attention_kernel",
+           "tir_debug_variant_name", "tir_debug_tile_of_block", "tir_debug_depthwise_pixels", "tir_debug_depthwise_rows", "tir_debug_block_plan", "tir_debug_attention_kernel",
            "tir_probe_mfma_rate", "tir_version",
            "tir_tune_batch_matmul", "tir_tune_conv2d", "tir_tune_count", "tir_tune_clear", "tir_tune_save",
            "tir_tune_load", "tir_gemm_fused", "tir_batch_matmul_fused", "tir_conv2d_fused", "tir_attention",
@@ -105,6 +105,8 @@ def lib() -> ctypes.CDLL:
     L.tir_debug_depthwise_pixels.restype = ci
     L.tir_debug_depthwise_rows.argtypes = [i64] * 4 + [ci] * 2
     L.tir_debug_depthwise_rows.restype = ci
+    L.tir_debug_block_plan.argtypes = [ctypes.POINTER(ci)] * 2
+    L.tir_debug_block_plan.restype = None
     L.tir_debug_attention_kernel.argtypes = [i64] * 4 + [ci]
     L.tir_debug_attention_kernel.restype = ctypes.c_char_p
     L.tir_probe_mfma_rate.argtypes = [vp, ci, ci, ctypes.POINTER(ctypes.c_double), vp]
@@ -301,6 +303,13 @@ def tir_debug_depthwise_pixels(N: int, P: int, Q: int, C: int, stride_w: int, in
 
 def tir_debug_depthwise_rows(N: int, P: int, Q: int, C: int, in_dtype, out_dtype) -> int:
     return int(lib().tir_debug_depthwise_rows(N, P, Q, C, _code(in_dtype), _code(out_dtype)))
+
+
+def tir_debug_block_plan() -> tuple[int, int]:
+    """(tiles and strip widths planned, strips) of this thread's last convolution call or variant query for the channel-block kernel."""
+    planned, strips = ctypes.c_int(0), ctypes.c_int(0)
+    lib().tir_debug_block_plan(ctypes.byref(planned), ctypes.byref(strips))
+    return planned.value, strips.value
 
 
 def tir_debug_attention_kernel(batch: int, M: int, N: int, d: int, out_dtype) -> str:

@@ -555,11 +555,10 @@ struct ConvGeom {
     int outpad_h, outpad_w;      // transposed only
 };
 
-// The channel-block kernel on one of its tiles: strips of output columns, patch, LDS, and what the launch is expected to take.
+// The channel-block kernel on one of its tiles: strips of output columns, patch, LDS.
 struct BlockPlan {
     const Variant* v;
     int tw, pw, vh, patch, lds, strips, strip_tiles;
-    double cycles;
 };
 // A stride-1 convolution as the kernel sees it: `batch` independent ones (groups, phases) of images x P x Q pixels, `cols` output channels each,
 // taps x taps of them dil_h and dil_w apart, `bytes` of channels per pixel.
@@ -577,28 +576,58 @@ struct BlockProblem {
 // 17 of 4312 calls more than 5 % slower than there, 5 more than 10 %.  Known ones, that time and this kernel's: 30x22x78, 272 -> 144, dilation 2 fp16 to fp32 61.8 and
 // 70.9 us, 2x58x63, 64 -> 480 in each of 8 groups, 5x5 int8 to int32 69.2 and 74, 20x20x26, 16 -> 160 in each of 4 groups fp16 to fp32 9.9 and 11.2, 7x19x80, 64 -> 96 in
 // each of 2 groups, dilation 2 6.8 and 7.5, 3x12x36, 496 -> 272, dilation 2 13.7 and 15.2, 1x106x15, 160 -> 16 in each of 4 groups, 5x5 12.1 and 12.9.
-static double whole_rounds(double rounds, double n) { return n * (double)(int64_t)((rounds + n) / n - 1e-9); }      // up to a multiple of n
-static double blocks_cycles(const Variant* v, const BlockProblem& b, int64_t ncb, int64_t units, int64_t lds, int64_t workgroups, int64_t strips) {
-    const double taps = (double)b.taps * b.taps, slab = v->bn * v->rowb / 1024.0;
-    const double mfma = (double)(v->bm / 32) * (v->bn / 32) * (v->rowb / 32) * 8.0;        // cycles of a tap's MFMAs on four SIMDs
-    const double copy = 16.5 * ((double)units + taps * slab), work = taps * (1.125 * mfma + 60.0);
-    // (the store of a phase or of more than one strip decodes its rows: 8x28x28, 32 -> 32 in each of 8 groups, dilation 2 int8 4.95 in one strip, 5.35 in two)
-    const double fixed = 4590.0 + 10.2 * (double)units + 10.4 * v->bm * v->bn * b.out_bytes / 1024.0 + (b.phased || strips > 1 ? 3.7 * v->bm : 0.0);
-    const double loop = (double)ncb * ((copy > work ? copy : work) + 590.0), rounds = (double)workgroups / kCUs;
+static double whole_rounds(double rounds, int n) { return n * (double)(int)((n == 1 ? rounds : rounds / n) + (1.0 - 1e-9)); }      // up to a multiple of n (launches are below 2^31 workgroups)
+// What a tile takes whatever the problem's extents, for filters of one size; worked out once.
+struct BlockTile {
+    const Variant* v;
+    int bm_shift, bn_shift, row_shift;      // log2 of bm, bn, rowb
+    unsigned ring;                          // LDS of the filter
+    bool pair;                              // registers allow two workgroups per CU (block_pair() in tir_conv_blocks.h)
+    double slabs, work, store;              // a block's filter copies and products, the set-up and store of a workgroup without its patch
+    double decode;                          // (the store of a phase or of more than one strip decodes its rows)
+    double own_units;                       // copy instructions of a patch of just the tile's pixels
+};
+static const int kBlockTaps[] = {2, 3, 5}, kMaxBlockTiles = 8;
+static const double kNoLimit = 1e300;
+struct BlockTiles {
+    BlockTile tile[kMaxBlockTiles];
+    int n;
+};
+static const BlockTiles& block_tiles(int dt, int out, int taps) {
+    struct Index {
+        BlockTiles of[kDtypes][kDtypes][3] = {};
+        Index() {
+            for (const Variant& v : kVariants)
+                for (int i = 0; i < 3 && v.amode == A_CONV_BLOCKS; ++i) {
+                    BlockTiles& list = of[v.dt][v.out][i];
+                    const double rs = kBlockTaps[i] * kBlockTaps[i], mfma = (v.bm / 32) * (v.bn / 32) * (v.rowb / 32) * 8.0;       // cycles of a tap's MFMAs on four SIMDs
+                    const int area = v.bm * v.bn;
+                    if (list.n == kMaxBlockTiles) continue;
+                    list.tile[list.n++] = BlockTile{&v, __builtin_ctz(v.bm), __builtin_ctz(v.bn), __builtin_ctz(v.rowb), 3u * kBlockTaps[i] * v.bn * v.rowb,
+                                                    area < 128 * 64 || (v.rowb == 64 && area < 256 * 64 && kBlockTaps[i] < 5), 16.5 * rs * v.bn * v.rowb / 1024.0,
+                                                    rs * (1.125 * mfma + 60.0), 4590.0 + 10.4 * area * elem_size(v.out) / 1024.0, 3.7 * v.bm, v.bm * v.rowb / 1024.0};
+                }
+        }
+    };
+    static const Index index;
+    return index.of[dt][out][taps == 2 ? 0 : taps == 3 ? 1 : 2];
+}
+// decode: 8x28x28, 32 -> 32 in each of 8 groups, dilation 2 int8 takes 4.95 us in one strip, 5.35 in two.
+static double blocks_cycles(const BlockTile& t, double ncb, double units, bool decode, bool pair, double rounds) {
+    const double copy = 16.5 * units + t.slabs, fixed = t.store + 10.2 * units + (decode ? t.decode : 0.0);
+    const double loop = ncb * ((copy > t.work ? copy : t.work) + 590.0);
     if (rounds <= 1.0) return 2010.0 + loop + fixed;
     // A last round that is partly filled takes most of a whole one's time, which matters against 256x256 and 256x128 tiles of one round: 6x33x45, 192 -> 128
-    // transposed fp16 in 560 workgroups, two per CU, 17.9 us and 14.1.  Two share a CU where registers and LDS allow it
-    // (block_pair() in tir_conv_blocks.h) and cover each other's set-up and store.
-    const bool wide = v->bm * v->bn >= 128 * 64, pair = (!wide || (v->rowb == 64 && v->bm * v->bn < 256 * 64 && b.taps < 5)) && lds <= 80 * 1024;
-    if (pair) return 2010.0 + (loop + 0.36 * fixed) * 0.5 * (whole_rounds(rounds, 2.0) + rounds) + 0.5 * fixed;
-    return 2010.0 + (loop + fixed) * (0.85 * whole_rounds(rounds, 1.0) + 0.15 * (rounds + 0.5));
+    // transposed fp16 in 560 workgroups, two per CU, 17.9 us and 14.1.  Two on a CU cover each other's set-up and store.
+    if (pair) return 2010.0 + (loop + 0.36 * fixed) * 0.5 * (whole_rounds(rounds, 2) + rounds) + 0.5 * fixed;
+    return 2010.0 + (loop + fixed) * (0.85 * whole_rounds(rounds, 1) + 0.15 * (rounds + 0.5));
 }
 static double gather_cycles(const Variant* v, const BlockProblem& b, int ksplit) {
     const bool ragged = v->amode == A_CONV_RAGGED;
-    const int64_t taps = (int64_t)b.taps * b.taps;
-    const int64_t stages = b.phased ? taps * ((b.bytes + v->rowb - 1) / v->rowb) : (taps * b.bytes + v->rowb - 1) / v->rowb;        // by phase a stage holds channels of one tap
-    const int64_t pixels = b.images * b.P * b.Q, tiles = ((pixels + v->bm - 1) / v->bm) * ((b.cols + v->bn - 1) / v->bn) * b.batch * ksplit;
-    const double rounds = (double)tiles / kCUs, area = v->bm * v->bn, busy = rounds < 1.0 ? rounds : 1.0;
+    const unsigned taps = (unsigned)(b.taps * b.taps), bytes = (unsigned)b.bytes, rowb = (unsigned)v->rowb;
+    const unsigned stages = b.phased ? taps * ((bytes + rowb - 1u) / rowb) : (taps * bytes + rowb - 1u) / rowb;        // by phase a stage holds channels of one tap
+    const unsigned tiles_m = ((unsigned)(b.images * b.P * b.Q) + (unsigned)v->bm - 1u) / (unsigned)v->bm, tiles_n = ((unsigned)b.cols + (unsigned)v->bn - 1u) / (unsigned)v->bn;
+    const double rounds = (double)tiles_m * (double)tiles_n * (double)(b.batch * ksplit) * (1.0 / kCUs), area = v->bm * v->bn, busy = rounds < 1.0 ? rounds : 1.0;
     // Pixels that straddle 128-byte lines cost large tiles a fifth more copy time (11x38x24, 416 -> 240 in 128x96 tiles 30.2 us, 16 us of MFMAs).
     const bool straddle = !b.phased && b.bytes > 128 && b.bytes % 128 != 0 && v->rowb == 128 && v->kw == 1 && area >= 128 * 64;
     const double copy = (straddle ? 35.9 : 30.4) * (v->bm + v->bn) * v->rowb / 1024.0;
@@ -618,31 +647,73 @@ static double patch_cycles(const BlockProblem& b) {        // (2x2 or 3x3: the s
     return 560.0 + (8180.0 + 588.0 * b.taps * b.taps) * whole_rounds(rounds, 1.0);
 }
 
-// Strips for tile v: the cheapest of a few widths whose patch fits LDS; false where none does.
-static bool plan_blocks(const Variant* v, const BlockProblem& b, BlockPlan* plan) {
-    const unsigned bm = (unsigned)v->bm, P = (unsigned)b.P, Q = (unsigned)b.Q, rows_all = (unsigned)(b.images * b.P);
-    const unsigned span_h = (unsigned)((b.taps - 1) * b.dil_h + 1), span_w = (unsigned)((b.taps - 1) * b.dil_w + 1), shift = v->rowb == 128 ? 3 : 2;
-    const int64_t ncb = (b.bytes + v->rowb - 1) / v->rowb, ring = 3ll * b.taps * v->bn * v->rowb, tiles_n = (b.cols + v->bn - 1) / v->bn * b.batch;
+// What the calling thread's last convolution call or query worked out for the channel-block kernel (tir_debug_block_plan).
+static thread_local struct {
+    int planned, strips;
+} g_block_plan = {0, 0};
+
+// The cheapest of a few strip widths whose patch fits LDS, over all tiles or `only` one (a record's or a forced one), if it is expected to take less than
+// `limit` cycles; false where none is.  Every stride-1 3x3 and 5x5 call comes through here: a tile is planned only where its floor - no patch beyond its own
+// pixels, no workgroups beyond those of one strip - passes the limit, which each plan found lowers, and what depends on the width and the tile's rows alone is worked out once
+// for the tiles that share it.  ns of a variant query (the C call, a container's CPU) without this kernel, with every tile planned in every width, and so: 16x56x56, 64 -> 64,
+// where the patch kernel stays, 360, 930, 420; 28x28, 16 -> 16 in each of 8 groups 615, 960, 670; 4x40x90, 96 -> 160, 5x5 dilation 2 720, 1230, 880.
+static bool plan_blocks(int dt, int out, const Variant* only, const BlockProblem& b, double limit, BlockPlan* plan) {
+    struct Live {
+        const BlockTile* t;
+        double ncb, tiles_n, floor;
+    } live[kMaxBlockTiles];
+    int count = 0;
+    const BlockTiles& tiles = block_tiles(dt, out, b.taps);
+    const unsigned P = (unsigned)b.P, Q = (unsigned)b.Q, rows_all = (unsigned)(b.images * b.P), pixels_all = rows_all * Q;
+    for (int i = 0; i < tiles.n; ++i) {
+        const BlockTile& t = tiles.tile[i];
+        if (only && t.v != only) continue;
+        const double ncb = (double)(int)(((unsigned)b.bytes + (1u << t.row_shift) - 1u) >> t.row_shift), tiles_n = (double)(((b.cols + (1 << t.bn_shift) - 1) >> t.bn_shift) * b.batch);
+        const double rounds = (double)(int)((pixels_all + (1u << t.bm_shift) - 1u) >> t.bm_shift) * tiles_n * (1.0 / kCUs);
+        double floor = blocks_cycles(t, ncb, t.own_units, b.phased, false, rounds);
+        if (t.pair && rounds > 1.0) {
+            const double shared = blocks_cycles(t, ncb, t.own_units, b.phased, true, rounds);
+            if (shared < floor) floor = shared;
+        }
+        if (floor < limit) live[count++] = Live{&t, ncb, tiles_n, floor};
+    }
+    if (!count) return false;
+    const unsigned span_h = (unsigned)((b.taps - 1) * b.dil_h + 1), span_w = (unsigned)((b.taps - 1) * b.dil_w + 1);
     bool found = false;
     static const unsigned kStrips[] = {1, 2, 3, 4, 6, 8};
     for (unsigned want : kStrips) {
         const unsigned tw = (Q + want - 1) / want, strips = (Q + tw - 1) / tw;
         if (want > 1 && (tw < 8 || strips != want)) break;
-        // rows a tile can touch (it starts at a multiple of bm, a power of two), and the images among them
-        const unsigned step = tw & (0u - tw), align = step < bm ? step : bm;
-        unsigned rows = (tw - align + bm - 1) / tw + 1;
-        if (rows > rows_all) rows = rows_all;
-        const unsigned crossings = (rows - 1 + P - 1) / P;
-        const int64_t vrows = (int64_t)rows - 1 + (int64_t)crossings * (span_h - 1) + span_h;
-        const int64_t pw = (int64_t)tw + span_w - 1, units = ((vrows * pw + (1 << (7 - shift)) - 1) >> (7 - shift)) * 2;      // copy instructions; a buffer is a whole number of the swizzle's 2 KiB
-        if (units > 4 * kBlockPatchUnits) continue;
-        const int64_t lds = ring + units * 1024 * (ncb > 1 ? 2 : 1);
-        if (lds > 160 * 1024) continue;
-        const int64_t strip_tiles = ((int64_t)rows_all * tw + bm - 1) / bm;
-        const double cycles = blocks_cycles(v, b, ncb, units, lds, strip_tiles * strips * tiles_n, strips);
-        if (found && cycles >= plan->cycles) continue;
-        found = true;
-        *plan = BlockPlan{v, (int)tw, (int)pw, (int)(P - 1 + span_h), (int)(units * 1024), (int)lds, (int)strips, (int)strip_tiles, cycles};
+        const unsigned pw = tw + span_w - 1, step = tw & (0u - tw);
+        const bool decode = b.phased || strips > 1;
+        int have_bm = 0;
+        int64_t pixels = 0;             // of the patch
+        unsigned strip_tiles = 0;
+        for (int i = 0; i < count; ++i) {
+            const BlockTile& t = *live[i].t;
+            if (live[i].floor + (decode && !b.phased ? t.decode : 0.0) >= limit) continue;
+            if (have_bm != t.bm_shift) {
+                have_bm = t.bm_shift;
+                // rows a tile can touch (it starts at a multiple of bm, a power of two), and the images among them
+                const unsigned bm = 1u << t.bm_shift, align = step < bm ? step : bm;
+                unsigned rows = (tw - align + bm - 1) / tw + 1;
+                if (rows > rows_all) rows = rows_all;
+                const unsigned crossings = rows - 1 <= P ? rows > 1 : (rows - 1 + P - 1) / P;
+                pixels = ((int64_t)rows - 1 + (int64_t)crossings * (span_h - 1) + span_h) * pw;
+                strip_tiles = (rows_all * tw + bm - 1) >> t.bm_shift;
+            }
+            const int shift = t.row_shift == 7 ? 4 : 5;        // a buffer is a whole number of the swizzle's 2 KiB: pixels of it, two copy instructions
+            const int64_t units = ((pixels + (1 << shift) - 1) >> shift) * 2;
+            if (units > 4 * kBlockPatchUnits) continue;
+            const int lds = (int)t.ring + (int)units * 1024 * (live[i].ncb > 1.0 ? 2 : 1);
+            if (lds > 160 * 1024) continue;
+            ++g_block_plan.planned;
+            const double cycles = blocks_cycles(t, live[i].ncb, (double)(int)units, decode, t.pair && lds <= 80 * 1024, (double)(int)strip_tiles * (double)(int)strips * live[i].tiles_n * (1.0 / kCUs));
+            if (cycles >= limit) continue;
+            limit = cycles;
+            found = true;
+            *plan = BlockPlan{t.v, (int)tw, (int)pw, (int)(P - 1 + span_h), (int)units * 1024, lds, (int)strips, (int)strip_tiles};
+        }
     }
     return found;
 }
@@ -743,6 +814,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
                            Mg * K * elem_size(out) < kMaxExtent && Cg * es < 65536;
     const BlockProblem block_problem = {N, phased ? Pp : P, phased ? Qp : Q, Kg, phased ? groups * phases : groups, Cg * es, (int)taps, g.dil_h, g.dil_w, elem_size(out), phased};
     BlockPlan blocks = {};
+    g_block_plan = {0, 0};
     // records are kept under the implicit-GEMM signature; a record (or a trial) may name either kernel family
     const int64_t geom[21] = {N, groups, D, H, W, T, R, S, g.stride_d, g.stride_h, g.stride_w, g.pad_d, g.pad_h, g.pad_w, g.dil_d, g.dil_h, g.dil_w,
                               g.transposed ? 1 : 0, g.transposed ? g.outpad_h : 0, g.transposed ? g.outpad_w : 0, 0};
@@ -760,14 +832,14 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
     else if (g_trial.v) ch = g_trial;
     else if (!g_force_name[0] && !g_force_bm && !g_force_ksplit) ch = tuned_lookup(plan->key);
     if (ch.v && ch.v->amode == A_CONV_PATCH && !patch_ok) ch = kNoChoice;
-    if (ch.v && ch.v->amode == A_CONV_BLOCKS && !(blocks_ok && plan_blocks(ch.v, block_problem, &blocks))) {
+    if (ch.v && ch.v->amode == A_CONV_BLOCKS && !(blocks_ok && plan_blocks(in, out, ch.v, block_problem, kNoLimit, &blocks))) {
         if (g_trial.v) return fail(TIR_ERR_UNSUPPORTED, "%s: not for this convolution", ch.v->name);
         ch = kNoChoice;
     }
     if (!ch.v && blocks_ok && g_force_name[0] && strstr(g_force_name, "patch")) {
         const VariantRange c = variants_of(in, out, A_CONV_BLOCKS, B_KMAJOR);
         for (int i = 0; i < c.n && !ch.v; ++i)
-            if (strstr(c.first[i].v->name, g_force_name) && plan_blocks(c.first[i].v, block_problem, &blocks)) ch = Choice{c.first[i].v, 1};
+            if (strstr(c.first[i].v->name, g_force_name) && plan_blocks(in, out, c.first[i].v, block_problem, kNoLimit, &blocks)) ch = Choice{c.first[i].v, 1};
     }
     if (!ch.v) {
         // A filter of one tap reads no pixel twice, and the patch kernel would copy the pixels again for every 64 output channels: 1x1, 64 -> 256 channels,
@@ -781,15 +853,8 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         // From 0.94 of the other kernel's expected time on: beyond, calls are lost to the estimates' error that gain nothing in the mean (at 0.97 three times as many
         // are more than 5 % slower).
         if (blocks_ok && ch.v && !g_force_name[0] && !g_force_bm && !g_force_ksplit) {
-            double limit = 0.94 * (use_patch ? patch_cycles(block_problem) : gather_cycles(ch.v, block_problem, ch.ksplit));
-            const VariantRange c = variants_of(in, out, A_CONV_BLOCKS, B_KMAJOR);
-            for (int i = 0; i < c.n; ++i) {
-                BlockPlan tile;
-                if (!plan_blocks(c.first[i].v, block_problem, &tile) || tile.cycles >= limit) continue;
-                limit = tile.cycles;
-                blocks = tile;
-                ch = Choice{tile.v, 1};
-            }
+            const double other = use_patch ? patch_cycles(block_problem) : gather_cycles(ch.v, block_problem, ch.ksplit);
+            if (plan_blocks(in, out, nullptr, block_problem, 0.94 * other, &blocks)) ch = Choice{blocks.v, 1};
         }
     }
     if (phased && ch.v && tuned_or_trial_mismatch(ch.v, Cg * es)) ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, kNoSplit, 128);
@@ -859,6 +924,7 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         p.tap_sign = 1; p.up_h = 1; p.up_w = 1;
     }
     if (amode == A_CONV_BLOCKS) {
+        g_block_plan.strips = blocks.strips;
         p.tiles_m = blocks.strips * blocks.strip_tiles;
         p.blk_tw = blocks.tw; p.blk_pw = blocks.pw; p.blk_vh = blocks.vh; p.blk_taps = (int)taps; p.blk_patch = blocks.patch; p.blk_strip_tiles = blocks.strip_tiles; p.blk_lds = blocks.lds;
     }
@@ -1258,6 +1324,11 @@ unsigned tir_debug_fastdiv(unsigned d, unsigned m) {
 
 int tir_debug_depthwise_pixels(int64_t N, int64_t P, int64_t Q, int64_t C, int stride_w, tir_dtype in, tir_dtype out) {
     return depthwise_pixels((int)in, (int)out, N, P, Q, C, stride_w);
+}
+
+void tir_debug_block_plan(int* planned, int* strips) {
+    if (planned) *planned = g_block_plan.planned;
+    if (strips) *strips = g_block_plan.strips;
 }
 
 int tir_debug_depthwise_rows(int64_t N, int64_t P, int64_t Q, int64_t C, tir_dtype in, tir_dtype out) {

@@ -225,6 +225,23 @@ def test_channel_block_choice_of_measured_calls(call, variant):
     test_variant_choice_of_measured_calls(call, variant)
 
 
+def test_channel_block_plans_are_few():
+    """Tiles of the channel-block kernel that cannot win are not planned: small convolutions are bound by the host, and there are six tiles in up to six strip widths."""
+    def plan(n, h, w, c, k, r, dil, groups, dtype="f16"):
+        pad = dil * (r - 1) // 2
+        assert B.tir_conv2d_variant(n, h, w, c, k, r, r, 1, 1, pad, pad, dil, dil, groups, dtype, dtype)
+        return B.tir_debug_block_plan()
+    assert plan(16, 56, 56, 64, 64, 3, 1, 1) == (0, 0)                # the patch kernel's
+    assert plan(1, 112, 112, 32, 32, 3, 1, 1) == (0, 0)
+    assert plan(8, 28, 28, 256, 256, 3, 2, 8, "i8") == (1, 1)         # one strip of 28 columns 4.95 us, two 5.35
+    rng = np.random.default_rng(11)
+    planned = []
+    for _ in range(400):
+        n, h, w, r, groups = (int(v) for v in (rng.integers(1, 33), rng.integers(7, 113), rng.integers(7, 113), rng.choice([3, 5]), rng.choice([1, 1, 2, 4, 8])))
+        planned.append(plan(n, h, w, int(rng.integers(1, 33)) * 16 * groups, int(rng.integers(1, 33)) * 16 * groups, r, int(rng.integers(1, 3)), groups)[0])
+    assert np.mean(planned) < 6 and max(planned) <= 36, (np.mean(planned), max(planned))
+
+
 def test_few_channels_take_the_row_kernel_where_it_pays():
     """Vectors of one tap that are not whole: filter rows as the unit of the reduction, unless the reduction is one
     stage in one round of workgroups and the patch (wide strides, many channels) takes longer to copy than the element-wise kernel takes
