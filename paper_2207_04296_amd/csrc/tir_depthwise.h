@@ -260,17 +260,21 @@ inline int depthwise_pixels(int dt, int out, long long N, long long P, long long
 // Rows of output pixels per thread of the blocked kernel at stride 1, undilated, P x Q output pixels: two rows of four, or one (of depthwise_pixels()).  Two
 // rows fetch a fifth less per pixel than eight in a row, but hold 24 vectors at once (fp16 170 registers, bf16 245: two workgroups per CU, where four in a
 // row have four and two), so a launch that has not a workgroup of four for every CU is slower (1.2 - 1.3 of the time: half as many CUs work).  From there on:
-// bf16 gains everywhere, 103 of 105 drawn calls 0.74 - 0.99 of the time (0.89 in the mean), but for a last round of a few workgroups.  fp16 gains while every
-// CU has at most one workgroup (and a whole block of 64 channels: 3x98x112x48 4.7 / 4.9), 0.88 - 1.01, and from 800 on, 0.84 - 0.99; between, four or eight in a row
+// bf16 gains, 241 of 246 drawn calls less than the time, down to 0.71 of it (0.89 in the mean), but where the workgroups of one row just fill one or two rounds of two per CU and those
+// of two rows, half as many and a few more from padding, begin another: seven calls of 257 to 260 and 513 to 520, 1.01 - 1.25 of the time, one row by the rule (23x13x105x224, 544 and 1012, gains: 11.3 / 10.3).  (No such
+// line after 1024, 1536 and 2048: 0.71 - 0.97.)  fp16 gains while every
+// CU has at most one workgroup (and a whole block of 64 channels: 3x98x112x48 4.7 / 4.9), 0.88 - 1.04, and from 800 on, 0.78 - 1.04 (both 0.95 in the mean); between, four or eight in a row
 // have more workgroups in flight.  One row and two, us, three sets of buffers in turn:
-//   bf16: 10x72x22x208 8.4 / 7.7, 32x56x56x128 15.4 / 13.2, 32x112x112x64 31.2 / 26.6, 11x100x49x176 16.4 / 12.1; slower: 8x85x19x464 8.7 / 9.9, 25x47x39x80 7.5 / 7.8,
-//         25x43x57x112 (516 workgroups, one row by the rule) 11.2 / 11.9
+//   bf16: 10x72x22x208 8.4 / 7.7, 24x18x75x208 (516 workgroups, 1028 of one row) 13.0 / 10.6, 32x56x56x128 15.4 / 13.2, 32x112x112x64 31.2 / 26.6, 11x100x49x176 16.4 / 12.1; slower: 8x85x19x464
+//         8.7 / 9.9, 25x47x39x80 7.5 / 7.8; one row by the rule: 14x65x69x112 (520, 1024 of one row) 9.8 / 12.2, 3x110x25x448 (259, 511) 5.7 / 6.9
 //   fp16: 18x14x41x144 5.7 / 5.0, 20x43x11x336 6.2 / 5.7, 17x32x105x240 20.2 / 17.5, 32x112x112x64 28.4 / 26.1; one row by the rule: 16x56x56x128 (392 workgroups) 7.85 / 8.08, 16x56x56x256 (784) 13.3 / 13.7
 // Not measured, and left with one row: fewer than seven rows of output, other types of output.
 inline int depthwise_rows(int dt, int out, long long N, long long P, long long Q, long long C) {
-    if (out != dt || dt == DT_I8 || P < 7 || depthwise_workgroups(dt, N, P, Q, C, kDwBlockPix) <= 256) return 1;
+    if (out != dt || dt == DT_I8 || P < 7) return 1;
+    const long long one = depthwise_workgroups(dt, N, P, Q, C, kDwBlockPix);
+    if (one <= 256) return 1;
     const long long two = depthwise_workgroups(dt, N, (P + 1) / 2, Q, C, kDwBlockPix);
-    if (dt == DT_BF16) return two <= 512 || two > 528 ? 2 : 1;
+    if (dt == DT_BF16) return (two > 256 && two <= 256 + 16 && one <= 512) || (two > 512 && two <= 512 + 16 && one <= 1024) ? 1 : 2;
     return (two <= 256 && C >= kDwChannels) || two > 800 ? 2 : 1;
 }
 

@@ -134,6 +134,25 @@ def test_depthwise_pixels_per_thread(dtype, out, n, p, q, c, pixels):
     assert B.tir_debug_depthwise_pixels(n, p, q, c, 2, dtype, out) == 4
 
 
+@pytest.mark.parametrize("dtype,n,p,q,c,rows", [
+    # us with one row of pixels per thread and with two
+    ("bf16", 10, 72, 22, 208, 2),        # 8.4, 7.7
+    ("bf16", 3, 110, 25, 448, 1),        # 5.7, 6.9: 511 workgroups of one row, 259 of two
+    ("bf16", 29, 37, 9, 304, 1),         # 6.1, 7.0: 505, 260
+    ("bf16", 27, 40, 62, 32, 2),         # 7.0, 6.7: 540, 270
+    ("bf16", 14, 65, 69, 112, 1),        # 9.8, 12.2: 1024, 520
+    ("bf16", 24, 18, 75, 208, 2),        # 13.0, 10.6: 1028, 516
+    ("bf16", 8, 78, 105, 96, 2),         # 12.1, 10.2: 1054, 528
+    ("bf16", 17, 45, 83, 224, 2),        # 19.9, 16.9: 2012, 1028
+    ("f16", 20, 43, 11, 336, 2),         # 6.2, 5.7
+    ("f16", 16, 56, 56, 128, 1),         # 7.85, 8.08
+    ("f16", 32, 112, 112, 64, 2),        # 28.4, 26.1
+])
+def test_depthwise_rows_per_thread(dtype, n, p, q, c, rows):
+    """Two rows of pixels per thread, except where one row's workgroups just fill the CUs and those of two begin another round."""
+    assert B.tir_debug_depthwise_rows(n, p, q, c, dtype, dtype) == rows
+
+
 @pytest.mark.parametrize("batch,m,n,d,out,kernel", [
     # us with this kernel and with another, the same operands again / three sets of operands in turn
     (512, 256, 256, 64, "bf16", "t128_sequential"),       # 15.7 / 16.1, in tiles of 256 15.7 / 18.7
