@@ -261,6 +261,90 @@ def test_channel_block_plans_are_few():
     assert np.mean(planned) < 6 and max(planned) <= 36, (np.mean(planned), max(planned))
 
 
+R128, R64 = ["patch64x64w2x2r128", "patch128x64w2x2r128", "patch128x32w4x1r128"], ["patch128x64w2x2r64", "patch256x64w4x1r64", "patch256x32w4x1r64"]
+
+
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("bf16", "f32"), ("i8", "i32")])
+@pytest.mark.parametrize("kind,n,h,w,vecs,k,r,pad,dil,groups,tiles", [
+    ("conv", 7, 5, 6, 9, 40, 3, (1, 1), (1, 1), 1, R128 + R64),
+    ("conv", 2, 9, 150, 4, 24, 3, (1, 1), (1, 1), 2, R128 + R64),                          # 128-byte blocks in strips
+    ("conv", 1, 9, 700, 12, 40, 3, (1, 1), (1, 1), 1, R64),                                # eight strips of 88 columns: 270 pixels of two buffers do not fit beside the filter
+    ("conv", 1, 9, 2000, 12, 40, 3, (1, 1), (1, 1), 1, []),                                # too wide for the strips there are
+    ("conv", 1, 40, 30, 12, 40, 3, (8, 8), (8, 8), 1, []),                                 # dilated rows: too many copy instructions per patch
+    ("conv", 1, 12, 17, 8, 72, 5, (2, 2), (1, 1), 1, R128 + R64),                          # 5x5, one block
+    ("conv", 1, 12, 17, 20, 72, 5, (2, 2), (1, 1), 1, R128[2:] + R64),                     # several: no room for the patch beside 120 KiB of filter
+    ("conv", 1, 20, 20, 12, 40, 4, (1, 1), (1, 1), 1, []),                                 # sixteen taps are not compiled
+    ("tconv", 1, 3, 300, 12, 40, 4, (1, 1), (1, 1), 1, R128 + R64),
+    ("tconv", 2, 6, 9, 19, 42, 10, (4, 4), (1, 1), 1, R128[2:] + R64),                     # 5x5 taps per phase
+    ("tconv", 2, 6, 9, 19, 42, 5, (2, 2), (1, 1), 1, []),                                  # phases of unequal taps
+])
+def test_channel_block_tiles_that_fit(dtype, out, kind, n, h, w, vecs, k, r, pad, dil, groups, tiles):
+    """Which tiles of the channel-block kernel a problem can run in: forced by name, and from a tuning record; where none fits, the built-in choice stays another kernel."""
+    c = vecs * (16 if dtype == "i8" else 8) * groups
+    if kind == "conv":
+        query = lambda: B.tir_conv2d_variant(n, h, w, c, k, r, r, 1, 1, *pad, *dil, groups, dtype, out)
+    else:
+        query = lambda: B.tir_conv2d_transpose_variant(n, h, w, c, k, r, r, (2, 2), pad, dil, (0, 0), groups, dtype, out)
+    every = [f"{dtype}_{out}_{t}_conv" for t in R128 + R64]
+    assert set(every) == {v for v in B.tir_debug_variant_names() if v.startswith(f"{dtype}_{out}_patch") and "patch256x64_conv" not in v}
+    fit = set()
+    try:
+        for name in every:
+            B.tir_debug_force_variant(name)
+            if query().split("/")[0] == name:
+                assert B.tir_debug_block_plan()[1] >= 1
+                fit.add(name)
+    finally:
+        B.tir_debug_force_variant("")
+    assert fit == {f"{dtype}_{out}_{t}_conv" for t in tiles}
+    if not tiles:
+        assert "w2x2r" not in query() and "w4x1r" not in query()
+
+
+def _geometry_hash(fields):
+    """FNV-1a over the 64-bit fields of a convolution's geometry, as tuning records store it."""
+    h = 1469598103934665603
+    for f in fields:
+        for b in range(8):
+            h = ((h ^ (f >> (8 * b) & 0xff)) * 1099511628211) % 2 ** 64
+    return h
+
+
+@pytest.mark.parametrize("n,h,w,c,k,r,stride,dil,fits", [
+    (2, 20, 23, 96, 40, 3, 1, 1, True),
+    (2, 20, 23, 96, 40, 3, 2, 1, False),        # strided
+    (2, 20, 23, 96, 40, 1, 1, 1, False),        # one tap
+    (2, 9, 700, 96, 40, 3, 1, 1, False),        # no strip of it fits LDS in this tile
+    (2, 60, 60, 96, 40, 3, 1, 9, False),        # nor its dilated rows
+])
+def test_channel_block_record_is_taken_only_where_the_tile_fits(tmp_path, n, h, w, c, k, r, stride, dil, fits):
+    name = "f16_f16_patch128x64w2x2r128_conv"
+    pad = dil * (r - 1) // 2
+    query = lambda: B.tir_conv2d_variant(n, h, w, c, k, r, r, stride, stride, pad, pad, dil, dil, 1, "f16", "f16")
+    P, Q = ((x + 2 * pad - dil * (r - 1) - 1) // stride + 1 for x in (h, w))
+    geom = _geometry_hash([n, 1, 1, h, w, 1, r, r, 1, stride, stride, 0, pad, pad, 1, dil, dil, 0, 0, 0, 0])
+    B.tir_tune_clear()
+    try:
+        default = query()
+        rec = tmp_path / "records.txt"
+        lines = lambda v: f"tir-tune-records 1\n1 0 0 1 0 {n} {P * Q} {k} {r * r * c} {geom} {v} 1\n"
+        other = "f16_f16_t128x128w2x2s2_conv"         # the record's signature is this call's
+        assert default not in (name, other)
+        rec.write_text(lines(other))
+        B.tir_tune_load(rec)
+        assert B.tir_tune_count() == 1 and query() == other
+        B.tir_tune_clear()
+        rec.write_text(lines(name))
+        B.tir_tune_load(rec)
+        assert B.tir_tune_count() == 1
+        assert query() == (name if fits else default)
+        B.tir_debug_force_variant("t64x64w2x2s3_conv")      # a forced variant wins over a record
+        assert query() == "f16_f16_t64x64w2x2s3_conv"
+    finally:
+        B.tir_debug_force_variant("")
+        B.tir_tune_clear()
+
+
 def test_few_channels_take_the_row_kernel_where_it_pays():
     """Vectors of one tap that are not whole: filter rows as the unit of the reduction, unless the reduction is one
     stage in one round of workgroups and the patch (wide strides, many channels) takes longer to copy than the element-wise kernel takes

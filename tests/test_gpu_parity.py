@@ -602,8 +602,8 @@ PATCH_CASES = [
 
 @pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("f16", "f32"), ("bf16", "f32"), ("i8", "i32")])
 def test_conv_patch_kernel(B, oracle, dtype, out):
-    """Shapes with exactly 128 bytes of channels per pixel and group take the LDS-resident-patch kernel;
-    the same shapes are also pushed through the implicit-GEMM kernel."""
+    """Shapes with exactly 128 bytes of channels per pixel and group take the LDS-resident-patch kernel or, at stride 1 with equal filter extents, the
+    channel-block kernel; the same shapes are also pushed through the implicit-GEMM kernel."""
     cg = 128 if dtype == "i8" else 64
     for (n, h, w, groups, k, r, s, stride, pad, dil) in PATCH_CASES:
         c = cg * groups
@@ -626,7 +626,7 @@ def test_conv_patch_kernel(B, oracle, dtype, out):
 
 def test_conv_patch_kernel_seeded_shapes(B, oracle):
     """Two dozen seeded geometries (filter extents 1..4, strides, paddings, dilations, groups, ragged channel counts) through
-    the LDS-resident-patch kernel where it applies, element by element against the oracle."""
+    the kernel the built-in choice takes for 128-byte pixels, the LDS-resident patch or channel blocks, element by element against the oracle."""
     rng = np.random.default_rng(20240607)
     done = 0
     for case in range(200):
@@ -658,6 +658,27 @@ def test_conv_patch_kernel_seeded_shapes(B, oracle):
         PT.check_workload(wl, oracle)
         done += 1
     assert done == 24
+
+
+@pytest.mark.parametrize("dtype,out", PAIRS)
+def test_conv_patch_kernel_by_name(B, oracle, dtype, out):
+    """The same shapes through the patch kernel forced by name: by itself half of them go to the channel-block kernel, whose names hold "patch" as well."""
+    cg = 128 if dtype == "i8" else 64
+    kernel = f"{dtype}_{out}_patch256x64_conv"
+    for i, (n, h, w, groups, k, r, s, stride, pad, dil) in enumerate(PATCH_CASES):
+        wl = I.Workload(f"patch_by_name_{i}_{dtype}_{out}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 7700 + h + k, n=n, h=h, w=w, c=cg * groups, k=k,
+                        r=r, s=s, stride=stride, pad=pad, dil=dil, groups=groups, ep_bias=i % 2 == 0, ep_relu=i % 3 == 0, ep_scale=0.01 if out == "i8" else 0.0)
+        a_bits, b_bits = wl.operands()
+        ref, S = PT.run_oracle(wl, a_bits, b_bits, oracle)
+        if out == "bf16":       # its own rounding, 2^-8 |c|
+            S = S + 2.0 ** -8 * np.abs(ref) / PT.RTOL_S
+        B.tir_debug_force_variant("patch256x64_conv")
+        try:
+            assert PT.variant_name(B, wl) == kernel
+            _say(f"{wl.name} via {kernel}")
+            PT.assert_close(PT.run_gpu(wl, a_bits, b_bits), ref, S, wl.name)
+        finally:
+            B.tir_debug_force_variant("")
 
 
 # ------------------------------------------------------------------------------ channel-block convolution
@@ -727,6 +748,153 @@ def test_channel_block_convolution_by_output_phase(B, oracle, dtype, out, R, S_,
         B.tir_debug_force_variant("")
 
 
+BLOCK_PHASE_CASES = [
+    # images, h, w, 16-byte vectors per pixel, output channels, filter, padding, strips in more than one tile
+    (1, 3, 300, 12, 40, 4, (1, 1), True),         # 2x2 taps per phase, a wide image in strips
+    (2, 4, 163, 19, 42, 6, (2, 1), True),         # 3x3, three blocks, the last a third full, columns that no strip count divides
+    (2, 6, 9, 19, 42, 10, (4, 4), False),         # 5x5, several blocks
+    (1, 5, 300, 7, 24, 10, (4, 5), True),         # 5x5, one block, strips
+]
+
+
+@pytest.mark.parametrize("dtype,out", PAIRS)
+@pytest.mark.parametrize("N,H,W,vecs,K,R,pad,strips", BLOCK_PHASE_CASES)
+def test_channel_block_convolution_by_phase_in_strips(B, oracle, dtype, out, N, H, W, vecs, K, R, pad, strips):
+    """Transposed convolutions of stride 2 through every tile that takes them: output phases and strips of columns in one launch, up to 5x5 taps per phase."""
+    import torch
+    C = vecs * (16 if dtype == "i8" else 8)
+    dist = "i" if dtype == "i8" else "n0.1"
+    xb, wb = I.make_tensor(dtype, dist, 9240 + R, (N, H, W, C)), I.make_tensor(dtype, dist, 9241 + W, (K, R, R, C))
+    ref, S = oracle.conv2d_transpose(dtype, xb, wb, (2, 2), pad, (1, 1), (0, 0), 1)
+    ep, bias, ref, S = _consumer(B, oracle, dtype, out, K, R * R * C // 4, True, ref, S)
+    xd, wd = B.to_device(xb, dtype), B.to_device(wb, dtype)
+    args = (N, H, W, C, K, R, R, (2, 2), pad, (1, 1), (0, 0), 1, dtype, out)
+    names = [n for n in B.tir_debug_variant_names() if n.startswith(f"{dtype}_{out}_patch") and "patch256x64_conv" not in n]
+    ran, cut = 0, 0
+    try:
+        for name in names:
+            B.tir_debug_force_variant(name)
+            if B.tir_conv2d_transpose_variant(*args) != f"{name}/ph2x2":        # which ones fit: test_channel_block_tiles_that_fit
+                continue
+            ran, cut = ran + 1, cut + (B.tir_debug_block_plan()[1] > 1)
+            _say(f"conv2d_transpose {H}x{W}, {C} channels, {R}x{R} via {name}, {B.tir_debug_block_plan()[1]} strips")
+            y = _gpu_out(B, ref.shape, out)
+            B.tir_conv2d_transpose(xd, wd, y, *args, ep=ep)
+            torch.cuda.synchronize()
+            PT.assert_close(PT.gpu_to_f64(y), ref, S, name)
+    finally:
+        B.tir_debug_force_variant("")
+    assert ran >= 3 and (cut >= 2) == strips, (ran, cut)
+
+
+def test_channel_block_convolution_keeps_groups_and_pixels_apart(B):
+    """An infinity and a NaN in one pixel of one group reach the outputs whose receptive field holds it and no other: lanes past a group's channels, the image's edges and
+    a tile's last row are zeros, not neighbours.  Every other output is bit-identical to the clean run's."""
+    import torch
+    n, h, w, cg, kg, groups, r = 3, 9, 13, 24, 20, 2, 3         # a block of 48 bytes: the second half of a 64-byte one is another group's
+    dev = torch.device("cuda")
+    gen = torch.Generator().manual_seed(5)
+    x = torch.randn(n, h, w, cg * groups, generator=gen).to(torch.float16)
+    wt = torch.randn(kg * groups, r, r, cg, generator=gen).to(torch.float16).to(dev)
+    bad = x.clone()
+    bad[1, 0, 12, 3] = float("inf")
+    bad[1, 8, 0, cg + 5] = float("nan")
+    hit = torch.zeros(n, h, w, kg * groups, dtype=torch.bool)
+    hit[1, 0:2, 11:13, :kg] = True
+    hit[1, 7:9, 0:2, kg:] = True
+    args = (n, h, w, cg * groups, kg * groups, r, r, 1, 1, 1, 1, 1, 1, groups, "f16", "f32")
+    try:
+        for name in [v for v in B.tir_debug_variant_names() if v.startswith("f16_f32_patch") and "patch256x64_conv" not in v]:
+            B.tir_debug_force_variant(name)
+            assert B.tir_conv2d_variant(*args) == name
+            ys = []
+            for v in (x, bad):
+                y = torch.full((n, h, w, kg * groups), -77.0, dtype=torch.float32, device=dev)
+                B.tir_conv2d(v.to(dev), wt, y, *args)
+                torch.cuda.synchronize()
+                ys.append(y.cpu())
+            assert torch.isfinite(ys[0]).all()
+            assert torch.equal(ys[0][~hit], ys[1][~hit]), name
+            assert not torch.isfinite(ys[1][hit]).any(), name
+    finally:
+        B.tir_debug_force_variant("")
+
+
+def _block_workloads(B, count):
+    """Seeded stride-1 convolutions whose built-in choice is the channel-block kernel."""
+    rng = np.random.default_rng(31)
+    wls = []
+    while len(wls) < count:
+        dtype, out = PAIRS[int(rng.integers(len(PAIRS)))]
+        vec, groups, r = (16 if dtype == "i8" else 8), int(rng.choice([1, 1, 2, 4])), int(rng.choice([2, 3, 3, 5]))
+        dil, pad = (int(rng.integers(1, 3)), int(rng.integers(1, 3))), (int(rng.integers(0, 4)), int(rng.integers(0, 4)))
+        wl = I.Workload(f"blocks_seeded_{len(wls)}_{dtype}_{out}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 9300 + len(wls), n=int(rng.integers(1, 4)),
+                        h=int(rng.integers(9, 40)), w=int(rng.integers(9, 60)), c=vec * int(rng.integers(1, 20)) * groups, k=int(rng.integers(4, 90)) * groups, r=r, s=r, pad=pad,
+                        dil=dil, groups=groups, ep_bias=bool(rng.random() < 0.5), ep_relu=bool(rng.random() < 0.5), ep_scale=0.01 if out == "i8" else 0.0)
+        if PT.variant_name(B, wl) and B.tir_debug_block_plan()[1]:
+            wls.append(wl)
+    return wls
+
+
+def test_channel_block_convolution_seeded_shapes(B, oracle):
+    """Seeded problems that the built-in choice gives to the channel-block kernel: through that choice, and through a random implicit-GEMM tile of the same type pair."""
+    rng = np.random.default_rng(32)
+    tiles = set()
+    for wl in _block_workloads(B, 24):
+        a_bits, b_bits = wl.operands()
+        ref, S = PT.run_oracle(wl, a_bits, b_bits, oracle)
+        if wl.out == "bf16":
+            S = S + 2.0 ** -8 * np.abs(ref) / PT.RTOL_S
+        default = PT.variant_name(B, wl)
+        tiles.add(default.split("_")[2])
+        other = str(rng.choice([v for v in B.tir_debug_variant_names() if v.startswith(f"{wl.dtype}_{wl.out}_t") and v.endswith("_conv")]))
+        try:
+            for force in ("", other):
+                B.tir_debug_force_variant(force)
+                name = PT.variant_name(B, wl).split("/")[0]
+                assert name == (force or default)
+                _say(f"{wl.name}: {wl.n}x{wl.h}x{wl.w}, {wl.c} -> {wl.k} in {wl.groups} groups, {wl.r}x{wl.r} pad {wl.pad} dil {wl.dil} via {name}")
+                PT.assert_close(PT.run_gpu(wl, a_bits, b_bits), ref, S, f"{wl.name} via {name}")
+        finally:
+            B.tir_debug_force_variant("")
+    assert len(tiles) >= 3, tiles
+
+
+def test_channel_block_convolution_in_a_captured_graph(B):
+    """Captured and replayed on new operands: every replay is the eager result."""
+    import torch
+    args = (2, 14, 15, 96, 64, 3, 3, 1, 1, 1, 1, 1, 1, 1, "f16", "f16")
+    up = (2, 14, 15, 96, 64, 4, 4, (2, 2), (1, 1), (1, 1), (0, 0), 1, "f16", "f16")
+    B.tir_debug_force_variant("patch128x64w2x2r128_conv")
+    try:
+        assert B.tir_conv2d_variant(*args) == "f16_f16_patch128x64w2x2r128_conv" and B.tir_conv2d_transpose_variant(*up).startswith("f16_f16_patch128x64w2x2r128_conv")
+        gen = torch.Generator(device="cuda").manual_seed(7)
+        rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(torch.float16)
+        x, w, w4 = rand(2, 14, 15, 96), rand(64, 3, 3, 96), rand(64, 4, 4, 96)
+        y, z = torch.empty(2, 14, 15, 64, dtype=torch.float16, device="cuda"), torch.empty(2, 28, 30, 64, dtype=torch.float16, device="cuda")
+
+        def step(a, b):
+            B.tir_conv2d(x, w, a, *args)
+            B.tir_conv2d_transpose(x, w4, b, *up)
+        step(y, z)
+        torch.cuda.synchronize()
+        graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=stream):
+            step(y, z)
+        for _ in range(4):
+            x.copy_(rand(2, 14, 15, 96))
+            y.fill_(float("nan"))
+            z.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            ey, ez = torch.empty_like(y), torch.empty_like(z)
+            step(ey, ez)
+            torch.cuda.synchronize()
+            assert torch.equal(y, ey) and torch.equal(z, ez)
+    finally:
+        B.tir_debug_force_variant("")
+
+
 # ------------------------------------------------------------------------------ choice by measurement
 def test_tuning_measures_records_and_keeps_results_correct(B, oracle, tmp_path):
     """tir_tune_* runs every variant that can compute the problem, records the fastest, and the
@@ -787,10 +955,10 @@ FUSED_SMALL = [
     ("gemm", "i8", "i8", False, True, 1.0 / 64.0, dict(M=65, N=33, K=31)),                  # element-wise kernel, saturating
     ("bmm", "f16", "f16", True, True, 0.0, dict(batch=5, M=130, N=72, K=64, trans_b=True)),
     ("bmm", "i8", "i8", True, True, 1.0 / 500.0, dict(batch=3, M=100, N=48, K=96)),
-    ("conv2d", "f16", "f16", True, True, 0.0, dict(n=2, h=20, w=23, c=64, k=64, r=3, s=3, pad=(1, 1))),          # patch kernel
+    ("conv2d", "f16", "f16", True, True, 0.0, dict(n=2, h=20, w=23, c=64, k=64, r=3, s=3, pad=(1, 1))),          # channel blocks (the patch kernel with consumers: test_conv_patch_kernel_by_name)
     ("conv2d", "f16", "f32", True, False, 0.0, dict(n=2, h=13, w=11, c=16, k=40, r=3, s=3, stride=(2, 1), pad=(1, 2))),
     ("conv2d", "i8", "i8", True, True, 1.0 / 700.0, dict(n=2, h=14, w=14, c=64, k=48, r=3, s=3, pad=(1, 1), groups=2)),
-    ("conv2d", "i8", "i8", True, False, 1.0 / 300.0, dict(n=1, h=20, w=20, c=256, k=96, r=3, s=3, pad=(2, 2), dil=(2, 2), groups=2)),  # patch kernel, groups
+    ("conv2d", "i8", "i8", True, False, 1.0 / 300.0, dict(n=1, h=20, w=20, c=256, k=96, r=3, s=3, pad=(2, 2), dil=(2, 2), groups=2)),  # channel blocks, groups
     ("conv2d", "bf16", "bf16", True, True, 0.0, dict(n=1, h=9, w=9, c=6, k=10, r=3, s=3, pad=(1, 1), groups=2)),   # element-wise conv
 ]
 
