@@ -573,8 +573,9 @@ struct BlockProblem {
 // copying and multiplying) and its set-up and store.  Fitted to half of 8623 drawn stride-1 convolutions (3x3, 5x5 and 4x4 stride 2 by
 // phase), every tile timed in every number of strips with three sets of operands in turn, first to the times and then to the choice that follows.  On the other
 // half: times met to 7 % (root mean square; implicit GEMM 8), the choice at 0.85 of the other kernels' time in the geometric mean (the best tile of each call 0.84), and
-// 17 of 4312 calls more than 5 % slower than there, 5 more than 10 %.  Known ones, that time and this kernel's: 30x22x78, 272 -> 144, dilation 2 fp16 to fp32 61.8 and
-// 70.9 us, 2x58x63, 64 -> 480 in each of 8 groups, 5x5 int8 to int32 69.2 and 74, 20x20x26, 16 -> 160 in each of 4 groups fp16 to fp32 9.9 and 11.2, 7x19x80, 64 -> 96 in
+// 17 of 4312 calls more than 5 % slower than there, 5 more than 10 %; of 4329 drawn afterwards 25 and 5.  Known ones, that time and this kernel's: 28x32x11, 32 -> 256 in each of 4 groups, 5x5
+// bf16 to fp32 25.3 us and 32.6, 12x10x13, 144 -> 16 in each of 4 groups, 5x5 11.5 and 13.1, 13x22x42, 64 -> 368 13.1 and 15.1, 30x22x78, 272 -> 144, dilation 2 fp16 to fp32 61.8 and
+// 70.9, 2x58x63, 64 -> 480 in each of 8 groups, 5x5 int8 to int32 69.2 and 74, 20x20x26, 16 -> 160 in each of 4 groups fp16 to fp32 9.9 and 11.2, 7x19x80, 64 -> 96 in
 // each of 2 groups, dilation 2 6.8 and 7.5, 3x12x36, 496 -> 272, dilation 2 13.7 and 15.2, 1x106x15, 160 -> 16 in each of 4 groups, 5x5 12.1 and 12.9.
 static double whole_rounds(double rounds, int n) { return n * (double)(int)((n == 1 ? rounds : rounds / n) + (1.0 - 1e-9)); }      // up to a multiple of n (launches are below 2^31 workgroups)
 // What a tile takes whatever the problem's extents, for filters of one size; worked out once.

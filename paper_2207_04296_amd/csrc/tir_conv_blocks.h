@@ -19,10 +19,12 @@
 // Channels past the group's last one and pixels outside the image are lanes outside the buffer descriptor: zeros.
 //
 // What bounds it now: a 128x64 tile of 16x14x14, 256 -> 128, 4x4 stride 2 by phase (4 blocks of 4 taps) spends 4000 cycles until its first MFMA, ~340 per tap and
-// 3400 in the store.  us, implicit GEMM (or, 64 channels, the patch kernel) -> here: that call 10.7 -> 8.5, 8x28x28, 32 -> 32 in each of 8 groups, dilation 2 int8
-// 5.8 -> 5.3, 14x11x34, 112 -> 16 in each of 8 groups, 5x5 25.5 -> 16.1, 21x37x7, 64 -> 16 in each of 8 groups 12.9 -> 5.9.  Tried: the unit's place worked out
+// 3400 in the store.  The swizzle follows the patch's pixels, so the lanes of a fragment that crosses a row of the patch meet on banks: 2007 cycles per
+// workgroup of that call (SQ_LDS_BANK_CONFLICT), 484 of 8x28x28, 32 -> 32 in each of 8 groups, dilation 2 int8 in one strip, 975 in two.  us, implicit GEMM (or, 64 channels,
+// the patch kernel) -> here: the first call 10.7 -> 8.6, the second 5.6 -> 4.9, 14x11x34, 112 -> 16 in each of 8 groups, 5x5 25.8 -> 14.6, 21x37x7, 64 -> 16 in each of 8
+// groups 12.9 -> 5.9.  Tried: the unit's place worked out
 // by scalars in each block instead of an address register per copy instruction (8.9 -> 10.2), a ring of four stages (the same), half of the first patch copied by
-// the multiplying waves instead of a quarter (8.6 -> 8.9) or none (the same; 8x28x28 5.3 -> 5.65), two sets of multiplying waves splitting a tap's k-steps (9.2, was 8.9).
+// the multiplying waves instead of a quarter (8.6 -> 8.9) or none (the same; the second call in two strips 5.3 -> 5.65), two sets of multiplying waves splitting a tap's k-steps (9.2, was 8.9).
 #pragma once
 #include "tir_kernel.h"
 
