@@ -854,8 +854,12 @@ static tir_status plan_conv_geom(bool need_ptrs, const void* x, const void* w, v
         // From 0.94 of the other kernel's expected time on: beyond, calls are lost to the estimates' error that gain nothing in the mean (at 0.97 three times as many
         // are more than 5 % slower).
         if (blocks_ok && ch.v && !g_force_name[0] && !g_force_bm && !g_force_ksplit) {
+            // 2x2 filters at stride 1 are not among the fitted calls: with so few products per output the chip's stores count, which cost this kernel's narrow tiles more than the wide
+            // ones they stand against (30x43x72, 160 -> 152 bf16 to fp32 39.8 us, 49.5 in blocks): a cycle per 6000 bytes.  1380 drawn ones 0.896 of the time without the kernel, 33 of
+            // them more than 5 % slower, 17 more than 10 %; without the term 0.896, 99 and 57.  (At larger filters it gives away as many calls as it mends.)
+            const double store = taps == 2 && !phased ? (double)Mg * (double)K * block_problem.out_bytes * (1.0 / 6000.0) : 0.0;
             const double other = use_patch ? patch_cycles(block_problem) : gather_cycles(ch.v, block_problem, ch.ksplit);
-            if (plan_blocks(in, out, nullptr, block_problem, 0.94 * other, &blocks)) ch = Choice{blocks.v, 1};
+            if (plan_blocks(in, out, nullptr, block_problem, 0.94 * other - store, &blocks)) ch = Choice{blocks.v, 1};
         }
     }
     if (phased && ch.v && tuned_or_trial_mismatch(ch.v, Cg * es)) ch = pick(in, out, amode, bmode, sc_batch, sc_M, Kg, sc_K, kNoSplit, 128);

@@ -238,6 +238,11 @@ def test_variant_choice_of_measured_calls(call, variant):
     (("conv", 3, 42, 48, 64, 16, 3, 1, 1, 1, "f16", "f16"), "patch64x64w2x2r128_conv"),           # 6.4, 4.4
     (("conv", 2, 57, 59, 896, 128, 5, 1, 1, 8, "bf16", "f32"), "patch256x32w4x1r64_conv"),        # 46.9, 15.7
     (("tconv", 29, 17, 54, 64, 32, "bf16", "bf16"), "patch256x32w4x1r64_conv/ph2x2"),             # 10.4, 7.1
+    (("conv", 30, 43, 72, 160, 152, 2, 1, 1, 1, "bf16", "f32"), "t128x192w2x2s3c4_conv"),         # 39.8, 49.5: two by two taps, stores
+    (("conv", 3, 69, 48, 16, 374, 2, 1, 1, 1, "bf16", "f32"), "t128x128w2x2s2_conv"),             # 6.5, 6.9
+    (("conv", 38, 26, 18, 5120, 24, 2, 1, 1, 8, "i8", "i32"), "patch256x32w4x1r64_conv"),         # 39.5, 22.6
+    (("conv", 14, 25, 230, 72, 24, 2, 1, 2, 3, "bf16", "bf16"), "patch256x32w4x1r64_conv"),       # 15.4, 10.1
+    (("conv", 4, 66, 4, 512, 24, 2, 1, 1, 8, "bf16", "f32"), "patch64x64w2x2r128_conv"),          # 6.0, 3.7
 ])
 def test_channel_block_choice_of_measured_calls(call, variant):
     """Stride-1 convolutions on both sides of the line between the channel-block kernel and the others."""
