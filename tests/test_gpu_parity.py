@@ -821,17 +821,19 @@ def test_channel_block_convolution_keeps_groups_and_pixels_apart(B):
 
 
 def _block_workloads(B, count):
-    """Seeded stride-1 convolutions whose built-in choice is the channel-block kernel."""
+    """Seeded stride-1 convolutions whose built-in choice is the channel-block kernel, at most a third of them in one of its tiles."""
     rng = np.random.default_rng(31)
-    wls = []
+    wls, tiles = [], {}
     while len(wls) < count:
         dtype, out = PAIRS[int(rng.integers(len(PAIRS)))]
         vec, groups, r = (16 if dtype == "i8" else 8), int(rng.choice([1, 1, 2, 4])), int(rng.choice([2, 3, 3, 5]))
         dil, pad = (int(rng.integers(1, 3)), int(rng.integers(1, 3))), (int(rng.integers(0, 4)), int(rng.integers(0, 4)))
-        wl = I.Workload(f"blocks_seeded_{len(wls)}_{dtype}_{out}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 9300 + len(wls), n=int(rng.integers(1, 4)),
+        wl = I.Workload(f"blocks_seeded_{len(wls)}_{dtype}_{out}", "conv2d", dtype, out, "i" if dtype == "i8" else "n0.1", 9300 + len(wls), n=int(rng.choice([1, 2, 3, 8])),
                         h=int(rng.integers(9, 40)), w=int(rng.integers(9, 60)), c=vec * int(rng.integers(1, 20)) * groups, k=int(rng.integers(4, 90)) * groups, r=r, s=r, pad=pad,
                         dil=dil, groups=groups, ep_bias=bool(rng.random() < 0.5), ep_relu=bool(rng.random() < 0.5), ep_scale=0.01 if out == "i8" else 0.0)
-        if PT.variant_name(B, wl) and B.tir_debug_block_plan()[1]:
+        tile = PT.variant_name(B, wl).split("_")[2]
+        if B.tir_debug_block_plan()[1] and tiles.get(tile, 0) < count // 3:
+            tiles[tile] = tiles.get(tile, 0) + 1
             wls.append(wl)
     return wls
 
